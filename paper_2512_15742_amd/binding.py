@@ -1,9 +1,12 @@
-"""ctypes binding of libkan_mi355x.so (declared in include/kan.h).
+"""Python binding of libkan_mi355x.so (declared in include/kan.h).
 
 Argument marshalling only: every step of the forward pass runs in the HIP
 kernels behind the C-ABI.  PyTorch supplies device memory and the stream.
 There is no CPU fallback: if the library has not been built, importing a symbol
 from it raises.
+
+The calls that run once per request (forward, dense, assign) go through the
+extension module _kan_host (csrc/kan_host.cpp), everything else through ctypes.
 """
 from __future__ import annotations
 
@@ -54,6 +57,25 @@ class KanError(RuntimeError):
 
 
 _lib = None
+_host_module = None
+
+# Outputs that the binding allocates itself are uninitialised memory; with KAN_POISON_OUTPUTS set (the tests
+# set it) they start as NaN, so that an element no kernel wrote cannot pass for a result.
+POISON_OUTPUTS = os.environ.get("KAN_POISON_OUTPUTS", "0") not in ("", "0")
+
+
+def _host():
+    """The extension module with the per-request calls (torch has to be loaded before it)."""
+    global _host_module
+    if _host_module is None:
+        _torch()
+        lib()
+        try:
+            from . import _kan_host
+        except ImportError as e:
+            raise RuntimeError("_kan_host is not built: build it with `python -m paper_2512_15742_amd.build`") from e
+        _host_module = _kan_host
+    return _host_module
 
 
 def lib():
@@ -205,11 +227,20 @@ def _desc_array(heads):
     return arr, n_layers, n_heads
 
 
-def _new_output(shape, device):
-    """An output tensor the binding allocates itself starts as NaN, so that an element no kernel
-    wrote cannot pass for a result (callers that time a call pass their own y)."""
-    torch = _torch()
-    return torch.full(shape, float("nan"), dtype=torch.float32, device=device)
+def _poisoned(y, shape, device):
+    """The output of a call: the caller's, or NaN-filled memory when POISON_OUTPUTS asks for it, or None (the
+    call brings its own)."""
+    if y is None and POISON_OUTPUTS:
+        torch = _torch()
+        return torch.full(shape, float("nan"), dtype=torch.float32, device=device)
+    return y
+
+
+def _done(result, where):
+    """The output of a _kan_host call, which returns the kan_status as an int when the call was refused."""
+    if type(result) is int:
+        raise KanError(result, where)
+    return result
 
 
 def _workspace(nbytes, device):
@@ -262,47 +293,24 @@ def kan_vq_workspace_bytes(heads, B, path=KAN_PATH_AUTO, strict=True) -> int:
 
 
 def kan_vq_layer_forward(layer: VQLayer, x, path=KAN_PATH_AUTO, ws=None, y=None):
-    torch = _torch()
-    assert x.dtype == torch.float32 and x.is_contiguous() and x.shape[1] == layer.n_in
-    B = x.shape[0]
-    if ws is None:
-        ws = _workspace(kan_vq_workspace_bytes([[layer]], B, path, strict=False), x.device)
-    if y is None:
-        y = _new_output((B, layer.n_out), x.device)
-    st = lib().kan_vq_layer_forward(C.byref(layer.desc), _ptr(x), B, _ptr(y), _ptr(ws),
-                                    0 if ws is None else ws.numel(), int(path), _stream_ptr())
-    _check(st, "kan_vq_layer_forward")
-    return y
+    if POISON_OUTPUTS:
+        y = _poisoned(y, (x.shape[0], layer.n_out), x.device)
+    return _done(_host().layer_forward(layer, x, path, ws, y), "kan_vq_layer_forward")
 
 
 def kan_vq_head_forward(heads, x, path=KAN_PATH_AUTO, ws=None, y=None):
     """heads: list of heads, each a list of VQLayer; x [B][in0] shared -> y [n_heads][B][out_last]."""
-    torch = _torch()
-    assert x.dtype == torch.float32 and x.is_contiguous()
-    arr, n_layers, n_heads = _desc_array(heads)
-    B = x.shape[0]
-    if ws is None:
-        ws = _workspace(kan_vq_workspace_bytes(heads, B, path, strict=False), x.device)
-    if y is None:
-        y = _new_output((n_heads, B, heads[0][-1].n_out), x.device)
-    st = lib().kan_vq_head_forward(arr, n_layers, n_heads, _ptr(x), B, _ptr(y), _ptr(ws),
-                                   0 if ws is None else ws.numel(), int(path), _stream_ptr())
-    _check(st, "kan_vq_head_forward")
-    return y
+    if POISON_OUTPUTS:
+        y = _poisoned(y, (len(heads), x.shape[0], heads[0][-1].n_out), x.device)
+    return _done(_host().head_forward(heads, x, path, ws, y), "kan_vq_head_forward")
 
 
 def kan_vq_head_forward_static(heads, x, path=KAN_PATH_AUTO, y=None):
     """kan_vq_head_forward on the library's own fixed scratch array: no workspace argument, and the
     call itself allocates nothing when y is given."""
-    torch = _torch()
-    assert x.dtype == torch.float32 and x.is_contiguous()
-    arr, n_layers, n_heads = _desc_array(heads)
-    B = x.shape[0]
-    if y is None:
-        y = _new_output((n_heads, B, heads[0][-1].n_out), x.device)
-    st = lib().kan_vq_head_forward_static(arr, n_layers, n_heads, _ptr(x), B, _ptr(y), int(path), _stream_ptr())
-    _check(st, "kan_vq_head_forward_static")
-    return y
+    if POISON_OUTPUTS:
+        y = _poisoned(y, (len(heads), x.shape[0], heads[0][-1].n_out), x.device)
+    return _done(_host().head_forward_static(heads, x, path, y), "kan_vq_head_forward_static")
 
 
 def kan_dense_workspace_bytes(n_in, n_out, B) -> int:
@@ -314,18 +322,9 @@ def kan_dense_workspace_bytes(n_in, n_out, B) -> int:
 
 def kan_dense_layer_forward(coef, x, ws=None, y=None):
     """coef [in][out][10] float32, x [B][in] float32 -> y [B][out]."""
-    torch = _torch()
-    assert coef.dtype == torch.float32 and coef.is_contiguous() and x.is_contiguous()
-    n_in, n_out, g = coef.shape
-    B = x.shape[0]
-    if ws is None:
-        ws = _workspace(kan_dense_workspace_bytes(n_in, n_out, B), x.device)
-    if y is None:
-        y = _new_output((B, n_out), x.device)
-    st = lib().kan_dense_layer_forward(_ptr(coef), n_in, n_out, g, _ptr(x), B, _ptr(y), _ptr(ws),
-                                       0 if ws is None else ws.numel(), _stream_ptr())
-    _check(st, "kan_dense_layer_forward")
-    return y
+    if POISON_OUTPUTS:
+        y = _poisoned(y, (x.shape[0], coef.shape[1]), x.device)
+    return _done(_host().dense_layer_forward(coef, x, ws, y), "kan_dense_layer_forward")
 
 
 def kan_vq_debug_gather(layer: VQLayer, want_rows=True):
@@ -374,21 +373,7 @@ def kan_vq_prepare(layer: VQLayer, out=None):
 def kan_vq_assign(coef, codebook, ws=None):
     """coef [in][out][10] float32, codebook [K][10] float32 (CUDA tensors) ->
     (idx int16/int32 carrying uint16/uint32 bits [in][out], gain float32 [in][out], bias float32 [in][out])."""
-    torch = _torch()
-    assert coef.dtype == torch.float32 and coef.is_contiguous() and coef.shape[2] == 10
-    assert codebook.dtype == torch.float32 and codebook.is_contiguous() and codebook.shape[1] == 10
-    n_in, n_out, _ = coef.shape
-    K = codebook.shape[0]
-    u16 = K <= 65536
-    idx = torch.empty((n_in, n_out), dtype=torch.int16 if u16 else torch.int32, device=coef.device)
-    gain = torch.empty((n_in, n_out), dtype=torch.float32, device=coef.device)
-    bias = torch.empty((n_in, n_out), dtype=torch.float32, device=coef.device)
-    if ws is None:
-        ws = _workspace(lib().kan_vq_assign_workspace_bytes(K), coef.device)
-    st = lib().kan_vq_assign(_ptr(coef), n_in, n_out, _ptr(codebook), K, KAN_U16 if u16 else KAN_U32, _ptr(idx),
-                             _ptr(gain), _ptr(bias), _ptr(ws), ws.numel(), _stream_ptr())
-    _check(st, "kan_vq_assign")
-    return idx, gain, bias
+    return _done(_host().assign(coef, codebook, ws), "kan_vq_assign")
 
 
 def kan_vq_reconstruction_r2(coef, codebook, idx, gain, bias) -> float:

@@ -1,4 +1,5 @@
-"""Builds libkan_mi355x.so (gfx950) in-tree with hipcc.
+"""Builds libkan_mi355x.so (gfx950) in-tree with hipcc, and the extension module _kan_host.so (host
+code of the binding's per-request calls) beside it with g++ against the installed torch.
 
     python -m paper_2512_15742_amd.build
 
@@ -18,6 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libkan_mi355x.so")
+HOST = os.path.join(HERE, "_kan_host.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 COMMON = [
@@ -65,9 +67,27 @@ def build(verbose: bool = True, extra_flags=(), jobs: int = 6) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
+    build_host()
     if verbose:
-        print(f"built {LIB}")
+        print(f"built {LIB} and {HOST}")
     return LIB
+
+
+def build_host() -> str:
+    """The extension module: plain C++ against torch's headers and this library's C-ABI."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-isystem", os.path.join(t, "include"), "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "kan_host.cpp"), "-o", HOST, "-L" + os.path.join(t, "lib"), "-L" + HERE,
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on kan_host.cpp:\n" + r.stdout + r.stderr)
+    return HOST
 
 
 if __name__ == "__main__":

@@ -7,6 +7,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
+# outputs that the binding allocates start as NaN in the tests: one that no kernel wrote fails them
+os.environ.setdefault("KAN_POISON_OUTPUTS", "1")
+
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: test needs a real MI355X (run with -m gpu)")
