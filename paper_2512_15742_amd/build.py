@@ -39,9 +39,8 @@ UNITS = [
     ("kan_fused.hip", "kan_fused_chained.o", ["-DKAN_FUSED_CH=1"]),
     ("kan_bucket.hip", "kan_bucket.o", []),
     ("kan_assign.hip", "kan_assign.o", []),
-    ("kan_gather.hip", "kan_gather_bt1.o", ["-DKAN_BT=1"]),
-    ("kan_gather.hip", "kan_gather_bt4.o", ["-DKAN_BT=4"]),
-    ("kan_gather.hip", "kan_gather_bt16.o", ["-DKAN_BT=16"]),
+    ("kan_gather.hip", "kan_gather.o", []),
+    ("kan_dense.hip", "kan_dense.o", []),
 ]
 
 

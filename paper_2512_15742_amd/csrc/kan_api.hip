@@ -106,7 +106,7 @@ kan_status validate_layer(const kan_vq_layer* L) {
 // Everything below is a pure function of shapes, dtypes, batch, head count and
 // pointer alignment, so the workspace query and the forward call always agree.
 
-enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5 };
+enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5, kPlanDense = 6 };
 
 struct LayerPlan {
   GatherCfg cfg;
@@ -135,8 +135,7 @@ void gather_geometry(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, 
   p.n_bt = (int)((B + p.cfg.bt - 1) / p.cfg.bt);
   const long long base = (long long)n_heads * p.n_jt * p.n_bt;
   long long chunks = (kTargetWorkgroups + base - 1) / (base > 0 ? base : 1);
-  const int rows_per_wave = p.cfg.bt == 1 ? 4 : 2;
-  const long long max_by_rows = n_in / (wi * rows_per_wave);
+  const long long max_by_rows = n_in / (wi * 4);
   const long long max_by_bytes = (long long)n_in * bytes_per_edge / (16 * (B > 0 ? B : 1));
   if (chunks > max_by_rows) chunks = max_by_rows;
   if (chunks > max_by_bytes) chunks = max_by_bytes;
@@ -147,6 +146,7 @@ void gather_geometry(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, 
   p.n_chunks = (n_in + rows - 1) / rows;
 }
 
+// VQ layers at batch 1.
 LayerPlan plan_gather(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code,
                       bool vec_ok) {
   LayerPlan p;
@@ -155,10 +155,10 @@ LayerPlan plan_gather(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
   p.cfg.idx_u32 = idx_u32;
   p.cfg.gb_kind = gb_kind;
   p.cfg.code = code;
-  p.cfg.bt = B <= 1 ? 1 : (B <= 4 ? 4 : 16);
-  p.name = p.cfg.bt == 1 ? "kan_gather_bt1" : (p.cfg.bt == 4 ? "kan_gather_bt4" : "kan_gather_bt16");
-  const int bytes_per_edge = code == kDense ? 40 : (idx_u32 ? 4 : 2) + 2 * gb_bytes(gb_kind);
-  const int jpl_max = p.cfg.bt == 16 ? 4 : 8;
+  p.cfg.bt = 1;
+  p.name = "kan_gather_bt1";
+  const int bytes_per_edge = (idx_u32 ? 4 : 2) + 2 * gb_bytes(gb_kind);
+  const int jpl_max = 8;
   // Widest per-lane vector that divides the row and still gives the chip enough workgroups;
   // narrower vectors mean more output tiles (load width does not matter to the stream).
   int best = 1;
@@ -191,9 +191,14 @@ constexpr int kFusedMinWgsPerHead = 20;      // fused kernel, several heads: wor
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
 // its second tile of 64 samples (config 3: 97 us at 64, 113 at 80; config 2: 33 and 57).
 constexpr int64_t kSplitMinBatch = 65;
-// The dense baseline's switch from its fp32 FMA kernel (config 2's twin: 35 us at batch 16, 54 at 24;
-// the split form 35-37 us anywhere below batch 64).
+// Dense baseline: fp32 operands up to 16 samples (one tile of the fp32 instruction), split operands above; one pass
+// over the coefficients per tile of 64 samples up to batch 128, on small layers (which do not fill the chip with the
+// tiles of the streaming form) up to 256, converted records above.  One pass against records: 2048 x 512 at batch
+// 128 / 192 29.7 / 64.1 against 38.8 / 41.7 us, 4096 x 1024 at 128 / 192 107 / 241 against 110 / 137, 500 x 333 at
+// 192 / 256 23.4 / 28.0 against 36.0 / 35.5, 2048 x 64 22.9 / 27.9 against 30.4 / 31.7.
 constexpr int64_t kDenseSplitMinBatch = 17;
+constexpr int64_t kDenseOnePassMaxBatch = 128, kDenseOnePassSmallMaxBatch = 256;
+constexpr long long kDenseOnePassSmallEdges = 1ll << 18;
 constexpr int64_t kAutoMfmaBatch = 32;    // KAN_PATH_AUTO switches to the matrix cores from here (measured crossover 16-32)
 
 LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3 = false) {
@@ -439,15 +444,6 @@ struct WsLayout {
 size_t mfma_cf_records(int n_in, int n_out) { return (size_t)((n_in + 15) / 16) * 20 * (size_t)n_out; }
 size_t mfma_bp_floats(int n_in, int n_out) { return (size_t)((n_in + kMfmaPrepRows - 1) / kMfmaPrepRows) * n_out; }
 
-hipError_t launch_gather(const LayerPlan& p, const GatherArgs& a, int heads, hipStream_t s) {
-  dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
-  switch (p.cfg.bt) {
-    case 1: return launch_gather_bt1(p.cfg, a, grid, s);
-    case 4: return launch_gather_bt4(p.cfg, a, grid, s);
-    default: return launch_gather_bt16(p.cfg, a, grid, s);
-  }
-}
-
 // Pointers of the scratch regions for the current call.
 struct WsPtrs {
   float* hid[2];
@@ -632,6 +628,19 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
     if (chain.in_parts > 1) st = run(p.name, s, [&] { return launch_fused_chained(p.cfg, f, f32, grid, s); });
     else st = run(p.name, s, [&] { return launch_fused(p.cfg, f, f32, grid, s); });
+  } else if (p.kind == kPlanDense) {
+    DenseArgs d;
+    d.coef = (const float*)a.h[0].cb;
+    d.x = a.x;
+    d.dst = dst;
+    d.dst_chunk_stride = dst_chunk_stride;
+    d.n_in = a.n_in;
+    d.n_out = a.n_out;
+    d.B = a.B;
+    d.rows_per_chunk = p.rows_per_chunk;
+    d.n_jt = p.n_jt;
+    dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks);
+    st = run(p.name, s, [&] { return launch_dense(d, p.cfg.bt, grid, s); });
   } else {
     a.dst = dst;
     a.dst_head_stride = dst_head_stride;
@@ -640,7 +649,8 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     a.x_parts = chain.in_parts;
     a.x_part_stride = chain.in_part_stride;
     a.x_tanh = chain.in_tanh;
-    st = run(p.name, s, [&] { return launch_gather(p, a, heads, s); });
+    dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
+    st = run(p.name, s, [&] { return launch_gather(p.cfg, a, grid, s); });
   }
   if (st != KAN_OK || !split || chain.out) return st;
   return run("kan_reduce", s, [&] {
@@ -669,8 +679,7 @@ bool chained(const std::vector<LayerPlan>& plans, int l, int n_heads, const kan_
   // the vector-ALU kernel at batch 1: the threads that share a row of the basis table split the
   // slices; few output tiles (each adds the slices again)
   if (plans[l + 1].kind == kPlanGather)
-    return plans[l + 1].cfg.bt == 1 && plans[l + 1].cfg.code != kDense && plans[l].n_chunks <= kGatherChainMaxParts &&
-           plans[l + 1].n_jt <= 4;
+    return plans[l].n_chunks <= kGatherChainMaxParts && plans[l + 1].n_jt <= 4;
   return plans[l + 1].kind == kPlanMfma && plans[l].n_chunks <= kMaxChainedSlices;
 }
 
@@ -967,16 +976,35 @@ kan_status kan_vq_layer_forward(const kan_vq_layer* L, const float* x, int64_t B
   return kan_vq_head_forward(L, 1, 1, x, B, y, ws, ws_bytes, path, stream);
 }
 
-// The dense baseline: the fp32 FMA kernel, and from kDenseSplitMinBatch the split-operand matrix-core
-// form the precise VQ path uses (a converter of the coefficients in place of gather + dequantise).
+// The dense baseline: the one-pass kernels of kan_dense.hip (fp32 operands up to 16 samples, split operands above)
+// while reading the coefficients once per tile of 64 samples costs less than converting them, from there the
+// split-operand streaming form the precise VQ path uses (a converter of the coefficients in place of gather +
+// dequantise).
 static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
-  if (B >= kDenseSplitMinBatch) {
+  if (B > kDenseOnePassMaxBatch && (B > kDenseOnePassSmallMaxBatch || (long long)in * out > kDenseOnePassSmallEdges)) {
     LayerPlan p = plan_mfma(in, out, B, 1, 0, 0, kDense, true);
     p.name = "kan_dense_split";
     return p;
   }
-  LayerPlan p = plan_gather(in, out, B, 1, 0, 0, kDense, true);
-  p.name = "kan_dense";
+  LayerPlan p;
+  p.mfma = false;
+  p.kind = kPlanDense;
+  p.name = B < kDenseSplitMinBatch ? "kan_dense" : "kan_dense_split";
+  p.cfg = GatherCfg{B < kDenseSplitMinBatch ? 16 : (B <= 32 ? 32 : 64), 1, 1, 0, 0, kDense};
+  const int tile_n = p.cfg.bt == 16 ? 16 : 64, step = p.cfg.bt == 16 ? kDenseStep16 : kDenseStep64;
+  p.n_jt = (out + tile_n - 1) / tile_n;
+  p.n_bt = (int)((B + p.cfg.bt - 1) / p.cfg.bt);
+  // Workgroups for the whole chip (two per CU of four waves, one of eight), while the partial sums stay below a
+  // quarter of the coefficients.
+  const long long base = (long long)p.n_jt * p.n_bt, target = p.cfg.bt == 16 ? kTargetWorkgroups : kTargetWorkgroups / 2;
+  long long chunks = (target + base - 1) / base;
+  const long long max_by_rows = (in + step - 1) / step, max_by_bytes = (long long)in * 40 / (16 * B);
+  if (chunks > max_by_rows) chunks = max_by_rows;
+  if (chunks > max_by_bytes) chunks = max_by_bytes;
+  if (chunks < 1) chunks = 1;
+  const int rows = (int)((in + chunks - 1) / chunks);
+  p.rows_per_chunk = (rows + step - 1) / step * step;
+  p.n_chunks = (in + p.rows_per_chunk - 1) / p.rows_per_chunk;
   return p;
 }
 

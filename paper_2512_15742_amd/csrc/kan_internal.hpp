@@ -27,7 +27,7 @@ constexpr int gb_bytes(int kind) { return kind == kGbF32 ? 4 : (kind == kGbF16 ?
 
 // ---- gather path (fp32 vector arithmetic) --------------------------------------
 struct GatherCfg {
-  int bt;          // batch tile: 1, 4 or 16 samples per workgroup
+  int bt;          // batch tile: samples per workgroup
   int jpl;         // consecutive outputs per lane: 1, 2, 4 or 8
   int wj;          // waves of the 4-wave workgroup laid along j (1, 2 or 4); 4/wj along i
   int idx_u32;     // 0: uint16 indices, 1: uint32
@@ -47,7 +47,7 @@ struct GatherArgs {
   int apply_tanh;              // only honoured when the kernel writes final values
   long long cb_bytes;          // codebook bytes per head (0: no L2 warm-up of the codebook)
   int rule;                    // edge function: 0 cubic B-spline, 1 two-tap linear interpolation
-  // Chained input (VQ layers at batch tile 1 only): x is the previous layer's partial sums,
+  // Chained input: x is the previous layer's partial sums,
   // [head][x_parts][B][n_in]; a workgroup adds the slices of its own rows in a fixed order and
   // squashes them (x_tanh) while it builds its basis data.
   int x_parts;                 // 0 or 1: plain x
@@ -57,9 +57,22 @@ struct GatherArgs {
 };
 constexpr int kGatherChainMaxParts = 256;
 
-hipError_t launch_gather_bt1(const GatherCfg&, const GatherArgs&, dim3 grid, hipStream_t);
-hipError_t launch_gather_bt4(const GatherCfg&, const GatherArgs&, dim3 grid, hipStream_t);
-hipError_t launch_gather_bt16(const GatherCfg&, const GatherArgs&, dim3 grid, hipStream_t);
+hipError_t launch_gather(const GatherCfg&, const GatherArgs&, dim3 grid, hipStream_t);
+
+// ---- dense baseline, tiles of up to 64 samples -----------------------------------
+struct DenseArgs {
+  const float* coef;           // [n_in][n_out][10]
+  const float* x;              // [B][n_in]
+  float* dst;                  // y, or partial sums (slices dst_chunk_stride elements apart)
+  long long dst_chunk_stride;
+  int n_in, n_out, B;
+  int rows_per_chunk;          // inputs per workgroup, a multiple of kDenseStep16 (tiles of 16 samples) / kDenseStep64
+  int n_jt;                    // output tiles; blockIdx.x = batch_tile * n_jt + jt
+};
+// Tiles of 16 samples: 16 outputs, four waves of 16 inputs a step.  Tiles of 32 and 64: 64 outputs, two groups of
+// 16 inputs a step.
+constexpr int kDenseStep16 = 64, kDenseStep64 = 32;
+hipError_t launch_dense(const DenseArgs&, int tile_m, dim3 grid, hipStream_t);   // tile_m: 16, 32 or 64 samples
 
 // ---- matrix-core path (fp16 operands, fp32 accumulate) ----------------------------
 constexpr int kMfmaPrepRows = 32;   // input rows per partial bias sum (and per prep workgroup)

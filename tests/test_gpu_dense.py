@@ -1,0 +1,47 @@
+"""Dense baseline, one-pass kernels (kan_dense.hip): tiles of 16, 32 and 64 samples at the edges of
+their tiles, against the oracle's dense layer."""
+import numpy as np
+import pytest
+
+from oracle import kan_oracle as ko
+from paper_2512_15742_amd import synth
+
+from kan_testlib import TOL_FP32, check_dense_output, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def kb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_15742_amd import binding
+    binding.lib()
+    return binding
+
+
+# (inputs: one, below / at / past a step of 16, of a wave group's 64 and of several chunks; outputs: one, tiles of
+# 16 and 64 and one past them; batches: every tile, full and one past, two tiles of 64 and the last of the rule)
+@pytest.mark.parametrize("n_in,n_out,B", [(1, 1, 1), (15, 16, 2), (16, 17, 16), (65, 15, 7), (129, 33, 16), (2050, 48, 9),
+                                          (1, 1, 17), (17, 63, 32), (32, 64, 33), (33, 65, 64), (130, 129, 65),
+                                          (300, 70, 128), (97, 40, 129), (64, 20, 256)])
+def test_one_pass_kernels(kb, n_in, n_out, B):
+    rng = np.random.default_rng(n_in * 7 + n_out + B)
+    coef = (rng.standard_normal((n_in, n_out, 10)) * rng.uniform(1e-3, 2.0, (n_in, n_out, 1))).astype(np.float32)
+    x = synth.make_x(B, B, n_in)
+    x[0, 0], x[-1, -1] = 1.0, -1.0
+    x[B // 2, n_in // 2] = np.float32(1.0 / 7.0)          # beside a knot
+    y = kb.kan_dense_layer_forward(to_dev(coef), to_dev(x)).cpu().numpy()
+    check_dense_output(y, x, coef, TOL_FP32)
+
+
+def test_fp32_operands_have_no_fp16_range(kb):
+    """Up to 16 samples the operands stay fp32: coefficients beyond fp16's range on either side."""
+    rng = np.random.default_rng(5)
+    coef = (rng.standard_normal((40, 24, 10)) * 10.0 ** rng.uniform(-9, 9, (1, 24, 1))).astype(np.float32)
+    x = synth.make_x(6, 16, 40)
+    y = kb.kan_dense_layer_forward(to_dev(coef), to_dev(x)).cpu().numpy()
+    y_ref, A = ko.dense_layer_forward(coef, x, return_abs=True)
+    assert np.all(np.abs(y - y_ref) <= TOL_FP32 * A)
