@@ -29,7 +29,7 @@ EXPORTS = [
     "kan_dense_workspace_bytes", "kan_dense_layer_forward", "kan_vq_head_forward",
     "kan_vq_debug_gather", "kan_vq_count_bad_indices", "kan_prof_begin", "kan_prof_end",
     "kan_status_string", "kan_vq_planned_kernel", "kan_dense_planned_kernel", "kan_vq_prepared_bytes", "kan_vq_prepare", "kan_pli_basis",
-    "kan_vq_assign_workspace_bytes", "kan_vq_assign", "kan_vq_reconstruction_workspace_bytes",
+    "kan_vq_assign_workspace_bytes", "kan_vq_assign_fast_workspace_bytes", "kan_vq_assign", "kan_vq_reconstruction_workspace_bytes",
     "kan_vq_reconstruction_sums", "kan_basis_window", "kan_vq_coef_range", "kan_vq_head_forward_static",
 ]
 KAN_LAYER_NO_COLUMN = 1
@@ -127,6 +127,8 @@ def lib():
         L.kan_vq_prepare.restype = I32
         L.kan_vq_assign_workspace_bytes.argtypes = [I32]
         L.kan_vq_assign_workspace_bytes.restype = SZ
+        L.kan_vq_assign_fast_workspace_bytes.argtypes = [I32, I32, I32]
+        L.kan_vq_assign_fast_workspace_bytes.restype = SZ
         L.kan_vq_assign.argtypes = [P, I32, I32, P, I32, I32, P, P, P, P, SZ, P]
         L.kan_vq_assign.restype = I32
         L.kan_vq_reconstruction_workspace_bytes.argtypes = [I32, I32]

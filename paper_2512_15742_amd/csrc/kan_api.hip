@@ -1087,6 +1087,15 @@ kan_status check_assign_shapes(int32_t in, int32_t out, int32_t K, int32_t idx_d
 }
 }  // namespace
 
+size_t kan_vq_assign_fast_workspace_bytes(int32_t in, int32_t out, int32_t K) {
+  if (check_assign_shapes(in, out, K, KAN_U32) != KAN_OK) return (size_t)-1;
+  const long long E = (long long)in * out;
+  const size_t least = kan_vq_assign_workspace_bytes(K);
+  if (!assign_bounded_ok(E, K)) return least;
+  const size_t bounded = round_up(assign_bounded_bytes(E, K), 256);
+  return bounded > least ? bounded : least;
+}
+
 kan_status kan_vq_assign(const float* coef, int32_t in, int32_t out, const float* codebook, int32_t K,
                          int32_t idx_dtype, void* idx, float* gain, float* bias, void* ws, size_t ws_bytes,
                          void* stream) {
@@ -1098,7 +1107,10 @@ kan_status kan_vq_assign(const float* coef, int32_t in, int32_t out, const float
     return KAN_ERR_SHAPE;
   if (!ws || !aligned(ws, 256) || ws_bytes < kan_vq_assign_workspace_bytes(K)) return KAN_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
+  const bool bounded = assign_bounded_ok((long long)in * out, K) && ws_bytes >= kan_vq_assign_fast_workspace_bytes(in, out, K);
   return run("kan_vq_assign", s, [&] {
+    if (bounded)
+      return launch_assign_bounded(coef, (long long)in * out, codebook, K, idx_dtype == KAN_U32, idx, gain, bias, ws, s);
     return launch_assign(coef, (long long)in * out, codebook, K, idx_dtype == KAN_U32, idx, gain, bias, ws, s);
   });
 }

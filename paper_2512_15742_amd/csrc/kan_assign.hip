@@ -20,6 +20,9 @@
 // resolve to the lower index within a half-wave's rows; which of two half-waves' equal scores
 // wins is decided by index at the end.
 
+// That is the whole search (kan_assign_kernel).  Large codebooks take the bounded search further down, which
+// finds the same shapes from a small part of the scores.
+
 #include "kan_device.hpp"
 #include "kan_internal.hpp"
 #include "kan_mfma_common.hpp"
@@ -30,6 +33,7 @@ namespace {
 constexpr int kAssignThreads = 256;
 constexpr int kEdgeTilesPerWave = 4;                                   // 4 x 32 edges per wave
 constexpr int kEdgesPerWg = (kAssignThreads / kWave) * kEdgeTilesPerWave * 32;   // 512
+constexpr long long kSplitMaxEdges = 1ll << 17;                         // whole search: up to here eight waves share their edges
 constexpr int kSlots = 32;                                             // contraction length
 
 __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
@@ -37,25 +41,18 @@ __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
   lo = (_Float16)(v - (float)hi);
 }
 
-// Centroid-side operands in MFMA A-fragment order: record [(tile * 2 + kstep) * 64 + lane]
-// holds slots kstep*16 + (lane/32)*8 .. +8 of centroid tile*32 + (lane & 31).  Rows past K get
-// a hugely negative norm term so that they never win.
-__global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __restrict__ cb, int K, int n_tiles,
-                                                              uint4* __restrict__ out) {
-  const long long rec = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (rec >= (long long)n_tiles * 2 * 64) return;
-  const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
-  const int c = (int)(rec >> 7) * 32 + (lane & 31);
-  const int s0 = ks * 16 + (lane >> 5) * 8;
+// Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) a hugely negative norm term,
+// so that the row never wins.
+__device__ __forceinline__ uint4 centroid_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
   _Float16 v[8];
   float nrm = 0.f;
   float row[kG];
 #pragma unroll
   for (int m = 0; m < kG; ++m) {
-    row[m] = c < K ? cb[(long long)c * kG + m] : 0.f;
+    row[m] = there ? cb[c * kG + m] : 0.f;
     nrm = fmaf(row[m], row[m], nrm);
   }
-  const float half_norm = c < K ? -0.5f * nrm : -30000.0f;
+  const float half_norm = there ? -0.5f * nrm : -30000.0f;
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int s = s0 + t;
@@ -69,52 +66,130 @@ __global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __res
     }
   }
   h16x8 pk = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
-  out[rec] = __builtin_bit_cast(uint4, pk);
+  return __builtin_bit_cast(uint4, pk);
+}
+
+// The same terms for the tiles of the bounded search, in two instructions of which the first alone bounds the score
+// from above: it has the products of the high parts, half of the low ones, and the norm raised by what the others can
+// amount to (2^-11 of |C| from the low parts of either side, and what lies below fp16's normal range).
+//     shape  [ hi(C) (10) | raised -|C|^2/2 | lo(C) 0..4 ]   [ lo(C) 5..9 | hi(C) (10) | rest of the norm ]
+//     edge   [ hi(n) (10) |        1        | hi(n) 0..4 ]   [ hi(n) 5..9 | lo(n) (10) |         1        ]
+__device__ __forceinline__ uint4 tile_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
+  h16x8 v;
+  float row[kG], nrm = 0.f;
+#pragma unroll
+  for (int m = 0; m < kG; ++m) {
+    row[m] = there ? cb[c * kG + m] : 0.f;
+    nrm = fmaf(row[m], row[m], nrm);
+  }
+  const float half_norm = there ? -0.5f * nrm : -30000.0f;
+  float up = half_norm + 1.3e-3f * sqrtf(nrm) + 1e-4f;
+  up = (float)(_Float16)(up + fabsf(up) * (1.0f / 1024.0f));        // (rounds to half a unit: never below)
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int s = s0 + t;
+    float src = s == 10 ? up : half_norm - up;
+    bool low = false;
+#pragma unroll
+    for (int m = 0; m < kG; ++m)
+      if (s == m || s == 11 + m || s == 21 + m) {
+        src = row[m];
+        low = s >= 11 && s < 21;
+      }
+    _Float16 hi, lo;
+    split_h(src, hi, lo);
+    v[t] = low ? lo : hi;
+  }
+  return __builtin_bit_cast(uint4, v);
+}
+
+// Centroid-side operands in MFMA A-fragment order: record [(tile * 2 + kstep) * 64 + lane]
+// holds slots kstep*16 + (lane/32)*8 .. +8 of centroid tile*32 + (lane & 31).
+__global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __restrict__ cb, int K, int n_tiles,
+                                                              const uint32_t* __restrict__ n_list,
+                                                              uint4* __restrict__ out) {
+  if (n_list && *n_list == 0) return;
+  const long long rec = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (rec >= (long long)n_tiles * 2 * 64) return;
+  const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
+  const int c = (int)(rec >> 7) * 32 + (lane & 31);
+  out[rec] = centroid_slots(cb, c, c < K, ks * 16 + (lane >> 5) * 8);
+}
+
+// Step 1 of an edge: bias = mean, gain = norm of the centred grid, direction = centred / gain.
+__device__ __forceinline__ void normalise(const float* __restrict__ coef, float (&c)[kG], float& mean, float& g) {
+#pragma unroll
+  for (int m = 0; m < kG / 2; ++m) {
+    const float2 v = ((const float2*)coef)[m];
+    c[2 * m] = v.x;
+    c[2 * m + 1] = v.y;
+  }
+  mean = 0.f;
+#pragma unroll
+  for (int m = 0; m < kG; ++m) mean += c[m];
+  mean /= (float)kG;       // a true division: the mean of ten equal values is that value
+  float ss = 0.f;
+#pragma unroll
+  for (int m = 0; m < kG; ++m) {
+    c[m] -= mean;
+    ss = fmaf(c[m], c[m], ss);
+  }
+  g = sqrtf(ss);
+  const float inv = g > 0.f ? 1.0f / g : 0.f;
+#pragma unroll
+  for (int m = 0; m < kG; ++m) c[m] *= inv;
+}
+
+__device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+// Maximum of a lane's 16 scores: 8 three-input maxima.
+__device__ __forceinline__ float max_of(const f32x16& v) {
+  const float m0 = max3(v[0], v[1], v[2]), m1 = max3(v[3], v[4], v[5]);
+  const float m2 = max3(v[6], v[7], v[8]), m3 = max3(v[9], v[10], v[11]);
+  const float m4 = max3(v[12], v[13], v[14]);
+  return max3(max3(m0, m1, m2), m3, max3(m4, v[15], -3.0e38f));
+}
+// The first register that holds it.
+__device__ __forceinline__ int row_of(const f32x16& v, float m) {
+  int r_best = 15;
+#pragma unroll
+  for (int r = 14; r >= 0; --r) r_best = v[r] == m ? r : r_best;
+  return r_best;
 }
 
 struct AssignArgs {
   const float* coef;        // [E][10]
   const uint4* cent;        // prepared centroid operands
   long long E;
+  const uint32_t* list;     // null, or the edges to serve: list[0 .. *n_list - 1], E the most there can be
+  const uint32_t* n_list;
   int n_tiles;              // ceil(K / 32)
   void* idx;
   float* gain;
   float* bias;
 };
 
-__device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
-
-template <typename IdxT>
-__global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_kernel(const AssignArgs a) {
-  // edge-side operands of the workgroup's 512 edges: [edge][32 slots] fp16
-  __shared__ __attribute__((aligned(16))) _Float16 sB[kEdgesPerWg * kSlots];
+// SPLIT = 1: four waves with 128 edges of their own each.  SPLIT > 1: that many waves share 128 edges and take the
+// centroid tiles in turn: with few edges a wave's chain of tiles is what takes the time (K = 4,096 and 2^11 / 2^16 /
+// 2^17 edges 21 / 34 / 58 us with eight waves against 85 / 89 / 91 us, with 2^18 edges 104 against 107, above it loses).
+template <typename IdxT, int SPLIT>
+__global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void kan_assign_kernel(const AssignArgs a) {
+  constexpr int kThreads = SPLIT > 1 ? SPLIT * kWave : kAssignThreads;
+  constexpr int kEdges = SPLIT > 1 ? kEdgeTilesPerWave * 32 : kEdgesPerWg;
+  // edge-side operands of the workgroup's edges: [edge][32 slots] fp16
+  __shared__ __attribute__((aligned(16))) _Float16 sB[kEdges * kSlots];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const long long e_wg = (long long)blockIdx.x * kEdgesPerWg;
+  const int first_tile = SPLIT > 1 ? 0 : wave * kEdgeTilesPerWave;        // of the wave's edges
+  const long long e_wg = (long long)blockIdx.x * kEdges;
+  const long long E = a.list ? (long long)*a.n_list : a.E;
+  if (e_wg >= E) return;
 
   // ---- step 1: bias = mean, gain = norm of the centred grid, n = centred / gain ------------
-  for (int q = tid; q < kEdgesPerWg; q += kAssignThreads) {
-    const long long e = e_wg + q;
-    const long long ec = e < a.E ? e : a.E - 1;
-    float c[kG];
-#pragma unroll
-    for (int m = 0; m < kG / 2; ++m) {
-      const float2 v = ((const float2*)(a.coef + ec * kG))[m];
-      c[2 * m] = v.x;
-      c[2 * m + 1] = v.y;
-    }
-    float mean = 0.f;
-#pragma unroll
-    for (int m = 0; m < kG; ++m) mean += c[m];
-    mean /= (float)kG;       // a true division: the mean of ten equal values is that value
-    float ss = 0.f;
-#pragma unroll
-    for (int m = 0; m < kG; ++m) {
-      c[m] -= mean;
-      ss = fmaf(c[m], c[m], ss);
-    }
-    const float g = sqrtf(ss);
-    const float inv = g > 0.f ? 1.0f / g : 0.f;
-    if (e < a.E) {
+  for (int q = tid; q < kEdges; q += kThreads) {
+    const long long at = e_wg + q, e = a.list ? (long long)a.list[min(at, E - 1)] : min(at, E - 1);
+    float c[kG], mean, g;
+    normalise(a.coef + e * kG, c, mean, g);
+    if (at < E) {
       a.gain[e] = g;
       a.bias[e] = mean;
     }
@@ -122,7 +197,7 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_kernel(const Ass
 #pragma unroll
     for (int m = 0; m < kG; ++m) {
       _Float16 hi, lo;
-      split_h(c[m] * inv, hi, lo);
+      split_h(c[m], hi, lo);
       p[m] = hi;
       p[10 + m] = hi;
       p[20 + m] = lo;
@@ -138,7 +213,7 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_kernel(const Ass
   for (int nb = 0; nb < kEdgeTilesPerWave; ++nb)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      const int q = (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
+      const int q = (first_tile + nb) * 32 + (lane & 31);
       fb[nb][ks] = *(const h16x8*)(sB + q * kSlots + ks * 16 + (lane >> 5) * 8);
     }
 
@@ -167,34 +242,30 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_kernel(const Ass
     for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
       f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
-      // maximum of the lane's 16 scores: 8 three-input maxima
-      const float m0 = max3(acc[0], acc[1], acc[2]), m1 = max3(acc[3], acc[4], acc[5]);
-      const float m2 = max3(acc[6], acc[7], acc[8]), m3 = max3(acc[9], acc[10], acc[11]);
-      const float m4 = max3(acc[12], acc[13], acc[14]);
-      const float m = max3(max3(m0, m1, m2), m3, max3(m4, acc[15], -3.0e38f));
+      const float m = max_of(acc);
       // A new best is rare (the t-th tile improves a lane's running maximum with probability
       // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
       // it the lowest register, keeps a tie.
       if (m > best[nb]) {
-        int r_best = 15;
-#pragma unroll
-        for (int r = 14; r >= 0; --r) r_best = acc[r] == m ? r : r_best;
         best[nb] = m;
         best_tile[nb] = t;
-        best_row[nb] = r_best;
+        best_row[nb] = row_of(acc, m);
       }
     }
   };
   uint4 fa0[2], fa1[2];
-  load_tile(0, fa0);
-  load_tile(1, fa1);
-  for (int t = 0; t < a.n_tiles; t += 2) {
+  const int t0 = SPLIT > 1 ? wave : 0;
+  load_tile(t0, fa0);
+  load_tile(t0 + SPLIT, fa1);
+  for (int t = t0; t < a.n_tiles; t += 2 * SPLIT) {
     score_tile(t, fa0);
-    load_tile(t + 2, fa0);
-    if (t + 1 < a.n_tiles) score_tile(t + 1, fa1);
-    load_tile(t + 3, fa1);
+    load_tile(t + 2 * SPLIT, fa0);
+    if (t + SPLIT < a.n_tiles) score_tile(t + SPLIT, fa1);
+    load_tile(t + 3 * SPLIT, fa1);
   }
 
+  __shared__ float s_best[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
+  __shared__ int s_id[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
   // ---- the two half-waves hold different rows of the same edges: keep the better one ------------
 #pragma unroll
   for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
@@ -204,10 +275,657 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_kernel(const Ass
     float sc = best[nb];
     const float sc_o = __shfl_xor(sc, 32, kWave);
     const int id_o = __shfl_xor(id, 32, kWave);
-    if (sc_o > sc || (sc_o == sc && id_o < id)) id = id_o;
-    const long long e = e_wg + (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
-    if (lane < 32 && e < a.E) ((IdxT*)a.idx)[e] = (IdxT)id;
+    if (sc_o > sc || (sc_o == sc && id_o < id)) {
+      id = id_o;
+      sc = sc_o;
+    }
+    const int q = (first_tile + nb) * 32 + (lane & 31);
+    if constexpr (SPLIT > 1) {
+      if (lane < 32) {
+        s_best[wave][q] = sc;
+        s_id[wave][q] = id;
+      }
+    } else {
+      const long long at = e_wg + q;
+      if (lane < 32 && at < E) ((IdxT*)a.idx)[a.list ? (long long)a.list[at] : at] = (IdxT)id;
+    }
   }
+  if constexpr (SPLIT > 1) {
+    __syncthreads();
+    const long long at = e_wg + tid;
+    if (tid < kEdges && at < E) {
+      float sc = s_best[0][tid];
+      int id = s_id[0][tid];
+#pragma unroll
+      for (int w = 1; w < SPLIT; ++w) {
+        const float o = s_best[w][tid];
+        const int io = s_id[w][tid];
+        if (o > sc || (o == sc && io < id)) {
+          sc = o;
+          id = io;
+        }
+      }
+      ((IdxT*)a.idx)[a.list ? (long long)a.list[at] : at] = (IdxT)id;
+    }
+  }
+}
+
+// ---- bounded search -------------------------------------------------------------------------------
+// The codebook is cut into cells (the shapes nearest to one of M = K / 32 sampled shapes, the cell's centre c)
+// and a cell into tiles of 32 shapes sorted by their distance to c.  A tile whose shapes all lie within R of c can be
+// left out for an edge n that knows a shape at distance d already when |n - c| > R + d; in scores (|n| = 1)
+//     n . c - |c|^2 / 2 + R^2 / 2 + R d  <  (1 - d^2) / 2 .
+// The left side is a product of an edge's vector (n, 1, d) with a tile's vector (c, (R^2 - |c|^2) / 2, R), so one
+// v_mfma_f32_32x32x16_f16 tests 32 edges against 32 tiles, the right side included; what the fp16 operands
+// round away is covered by a margin.  The edges are sorted by their nearest centre, so that the 32 of a wave ask for
+// about the same tiles, and a wave scores every tile that any of its edges asks for:
+//     (1) the tiles of the edges' own cells: seven of ten edges with 5 % noise find their shape here;
+//     (2) the tiles within R + min(d, the wave's mean d): finds nearly all of the others, whose d of step 1 alone
+//         would ask for a large part of the codebook;
+//     (3) where an edge is left with a larger d: what that one still asks for.
+// The scores are those of the whole search, and no tile that can hold the best one is left out.  A wave that would
+// visit more than kRestShare of the tiles hands its edges to the whole search, which shares a tile's operands among
+// four times as many: codebooks or grids that the cells do not separate cost what they did without them.
+//
+// What bounds it: instructions issued.  A wave of the search makes (tiles / 32) bound tests and visits about 250 of
+// 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each one matrix and about ten vector instructions; the
+// counters show every SIMD issuing something nearly all the time, the matrix pipe busy for a quarter of it.  What that
+// took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
+// scalar code 1057 us, one instruction a visit 1084, more loads in flight 998, tiles listed in LDS and taken in
+// pairs 818, the second instruction in place of vector arithmetic for near scores 761, six waves per SIMD
+// 690; cells of 64 instead of 32 shapes (the choice of the cells 154 -> 87 us).  The whole search takes 3.8 ms.
+
+constexpr int kCellShapes = 64;                   // shapes per cell on average
+constexpr int kCellMaxTiles = 16384;              // (a wave marks the tiles it has visited in LDS)
+constexpr float kRestShare = 0.7f, kMeanFactor = 1.0f;
+constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
+constexpr int kAhead = 2;                         // tiles in flight per wave
+constexpr int kSortThreads = 1024, kSortGroups = 64;
+constexpr int kBuildChunk = 1024;                 // members of a cell that are sorted together
+
+// Where the pieces of the search lie in the workspace.
+struct CellLayout {
+  int M;                   // cells, a multiple of 32
+  int tiles_max;
+  int groups[2];           // workgroups of the sort: over the shapes, over the edges
+  long long chunk[2];      // items per workgroup
+  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, rest, n_rest, whole, bytes;
+};
+
+size_t centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(uint4); }
+
+CellLayout cell_layout(long long E, int K) {
+  CellLayout g;
+  g.M = (K / kCellShapes + 31) / 32 * 32;
+  g.tiles_max = (K + 31) / 32 + g.M;
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    const size_t here = at;
+    at += (bytes + 255) / 256 * 256;
+    return here;
+  };
+  g.centres = take((size_t)g.M * 2 * sizeof(uint4));
+  g.frag = take((size_t)g.tiles_max * 2 * 64 * sizeof(uint4));
+  g.ids = take((size_t)g.tiles_max * 32 * 4);
+  g.bound = take((size_t)((g.tiles_max + 31) / 32) * 64 * sizeof(uint4));
+  g.member = take((size_t)K * 4);
+  g.perm = take((size_t)E * 4);
+  for (int p = 0; p < 2; ++p) {
+    const long long n = p ? E : K;
+    const long long groups = (n + kSortThreads - 1) / kSortThreads;
+    g.groups[p] = (int)(groups < kSortGroups ? groups : kSortGroups);
+    g.chunk[p] = (n + g.groups[p] - 1) / g.groups[p];
+    g.key[p] = take((size_t)n * 2);
+    g.hist[p] = take((size_t)g.groups[p] * (g.M + 1) * 4);
+    g.total[p] = take((size_t)(g.M + 1) * 4);
+    g.first[p] = take((size_t)(g.M + 1) * 4);
+  }
+  g.first_tile = take((size_t)(g.M + 1) * 4);
+  g.wg_least = take((size_t)((K + kEdgesPerWg - 1) / kEdgesPerWg) * 8);
+  g.least = take(4);
+  g.rest = take((size_t)E * 4);
+  g.n_rest = take(4);
+  g.whole = take(centroid_bytes(K));
+  g.bytes = at;
+  return g;
+}
+
+struct CellArgs {
+  const float* coef;
+  const float* cb;
+  long long E;
+  int K, M;
+  int shape_wgs;                 // kan_cells_kernel: workgroups over the shapes, in front of those over the edges
+  int groups[2];
+  long long chunk[2];
+  uint4* centres;                // operands of the centres
+  uint4* frag;                   // operands of the tiles
+  uint32_t* ids;                 // shape of every tile row
+  uint4* bound;                  // bound operands of the tiles
+  uint32_t* sorted[2];           // shapes, edges in the order of their cells
+  uint16_t* key[2];              // cell of every shape, edge (M: an edge without direction)
+  uint32_t *hist[2], *total[2], *first[2];
+  uint32_t* first_tile;          // [M + 1]
+  unsigned long long* wg_least;
+  uint32_t *rest, *n_rest;       // edges left to the whole search
+  uint32_t* least;               // shape of the smallest norm: the nearest to an edge of gain 0
+  void* idx;
+  float *gain, *bias;
+};
+
+// A row's sixteen slots as the two halves of a wave hold them.
+__device__ __forceinline__ uint4 pack_slots(const float (&v)[8]) {
+  h16x8 p;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) p[t] = (_Float16)v[t];
+  return __builtin_bit_cast(uint4, p);
+}
+__device__ __forceinline__ float fp16_of(float v) { return (float)(_Float16)v; }
+__device__ __forceinline__ float fp16_up(float v) {           // v >= 0: an fp16 number of at least v
+  return fp16_of(fmaf(v, 1.0f + 1.0f / 1024.0f, 1e-7f));
+}
+
+__device__ __forceinline__ const float* centre_row(const CellArgs& a, int m) {
+  return a.cb + (long long)m * a.K / a.M * kG;
+}
+
+// Centres as matrix operands [c (10) | hi, lo of -|c|^2/2 | 0 (4)]: fp16 is enough to choose a cell.
+__global__ __launch_bounds__(256) void kan_cell_centres_kernel(const CellArgs a) {
+  const int rec = blockIdx.x * 256 + threadIdx.x;
+  if (rec >= a.M * 2) return;
+  const float* c = centre_row(a, (rec >> 6) * 32 + (rec & 31));
+  float nrm = 0.f;
+#pragma unroll
+  for (int k = 0; k < kG; ++k) nrm = fmaf(c[k], c[k], nrm);
+  const float hn = -0.5f * nrm, hi = fp16_of(hn);
+  const float v0[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
+  const float v1[8] = {c[8], c[9], hi, hn - hi, 0.f, 0.f, 0.f, 0.f};
+  a.centres[rec] = (rec & 32) ? pack_slots(v1) : pack_slots(v0);
+}
+
+// Nearest centre of every shape and every edge; gains and biases of the edges.  Any cell is a valid one, so the
+// choice is cheap: the maxima of four rows each, the group's number in the low two bits of the mantissa, one running
+// maximum - sixteen vector instructions per 32 x 32 scores - and the four rows of the winning group
+// are told apart at the end.
+__global__ __launch_bounds__(kAssignThreads, 4) void kan_cells_kernel(const CellArgs a) {
+  __shared__ uint4 sB[kEdgesPerWg * 2];
+  __shared__ uint8_t s_flat[kEdgesPerWg];
+  __shared__ unsigned long long s_least;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool shapes = (int)blockIdx.x < a.shape_wgs;
+  const long long n = shapes ? a.K : a.E;
+  const long long first = (long long)(shapes ? blockIdx.x : blockIdx.x - a.shape_wgs) * kEdgesPerWg;
+  uint16_t* key = a.key[shapes ? 0 : 1];
+  if (tid == 0) s_least = ~0ull;
+  __syncthreads();
+  for (int q = tid; q < kEdgesPerWg; q += kAssignThreads) {
+    const long long e = first + q, ec = e < n ? e : n - 1;
+    float c[kG];
+    bool flat = false;
+    if (shapes) {
+      float nrm = 0.f;
+#pragma unroll
+      for (int m = 0; m < kG; ++m) {
+        c[m] = a.cb[ec * kG + m];
+        nrm = fmaf(c[m], c[m], nrm);
+      }
+      atomicMin(&s_least, ((unsigned long long)__float_as_uint(nrm) << 32) | (uint32_t)ec);
+    } else {
+      float mean, g;
+      normalise(a.coef + ec * kG, c, mean, g);
+      flat = !(g > 0.f);
+      if (e < n) {
+        a.gain[e] = g;
+        a.bias[e] = mean;
+      }
+    }
+    const float v0[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
+    const float v1[8] = {c[8], c[9], 1.f, 1.f, 0.f, 0.f, 0.f, 0.f};
+    sB[q * 2] = pack_slots(v0);
+    sB[q * 2 + 1] = pack_slots(v1);
+    s_flat[q] = flat;
+  }
+  __syncthreads();
+  if (shapes && tid == 0) a.wg_least[blockIdx.x] = s_least;
+
+  h16x8 fb[kEdgeTilesPerWave];
+  float best[kEdgeTilesPerWave];
+  int best_tile[kEdgeTilesPerWave];
+#pragma unroll
+  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+    const int q = (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
+    fb[nb] = __builtin_bit_cast(h16x8, sB[q * 2 + (lane >> 5)]);
+    best[nb] = -3.0e38f;
+    best_tile[nb] = 0;
+  }
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  const uint4* cp = a.centres + lane;
+  const int n_tiles = a.M / 32;
+  uint4 next = cp[0];
+  for (int t = 0; t < n_tiles; ++t) {
+    const h16x8 fa = __builtin_bit_cast(h16x8, next);
+    next = cp[min(t + 1, n_tiles - 1) * 64];
+#pragma unroll
+    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+      f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fb[nb], zero, 0, 0, 0);
+      float m = best[nb];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = fmaxf(max3(acc[q], acc[q + 4], acc[q + 8]), acc[q + 12]);
+        m = fmaxf(m, __uint_as_float((__float_as_uint(v) & ~3u) | (uint32_t)q));
+      }
+      best_tile[nb] = m > best[nb] ? t : best_tile[nb];
+      best[nb] = m;
+    }
+  }
+#pragma unroll
+  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+    const float sc_o = __shfl_xor(best[nb], 32, kWave);
+    const int tile_o = __shfl_xor(best_tile[nb], 32, kWave);
+    const bool other = sc_o > best[nb] || (sc_o == best[nb] && lane >= 32);
+    const int grp = (int)(__float_as_uint(other ? sc_o : best[nb]) & 3u), tile = other ? tile_o : best_tile[nb];
+    const int row0 = tile * 32 + 4 * ((lane >> 5) ^ (int)other) + grp;          // rows row0 + 8 k
+    const int q = (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
+    // this half's two of the four rows
+    float top = -3.0e38f;
+    int id = row0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int m = row0 + 8 * (2 * (lane >> 5) + k);
+      const float* c = centre_row(a, m);
+      const _Float16* v = (const _Float16*)(sB + q * 2);
+      float dot = 0.f, nrm = 0.f;
+#pragma unroll
+      for (int z = 0; z < kG; ++z) {
+        dot = fmaf((float)v[z], c[z], dot);
+        nrm = fmaf(c[z], c[z], nrm);
+      }
+      dot -= 0.5f * nrm;
+      id = dot > top ? m : id;
+      top = fmaxf(top, dot);
+    }
+    const float top_o = __shfl_xor(top, 32, kWave);
+    const int id_o = __shfl_xor(id, 32, kWave);
+    if (top_o > top) id = id_o;
+    if (lane < 32 && first + q < n) key[first + q] = (uint16_t)(s_flat[q] ? a.M : id);
+  }
+}
+
+// Counting sort of shapes (blockIdx.y = 0) and edges (1) by cell, in chunks: cells counted per chunk, added up over the
+// chunks, over the cells, items put in their places.  No order is kept within a cell of a chunk.
+__global__ __launch_bounds__(kSortThreads) void kan_cell_count_kernel(const CellArgs a) {
+  extern __shared__ uint32_t h[];
+  const int p = blockIdx.y, g = blockIdx.x;
+  if (g >= a.groups[p]) return;
+  for (int m = threadIdx.x; m <= a.M; m += kSortThreads) h[m] = 0;
+  __syncthreads();
+  const long long n = p ? a.E : a.K, begin = g * a.chunk[p], end = min(n, begin + a.chunk[p]);
+  for (long long i = begin + threadIdx.x; i < end; i += kSortThreads) atomicAdd(&h[a.key[p][i]], 1u);
+  __syncthreads();
+  for (int m = threadIdx.x; m <= a.M; m += kSortThreads) a.hist[p][(long long)g * (a.M + 1) + m] = h[m];
+}
+
+__global__ __launch_bounds__(256) void kan_cell_chunks_kernel(const CellArgs a) {
+  const int p = blockIdx.y, m = blockIdx.x * 256 + threadIdx.x;
+  if (m > a.M) return;
+  uint32_t* h = a.hist[p] + m;
+  uint32_t sum = 0;
+  for (int g0 = 0; g0 < a.groups[p]; g0 += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = g0 + k < a.groups[p] ? h[(long long)(g0 + k) * (a.M + 1)] : 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (g0 + k < a.groups[p]) {
+        h[(long long)(g0 + k) * (a.M + 1)] = sum;
+        sum += v[k];
+      }
+  }
+  a.total[p][m] = sum;
+}
+
+// One workgroup: running sums over the cells (shapes, tiles, edges) and the shape of the smallest norm.
+__global__ __launch_bounds__(kSortThreads) void kan_cell_scan_kernel(const CellArgs a) {
+  __shared__ uint32_t part[kSortThreads];
+  __shared__ unsigned long long least;
+  const int tid = threadIdx.x;
+  if (tid == 0) least = ~0ull;
+  __syncthreads();
+  unsigned long long l = ~0ull;
+  for (int k = tid; k < a.shape_wgs; k += kSortThreads) l = min(l, a.wg_least[k]);
+  atomicMin(&least, l);
+  const int per = (a.M + 1 + kSortThreads - 1) / kSortThreads, m0 = tid * per, m1 = min(a.M + 1, m0 + per);
+  for (int pass = 0; pass < 3; ++pass) {       // shapes, tiles, edges
+    const uint32_t* total = a.total[pass == 2 ? 1 : 0];
+    uint32_t* out = pass == 1 ? a.first_tile : a.first[pass == 2 ? 1 : 0];
+    auto item = [&](int m) { return pass == 1 ? (total[m] + 31) / 32 : total[m]; };
+    uint32_t sum = 0;
+    for (int m = m0; m < m1; ++m) sum += item(m);
+    __syncthreads();
+    part[tid] = sum;
+    __syncthreads();
+    for (int o = 1; o < kSortThreads; o <<= 1) {
+      const uint32_t v = tid >= o ? part[tid - o] : 0;
+      __syncthreads();
+      part[tid] += v;
+      __syncthreads();
+    }
+    uint32_t run = part[tid] - sum;
+    for (int m = m0; m < m1; ++m) {
+      out[m] = run;
+      run += item(m);
+    }
+  }
+  if (tid == 0) {
+    *a.least = (uint32_t)least;
+    *a.n_rest = 0;
+  }
+}
+
+__global__ __launch_bounds__(kSortThreads) void kan_cell_place_kernel(const CellArgs a) {
+  extern __shared__ uint32_t at[];
+  const int p = blockIdx.y, g = blockIdx.x;
+  if (g >= a.groups[p]) return;
+  for (int m = threadIdx.x; m <= a.M; m += kSortThreads)
+    at[m] = a.first[p][m] + a.hist[p][(long long)g * (a.M + 1) + m];
+  __syncthreads();
+  const long long n = p ? a.E : a.K, begin = g * a.chunk[p], end = min(n, begin + a.chunk[p]);
+  for (long long i = begin + threadIdx.x; i < end; i += kSortThreads)
+    a.sorted[p][atomicAdd(&at[a.key[p][i]], 1u)] = (uint32_t)i;
+}
+
+// Tiles of one cell: members sorted by distance to the centre (then by id), operands of the search and of the bound.
+__global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
+  __shared__ unsigned long long sorted[kBuildChunk];       // {squared distance to the centre, id}
+  const int tid = threadIdx.x, m = blockIdx.x;
+  const float* cr = centre_row(a, m);
+  float c[kG], cn = 0.f;
+#pragma unroll
+  for (int k = 0; k < kG; ++k) {
+    c[k] = cr[k];
+    cn = fmaf(c[k], c[k], cn);
+  }
+  const int n = (int)a.total[0][m];
+  const uint32_t* member = a.sorted[0] + a.first[0][m];
+  for (int n0 = 0; n0 < n; n0 += kBuildChunk) {
+    const int nc = min(kBuildChunk, n - n0), tile0 = (int)a.first_tile[m] + n0 / 32, tiles = (nc + 31) / 32;
+    int full = 32;
+    while (full < nc) full <<= 1;
+    __syncthreads();
+    for (int i = tid; i < full; i += 256) {
+      if (i >= nc) {
+        sorted[i] = ~0ull;
+        continue;
+      }
+      const uint32_t k = member[n0 + i];
+      float d2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < kG; ++q) {
+        const float d = a.cb[(long long)k * kG + q] - c[q];
+        d2 = fmaf(d, d, d2);
+      }
+      if (!(d2 >= 0.f)) d2 = 3.0e38f;           // (a row that is no number sorts last and is never skipped)
+      sorted[i] = ((unsigned long long)__float_as_uint(d2) << 32) | k;
+    }
+    __syncthreads();
+    for (int size = 2; size <= full; size <<= 1)           // bitonic
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = tid; i < full / 2; i += 256) {
+          const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+          const unsigned long long u = sorted[lo], v = sorted[hi];
+          if ((u > v) == ((lo & size) == 0)) {
+            sorted[lo] = v;
+            sorted[hi] = u;
+          }
+        }
+        __syncthreads();
+      }
+    for (int rec = tid; rec < tiles * 128; rec += 256) {
+      const int row = rec >> 2, part = rec & 3, ks = part >> 1, half = part & 1;       // (a row's four records)
+      const int tile = tile0 + (row >> 5), r = row & 31;
+      const uint32_t k = row < nc ? (uint32_t)sorted[row] : 0xffffffffu;
+      a.frag[((long long)tile * 2 + ks) * 64 + half * 32 + r] = tile_slots(a.cb, k, row < nc, ks * 16 + half * 8);
+      if (part == 0) a.ids[tile * 32 + r] = k;
+    }
+    for (int t = tid; t < tiles; t += 256) {
+      const float far = __uint_as_float((uint32_t)(sorted[min(nc, t * 32 + 32) - 1] >> 32));
+      const float R = fp16_up(sqrtf(far) * 1.00001f);
+      // (fp16 operands: n and c are off by 2^-11 of themselves each, or flushed below 6e-5)
+      float cst = 0.5f * (R * R - cn) + 1.5e-3f * sqrtf(cn) + 1e-4f;
+      if (!(cn < 1e5f) || !(R < 300.f) || !(fabsf(cst) < 6e4f)) cst = 6e4f;      // beyond fp16: always visited
+      const float hi = fp16_of(cst), Rf = R < 300.f ? R : 300.f;
+      const float v0[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
+      const float v1[8] = {c[8], c[9], hi, cst - hi, Rf, 1.f, 1.f, 0.f};
+      uint4* rec = a.bound + (long long)((tile0 + t) >> 5) * 64 + ((tile0 + t) & 31);
+      rec[0] = pack_slots(v0);
+      rec[32] = pack_slots(v1);
+    }
+  }
+  if (m == 0 && tid < 32) {                      // rows of the last bound operand past the last tile: never visited
+    const int T = (int)a.first_tile[a.M], t = (T & ~31) + tid;
+    if (t >= T && (T & 31)) {
+      const float v0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const float v1[8] = {0.f, 0.f, -6e4f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      uint4* rec = a.bound + (long long)(t >> 5) * 64 + (t & 31);
+      rec[0] = pack_slots(v0);
+      rec[32] = pack_slots(v1);
+    }
+  }
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+}
+
+template <typename IdxT>
+__global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellArgs a) {
+  __shared__ uint32_t s_seen[4][kCellMaxTiles / 32];       // tiles visited, a row per wave
+  __shared__ uint16_t s_list[4][64 * 32 + 2 * kAhead];     // tiles to visit
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  // runs of consecutive workgroups on one XCD (workgroups go to the eight in turn): neighbours ask for the same tiles
+  const unsigned W = gridDim.x, xcd = blockIdx.x & 7u, q8 = W >> 3, r8 = W & 7u;
+  const long long wg = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
+  const long long pos = (wg * 4 + wave) * 32 + (lane & 31);
+  if ((wg * 4 + wave) * 32 >= a.E) return;                 // (no barrier in this kernel)
+  volatile uint32_t* seen = s_seen[wave];
+  volatile uint16_t* list = s_list[wave];
+  const int T = (int)a.first_tile[a.M], words = (T + 31) / 32, most = (int)(kRestShare * T);
+  for (int w = lane; w < words; w += 64) seen[w] = 0;
+
+  const uint32_t e = a.sorted[1][min(pos, a.E - 1)];
+  const int key = a.key[1][e];
+  const bool live = pos < a.E && key < a.M;
+
+  // edge operands of the search (see tile_slots) and of the bound
+  h16x8 fb[2], fe;
+  {
+    float n[kG], mean, gain;
+    normalise(a.coef + (long long)e * kG, n, mean, gain);
+    _Float16 hi[kG], lo[kG];
+#pragma unroll
+    for (int m = 0; m < kG; ++m) split_h(n[m], hi[m], lo[m]);
+    auto slot = [&](int s) {
+      return s < 10 ? hi[s] : (s == 10 || s == 31 ? (_Float16)1.0f : (s < 21 ? hi[s - 11] : lo[s - 21]));
+    };
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      fb[0][t] = half ? slot(8 + t) : slot(t);
+      fb[1][t] = half ? slot(24 + t) : slot(16 + t);
+      fe[t] = half ? (t < 2 ? hi[8 + t] : (_Float16)(t < 4 ? 1.0f : 0.0f)) : hi[t];
+    }
+  }
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+
+  float best = -3.0e38f;
+  uint32_t best_id = 0;
+  auto id_of = [&](int t, int r) { return a.ids[t * 32 + 8 * (r >> 2) + 4 * half + (r & 3)]; };
+  auto take = [&](float sc, uint32_t id) {       // (equal scores: the lower id)
+    if (sc > best || (sc == best && id < best_id)) best_id = id;
+    best = fmaxf(best, sc);
+  };
+  auto leave = [&] {                             // to the whole search
+    uint32_t to = 0;
+    const unsigned long long w = __ballot(live && half == 0);
+    if (lane == 0) to = atomicAdd(a.n_rest, (uint32_t)__popcll(w));
+    to = (uint32_t)__builtin_amdgcn_readfirstlane((int)to);
+    if (live && half == 0) a.rest[to + __popcll(w & ((1ull << lane) - 1))] = e;
+    if (pos < a.E && half == 0 && !live) ((IdxT*)a.idx)[e] = (IdxT)*a.least;
+  };
+
+  // (1) own cells, both instructions of every tile
+  int visits = 0;
+  bool pending = live;
+  for (unsigned long long w; (w = __ballot(pending)) != 0;) {
+    const int cell = __builtin_amdgcn_readlane(key, __ffsll(w) - 1);
+    pending = pending && key != cell;
+    const int t0 = (int)a.first_tile[cell], t1 = (int)a.first_tile[cell + 1];
+    visits += t1 - t0;
+    if (visits > most) {
+      leave();
+      return;
+    }
+    for (int t = t0; t < t1; ++t) {
+      const h16x8 f0 = __builtin_bit_cast(h16x8, (a.frag + (long long)t * 128)[lane]);
+      const h16x8 f1 = __builtin_bit_cast(h16x8, (a.frag + (long long)t * 128 + 64)[lane]);
+      f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f0, fb[0], zero, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f1, fb[1], acc, 0, 0, 0);
+      const float m = max_of(acc);
+      if (m >= best) take(m, id_of(t, row_of(acc, m)));
+      if (lane == 0) seen[t >> 5] = seen[t >> 5] | (1u << (t & 31));
+    }
+  }
+
+  // Distance to the best shape so far (scores are good to 1e-6).  The two lanes of an edge hold different rows:
+  // they agree on the better shape first.
+  auto distance = [&] {
+    const float sc_o = __shfl_xor(best, 32, kWave);
+    take(sc_o, (uint32_t)__shfl_xor((int)best_id, 32, kWave));
+    return live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
+  };
+  const __amdgpu_buffer_rsrc_t bound_rsrc = buffer_of(a.bound, (size_t)((T + 31) / 32) * 1024);
+  const __amdgpu_buffer_rsrc_t frag_rsrc = buffer_of(a.frag, (size_t)T * 2048);
+  auto load = [&](const __amdgpu_buffer_rsrc_t& rsrc, int at) {
+    return __builtin_bit_cast(h16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, at, 0));
+  };
+  // A tile with a bound that reaches the best score gets the second instruction.
+  auto examine = [&](int t, const f32x16& bound) {
+    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(load(frag_rsrc, t * 2048 + 1024), fb[1], bound, 0, 0, 0);
+    const float m = max_of(acc);
+    if (m >= best) take(m, id_of(t, row_of(acc, m)));
+  };
+  // Every tile not visited yet that an edge with its bit in `who` asks for at distance d.  False: too many.
+  // (An instruction of any kind takes its wave's SIMD an issue slot: tiles are listed first, so that a visit is a
+  // lane read, a load, a matrix instruction and the maxima of a pair of tiles.)
+  auto search = [&](bool who, float d) -> bool {
+    const bool far = d > kFar;                   // (no shape known yet, or beyond fp16: every tile)
+    const float thr = who ? (far ? -6e4f : 0.5f * (1.0f - d * d) - 1e-5f) : 6e4f;
+    const float thr_hi = fp16_of(thr);
+    if (half) {
+      fe[4] = (_Float16)(far ? 0.f : fp16_up(d));
+      fe[5] = (_Float16)-thr_hi;
+      fe[6] = (_Float16)(thr_hi - thr);
+    }
+    for (int w0 = 0; w0 < words; w0 += 64) {
+      const int w1 = min(words, w0 + 64);
+      uint32_t mine = 0;                         // lane w: the tiles of word w0 + w
+      h16x8 f[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) f[k] = load(bound_rsrc, min(w0 + k, words - 1) * 1024);
+      for (int w = 0; w < w1 - w0; w += kAhead) {        // (past the last word: that one again, struck out below)
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+          // rows: edges, columns: tiles
+          const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fe, f[k], zero, 0, 0, 0);
+          f[k] = load(bound_rsrc, min(w0 + w + k + kAhead, words - 1) * 1024);
+          const unsigned long long any = __ballot(!(max_of(acc) <= 0.f));
+          mine = lane == w + k ? (uint32_t)any | (uint32_t)(any >> 32) : mine;
+        }
+      }
+      if (w0 + lane < w1) {
+        const uint32_t before = seen[w0 + lane];
+        mine &= ~before;
+        seen[w0 + lane] = before | mine;
+      } else {
+        mine = 0;
+      }
+      // the list of these tiles
+      int upto = __popc(mine);
+      const int own = upto;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(upto, o, kWave);
+        upto += lane >= o ? v : 0;
+      }
+      const int count = __builtin_amdgcn_readlane(upto, 63);
+      visits += count;
+      if (visits > most) return false;
+      if (count == 0) continue;
+      int last = 0;
+      for (int at = upto - own; mine; ++at) {
+        last = (w0 + lane) * 32 + __ffs(mine) - 1;
+        mine &= mine - 1;
+        list[at] = (uint16_t)last;
+      }
+      const unsigned long long some = __ballot(own != 0);
+      last = __builtin_amdgcn_readlane(last, 63 - __clzll(some));
+      if (lane < 2 * kAhead) list[count + lane] = (uint16_t)last;      // (to whole groups, and one ahead: the last again)
+      for (int i0 = 0; i0 < count; i0 += 64) {
+        const int tiles = list[min(i0 + lane, count)];
+        auto tile = [&](int i) { return __builtin_amdgcn_readlane(tiles, i); };
+        int t[kAhead];
+        const int n_here = min(64, count - i0);
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+          t[k] = tile(k);
+          f[k] = load(frag_rsrc, t[k] * 2048);
+        }
+        for (int i = 0; i < n_here; i += kAhead) {
+#pragma unroll
+          for (int k = 0; k < kAhead; k += 2) {
+            const f32x16 acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[k], fb[0], zero, 0, 0, 0);
+            const f32x16 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[k + 1], fb[0], zero, 0, 0, 0);
+            const int u0 = t[k], u1 = t[k + 1];
+            t[k] = tile(min(i + k + kAhead, 63));
+            t[k + 1] = tile(min(i + k + 1 + kAhead, 63));
+            f[k] = load(frag_rsrc, t[k] * 2048);
+            f[k + 1] = load(frag_rsrc, t[k + 1] * 2048);
+            const float m0 = max_of(acc0), m1 = max_of(acc1);
+            if (__ballot(fmaxf(m0, m1) >= best)) {
+              if (__ballot(m0 >= best)) examine(u0, acc0);
+              if (__ballot(m1 >= best)) examine(u1, acc1);
+            }
+          }
+        }
+      }
+    }
+    return true;
+  };
+
+  float d = distance();
+  const bool in = live && d <= kFar;
+  float sum = in ? d : 0.f, cnt = in ? 1.f : 0.f;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    sum += __shfl_xor(sum, o, kWave);
+    cnt += __shfl_xor(cnt, o, kWave);
+  }
+  const float mean = cnt > 0.f ? kMeanFactor * sum / cnt : 2.0f * kFar;
+  bool done = search(live, fminf(d, mean));      // (2)
+  if (done) {
+    d = distance();
+    const bool left = live && d > mean;
+    if (__ballot(left)) done = search(left, d);  // (3)
+  }
+  if (!done) {
+    leave();
+    return;
+  }
+  (void)distance();
+  if (lane < 32 && pos < a.E) ((IdxT*)a.idx)[e] = (IdxT)(live ? best_id : *a.least);
 }
 
 // ---- reconstruction quality ---------------------------------------------------------------------
@@ -263,29 +981,105 @@ __global__ void kan_recon_final_kernel(const double* __restrict__ part, int n_bl
 
 }  // namespace
 
-size_t assign_centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(uint4); }
+size_t assign_centroid_bytes(int K) { return centroid_bytes(K); }
 int recon_blocks(long long E) {
   const long long b = (E + 255) / 256;
   return (int)(b < 1024 ? b : 1024);
 }
 
-hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx, float* gain,
-                         float* bias, void* ws, hipStream_t s) {
+namespace {
+// Every edge, or the *n_list listed ones, against every shape.
+void launch_whole(const float* coef, long long E, const uint32_t* list, const uint32_t* n_list, const float* cb, int K,
+                  int idx_u32, void* idx, float* gain, float* bias, void* centroids, hipStream_t s) {
   const int n_tiles = (K + 31) / 32;
   const long long recs = (long long)n_tiles * 2 * 64;
   hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, n_tiles,
-                     (uint4*)ws);
+                     n_list, (uint4*)centroids);
   AssignArgs a;
   a.coef = coef;
-  a.cent = (const uint4*)ws;
+  a.cent = (const uint4*)centroids;
   a.E = E;
+  a.list = list;
+  a.n_list = n_list;
   a.n_tiles = n_tiles;
   a.idx = idx;
   a.gain = gain;
   a.bias = bias;
-  dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg));
-  if (idx_u32) hipLaunchKernelGGL(kan_assign_kernel<uint32_t>, grid, dim3(kAssignThreads), 0, s, a);
-  else hipLaunchKernelGGL(kan_assign_kernel<uint16_t>, grid, dim3(kAssignThreads), 0, s, a);
+  if (!list && E <= kSplitMaxEdges) {
+    const dim3 grid((unsigned)((E + kEdgeTilesPerWave * 32 - 1) / (kEdgeTilesPerWave * 32))), wg(8 * kWave);
+    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8>), grid, wg, 0, s, a);
+    return;
+  }
+  const dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg)), wg(kAssignThreads);
+  if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 1>), grid, wg, 0, s, a);
+  else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 1>), grid, wg, 0, s, a);
+}
+}  // namespace
+
+// The bounded search pays where its cells, launches and bound tests are small next to the scores they save.  Bounded
+// against whole search (5 % noise per coefficient): K = 65,536 and 2^20 / 2^18 / 2^16 edges 772 / 295 / 169 against
+// 3803 / 1174 / 370 us, K = 16,384 439 / 176 / 110 against 1110 / 337 / 90, K = 8,192 363 / 249 / 115 against
+// 625 / 195 / 55, K = 262,144 and 2^20 edges 1.9 against 14.9 ms.
+bool assign_bounded_ok(long long E, int K) {
+  const long long work = E * K;
+  return (work >= (3ll << 29) && K >= 16384 || work >= (1ll << 33) && K >= 8192) && cell_layout(1, K).tiles_max <= kCellMaxTiles;
+}
+size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
+
+hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx,
+                                 float* gain, float* bias, void* ws, hipStream_t s) {
+  const CellLayout g = cell_layout(E, K);
+  char* w = (char*)ws;
+  CellArgs a;
+  a.coef = coef;
+  a.cb = cb;
+  a.E = E;
+  a.K = K;
+  a.M = g.M;
+  a.shape_wgs = (K + kEdgesPerWg - 1) / kEdgesPerWg;
+  a.centres = (uint4*)(w + g.centres);
+  a.frag = (uint4*)(w + g.frag);
+  a.ids = (uint32_t*)(w + g.ids);
+  a.bound = (uint4*)(w + g.bound);
+  a.sorted[0] = (uint32_t*)(w + g.member);
+  a.sorted[1] = (uint32_t*)(w + g.perm);
+  for (int p = 0; p < 2; ++p) {
+    a.groups[p] = g.groups[p];
+    a.chunk[p] = g.chunk[p];
+    a.key[p] = (uint16_t*)(w + g.key[p]);
+    a.hist[p] = (uint32_t*)(w + g.hist[p]);
+    a.total[p] = (uint32_t*)(w + g.total[p]);
+    a.first[p] = (uint32_t*)(w + g.first[p]);
+  }
+  a.first_tile = (uint32_t*)(w + g.first_tile);
+  a.wg_least = (unsigned long long*)(w + g.wg_least);
+  a.rest = (uint32_t*)(w + g.rest);
+  a.n_rest = (uint32_t*)(w + g.n_rest);
+  a.least = (uint32_t*)(w + g.least);
+  a.idx = idx;
+  a.gain = gain;
+  a.bias = bias;
+  const unsigned edge_wgs = (unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg);
+  const dim3 sort_grid((unsigned)(g.groups[0] > g.groups[1] ? g.groups[0] : g.groups[1]), 2);
+  const size_t cells_lds = (size_t)(g.M + 1) * 4;
+  hipLaunchKernelGGL(kan_cell_centres_kernel, dim3((unsigned)((g.M * 2 + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(kan_cells_kernel, dim3((unsigned)a.shape_wgs + edge_wgs), dim3(kAssignThreads), 0, s, a);
+  hipLaunchKernelGGL(kan_cell_count_kernel, sort_grid, dim3(kSortThreads), cells_lds, s, a);
+  hipLaunchKernelGGL(kan_cell_chunks_kernel, dim3((unsigned)(g.M / 256 + 1), 2), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(kan_cell_scan_kernel, dim3(1), dim3(kSortThreads), 0, s, a);
+  hipLaunchKernelGGL(kan_cell_place_kernel, sort_grid, dim3(kSortThreads), cells_lds, s, a);
+  hipLaunchKernelGGL(kan_cell_build_kernel, dim3((unsigned)g.M), dim3(256), 0, s, a);
+  const dim3 grid((unsigned)((E + 127) / 128));
+  if (idx_u32) hipLaunchKernelGGL(kan_assign_bounded_kernel<uint32_t>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(kan_assign_bounded_kernel<uint16_t>, grid, dim3(256), 0, s, a);
+  launch_whole(coef, E, a.rest, a.n_rest, cb, K, idx_u32, idx, gain, bias, w + g.whole, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx, float* gain,
+                         float* bias, void* ws, hipStream_t s) {
+  launch_whole(coef, E, nullptr, nullptr, cb, K, idx_u32, idx, gain, bias, ws, s);
   return hipGetLastError();
 }
 

@@ -279,7 +279,7 @@ PyObject* assign(PyObject*, PyObject* const* a, Py_ssize_t n) {
   at::Tensor idx = at::empty({n_in, n_out}, coef->options().dtype(u16 ? at::kShort : at::kInt));
   at::Tensor gain = at::empty({n_in, n_out}, coef->options()), bias = at::empty({n_in, n_out}, coef->options());
   Buffers b;
-  size_t need = a[2] == Py_None ? kan_vq_assign_workspace_bytes((int32_t)K) : 0;
+  size_t need = a[2] == Py_None ? kan_vq_assign_fast_workspace_bytes((int32_t)n_in, (int32_t)n_out, (int32_t)K) : 0;
   if (need == (size_t)-1) return PyLong_FromLong(KAN_ERR_SHAPE);
   if (!b.use_ws(a[2], need, *coef)) return nullptr;
   void* stream;

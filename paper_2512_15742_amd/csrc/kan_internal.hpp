@@ -315,6 +315,11 @@ size_t assign_centroid_bytes(int K);       // prepared centroid operands (worksp
 int recon_blocks(long long E);             // workgroups of the reconstruction-sums pass
 hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx,
                          float* gain, float* bias, void* ws, hipStream_t);
+// The bounded search over cells of the codebook (large codebooks, many edges): the same result from a larger workspace.
+bool assign_bounded_ok(long long E, int K);
+size_t assign_bounded_bytes(long long E, int K);
+hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx,
+                                 float* gain, float* bias, void* ws, hipStream_t);
 hipError_t launch_recon_sums(const float* coef, long long E, const float* cb, int idx_u32, const void* idx,
                              const float* gain, const float* bias, double* part, double* sums, hipStream_t);
 

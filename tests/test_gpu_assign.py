@@ -114,3 +114,75 @@ def test_assigned_layer_runs_through_the_forward_pass(kb):
     assert ko.error_report(y, y_ref)["headline"] <= 1e-5
     y_dense = ko.dense_layer_forward(coef, x)
     assert ko.error_report(y, y_dense)["headline"] < 0.15          # 2 % noise per coefficient, summed over 128 inputs
+
+
+# ---- bounded search and the whole search's two forms ---------------------------------------------------
+
+
+def _grids(kind, K, E, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cb = torch.randn((K, 10), generator=g, device="cuda")
+    cb -= cb.mean(1, keepdim=True)
+    cb /= cb.norm(dim=1, keepdim=True)
+    if kind == "duplicates":
+        cb[K // 2:] = cb[:K - K // 2].clone()
+    if kind == "norms":
+        cb *= torch.rand((K, 1), generator=g, device="cuda") * 3
+    if kind == "one row":
+        cb[:] = cb[:1].clone()
+    k = torch.randint(0, K, (E, 1), generator=g, device="cuda")
+    if kind == "one cell":
+        k[:] = 5
+    noise = torch.randn((E, 1, 10), generator=g, device="cuda") * (0.5 if kind == "far" else 0.05)
+    gain = torch.randn((E, 1, 1), generator=g, device="cuda").abs_().mul_(0.1).add_(1e-3)
+    coef = gain * (cb[k] + noise) + 0.01 * torch.randn((E, 1, 1), generator=g, device="cuda")
+    if kind == "flat":
+        coef[::3] = 0.0
+    return coef.contiguous(), cb.contiguous()
+
+
+@pytest.mark.parametrize("kind,K,E", [("trained", 16384, 98304), ("trained", 16421, 98101), ("trained", 50001, 33333),
+                                      ("trained", 70000, 24001), ("far", 16384, 98337), ("duplicates", 16384, 98304),
+                                      ("norms", 16384, 98304), ("flat", 16384, 98304), ("one cell", 16384, 98304),
+                                      ("one row", 16384, 98304)])
+def test_bounded_search_finds_the_nearest_row(kb, kind, K, E):
+    """Every chosen row is as near as the nearest one (fp64, on the device), and the same as the whole
+    search's wherever no other row is that near."""
+    coef, cb = _grids(kind, K, E, K + E)
+    L = kb.lib()
+    whole = torch.empty(L.kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
+    assert L.kan_vq_assign_fast_workspace_bytes(E, 1, K) > whole.numel()
+    idx, gain, bias = kb.kan_vq_assign(coef, cb)
+    ref = kb.kan_vq_assign(coef, cb, ws=whole)
+    assert torch.equal(gain, ref[1]) and torch.equal(bias, ref[2])
+    mask = 0xffff if K <= 65536 else 0xffffffff
+    a, b = idx.view(-1).long() & mask, ref[0].view(-1).long() & mask
+    assert int(a.max()) < K and int(b.max()) < K
+    n = coef.view(E, 10).double()
+    n = n - n.mean(1, keepdim=True)
+    g = n.norm(dim=1, keepdim=True)
+    n = torch.where(g > 0, n / g, torch.zeros_like(n))
+    c = cb.double()
+    for s in range(0, E, 4096):
+        d2 = (n[s:s + 4096] ** 2).sum(1, keepdim=True) - 2 * n[s:s + 4096] @ c.T + (c ** 2).sum(1)
+        best, second = torch.topk(d2, 2, dim=1, largest=False).values.unbind(1)
+        for x in (a, b):
+            assert float((d2.gather(1, x[s:s + 4096, None])[:, 0] - best).max()) <= GAP
+        clear = second - best > GAP
+        assert torch.equal(a[s:s + 4096][clear], b[s:s + 4096][clear])
+
+
+@pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
+def test_whole_search_shared_and_separate_waves(kb, K, E):
+    """Either side of the switch between eight waves on 128 edges and four on 512: gathers the nearest row."""
+    coef, cb = _grids("trained", K, E, K + E)
+    idx, _, _ = kb.kan_vq_assign(coef, cb)
+    a = idx.view(-1).long() & 0xffff
+    n = coef.view(E, 10).double()
+    n = n - n.mean(1, keepdim=True)
+    n /= n.norm(dim=1, keepdim=True)
+    c = cb.double()
+    for s in range(0, E, 8192):
+        d2 = 1.0 - 2 * n[s:s + 8192] @ c.T + (c ** 2).sum(1)
+        assert float((d2.gather(1, a[s:s + 8192, None])[:, 0] - d2.min(1).values).max()) <= GAP
