@@ -106,7 +106,7 @@ kan_status validate_layer(const kan_vq_layer* L) {
 // Everything below is a pure function of shapes, dtypes, batch, head count and
 // pointer alignment, so the workspace query and the forward call always agree.
 
-enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5, kPlanDense = 6 };
+enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5, kPlanDense = 6, kPlanFusedWave = 7 };
 
 struct LayerPlan {
   GatherCfg cfg;
@@ -186,6 +186,11 @@ constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here
 constexpr long long kFusedTwoTilesMinEdges = 1ll << 22;    // this many edges whose codeword rows are one gather each
 constexpr long long kFusedMinEdgesForResidency = 1 << 17;   // ... for layers of at least this many edges per head
 constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernel: layers up to here may write partial sums as large as their stream
+// Precise path, 2 to 32 samples: the wave-by-wave kernel up to this many edges per launch, tiles of 128 outputs with the
+// basis tile in LDS above (there the wait of one step is another's work, and what counts is how little each does:
+// 4096 x 4096 at batch 16 / 31 105 / 125 against 118 / 132 us, fifty heads of 1024-128-21 at batch 16 68.8 against
+// 71; 2048 x 2048 33.2 against 30.5, ten heads of 2048-256-21 at batch 8 61.0 against 53.8 us).
+constexpr long long kFusedWaveMaxEdges = 6ll << 20;
 constexpr int kFusedMinWgsPerHead = 20;      // fused kernel, several heads: workgroups per head (L2 residency of the codebooks)
 // Precise path: from this batch on the split-operand matrix-core form.  Its time hardly depends on
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
@@ -312,6 +317,32 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
   return p;
 }
 
+// Precise path up to 32 samples: tiles of 64 outputs, the four waves of a workgroup over its inputs.  Two workgroups
+// per CU while a wave keeps two steps, and while the partial sums stay below a quarter of the parameter stream (the
+// whole of it for small layers, as above).
+LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code) {
+  LayerPlan p;
+  p.mfma = false;
+  p.kind = kPlanFusedWave;
+  p.name = "kan_fused_f32";
+  p.cfg = GatherCfg{32, 1, 1, idx_u32, gb_kind, code};
+  p.n_jt = (n_out + kFusedWaveCols - 1) / kFusedWaveCols;
+  p.n_bt = 1;
+  const int bytes_per_edge = (idx_u32 ? 4 : 2) + 2 * gb_bytes(gb_kind);
+  const long long base = (long long)n_heads * p.n_jt;
+  long long chunks = (kTargetWorkgroups + base - 1) / base;
+  const long long max_by_rows = n_in / (2 * kFusedWaveStep);
+  const long long max_by_bytes =
+      (long long)n_in * bytes_per_edge / ((long long)n_in * n_out <= kFusedSmallLayerEdges ? B : 4 * B);
+  if (chunks > max_by_rows) chunks = max_by_rows;
+  if (chunks > max_by_bytes) chunks = max_by_bytes;
+  if (chunks < 1) chunks = 1;
+  const int rows = (int)((n_in + chunks - 1) / chunks);
+  p.rows_per_chunk = (rows + kFusedWaveStep - 1) / kFusedWaveStep * kFusedWaveStep;
+  p.n_chunks = (n_in + p.rows_per_chunk - 1) / p.rows_per_chunk;
+  return p;
+}
+
 // Bucket path (prepared layers): one workgroup per (bucket, slice of the outputs, sample).
 // A workgroup occupies a whole CU (LDS), so the slices are cut to give every CU one: the
 // cuts come from the block table that the preparation made for this many (samples x heads).
@@ -414,7 +445,9 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     return column_ok && (long long)L.in * L.out * B <= kColumnMaxWork ? plan_column(L, B) : plan_bucket(L, B, n_heads);
   // large batches: the fp16 machinery with both operands split into high and low parts
   if (B >= kSplitMinBatch && B > fused_max) return plan_mfma(L.in, L.out, B, n_heads, u32, gbk, code, true);
-  if (B >= 2) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
+  const long long edges = (long long)L.in * L.out;
+  if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
+  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code);
   return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok);
 }
 
@@ -605,7 +638,7 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     }
     if (p.kind == kPlanColumn) st = run(p.name, s, [&] { return launch_column(p.cfg.code, p.cfg.gb_kind, k, heads, s); });
     else st = run(p.name, s, [&] { return launch_bucket(p.cfg.code, p.cfg.gb_kind, k, g.tab_w[table], heads, s); });
-  } else if (p.kind == kPlanFused16 || p.kind == kPlanFused32) {
+  } else if (p.kind == kPlanFused16 || p.kind == kPlanFused32 || p.kind == kPlanFusedWave) {
     const bool f32 = p.kind == kPlanFused32;
     FusedArgs f;
     memset(&f, 0, sizeof(f));
@@ -626,7 +659,8 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     f.x_tanh = chain.in_tanh;
     memcpy(f.h, a.h, sizeof(f.h));
     dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
-    if (chain.in_parts > 1) st = run(p.name, s, [&] { return launch_fused_chained(p.cfg, f, f32, grid, s); });
+    if (p.kind == kPlanFusedWave) st = run(p.name, s, [&] { return launch_fused_wave(p.cfg, f, grid, s); });
+    else if (chain.in_parts > 1) st = run(p.name, s, [&] { return launch_fused_chained(p.cfg, f, f32, grid, s); });
     else st = run(p.name, s, [&] { return launch_fused(p.cfg, f, f32, grid, s); });
   } else if (p.kind == kPlanDense) {
     DenseArgs d;
@@ -674,7 +708,12 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 bool chained(const std::vector<LayerPlan>& plans, int l, int n_heads, const kan_vq_layer* layers, int64_t B) {
   if (l < 0 || l + 1 >= (int)plans.size() || n_heads > kMaxGroup || plans[l].n_chunks <= 1) return false;
   if (plans[l + 1].kind == kPlanBucket || plans[l + 1].kind == kPlanColumn) return plans[l].kind == kPlanBucket;
-  if (plans[l + 1].kind == kPlanFused16 || plans[l + 1].kind == kPlanFused32)
+  if (plans[l + 1].kind == kPlanFusedWave)
+    return plans[l].n_chunks <= kFusedChainMaxParts && layers[l + 1].in % 4 == 0 && plans[l + 1].n_jt <= 16 &&
+           B * plans[l + 1].rows_per_chunk <= kFusedWaveChainFloats &&
+           (long long)plans[l].n_chunks * B * (plans[l + 1].rows_per_chunk / 4) <= 32 * 256;
+  if (plans[l + 1].kind == kPlanFused32) return false;
+  if (plans[l + 1].kind == kPlanFused16)
     return fused_takes_slices(plans[l], plans[l + 1], layers[l + 1].in, B);
   // the vector-ALU kernel at batch 1: the threads that share a row of the basis table split the
   // slices; few output tiles (each adds the slices again)

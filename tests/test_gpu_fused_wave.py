@@ -1,0 +1,49 @@
+"""Precise path, 2 to 32 samples, wave-by-wave kernel (kan_fused_wave.hip): loads of four edges at the ends of rows
+and arrays, chunks of one to several groups of steps, both sample tiles, every storage width, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import kan_oracle as ko
+from paper_2512_15742_amd import synth
+
+from kan_testlib import TOL_FP32, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def kb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_15742_amd import binding
+    binding.lib()
+    return binding
+
+
+TYPES = [("i8", "f16", "u16"), ("i8", "q8", "u16"), ("i8", "f32", "u32"), ("f16", "f16", "u32"), ("f32", "f32", "u16"),
+         ("bfp8", "f16", "u16")]
+
+
+@pytest.mark.parametrize("n_in,n_out", [(1, 1), (3, 1), (1, 3), (1, 4), (2, 2), (5, 3), (17, 2), (16, 61), (31, 65), (48, 64),
+                                        (65, 67), (130, 7), (1030, 5)])
+@pytest.mark.parametrize("B", [2, 16, 17, 32])
+def test_edges_of_rows_and_steps(kb, n_in, n_out, B):
+    for n, (cb, gb, idx) in enumerate(TYPES):
+        P = synth.make_layer(9000 + n, n_in, n_out, 257, cb_dtype=cb, gb_dtype=gb, idx_dtype=idx)
+        x = np.random.default_rng(B + n_in).uniform(-1.1, 1.1, size=(B, n_in)).astype(np.float32)
+        y_ref, A = ko.vq_layer_forward(x, **P.as_dict(), return_abs=True)
+        y = kb.kan_vq_layer_forward(kb.VQLayer(P), to_dev(x), path=kb.KAN_PATH_GATHER).cpu().numpy()
+        assert np.isfinite(y).all()
+        assert np.abs(y - y_ref).max() <= TOL_FP32 * max(np.abs(y_ref).max(), A.max()), (cb, gb, idx)
+
+
+@pytest.mark.parametrize("dims", [(2048, 64, 20), (1024, 36, 21), (640, 132, 68, 5)], ids=lambda d: "-".join(map(str, d)))
+@pytest.mark.parametrize("B", [2, 13, 32])
+def test_slices_into_the_next_layer(kb, dims, B):
+    Ps = [synth.make_layer(9100 + l, dims[l], dims[l + 1], 4099, cb_dtype="i8", gb_dtype="f16") for l in range(len(dims) - 1)]
+    x = synth.make_x(9200 + B, B, dims[0])
+    y = kb.kan_vq_head_forward([[kb.VQLayer(p) for p in Ps]], to_dev(x), path=kb.KAN_PATH_GATHER)[0].cpu().numpy()
+    rep = ko.error_report(y, ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
+    assert rep["headline"] <= TOL_FP32, rep
