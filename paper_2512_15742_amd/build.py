@@ -35,6 +35,7 @@ UNITS = [
     ("kan_api.hip", "kan_api.o", []),
     ("kan_misc.hip", "kan_misc.o", []),
     ("kan_mfma.hip", "kan_mfma.o", []),
+    ("kan_tail.hip", "kan_tail.o", []),
     ("kan_fused.hip", "kan_fused.o", []),
     ("kan_fused.hip", "kan_fused_chained.o", ["-DKAN_FUSED_CH=1"]),
     ("kan_fused_wave.hip", "kan_fused_wave.o", []),

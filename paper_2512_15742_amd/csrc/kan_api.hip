@@ -9,6 +9,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -106,14 +107,14 @@ kan_status validate_layer(const kan_vq_layer* L) {
 // Everything below is a pure function of shapes, dtypes, batch, head count and
 // pointer alignment, so the workspace query and the forward call always agree.
 
-enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5, kPlanDense = 6, kPlanFusedWave = 7 };
+enum PlanKind { kPlanGather = 0, kPlanMfma = 1, kPlanFused16 = 2, kPlanFused32 = 3, kPlanBucket = 4, kPlanColumn = 5, kPlanDense = 6, kPlanFusedWave = 7, kPlanTail = 8 };
 
 struct LayerPlan {
   GatherCfg cfg;
   int n_jt, n_bt, n_chunks, rows_per_chunk;
   int tile_n = 0;              // matrix-core path: outputs per workgroup tile (128: four waves, 256: eight)
   int kind;          // PlanKind
-  bool mfma;         // kind == kPlanMfma (coefficient + basis preparation, streaming contraction)
+  bool mfma;         // kind == kPlanMfma (coefficient + basis preparation, streaming contraction) or kPlanTail (coefficient preparation, one launch)
   int products = 1;  // 3: both operands in high and low fp16 parts, hi*hi + hi*lo + lo*hi (three passes inside the kernel)
   const char* name;
 };
@@ -179,7 +180,14 @@ LayerPlan plan_gather(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
 constexpr int kMfmaTileN = 128;
 constexpr int kMfmaRowsStep = kMfmaPrepRows;   // chunk boundaries coincide with partial bias sums
 constexpr int kMfmaTargetWorkgroups = 512;
-constexpr int kMfmaMinRows = 64;
+// A chunk of inputs is at least two steps: a layer that leaves CUs idle is a latency chain (first loads 3 us, then a
+// step per 1-1.5 us of memory latency), and the slices of more chunks cost its consumer less than the steps (with
+// 64 inputs against 32: a 160-64-31-11 head at batch 72 34.0 / 30.4 us, 1832-96-25-20 at 2846 63.9 / 59.5,
+// 1085-512-117 precise at 772 77.8 / 74.9, 2048-1024-256 at 1024 88.7 / 88.6).
+constexpr int kMfmaMinRows = 32, kMfmaMinRowsCompact = 64;    // (64: see plan_head)
+// (config 3 at batch 65-128, whose first layer is cut into 32 chunks: 55.3-56.4 us with the 32 slices handed
+// on against 56.7-57.4 us with a reduction launch)
+constexpr int kMaxChainedSlices = 32;   // more slices than this go through the reduction pass (more loads in flight per output)
 constexpr int kMfmaMaxSteps = 256;            // steps of 16 inputs per workgroup of the streaming contraction
 constexpr int64_t kHalfFusedMaxBatch = 64;   // fp16 path: fused kernel up to here, streaming contraction above
 constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here (both paths) for layers of at least
@@ -206,7 +214,8 @@ constexpr int64_t kDenseOnePassMaxBatch = 128, kDenseOnePassSmallMaxBatch = 256;
 constexpr long long kDenseOnePassSmallEdges = 1ll << 18;
 constexpr int64_t kAutoMfmaBatch = 32;    // KAN_PATH_AUTO switches to the matrix cores from here (measured crossover 16-32)
 
-LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3 = false) {
+LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3 = false,
+                    int min_rows = kMfmaMinRows) {
   LayerPlan p;
   p.mfma = true;
   p.kind = kPlanMfma;
@@ -216,7 +225,9 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
   p.cfg.idx_u32 = idx_u32;
   p.cfg.gb_kind = gb_kind;
   p.cfg.code = code;
-  const long long max_chunks = n_in / kMfmaMinRows;
+  // (finer chunks only as far as the next layer still takes the slices as they are)
+  long long max_chunks = n_in / min_rows;
+  if (max_chunks > kMaxChainedSlices) max_chunks = std::max<long long>(kMaxChainedSlices, n_in / kMfmaMinRowsCompact);
   // Tiles of 128 outputs by 128 samples (half the coefficient bytes per MFMA through the
   // vector cache), unless their grid would need more than eight chunks of inputs to give
   // every CU two workgroups (64-sample tiles then halve the chunks and with them the
@@ -256,6 +267,37 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
     p.products = 3;
     p.name = "kan_mfma_split";
   }
+  return p;
+}
+
+// Small layers take one launch (kan_tail.hip) in place of basis words, contraction and reduction.  A workgroup
+// evaluates the basis of all inputs for its 32 samples and reads the records of its outputs, so the line is where
+// that takes longer than the launches it saves: kTailMaxIn inputs (416-32 at batch 1166 17.9 -> 14.6 us, 475-52-13 at
+// 65 25.2 -> 26.6 without the limit), 32,768 edges (318-192-108 at batch 474 30.8 -> 25.5 us, 128-256 at
+// 225 16.4 -> 12.0; 8 or 16 thousand lose half of that), eight workgroups per CU (288-38-19 at batch 6842 34.6 ->
+// 21.8 us, with four 29.5), and 4,096 slices x inputs to add (2,048 where three or more output tiles add them again):
+// 1696-224-15 at batch 315 (26 slices) 39.3 -> 43.5 us, 800-159-147 at 137 (25 slices) 33.9 -> 38.8 without it.
+// Tiles of 32 outputs, of 64 once those of 32 would be more than one per CU (the basis is then evaluated once for both).
+constexpr long long kTailMaxEdges = 32768;
+constexpr long long kTailMaxWorkgroups = 2048;
+constexpr long long kTailSlicedInputs = 4096, kTailSlicedInputsManyTiles = 2048;
+
+// x_parts: slices the layer's input may come in.
+LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3,
+                      int x_parts, int min_rows) {
+  LayerPlan p = plan_mfma(n_in, n_out, B, n_heads, idx_u32, gb_kind, code, split3, min_rows);
+  const long long n_bt = (B + 31) / 32;
+  const int tile_n = split3 || n_out <= 32 || (n_out + 31) / 32 * n_bt * n_heads <= 256 ? 32 : 64;
+  const long long n_jt = (n_out + tile_n - 1) / tile_n;
+  if (n_in > kTailMaxIn || (long long)n_in * n_out > kTailMaxEdges || n_jt * n_bt * n_heads > kTailMaxWorkgroups) return p;
+  if (x_parts > 1 && (long long)x_parts * n_in > (n_jt > 2 ? kTailSlicedInputsManyTiles : kTailSlicedInputs)) return p;
+  p.kind = kPlanTail;
+  p.cfg.bt = 32;
+  p.tile_n = tile_n;
+  p.n_jt = (int)n_jt;
+  p.n_bt = (int)n_bt;
+  p.n_chunks = 1;
+  p.rows_per_chunk = n_in;
   return p;
 }
 
@@ -420,11 +462,11 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //     three passes (hi*lo, lo*hi, hi*hi: fp32-grade sums at matrix-core speed);
 //   fp16 path (KAN_PATH_MFMA, and AUTO from batch 32): up to kHalfFusedMaxBatch the fused
 //     kernel with fp16 operands, above that coefficient/basis preparation + the streaming
-//     contraction;
+//     contraction (small layers, on either path: coefficient preparation + one launch, plan_matrix);
 //   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) keep the fused kernel up to
 //     kFusedTwoTilesMaxBatch on either path.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
-                  bool column_ok) {
+                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
   const bool half_path = path == KAN_PATH_MFMA || (path == KAN_PATH_AUTO && B >= kAutoMfmaBatch);
@@ -439,12 +481,12 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
     if (B <= fused_max) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false);
-    return plan_mfma(L.in, L.out, B, n_heads, u32, gbk, code);
+    return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, false, x_parts, min_rows);
   }
   if (prepared_ok && B <= bucket_max_batch((long long)L.in * L.out))
     return column_ok && (long long)L.in * L.out * B <= kColumnMaxWork ? plan_column(L, B) : plan_bucket(L, B, n_heads);
   // large batches: the fp16 machinery with both operands split into high and low parts
-  if (B >= kSplitMinBatch && B > fused_max) return plan_mfma(L.in, L.out, B, n_heads, u32, gbk, code, true);
+  if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows);
   const long long edges = (long long)L.in * L.out;
   if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
   if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code);
@@ -494,10 +536,6 @@ struct WsPtrs {
 // neighbours: the partial sums of layer l (per bucket, or per chunk of inputs) are added and
 // squashed by layer l+1 itself: by the bucket kernel while it loads x, or by the basis
 // preparation of the matrix-core path.
-// (config 3 at batch 65-128, whose first layer is cut into 32 chunks: 55.3-56.4 us with the 32 slices handed
-// on against 56.7-57.4 us with a reduction launch)
-constexpr int kMaxChainedSlices = 32;   // more slices than this go through the reduction pass (more loads in flight per output)
-
 struct Chain {
   int in_parts = 1;              // slices of the input to add (1: plain x)
   long long in_part_stride = 0;
@@ -563,6 +601,31 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     const bool split3 = p.products == 3;
     st = run_prep_coef(p, a, heads, w, &pc, !chain.coef_done, s);
     if (st != KAN_OK) return st;
+    if (p.kind == kPlanTail) {
+      TailArgs t;
+      memset(&t, 0, sizeof(t));
+      t.cf = pc.cf;
+      t.cf_lo = pc.cf_lo;
+      t.cf_head_stride = pc.cf_head_stride;
+      t.bias_partial = pc.bias_partial;
+      t.bp_head_stride = pc.bp_head_stride;
+      t.x = a.x;
+      t.x_head_stride = a.x_head_stride;
+      t.x_part_stride = chain.in_part_stride;
+      t.x_parts = chain.in_parts;
+      t.x_tanh = chain.in_tanh;
+      t.vec = a.n_in % 4 == 0 && aligned(a.x, 16);      // (the strides are multiples of n_in)
+      t.dst = final_dst;
+      t.dst_head_stride = final_head_stride;
+      t.n_in = a.n_in;
+      t.n_out = a.n_out;
+      t.B = a.B;
+      t.n_jt = p.n_jt;
+      t.apply_tanh = apply_tanh;
+      t.rule = a.rule;
+      for (int h = 0; h < heads; ++h) t.scale[h] = p.cfg.code == kCbI8 ? a.h[h].scale : 1.0f;
+      return run(p.name, s, [&] { return launch_tail(t, split3, p.tile_n, dim3((unsigned)(p.n_jt * p.n_bt), 1, (unsigned)heads), s); });
+    }
     BasisBufs bb;
     st = run_prep_basis(p, a, heads, x_shared, w, chain, &bb, !chain.basis_done, s);
     if (st != KAN_OK) return st;
@@ -719,7 +782,7 @@ bool chained(const std::vector<LayerPlan>& plans, int l, int n_heads, const kan_
   // slices; few output tiles (each adds the slices again)
   if (plans[l + 1].kind == kPlanGather)
     return plans[l].n_chunks <= kGatherChainMaxParts && plans[l + 1].n_jt <= 4;
-  return plans[l + 1].kind == kPlanMfma && plans[l].n_chunks <= kMaxChainedSlices;
+  return plans[l + 1].mfma && plans[l].n_chunks <= kMaxChainedSlices;
 }
 
 // The fused kernel adds the slices of its own chunk of inputs before its first step when that
@@ -735,8 +798,8 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 }
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
-kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                     std::vector<LayerPlan>* plans, WsLayout* ws) {
+kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
+                          int min_rows, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -765,7 +828,7 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok);
+    LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? plans->back().n_chunks : 1, min_rows);
     plans->push_back(p);
     auto grow = [](size_t& dst, size_t v) { if (v > dst) dst = v; };
     grow(ws->partial, partial_bytes(p, R.out, B, group));
@@ -775,7 +838,7 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
       ws->cf += round_up((size_t)(p.products == 3 ? 2 : 1) * group * mfma_cf_records(R.in, R.out) * sizeof(uint4), 256);
       ws->bp += round_up((size_t)group * mfma_bp_floats(R.in, R.out) * sizeof(float), 256);
     }
-    if (p.mfma)
+    if (p.kind == kPlanMfma)
       grow(ws->u, round_up((size_t)(p.products == 3 ? 2 : 1) * (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16 * 16) * (size_t)B * sizeof(uint2), 256));
     if (l + 1 < n_layers) grow(ws->hidden, round_up((size_t)n_heads * (size_t)B * R.out * sizeof(float), 256));
   }
@@ -783,6 +846,22 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
   for (int l = 0; l + 1 < n_layers; ++l)
     if (chained(*plans, l, n_heads, layers, B)) ws->partial2 = ws->partial;
   return KAN_OK;
+}
+
+// Finer chunks write more partial sums: a call that fits the library's static scratch only without them is planned
+// without them.
+kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
+                     std::vector<LayerPlan>* plans, WsLayout* ws) {
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, plans, ws);
+  if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
+  std::vector<LayerPlan> compact;
+  WsLayout compact_ws;
+  st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRowsCompact, &compact, &compact_ws);
+  if (st == KAN_OK && compact_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
+    plans->swap(compact);
+    *ws = compact_ws;
+  }
+  return st;
 }
 
 }  // namespace
@@ -948,7 +1027,7 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     ps.x = x;
     ps.W = w.u;
     ps.W_lo = bb.u_lo;
-    ps.n_in = a0.n_in;
+    ps.n_in = p0.kind == kPlanMfma ? a0.n_in : 0;
     ps.B = a0.B;
     ps.rule = a0.rule;
     if (prep_start_blocks(ps) <= kPrepStartMaxBlocks) {

@@ -103,7 +103,7 @@ struct PrepStartArgs {
     int nx;                          // filled by the launcher: blocks along the outputs
     LayerPtrs h;
   } job[kStartJobs];
-  const float* x;                    // [B][n_in] of the first layer
+  const float* x;                    // [B][n_in] of the first layer; n_in = 0: no basis words
   uint2* W;
   uint2* W_lo;                       // split form only
   int n_in, B, rule;
@@ -152,6 +152,27 @@ hipError_t launch_prep_basis(const float* x, long long x_head_stride, int x_part
                              int x_tanh, uint2* W, uint2* W_lo, long long w_head_stride, int n_in, int B, int heads,
                              int rule, hipStream_t);
 hipError_t launch_mfma(const MfmaArgs&, int tile_m, int tile_n, dim3 grid, hipStream_t);   // samples (64 | 128) x outputs (128; 256 with 128 samples) per tile
+
+// ---- small layers of the matrix-core path: basis, contraction and sum over all inputs in one launch ----------
+constexpr int kTailMaxIn = 448;       // inputs (those of 32 samples are kept in LDS)
+struct TailArgs {
+  const uint4* cf;             // records as kan_mfma takes them
+  const uint4* cf_lo;          // split form only
+  long long cf_head_stride;
+  const float* bias_partial;
+  long long bp_head_stride;
+  const float* x;              // [head or 1][x_parts][B][n_in]: slices to add in order (and squash: x_tanh)
+  long long x_head_stride, x_part_stride;
+  int x_parts, x_tanh;
+  int vec;                     // 16-byte loads: n_in in fours, x and the slices 16-byte aligned
+  float* dst;                  // finished outputs
+  long long dst_head_stride;
+  int n_in, n_out, B;
+  int n_jt;                    // blockIdx.x = tile of 32 samples * n_jt + output tile (of tile_n outputs)
+  int apply_tanh, rule;
+  float scale[kMaxGroup];
+};
+hipError_t launch_tail(const TailArgs&, bool split, int tile_n, dim3 grid, hipStream_t);    // tile_n: 32, or 64 (not split)
 
 // ---- fused gather + matrix-core kernel (batch tiles of 32 or 64 samples) --------------
 constexpr int kFusedTileN = 128;      // outputs per workgroup

@@ -68,7 +68,6 @@ constexpr int kBufferFlags = 0x00020000;   // buffer resource word 3: raw 32-bit
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h16x16 __attribute__((ext_vector_type(16)));
 
 // Ten fp32 coefficients as high and low fp16 parts, in pairs (m, m + 5): c = hi + lo / 2048.
 __device__ __forceinline__ void split_pairs(const float (&c)[kG], uint32_t (&hi)[5], uint32_t (&lo)[5]) {
@@ -332,30 +331,8 @@ __device__ __forceinline__ void prep_basis_block(const float* __restrict__ xh, c
       float xv = xs[r];
       if (x_tanh) xv = tanhf(xv);
       const BasisW bw = basis_fast(xv, rule);
-      const uint32_t l = (uint32_t)bw.span;
-      const float w0 = bw.w0, w1 = bw.w1, w2 = bw.w2, w3 = bw.w3;
-      const uint32_t sx = ((l & 1u) << 15) | ((l & 2u) << 30), sy = (l & 4u) << 13;
-      uint32_t hx = pack_h2(w0, w1), hy = pack_h2(w2, w3);
-      if (wl) {
-        // split form: the high part is the weight cut to fp16 towards zero, so that the low
-        // part (w - hi) * 2048 is never negative and its sign bits are free for the span too
-        const float w[4] = {w0, w1, w2, w3};
-        uint32_t hb[4];
-        float rest[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          hb[k] = ((k & 1) ? ((k < 2 ? hx : hy) >> 16) : ((k < 2 ? hx : hy) & 0xffffu));
-          if (half_bits_to_float(hb[k]) > w[k]) hb[k] -= 1u;       // one fp16 step down (w > 0 there)
-          if ((hb[k] & 0x7c00u) == 0u) hb[k] = 0u;                 // no subnormal high parts (and no -0)
-          rest[k] = (w[k] - half_bits_to_float(hb[k])) * 2048.0f;
-        }
-        hx = hb[0] | (hb[1] << 16);
-        hy = hb[2] | (hb[3] << 16);
-        vlo.x = (flush_h2(pack_h2(rest[0], rest[1])) & 0x7fff7fffu) | sx;
-        vlo.y = (flush_h2(pack_h2(rest[2], rest[3])) & 0x7fff7fffu) | sy;
-      }
-      v.x = hx | sx;
-      v.y = hy | sy;
+      if (wl) basis_words_split(bw, v, vlo);
+      else v = basis_words(bw);
     }
     tile[ty + 8 * r][tx] = v;
     if (wl) tile_lo[ty + 8 * r][tx] = vlo;
@@ -433,31 +410,6 @@ __global__ __launch_bounds__(kThreads) void kan_prep_start_kernel(const PrepStar
 // MB = MFMA row blocks per wave (tile of 32 MB samples), NB = column blocks per wave (the
 // four waves cover 128 NB outputs).  MB = 4 reads half the Chat bytes per MFMA; MB = 2 is
 // for layers whose grid of 128-sample tiles would leave CUs idle (three workgroups per CU).
-
-// Per span l: byte-permute selectors that pick, from the four fp16 weights {w23:w01} of an
-// input, the stored values of its pairs (m, m+5): word 0 pairs 0 and 1, word 1 pairs 2 and 3,
-// word 2 pair 4 (high half zero); word 3 the index byte of the input's two full groups
-// (nibble = position of the first value | position of the second << 2) and, in bit 8, whether
-// pair 4 takes coefficient 9: one 16-byte table read per input.  Selector byte 0x0c yields 0.
-__device__ __forceinline__ void fill_sparse_selectors(uint32_t (*sel)[8], int tid) {
-  if (tid < kSpans) {
-    const int l = tid;
-    uint32_t half_sel[5], hi[5];
-#pragma unroll
-    for (int p = 0; p < 5; ++p) {
-      int k = -1;
-      hi[p] = 0;
-      if (p >= l && p <= l + 3) k = p - l;
-      else if (p + 5 >= l && p + 5 <= l + 3) { k = p + 5 - l; hi[p] = 1; }
-      half_sel[p] = k >= 0 ? (uint32_t)((2 * k) | ((2 * k + 1) << 8)) : 0x0c0cu;
-    }
-    sel[l][0] = half_sel[0] | (half_sel[1] << 16);
-    sel[l][1] = half_sel[2] | (half_sel[3] << 16);
-    sel[l][2] = half_sel[4] | 0x0c0c0000u;
-    sel[l][3] = (hi[0] | ((2u + hi[1]) << 2)) | ((hi[2] | ((2u + hi[3]) << 2)) << 4) | (hi[4] << 8);
-    sel[l][4] = sel[l][5] = sel[l][6] = sel[l][7] = 0;
-  }
-}
 
 template <int MB, int NB, bool THREE, int NW = 4>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : (MB == 2 ? 3 : 2)) void kan_mfma_kernel(const MfmaArgs a) {
@@ -940,7 +892,8 @@ hipError_t launch_prep_coef(const GatherCfg& c, const PrepCoefArgs& a, int heads
 }
 
 hipError_t launch_prep_start(const GatherCfg& c, PrepStartArgs& a, bool split, hipStream_t s) {
-  if (c.code == kDense || a.n_jobs < 1 || a.n_jobs > kStartJobs || !a.x || !a.W || (split && !a.W_lo)) return hipErrorInvalidValue;
+  if (c.code == kDense || a.n_jobs < 1 || a.n_jobs > kStartJobs) return hipErrorInvalidValue;
+  if (a.n_in > 0 && (!a.x || !a.W || (split && !a.W_lo))) return hipErrorInvalidValue;
   long long blocks = 0;
   for (int k = 0; k < a.n_jobs; ++k) {
     PrepStartArgs::Job& job = a.job[k];

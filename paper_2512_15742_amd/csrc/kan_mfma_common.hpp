@@ -8,6 +8,7 @@ namespace kan {
 
 typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h16x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ uint32_t pack_h2(float a, float b) {
@@ -214,6 +215,50 @@ __device__ __forceinline__ void unpack_basis(uint2 u, uint32_t& l, uint32_t& w01
   l = ((u.x >> 15) & 1u) | ((u.x >> 30) & 2u) | ((u.y >> 13) & 4u);
   w01 = u.x & 0x7fff7fffu;
   w23 = u.y & 0x7fff7fffu;
+}
+
+// An input's basis word for a sample = { half2(w0, w1), half2(w2, w3) } with span bit 0, 1, 2 in the
+// sign bits of w0, w1, w2 (the weights are never negative).
+__device__ __forceinline__ uint2 basis_words(const BasisW& bw) {
+  const uint32_t l = (uint32_t)bw.span;
+  return make_uint2(pack_h2(bw.w0, bw.w1) | ((l & 1u) << 15) | ((l & 2u) << 30), pack_h2(bw.w2, bw.w3) | ((l & 4u) << 13));
+}
+// Split form: the high parts are the weights cut to fp16 towards zero, so that the low parts (w - hi) * 2048
+// are never negative and their sign bits are free for the span too.
+__device__ __forceinline__ void basis_words_split(const BasisW& bw, uint2& v, uint2& lo) {
+  const uint32_t l = (uint32_t)bw.span;
+  const uint32_t sx = ((l & 1u) << 15) | ((l & 2u) << 30), sy = (l & 4u) << 13;
+  split_weights(bw.w0, bw.w1, v.x, lo.x);
+  split_weights(bw.w2, bw.w3, v.y, lo.y);
+  v.x |= sx;
+  v.y |= sy;
+  lo.x |= sx;
+  lo.y |= sy;
+}
+
+// Per span l: byte-permute selectors that pick, from the four fp16 weights {w23:w01} of an
+// input, the stored values of its pairs (m, m+5): word 0 pairs 0 and 1, word 1 pairs 2 and 3,
+// word 2 pair 4 (high half zero); word 3 the index byte of the input's two full groups
+// (nibble = position of the first value | position of the second << 2) and, in bit 8, whether
+// pair 4 takes coefficient 9: one 16-byte table read per input.  Selector byte 0x0c yields 0.
+__device__ __forceinline__ void fill_sparse_selectors(uint32_t (*sel)[8], int tid) {
+  if (tid < kSpans) {
+    const int l = tid;
+    uint32_t half_sel[5], hi[5];
+#pragma unroll
+    for (int p = 0; p < 5; ++p) {
+      int k = -1;
+      hi[p] = 0;
+      if (p >= l && p <= l + 3) k = p - l;
+      else if (p + 5 >= l && p + 5 <= l + 3) { k = p + 5 - l; hi[p] = 1; }
+      half_sel[p] = k >= 0 ? (uint32_t)((2 * k) | ((2 * k + 1) << 8)) : 0x0c0cu;
+    }
+    sel[l][0] = half_sel[0] | (half_sel[1] << 16);
+    sel[l][1] = half_sel[2] | (half_sel[3] << 16);
+    sel[l][2] = half_sel[4] | 0x0c0c0000u;
+    sel[l][3] = (hi[0] | ((2u + hi[1]) << 2)) | ((hi[2] | ((2u + hi[3]) << 2)) << 4) | (hi[4] << 8);
+    sel[l][4] = sel[l][5] = sel[l][6] = sel[l][7] = 0;
+  }
 }
 
 }  // namespace kan
