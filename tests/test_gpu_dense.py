@@ -45,3 +45,18 @@ def test_fp32_operands_have_no_fp16_range(kb):
     y = kb.kan_dense_layer_forward(to_dev(coef), to_dev(x)).cpu().numpy()
     y_ref, A = ko.dense_layer_forward(coef, x, return_abs=True)
     assert np.all(np.abs(y - y_ref) <= TOL_FP32 * A)
+
+
+@pytest.mark.parametrize("B", [1, 16])
+def test_fp32_operands_hold_weights_rounded_once(kb, B):
+    """Up to 16 samples every weight is the fp64 value rounded once to fp32.  One input, output m with the m-th unit
+    grid: the outputs are the ten basis values of the sample themselves (a one times a weight and zeros, exact in
+    fp32), so they lie within half a unit in the last place (2^-24 of the value) of the oracle's (whose own knots are good to 1e-16)."""
+    x = np.random.default_rng(77 + B).uniform(-1.0, 1.0, (400 * B, 1)).astype(np.float32)
+    x[:4 * B, 0] = np.linspace(-1.0, 1.0, 4 * B, dtype=np.float32)
+    coef = np.eye(10, dtype=np.float32)[None]
+    y_ref = ko.dense_layer_forward(coef, x)
+    for b in range(0, x.shape[0], B):
+        y = kb.kan_dense_layer_forward(to_dev(coef), to_dev(x[b:b + B])).cpu().numpy()
+        ref = y_ref[b:b + B]
+        assert np.all(np.abs(y - ref) <= 2.0 ** -24 * 1.0001 * np.abs(ref) + 1e-15), np.abs(y - ref).max()
