@@ -7,8 +7,8 @@
 // [K x 10] x [10 x E] contraction: it runs on the matrix cores.  To keep the decision at
 // fp32 quality with fp16 operands, both operands are split into a high and a low fp16 part
 // and the contraction runs over 32 slots (two v_mfma_f32_32x32x16_f16 per 32 x 32 tile):
-//     centroid side  [ hi(C) (10) | lo(C) (10) | hi(C) (10) | hi(-|C|^2/2) | lo(-|C|^2/2) ]
-//     edge side      [ hi(n) (10) | hi(n) (10) | lo(n) (10) |      1       |      1       ]
+//     shape  [ hi(C) (10) | hi(-|C|^2/2) | lo(C) 0..4 ]   [ lo(C) 5..9 | hi(C) (10) | lo(-|C|^2/2) ]
+//     edge   [ hi(n) (10) |      1       | hi(n) 0..4 ]   [ hi(n) 5..9 | lo(n) (10) |      1       ]
 // (the dropped lo x lo term is ~1e-7 of the score).  Centroids are the MFMA rows and edges
 // the columns, so a lane owns one edge and 16 of the 32 centroids of a tile: the running
 // maximum over centroids never crosses lanes until the very end.
@@ -42,39 +42,9 @@ __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
 }
 
 // Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) a hugely negative norm term,
-// so that the row never wins.
-__device__ __forceinline__ uint4 centroid_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
-  _Float16 v[8];
-  float nrm = 0.f;
-  float row[kG];
-#pragma unroll
-  for (int m = 0; m < kG; ++m) {
-    row[m] = there ? cb[c * kG + m] : 0.f;
-    nrm = fmaf(row[m], row[m], nrm);
-  }
-  const float half_norm = there ? -0.5f * nrm : -30000.0f;
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int s = s0 + t;
-    _Float16 hi, lo;
-    if (s < 30) {
-      split_h(row[s % kG], hi, lo);
-      v[t] = (s >= 10 && s < 20) ? lo : hi;
-    } else {
-      split_h(half_norm, hi, lo);
-      v[t] = s == 30 ? hi : lo;
-    }
-  }
-  h16x8 pk = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
-  return __builtin_bit_cast(uint4, pk);
-}
-
-// The same terms for the tiles of the bounded search, in two instructions of which the first alone bounds the score
-// from above: it has the products of the high parts, half of the low ones, and the norm raised by what the others can
-// amount to (2^-11 of |C| from the low parts of either side, and what lies below fp16's normal range).
-//     shape  [ hi(C) (10) | raised -|C|^2/2 | lo(C) 0..4 ]   [ lo(C) 5..9 | hi(C) (10) | rest of the norm ]
-//     edge   [ hi(n) (10) |        1        | hi(n) 0..4 ]   [ hi(n) 5..9 | lo(n) (10) |         1        ]
-__device__ __forceinline__ uint4 tile_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
+// so that the row never wins.  Both searches take these, and the products in this order: a score has the same bits in
+// either.
+__device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
   h16x8 v;
   float row[kG], nrm = 0.f;
 #pragma unroll
@@ -83,13 +53,11 @@ __device__ __forceinline__ uint4 tile_slots(const float* __restrict__ cb, long l
     nrm = fmaf(row[m], row[m], nrm);
   }
   const float half_norm = there ? -0.5f * nrm : -30000.0f;
-  float up = half_norm + 1.3e-3f * sqrtf(nrm) + 1e-4f;
-  up = (float)(_Float16)(up + fabsf(up) * (1.0f / 1024.0f));        // (rounds to half a unit: never below)
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int s = s0 + t;
-    float src = s == 10 ? up : half_norm - up;
-    bool low = false;
+    float src = half_norm;
+    bool low = s == 31;
 #pragma unroll
     for (int m = 0; m < kG; ++m)
       if (s == m || s == 11 + m || s == 21 + m) {
@@ -113,7 +81,7 @@ __global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __res
   if (rec >= (long long)n_tiles * 2 * 64) return;
   const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
   const int c = (int)(rec >> 7) * 32 + (lane & 31);
-  out[rec] = centroid_slots(cb, c, c < K, ks * 16 + (lane >> 5) * 8);
+  out[rec] = shape_slots(cb, c, c < K, ks * 16 + (lane >> 5) * 8);
 }
 
 // Step 1 of an edge: bias = mean, gain = norm of the centred grid, direction = centred / gain.
@@ -199,10 +167,10 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
       _Float16 hi, lo;
       split_h(c[m], hi, lo);
       p[m] = hi;
-      p[10 + m] = hi;
-      p[20 + m] = lo;
+      p[11 + m] = hi;
+      p[21 + m] = lo;
     }
-    p[30] = (_Float16)1.0f;
+    p[10] = (_Float16)1.0f;
     p[31] = (_Float16)1.0f;
   }
   __syncthreads();
@@ -686,7 +654,7 @@ __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
       const int row = rec >> 2, part = rec & 3, ks = part >> 1, half = part & 1;       // (a row's four records)
       const int tile = tile0 + (row >> 5), r = row & 31;
       const uint32_t k = row < nc ? (uint32_t)sorted[row] : 0xffffffffu;
-      a.frag[((long long)tile * 2 + ks) * 64 + half * 32 + r] = tile_slots(a.cb, k, row < nc, ks * 16 + half * 8);
+      a.frag[((long long)tile * 2 + ks) * 64 + half * 32 + r] = shape_slots(a.cb, k, row < nc, ks * 16 + half * 8);
       if (part == 0) a.ids[tile * 32 + r] = k;
     }
     for (int t = tid; t < tiles; t += 256) {
@@ -715,6 +683,13 @@ __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
   }
 }
 
+// What the second product can add to the score of a shape at distance d or less of an edge (|n| = 1): its norm is at
+// most 1 + d, the low parts are at most 2^-11 of what they complete, on either side of n . C and in |C|^2 / 2.
+__device__ __forceinline__ float first_product_slack(float d) {
+  const float r = 1.001f + d;
+  return d <= kFar ? fmaf(r, fmaf(r, 2.45e-4f, 9.8e-4f), 1e-5f) : INFINITY;
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
 }
@@ -738,7 +713,7 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   const int key = a.key[1][e];
   const bool live = pos < a.E && key < a.M;
 
-  // edge operands of the search (see tile_slots) and of the bound
+  // edge operands of the search (see the head of the file) and of the bound
   h16x8 fb[2], fe;
   {
     float n[kG], mean, gain;
@@ -763,9 +738,12 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   float best = -3.0e38f;
   uint32_t best_id = 0;
   auto id_of = [&](int t, int r) { return a.ids[t * 32 + 8 * (r >> 2) + 4 * half + (r & 3)]; };
+  // The first product of a shape that can win reaches `near` = best - slack (see first_product_slack).
+  float slack = 0.f, near = 0.f;
   auto take = [&](float sc, uint32_t id) {       // (equal scores: the lower id)
     if (sc > best || (sc == best && id < best_id)) best_id = id;
     best = fmaxf(best, sc);
+    near = best - slack;
   };
   auto leave = [&] {                             // to the whole search
     uint32_t to = 0;
@@ -804,16 +782,19 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   auto distance = [&] {
     const float sc_o = __shfl_xor(best, 32, kWave);
     take(sc_o, (uint32_t)__shfl_xor((int)best_id, 32, kWave));
-    return live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
+    const float dist = live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
+    slack = live ? first_product_slack(dist) : -INFINITY;      // (an edge without direction asks for nothing)
+    near = best - slack;
+    return dist;
   };
   const __amdgpu_buffer_rsrc_t bound_rsrc = buffer_of(a.bound, (size_t)((T + 31) / 32) * 1024);
   const __amdgpu_buffer_rsrc_t frag_rsrc = buffer_of(a.frag, (size_t)T * 2048);
   auto load = [&](const __amdgpu_buffer_rsrc_t& rsrc, int at) {
     return __builtin_bit_cast(h16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, at, 0));
   };
-  // A tile with a bound that reaches the best score gets the second instruction.
-  auto examine = [&](int t, const f32x16& bound) {
-    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(load(frag_rsrc, t * 2048 + 1024), fb[1], bound, 0, 0, 0);
+  // A tile whose first product comes near the best score gets the second instruction.
+  auto examine = [&](int t, const f32x16& first) {
+    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(load(frag_rsrc, t * 2048 + 1024), fb[1], first, 0, 0, 0);
     const float m = max_of(acc);
     if (m >= best) take(m, id_of(t, row_of(acc, m)));
   };
@@ -894,9 +875,9 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
             f[k] = load(frag_rsrc, t[k] * 2048);
             f[k + 1] = load(frag_rsrc, t[k + 1] * 2048);
             const float m0 = max_of(acc0), m1 = max_of(acc1);
-            if (__ballot(fmaxf(m0, m1) >= best)) {
-              if (__ballot(m0 >= best)) examine(u0, acc0);
-              if (__ballot(m1 >= best)) examine(u1, acc1);
+            if (__ballot(fmaxf(m0, m1) >= near)) {
+              if (__ballot(m0 >= near)) examine(u0, acc0);
+              if (__ballot(m1 >= near)) examine(u1, acc1);
             }
           }
         }

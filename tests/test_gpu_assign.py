@@ -131,6 +131,9 @@ def _grids(kind, K, E, seed):
         cb *= torch.rand((K, 1), generator=g, device="cuda") * 3
     if kind == "one row":
         cb[:] = cb[:1].clone()
+    if kind == "near ties":        # pairs of rows 1e-5 apart: scores that differ by less than a millionth
+        cb *= 0.97 + torch.rand((K, 1), generator=g, device="cuda") * 0.06
+        cb[K // 2:] = cb[:K - K // 2] + 3e-6 * torch.randn((K - K // 2, 10), generator=g, device="cuda")
     k = torch.randint(0, K, (E, 1), generator=g, device="cuda")
     if kind == "one cell":
         k[:] = 5
@@ -171,6 +174,32 @@ def test_bounded_search_finds_the_nearest_row(kb, kind, K, E):
             assert float((d2.gather(1, x[s:s + 4096, None])[:, 0] - best).max()) <= GAP
         clear = second - best > GAP
         assert torch.equal(a[s:s + 4096][clear], b[s:s + 4096][clear])
+
+
+def _both_searches(kb, coef, cb):
+    """Ids of the bounded and of the whole search."""
+    E, K = coef.shape[0] * coef.shape[1], cb.shape[0]
+    L = kb.lib()
+    whole = torch.empty(L.kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
+    assert L.kan_vq_assign_fast_workspace_bytes(coef.shape[0], coef.shape[1], K) > whole.numel()
+    mask = 0xffff if K <= 65536 else 0xffffffff
+    return [kb.kan_vq_assign(coef, cb, ws=ws)[0].view(-1).long() & mask for ws in (None, whole)]
+
+
+@pytest.mark.parametrize("K,E", [(16384, 98304), (20010, 90001)])
+def test_bounded_search_scores_as_well_as_the_whole_search(kb, K, E):
+    """Pairs of rows whose scores differ by less than a millionth: as many edges of the bounded search as of the whole
+    one get the farther row of the pair (fp64, on the device), up to four deviations of such a count."""
+    coef, cb = _grids("near ties", K, E, K + E + 1)
+    n = coef.view(E, 10).double()
+    n = n - n.mean(1, keepdim=True)
+    n /= n.norm(dim=1, keepdim=True)
+    wrong = []
+    for ids in _both_searches(kb, coef, cb):
+        twin = torch.where(ids < K // 2, ids + K // 2, ids - K // 2)
+        d2 = [((n - cb[i].double()) ** 2).sum(1) for i in (ids, twin)]
+        wrong.append(int((d2[0] > d2[1]).sum()))
+    assert wrong[0] <= wrong[1] + 4 * wrong[1] ** 0.5, wrong
 
 
 @pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
