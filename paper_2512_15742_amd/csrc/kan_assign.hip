@@ -291,9 +291,11 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 //     (2) the tiles within R + min(d, the wave's mean d): finds nearly all of the others, whose d of step 1 alone
 //         would ask for a large part of the codebook;
 //     (3) where an edge is left with a larger d: what that one still asks for.
-// The scores are those of the whole search, and no tile that can hold the best one is left out.  A wave that would
-// visit more than kRestShare of the tiles hands its edges to the whole search, which shares a tile's operands among
-// four times as many: codebooks or grids that the cells do not separate cost what they did without them.
+// The scores are those of the whole search, bit for bit, no tile that can hold the best one is left out and equal
+// scores go to the lowest id: the result is the whole search's, whichever edges share a wave (the sort places them in
+// no particular order) and whichever of them are handed over.  A wave that would visit more than kRestShare of the tiles
+// hands its edges to the whole search, which shares a tile's operands among four times as many: codebooks or grids
+// that the cells do not separate cost what they did without them.
 //
 // What bounds it: instructions issued.  A wave of the search makes (tiles / 32) bound tests and visits about 250 of
 // 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each one matrix and about ten vector instructions; the
@@ -437,7 +439,10 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_cells_kernel(const Cell
         c[m] = a.cb[ec * kG + m];
         nrm = fmaf(c[m], c[m], nrm);
       }
-      atomicMin(&s_least, ((unsigned long long)__float_as_uint(nrm) << 32) | (uint32_t)ec);
+      // (by the norm term as the operands hold it, so that equal ones are equal here as well)
+      _Float16 hi, lo;
+      split_h(-0.5f * nrm, hi, lo);
+      atomicMin(&s_least, ((unsigned long long)__float_as_uint(fabsf((float)hi + (float)lo)) << 32) | (uint32_t)ec);
     } else {
       float mean, g;
       normalise(a.coef + ec * kG, c, mean, g);
@@ -607,6 +612,7 @@ __global__ __launch_bounds__(kSortThreads) void kan_cell_place_kernel(const Cell
 // Tiles of one cell: members sorted by distance to the centre (then by id), operands of the search and of the bound.
 __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
   __shared__ unsigned long long sorted[kBuildChunk];       // {squared distance to the centre, id}
+  __shared__ uint32_t row_id[kBuildChunk];                 // a tile's rows by id
   const int tid = threadIdx.x, m = blockIdx.x;
   const float* cr = centre_row(a, m);
   float c[kG], cn = 0.f;
@@ -650,10 +656,19 @@ __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
         }
         __syncthreads();
       }
+    // Within a tile by id: of equal scores a lane keeps the first row, which is then the lowest id, as in the whole search.
+    for (int i = tid; i < nc; i += 256) {
+      const int t0 = i & ~31, t1 = min(nc, t0 + 32);
+      const uint32_t id = (uint32_t)sorted[i];
+      int at = t0;
+      for (int o = t0; o < t1; ++o) at += (uint32_t)sorted[o] < id;
+      row_id[at] = id;
+    }
+    __syncthreads();
     for (int rec = tid; rec < tiles * 128; rec += 256) {
       const int row = rec >> 2, part = rec & 3, ks = part >> 1, half = part & 1;       // (a row's four records)
       const int tile = tile0 + (row >> 5), r = row & 31;
-      const uint32_t k = row < nc ? (uint32_t)sorted[row] : 0xffffffffu;
+      const uint32_t k = row < nc ? row_id[row] : 0xffffffffu;
       a.frag[((long long)tile * 2 + ks) * 64 + half * 32 + r] = shape_slots(a.cb, k, row < nc, ks * 16 + half * 8);
       if (part == 0) a.ids[tile * 32 + r] = k;
     }
@@ -715,9 +730,11 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
 
   // edge operands of the search (see the head of the file) and of the bound
   h16x8 fb[2], fe;
+  bool number;
   {
     float n[kG], mean, gain;
     normalise(a.coef + (long long)e * kG, n, mean, gain);
+    number = gain == gain;
     _Float16 hi[kG], lo[kG];
 #pragma unroll
     for (int m = 0; m < kG; ++m) split_h(n[m], hi[m], lo[m]);
@@ -745,13 +762,15 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     best = fmaxf(best, sc);
     near = best - slack;
   };
+  // (an edge without direction; one that is no number has no scores and keeps row 0)
+  auto undirected = [&] { return number ? *a.least : 0u; };
   auto leave = [&] {                             // to the whole search
     uint32_t to = 0;
     const unsigned long long w = __ballot(live && half == 0);
     if (lane == 0) to = atomicAdd(a.n_rest, (uint32_t)__popcll(w));
     to = (uint32_t)__builtin_amdgcn_readfirstlane((int)to);
     if (live && half == 0) a.rest[to + __popcll(w & ((1ull << lane) - 1))] = e;
-    if (pos < a.E && half == 0 && !live) ((IdxT*)a.idx)[e] = (IdxT)*a.least;
+    if (pos < a.E && half == 0 && !live) ((IdxT*)a.idx)[e] = (IdxT)undirected();
   };
 
   // (1) own cells, both instructions of every tile
@@ -906,7 +925,7 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     return;
   }
   (void)distance();
-  if (lane < 32 && pos < a.E) ((IdxT*)a.idx)[e] = (IdxT)(live ? best_id : *a.least);
+  if (lane < 32 && pos < a.E) ((IdxT*)a.idx)[e] = (IdxT)(live ? best_id : undirected());
 }
 
 // ---- reconstruction quality ---------------------------------------------------------------------

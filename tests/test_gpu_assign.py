@@ -202,6 +202,23 @@ def test_bounded_search_scores_as_well_as_the_whole_search(kb, K, E):
     assert wrong[0] <= wrong[1] + 4 * wrong[1] ** 0.5, wrong
 
 
+@pytest.mark.parametrize("kind,K,E", [("trained", 16421, 98101), ("trained", 70000, 24001), ("far", 16384, 98337),
+                                      ("duplicates", 16384, 98304), ("norms", 16384, 98304), ("near ties", 16384, 98304),
+                                      ("flat", 16384, 98304), ("one cell", 16384, 98304), ("one row", 16384, 98304)])
+def test_bounded_search_gives_the_ids_of_the_whole_search(kb, kind, K, E):
+    """Not one id differs, whichever edges share a wave and are handed over: equal scores go to the lowest id in both,
+    edges of gain 0 to the same shape, and grids that are no numbers or overflow to what the whole search gives."""
+    coef, cb = _grids(kind, K, E, K + E + 2)
+    odd = coef.view(E, 10)[7:1007].view(10, 100, 10)
+    odd[0] = float("nan")
+    odd[1, :, 3] = float("inf")
+    odd[2] *= 1e30                                       # the gain overflows
+    odd[3] = 0.25
+    a, b = _both_searches(kb, coef, cb)
+    assert torch.equal(a, b), int((a != b).sum())
+    assert torch.equal(a, _both_searches(kb, coef, cb)[0])
+
+
 @pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
 def test_whole_search_shared_and_separate_waves(kb, K, E):
     """Either side of the switch between eight waves on 128 edges and four on 512: gathers the nearest row."""
