@@ -730,11 +730,15 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
 
   // edge operands of the search (see the head of the file) and of the bound
   h16x8 fb[2], fe;
-  bool number;
+  bool number, unit;
   {
     float n[kG], mean, gain;
     normalise(a.coef + (long long)e * kG, n, mean, gain);
     number = gain == gain;
+    float nn = 0.f;
+#pragma unroll
+    for (int m = 0; m < kG; ++m) nn = fmaf(n[m], n[m], nn);
+    unit = nn <= 1.000003f;      // longer ones (squares in the subnormal range, below 1e-38, lose bits): the bounds do not hold
     _Float16 hi[kG], lo[kG];
 #pragma unroll
     for (int m = 0; m < kG; ++m) split_h(n[m], hi[m], lo[m]);
@@ -801,7 +805,8 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   auto distance = [&] {
     const float sc_o = __shfl_xor(best, 32, kWave);
     take(sc_o, (uint32_t)__shfl_xor((int)best_id, 32, kWave));
-    const float dist = live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
+    float dist = live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
+    if (live && !unit) dist = 2.0f * kFar;       // (every tile: the wave goes to the whole search)
     slack = live ? first_product_slack(dist) : -INFINITY;      // (an edge without direction asks for nothing)
     near = best - slack;
     return dist;

@@ -219,6 +219,15 @@ def test_bounded_search_gives_the_ids_of_the_whole_search(kb, kind, K, E):
     assert torch.equal(a, _both_searches(kb, coef, cb)[0])
 
 
+@pytest.mark.parametrize("scale", [1e-19, 1e-21, 3e-22])
+def test_bounded_search_on_grids_with_subnormal_squares(kb, scale):
+    """Their normalised vectors are longer than one (the sum of squares has few bits left): still the whole search's ids."""
+    coef, cb = _grids("trained", 16384, 98304, 5)
+    coef *= scale
+    a, b = _both_searches(kb, coef, cb)
+    assert torch.equal(a, b), int((a != b).sum())
+
+
 @pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
 def test_whole_search_shared_and_separate_waves(kb, K, E):
     """Either side of the switch between eight waves on 128 edges and four on 512: gathers the nearest row."""
