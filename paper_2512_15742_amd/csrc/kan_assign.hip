@@ -41,8 +41,8 @@ __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
   lo = (_Float16)(v - (float)hi);
 }
 
-// Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) a hugely negative norm term,
-// so that the row never wins.  Both searches take these, and the products in this order: a score has the same bits in
+// Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) the norm term is minus infinity,
+// so that the row never wins, whatever the norms of the shapes.  Both searches take these, and the products in this order: a score has the same bits in
 // either.
 __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
   h16x8 v;
@@ -52,7 +52,7 @@ __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long 
     row[m] = there ? cb[c * kG + m] : 0.f;
     nrm = fmaf(row[m], row[m], nrm);
   }
-  const float half_norm = there ? -0.5f * nrm : -30000.0f;
+  const float half_norm = there ? -0.5f * nrm : -INFINITY;
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int s = s0 + t;
@@ -66,7 +66,7 @@ __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long 
       }
     _Float16 hi, lo;
     split_h(src, hi, lo);
-    v[t] = low ? lo : hi;
+    v[t] = low ? (there ? lo : (_Float16)0.0f) : hi;
   }
   return __builtin_bit_cast(uint4, v);
 }

@@ -228,6 +228,23 @@ def test_bounded_search_on_grids_with_subnormal_squares(kb, scale):
     assert torch.equal(a, b), int((a != b).sum())
 
 
+@pytest.mark.parametrize("K,E", [(16421, 98304), (1000, 3000)])
+def test_shapes_of_large_norm_win_over_rows_past_the_last(kb, K, E):
+    """Norms of 250 to 350 (half their square is still an fp16 number): every id is a shape, and as near as the nearest
+    up to the rounding of scores of 5e4 (22 bits: 0.012, twice that for a difference, twice that for distances)."""
+    coef, cb = _grids("trained", K, E, 9)
+    cb *= 250 + 100 * torch.rand((K, 1), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    idx = kb.kan_vq_assign(coef, cb)[0].view(-1).long() & 0xffff
+    assert int(idx.max()) < K
+    n = coef.view(E, 10).double()
+    n = n - n.mean(1, keepdim=True)
+    n /= n.norm(dim=1, keepdim=True)
+    c = cb.double()
+    for s in range(0, E, 4096):
+        d2 = 1.0 - 2 * n[s:s + 4096] @ c.T + (c ** 2).sum(1)
+        assert float((d2.gather(1, idx[s:s + 4096, None])[:, 0] - d2.min(1).values).max()) <= 0.05
+
+
 @pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
 def test_whole_search_shared_and_separate_waves(kb, K, E):
     """Either side of the switch between eight waves on 128 edges and four on 512: gathers the nearest row."""
