@@ -23,6 +23,8 @@
 // That is the whole search (kan_assign_kernel).  Large codebooks take the bounded search further down, which
 // finds the same shapes from a small part of the scores.
 
+#include <algorithm>
+
 #include "kan_device.hpp"
 #include "kan_internal.hpp"
 #include "kan_mfma_common.hpp"
@@ -74,9 +76,9 @@ __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long 
 // Centroid-side operands in MFMA A-fragment order: record [(tile * 2 + kstep) * 64 + lane]
 // holds slots kstep*16 + (lane/32)*8 .. +8 of centroid tile*32 + (lane & 31).
 __global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __restrict__ cb, int K, int n_tiles,
-                                                              const uint32_t* __restrict__ n_list,
+                                                              const uint32_t* __restrict__ any,
                                                               uint4* __restrict__ out) {
-  if (n_list && *n_list == 0) return;
+  if (any && *any == 0) return;
   const long long rec = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (rec >= (long long)n_tiles * 2 * 64) return;
   const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
@@ -129,8 +131,10 @@ struct AssignArgs {
   const float* coef;        // [E][10]
   const uint4* cent;        // prepared centroid operands
   long long E;
-  const uint32_t* list;     // null, or the edges to serve: list[0 .. *n_list - 1], E the most there can be
-  const uint32_t* n_list;
+  // LIST: the edges in the order of the bounded search, and of every 32 whether they are left (their gains and biases are
+  // there already)
+  const uint32_t* list;
+  const uint8_t* left;      // [4 * ceil(E / 128)]
   int n_tiles;              // ceil(K / 32)
   void* idx;
   float* gain;
@@ -140,141 +144,159 @@ struct AssignArgs {
 // SPLIT = 1: four waves with 128 edges of their own each.  SPLIT > 1: that many waves share 128 edges and take the
 // centroid tiles in turn: with few edges a wave's chain of tiles is what takes the time (K = 4,096 and 2^11 / 2^16 /
 // 2^17 edges 21 / 34 / 58 us with eight waves against 85 / 89 / 91 us, with 2^18 edges 104 against 107, above it loses).
-template <typename IdxT, int SPLIT>
+template <typename IdxT, int SPLIT, bool LIST>
 __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void kan_assign_kernel(const AssignArgs a) {
+  static_assert(!LIST || SPLIT > 1, "a workgroup's edges are four tiles of the list");
   constexpr int kThreads = SPLIT > 1 ? SPLIT * kWave : kAssignThreads;
   constexpr int kEdges = SPLIT > 1 ? kEdgeTilesPerWave * 32 : kEdgesPerWg;
   // edge-side operands of the workgroup's edges: [edge][32 slots] fp16
   __shared__ __attribute__((aligned(16))) _Float16 sB[kEdges * kSlots];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int first_tile = SPLIT > 1 ? 0 : wave * kEdgeTilesPerWave;        // of the wave's edges
-  const long long e_wg = (long long)blockIdx.x * kEdges;
-  const long long E = a.list ? (long long)*a.n_list : a.E;
-  if (e_wg >= E) return;
-
-  // ---- step 1: bias = mean, gain = norm of the centred grid, n = centred / gain ------------
-  for (int q = tid; q < kEdges; q += kThreads) {
-    const long long at = e_wg + q, e = a.list ? (long long)a.list[min(at, E - 1)] : min(at, E - 1);
-    float c[kG], mean, g;
-    normalise(a.coef + e * kG, c, mean, g);
-    if (at < E) {
-      a.gain[e] = g;
-      a.bias[e] = mean;
-    }
-    _Float16* p = sB + q * kSlots;
-#pragma unroll
-    for (int m = 0; m < kG; ++m) {
-      _Float16 hi, lo;
-      split_h(c[m], hi, lo);
-      p[m] = hi;
-      p[11 + m] = hi;
-      p[21 + m] = lo;
-    }
-    p[10] = (_Float16)1.0f;
-    p[31] = (_Float16)1.0f;
-  }
-  __syncthreads();
-
-  // ---- this wave's edge fragments (MFMA B operand: column = lane & 31, slots (lane/32)*8..+8) --
-  h16x8 fb[kEdgeTilesPerWave][2];
-#pragma unroll
-  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb)
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int q = (first_tile + nb) * 32 + (lane & 31);
-      fb[nb][ks] = *(const h16x8*)(sB + q * kSlots + ks * 16 + (lane >> 5) * 8);
-    }
-
-  float best[kEdgeTilesPerWave];
-  int best_tile[kEdgeTilesPerWave], best_row[kEdgeTilesPerWave];
-#pragma unroll
-  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-    best[nb] = -3.0e38f;
-    best_tile[nb] = 0;
-    best_row[nb] = 0;
-  }
-
-  // ---- step 3: stream the centroid tiles (two tiles in flight) -----------------------------------
-  const uint4* cp = a.cent + lane;
-  auto load_tile = [&](int t, uint4 (&fa)[2]) {
-    const int tc = t < a.n_tiles ? t : a.n_tiles - 1;        // past the end: a harmless re-read
-    fa[0] = cp[(long long)(tc * 2) * 64];
-    fa[1] = cp[(long long)(tc * 2 + 1) * 64];
-  };
-  f32x16 zero;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-  auto score_tile = [&](int t, const uint4 (&fa)[2]) {
-    const h16x8 a0 = __builtin_bit_cast(h16x8, fa[0]), a1 = __builtin_bit_cast(h16x8, fa[1]);
-#pragma unroll
-    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-      f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
-      const float m = max_of(acc);
-      // A new best is rare (the t-th tile improves a lane's running maximum with probability
-      // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
-      // it the lowest register, keeps a tie.
-      if (m > best[nb]) {
-        best[nb] = m;
-        best_tile[nb] = t;
-        best_row[nb] = row_of(acc, m);
-      }
-    }
-  };
-  uint4 fa0[2], fa1[2];
-  const int t0 = SPLIT > 1 ? wave : 0;
-  load_tile(t0, fa0);
-  load_tile(t0 + SPLIT, fa1);
-  for (int t = t0; t < a.n_tiles; t += 2 * SPLIT) {
-    score_tile(t, fa0);
-    load_tile(t + 2 * SPLIT, fa0);
-    if (t + SPLIT < a.n_tiles) score_tile(t + SPLIT, fa1);
-    load_tile(t + 3 * SPLIT, fa1);
-  }
-
   __shared__ float s_best[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
   __shared__ int s_id[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
-  // ---- the two half-waves hold different rows of the same edges: keep the better one ------------
-#pragma unroll
-  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-    const int r = best_row[nb];
-    // D layout of the 32x32 MFMA: register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4
-    int id = best_tile[nb] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    float sc = best[nb];
-    const float sc_o = __shfl_xor(sc, 32, kWave);
-    const int id_o = __shfl_xor(id, 32, kWave);
-    if (sc_o > sc || (sc_o == sc && id_o < id)) {
-      id = id_o;
-      sc = sc_o;
-    }
-    const int q = (first_tile + nb) * 32 + (lane & 31);
-    if constexpr (SPLIT > 1) {
-      if (lane < 32) {
-        s_best[wave][q] = sc;
-        s_id[wave][q] = id;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int first_tile = SPLIT > 1 ? 0 : wave * kEdgeTilesPerWave;        // of the wave's edges
+  const long long E = a.E;
+  auto edge_at = [&](long long at) { return LIST ? (long long)a.list[at] : at; };
+  // One workgroup's share: the edges from e_wg on, LIST: of these the tiles with their byte set in `tiles`.
+  auto serve = [&](long long e_wg, uint32_t tiles) {
+
+    // ---- step 1: bias = mean, gain = norm of the centred grid, n = centred / gain ------------
+    for (int q = tid; q < kEdges; q += kThreads) {
+      const long long at = e_wg + q, e = edge_at(min(at, E - 1));
+      float c[kG], mean, g;
+      normalise(a.coef + e * kG, c, mean, g);
+      if (!LIST && at < E) {
+        a.gain[e] = g;
+        a.bias[e] = mean;
       }
-    } else {
-      const long long at = e_wg + q;
-      if (lane < 32 && at < E) ((IdxT*)a.idx)[a.list ? (long long)a.list[at] : at] = (IdxT)id;
-    }
-  }
-  if constexpr (SPLIT > 1) {
-    __syncthreads();
-    const long long at = e_wg + tid;
-    if (tid < kEdges && at < E) {
-      float sc = s_best[0][tid];
-      int id = s_id[0][tid];
+      _Float16* p = sB + q * kSlots;
 #pragma unroll
-      for (int w = 1; w < SPLIT; ++w) {
-        const float o = s_best[w][tid];
-        const int io = s_id[w][tid];
-        if (o > sc || (o == sc && io < id)) {
-          sc = o;
-          id = io;
+      for (int m = 0; m < kG; ++m) {
+        _Float16 hi, lo;
+        split_h(c[m], hi, lo);
+        p[m] = hi;
+        p[11 + m] = hi;
+        p[21 + m] = lo;
+      }
+      p[10] = (_Float16)1.0f;
+      p[31] = (_Float16)1.0f;
+    }
+    __syncthreads();
+
+    // ---- this wave's edge fragments (MFMA B operand: column = lane & 31, slots (lane/32)*8..+8) --
+    h16x8 fb[kEdgeTilesPerWave][2];
+#pragma unroll
+    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int q = (first_tile + nb) * 32 + (lane & 31);
+        fb[nb][ks] = *(const h16x8*)(sB + q * kSlots + ks * 16 + (lane >> 5) * 8);
+      }
+
+    float best[kEdgeTilesPerWave];
+    int best_tile[kEdgeTilesPerWave], best_row[kEdgeTilesPerWave];
+#pragma unroll
+    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+      best[nb] = -3.0e38f;
+      best_tile[nb] = 0;
+      best_row[nb] = 0;
+    }
+
+    // ---- step 3: stream the centroid tiles (two tiles in flight) -----------------------------------
+    const uint4* cp = a.cent + lane;
+    auto load_tile = [&](int t, uint4 (&fa)[2]) {
+      const int tc = t < a.n_tiles ? t : a.n_tiles - 1;        // past the end: a harmless re-read
+      fa[0] = cp[(long long)(tc * 2) * 64];
+      fa[1] = cp[(long long)(tc * 2 + 1) * 64];
+    };
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+    auto score_tile = [&](int t, const uint4 (&fa)[2]) {
+      const h16x8 a0 = __builtin_bit_cast(h16x8, fa[0]), a1 = __builtin_bit_cast(h16x8, fa[1]);
+#pragma unroll
+      for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+        if (LIST && !((tiles >> (8 * nb)) & 1u)) continue;
+        f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
+        const float m = max_of(acc);
+        // A new best is rare (the t-th tile improves a lane's running maximum with probability
+        // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
+        // it the lowest register, keeps a tie.
+        if (m > best[nb]) {
+          best[nb] = m;
+          best_tile[nb] = t;
+          best_row[nb] = row_of(acc, m);
         }
       }
-      ((IdxT*)a.idx)[a.list ? (long long)a.list[at] : at] = (IdxT)id;
+    };
+    uint4 fa0[2], fa1[2];
+    const int t0 = SPLIT > 1 ? wave : 0;
+    load_tile(t0, fa0);
+    load_tile(t0 + SPLIT, fa1);
+    for (int t = t0; t < a.n_tiles; t += 2 * SPLIT) {
+      score_tile(t, fa0);
+      load_tile(t + 2 * SPLIT, fa0);
+      if (t + SPLIT < a.n_tiles) score_tile(t + SPLIT, fa1);
+      load_tile(t + 3 * SPLIT, fa1);
     }
+
+    // ---- the two half-waves hold different rows of the same edges: keep the better one ------------
+#pragma unroll
+    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+      const int r = best_row[nb];
+      // D layout of the 32x32 MFMA: register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4
+      int id = best_tile[nb] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      float sc = best[nb];
+      const float sc_o = __shfl_xor(sc, 32, kWave);
+      const int id_o = __shfl_xor(id, 32, kWave);
+      if (sc_o > sc || (sc_o == sc && id_o < id)) {
+        id = id_o;
+        sc = sc_o;
+      }
+      const int q = (first_tile + nb) * 32 + (lane & 31);
+      if constexpr (SPLIT > 1) {
+        if (lane < 32) {
+          s_best[wave][q] = sc;
+          s_id[wave][q] = id;
+        }
+      } else {
+        const long long at = e_wg + q;
+        if (lane < 32 && at < E) ((IdxT*)a.idx)[at] = (IdxT)id;
+      }
+    }
+    if constexpr (SPLIT > 1) {
+      __syncthreads();
+      const long long at = e_wg + tid;
+      if (tid < kEdges && at < E && (!LIST || ((tiles >> (8 * (tid >> 5))) & 1u))) {
+        float sc = s_best[0][tid];
+        int id = s_id[0][tid];
+#pragma unroll
+        for (int w = 1; w < SPLIT; ++w) {
+          const float o = s_best[w][tid];
+          const int io = s_id[w][tid];
+          if (o > sc || (o == sc && io < id)) {
+            sc = o;
+            id = io;
+          }
+        }
+        ((IdxT*)a.idx)[edge_at(at)] = (IdxT)id;
+      }
+    }
+  };
+  if constexpr (LIST) {
+    const long long groups = (E + kEdges - 1) / kEdges;
+    for (long long g0 = blockIdx.x; g0 < groups; g0 += (long long)kWave * gridDim.x) {
+      const long long mine = g0 + (long long)lane * gridDim.x;
+      const uint32_t flags = mine < groups ? ((const uint32_t*)a.left)[mine] : 0u;
+      for (unsigned long long m = __ballot(flags != 0); m; m &= m - 1) {
+        const int l = __ffsll(m) - 1;
+        serve((g0 + (long long)l * gridDim.x) * kEdges, (uint32_t)__builtin_amdgcn_readlane((int)flags, l));
+        __syncthreads();
+      }
+    }
+  } else {
+    serve((long long)blockIdx.x * kEdges, 0u);
   }
 }
 
@@ -293,9 +315,14 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 //     (3) where an edge is left with a larger d: what that one still asks for.
 // The scores are those of the whole search, bit for bit, no tile that can hold the best one is left out and equal
 // scores go to the lowest id: the result is the whole search's, whichever edges share a wave (the sort places them in
-// no particular order) and whichever of them are handed over.  A wave that would visit more than kRestShare of the tiles
-// hands its edges to the whole search, which shares a tile's operands among four times as many: codebooks or grids
-// that the cells do not separate cost what they did without them.
+// no particular order) and whichever of them are handed over: a wave that would visit more than kRestShare of the tiles
+// in (2) or in (3) leaves its edges to the whole search.  A visit costs about what a tile costs there, so that is worth
+// it only for edges that ask for nearly everything (vectors that the bounds do not hold for, codebooks of one shape):
+// grids that fit their codebook poorly ask for less, and stay.  With 25 % noise or unrelated grids, 2^20 edges: 234 of
+// 330 tiles for K = 8,192, 356 of 630 for 16,384, 636 of 2,500 for 65,536.  With 0.7 of the tiles for both steps
+// together and the left edges compacted by one counter, unrelated grids took 1003 us for K = 8,192 against 528 of the
+// whole search alone and 471 against 292 for K = 16,384, 2^18 edges (a few waves left behind there were one chain
+// through all tiles, 340 us); now 553 and 252.
 //
 // What bounds it: instructions issued.  A wave of the search makes (tiles / 32) bound tests and visits about 250 of
 // 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each one matrix and about ten vector instructions; the
@@ -307,8 +334,9 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 
 constexpr int kCellShapes = 64;                   // shapes per cell on average
 constexpr int kCellMaxTiles = 16384;              // (a wave marks the tiles it has visited in LDS)
-constexpr float kRestShare = 0.7f, kMeanFactor = 1.0f;
+constexpr float kRestShare = 0.9f, kMeanFactor = 1.0f;          // (0.6 / 0.7: K = 8,192, unrelated grids 1153 / 873 us)
 constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
+constexpr int kRestWorkgroups = 1024;             // of the whole search behind it: as many as are resident
 constexpr int kAhead = 2;                         // tiles in flight per wave
 constexpr int kSortThreads = 1024, kSortGroups = 64;
 constexpr int kBuildChunk = 1024;                 // members of a cell that are sorted together
@@ -319,7 +347,7 @@ struct CellLayout {
   int tiles_max;
   int groups[2];           // workgroups of the sort: over the shapes, over the edges
   long long chunk[2];      // items per workgroup
-  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, rest, n_rest, whole, bytes;
+  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, left, any, whole, bytes;
 };
 
 size_t centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(uint4); }
@@ -353,8 +381,8 @@ CellLayout cell_layout(long long E, int K) {
   g.first_tile = take((size_t)(g.M + 1) * 4);
   g.wg_least = take((size_t)((K + kEdgesPerWg - 1) / kEdgesPerWg) * 8);
   g.least = take(4);
-  g.rest = take((size_t)E * 4);
-  g.n_rest = take(4);
+  g.left = take((size_t)((E + 127) / 128) * 4);
+  g.any = take(4);
   g.whole = take(centroid_bytes(K));
   g.bytes = at;
   return g;
@@ -377,7 +405,8 @@ struct CellArgs {
   uint32_t *hist[2], *total[2], *first[2];
   uint32_t* first_tile;          // [M + 1]
   unsigned long long* wg_least;
-  uint32_t *rest, *n_rest;       // edges left to the whole search
+  uint8_t* left;                 // [4 * ceil(E / 128)] waves whose edges are left to the whole search
+  uint32_t* any;                 // some are
   uint32_t* least;               // shape of the smallest norm: the nearest to an edge of gain 0
   void* idx;
   float *gain, *bias;
@@ -593,7 +622,7 @@ __global__ __launch_bounds__(kSortThreads) void kan_cell_scan_kernel(const CellA
   }
   if (tid == 0) {
     *a.least = (uint32_t)least;
-    *a.n_rest = 0;
+    *a.any = 0;
   }
 }
 
@@ -658,10 +687,10 @@ __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
       }
     // Within a tile by id: of equal scores a lane keeps the first row, which is then the lowest id, as in the whole search.
     for (int i = tid; i < nc; i += 256) {
-      const int t0 = i & ~31, t1 = min(nc, t0 + 32);
       const uint32_t id = (uint32_t)sorted[i];
-      int at = t0;
-      for (int o = t0; o < t1; ++o) at += (uint32_t)sorted[o] < id;
+      int at = i & ~31;
+#pragma unroll
+      for (int o = 0; o < 32; ++o) at += (uint32_t)sorted[(i & ~31) + o] < id;      // (past the last one: the largest id)
       row_id[at] = id;
     }
     __syncthreads();
@@ -718,7 +747,10 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   const unsigned W = gridDim.x, xcd = blockIdx.x & 7u, q8 = W >> 3, r8 = W & 7u;
   const long long wg = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
   const long long pos = (wg * 4 + wave) * 32 + (lane & 31);
-  if ((wg * 4 + wave) * 32 >= a.E) return;                 // (no barrier in this kernel)
+  if ((wg * 4 + wave) * 32 >= a.E) {                       // (no barrier in this kernel)
+    if (lane == 0) a.left[wg * 4 + wave] = 0;
+    return;
+  }
   volatile uint32_t* seen = s_seen[wave];
   volatile uint16_t* list = s_list[wave];
   const int T = (int)a.first_tile[a.M], words = (T + 31) / 32, most = (int)(kRestShare * T);
@@ -726,15 +758,14 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
 
   const uint32_t e = a.sorted[1][min(pos, a.E - 1)];
   const int key = a.key[1][e];
-  const bool live = pos < a.E && key < a.M;
+  const bool there = pos < a.E, live = there && key < a.M;
 
   // edge operands of the search (see the head of the file) and of the bound
   h16x8 fb[2], fe;
-  bool number, unit;
+  bool unit;
   {
     float n[kG], mean, gain;
     normalise(a.coef + (long long)e * kG, n, mean, gain);
-    number = gain == gain;
     float nn = 0.f;
 #pragma unroll
     for (int m = 0; m < kG; ++m) nn = fmaf(n[m], n[m], nn);
@@ -766,15 +797,11 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     best = fmaxf(best, sc);
     near = best - slack;
   };
-  // (an edge without direction; one that is no number has no scores and keeps row 0)
-  auto undirected = [&] { return number ? *a.least : 0u; };
   auto leave = [&] {                             // to the whole search
-    uint32_t to = 0;
-    const unsigned long long w = __ballot(live && half == 0);
-    if (lane == 0) to = atomicAdd(a.n_rest, (uint32_t)__popcll(w));
-    to = (uint32_t)__builtin_amdgcn_readfirstlane((int)to);
-    if (live && half == 0) a.rest[to + __popcll(w & ((1ull << lane) - 1))] = e;
-    if (pos < a.E && half == 0 && !live) ((IdxT*)a.idx)[e] = (IdxT)undirected();
+    if (lane == 0) {
+      a.left[wg * 4 + wave] = 1;
+      *a.any = 1;
+    }
   };
 
   // (1) own cells, both instructions of every tile
@@ -826,6 +853,7 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   // (An instruction of any kind takes its wave's SIMD an issue slot: tiles are listed first, so that a visit is a
   // lane read, a load, a matrix instruction and the maxima of a pair of tiles.)
   auto search = [&](bool who, float d) -> bool {
+    int asked = 0;
     const bool far = d > kFar;                   // (no shape known yet, or beyond fp16: every tile)
     const float thr = who ? (far ? -6e4f : 0.5f * (1.0f - d * d) - 1e-5f) : 6e4f;
     const float thr_hi = fp16_of(thr);
@@ -866,8 +894,8 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
         upto += lane >= o ? v : 0;
       }
       const int count = __builtin_amdgcn_readlane(upto, 63);
-      visits += count;
-      if (visits > most) return false;
+      asked += count;
+      if (asked > most) return false;
       if (count == 0) continue;
       int last = 0;
       for (int at = upto - own; mine; ++at) {
@@ -930,7 +958,12 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     return;
   }
   (void)distance();
-  if (lane < 32 && pos < a.E) ((IdxT*)a.idx)[e] = (IdxT)(live ? best_id : undirected());
+  if (lane == 0) a.left[wg * 4 + wave] = 0;
+  // (an edge without direction: the shape of the smallest norm; one that is no number has no scores and keeps row 0)
+  if (lane < 32 && there) {
+    if (!live) best_id = a.gain[e] == a.gain[e] ? *a.least : 0u;
+    ((IdxT*)a.idx)[e] = (IdxT)best_id;
+  }
 }
 
 // ---- reconstruction quality ---------------------------------------------------------------------
@@ -993,39 +1026,35 @@ int recon_blocks(long long E) {
 }
 
 namespace {
-// Every edge, or the *n_list listed ones, against every shape.
-void launch_whole(const float* coef, long long E, const uint32_t* list, const uint32_t* n_list, const float* cb, int K,
-                  int idx_u32, void* idx, float* gain, float* bias, void* centroids, hipStream_t s) {
-  const int n_tiles = (K + 31) / 32;
-  const long long recs = (long long)n_tiles * 2 * 64;
-  hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, n_tiles,
-                     n_list, (uint4*)centroids);
+AssignArgs whole_args(const float* coef, long long E, const float* cb, int K, void* idx, float* gain, float* bias,
+                      void* centroids, const uint32_t* any, hipStream_t s) {
   AssignArgs a;
   a.coef = coef;
   a.cent = (const uint4*)centroids;
   a.E = E;
-  a.list = list;
-  a.n_list = n_list;
-  a.n_tiles = n_tiles;
+  a.list = nullptr;
+  a.left = nullptr;
+  a.n_tiles = (K + 31) / 32;
   a.idx = idx;
   a.gain = gain;
   a.bias = bias;
-  if (!list && E <= kSplitMaxEdges) {
-    const dim3 grid((unsigned)((E + kEdgeTilesPerWave * 32 - 1) / (kEdgeTilesPerWave * 32))), wg(8 * kWave);
-    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8>), grid, wg, 0, s, a);
-    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8>), grid, wg, 0, s, a);
-    return;
-  }
-  const dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg)), wg(kAssignThreads);
-  if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 1>), grid, wg, 0, s, a);
-  else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 1>), grid, wg, 0, s, a);
+  const long long recs = (long long)a.n_tiles * 2 * 64;
+  hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, a.n_tiles, any,
+                     (uint4*)centroids);
+  return a;
 }
+dim3 split_grid(long long E) { return dim3((unsigned)((E + kEdgeTilesPerWave * 32 - 1) / (kEdgeTilesPerWave * 32))); }
 }  // namespace
 
-// The bounded search pays where its cells, launches and bound tests are small next to the scores they save.  Bounded
-// against whole search (5 % noise per coefficient): K = 65,536 and 2^20 / 2^18 / 2^16 edges 772 / 295 / 169 against
-// 3803 / 1174 / 370 us, K = 16,384 439 / 176 / 110 against 1110 / 337 / 90, K = 8,192 363 / 249 / 115 against
-// 625 / 195 / 55, K = 262,144 and 2^20 edges 1.9 against 14.9 ms.
+// The bounded search pays where its cells, launches and bound tests are small next to the scores they save, for grids
+// that fit their codebook and at little loss for those that do not.  Bounded search with 2 % / 5 % / 15 % noise per
+// coefficient / unrelated grids against the whole search (which does not care), us:
+//     K = 65,536   2^20 edges  545 / 779 / 1290 / 1332  against 3820      2^16 edges  128 / 167 / 224 / 226  against 312
+//     K = 32,768   2^17 edges  110 / 148 / 203 / 212  against 313
+//     K = 16,384   2^20 edges  300 / 420 / 688 / 732  against 1024        2^18 edges  132 / 167 / 238 / 252  against 296
+//                  2^17 edges  98 / 126 / 160 / 165  against 173          98,304 edges  94 / 112 / 141 / 146  against 132
+//     K = 8,192    2^20 edges  252 / 335 / 522 / 553  against 547
+// (K = 8,192 and 2^18 edges with 5 % noise 249 against 195; K = 262,144 and 2^20 edges 1.9 against 14.9 ms).
 bool assign_bounded_ok(long long E, int K) {
   const long long work = E * K;
   return (work >= (3ll << 29) && K >= 16384 || work >= (1ll << 33) && K >= 8192) && cell_layout(1, K).tiles_max <= kCellMaxTiles;
@@ -1059,8 +1088,8 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   }
   a.first_tile = (uint32_t*)(w + g.first_tile);
   a.wg_least = (unsigned long long*)(w + g.wg_least);
-  a.rest = (uint32_t*)(w + g.rest);
-  a.n_rest = (uint32_t*)(w + g.n_rest);
+  a.left = (uint8_t*)(w + g.left);
+  a.any = (uint32_t*)(w + g.any);
   a.least = (uint32_t*)(w + g.least);
   a.idx = idx;
   a.gain = gain;
@@ -1078,13 +1107,26 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   const dim3 grid((unsigned)((E + 127) / 128));
   if (idx_u32) hipLaunchKernelGGL(kan_assign_bounded_kernel<uint32_t>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(kan_assign_bounded_kernel<uint16_t>, grid, dim3(256), 0, s, a);
-  launch_whole(coef, E, a.rest, a.n_rest, cb, K, idx_u32, idx, gain, bias, w + g.whole, s);
+  AssignArgs rest = whole_args(coef, E, cb, K, idx, gain, bias, w + g.whole, a.any, s);
+  rest.list = a.sorted[1];
+  rest.left = a.left;
+  const dim3 rest_grid((unsigned)std::min<long long>((E + 127) / 128, kRestWorkgroups));
+  if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
+  else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
   return hipGetLastError();
 }
 
 hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx, float* gain,
                          float* bias, void* ws, hipStream_t s) {
-  launch_whole(coef, E, nullptr, nullptr, cb, K, idx_u32, idx, gain, bias, ws, s);
+  const AssignArgs a = whole_args(coef, E, cb, K, idx, gain, bias, ws, nullptr, s);
+  const dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg));
+  if (E <= kSplitMaxEdges) {
+    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, false>), split_grid(E), dim3(8 * kWave), 0, s, a);
+    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8, false>), split_grid(E), dim3(8 * kWave), 0, s, a);
+  } else {
+    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 1, false>), grid, dim3(kAssignThreads), 0, s, a);
+    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 1, false>), grid, dim3(kAssignThreads), 0, s, a);
+  }
   return hipGetLastError();
 }
 
