@@ -131,6 +131,8 @@ def _grids(kind, K, E, seed):
         cb *= torch.rand((K, 1), generator=g, device="cuda") * 3
     if kind == "one row":
         cb[:] = cb[:1].clone()
+    if kind == "unused":           # rows that no edge was ever assigned to
+        cb[torch.rand(K, generator=g, device="cuda") < 0.4] = 0.0
     if kind == "near ties":        # pairs of rows 1e-5 apart: scores that differ by less than a millionth
         cb *= 0.97 + torch.rand((K, 1), generator=g, device="cuda") * 0.06
         cb[K // 2:] = cb[:K - K // 2] + 3e-6 * torch.randn((K - K // 2, 10), generator=g, device="cuda")
@@ -148,7 +150,7 @@ def _grids(kind, K, E, seed):
 @pytest.mark.parametrize("kind,K,E", [("trained", 16384, 98304), ("trained", 16421, 98101), ("trained", 50001, 33333),
                                       ("trained", 70000, 24001), ("far", 16384, 98337), ("duplicates", 16384, 98304),
                                       ("norms", 16384, 98304), ("flat", 16384, 98304), ("one cell", 16384, 98304),
-                                      ("one row", 16384, 98304)])
+                                      ("one row", 16384, 98304), ("unused", 20000, 98304)])
 def test_bounded_search_finds_the_nearest_row(kb, kind, K, E):
     """Every chosen row is as near as the nearest one (fp64, on the device), and the same as the whole
     search's wherever no other row is that near."""
@@ -204,7 +206,8 @@ def test_bounded_search_scores_as_well_as_the_whole_search(kb, K, E):
 
 @pytest.mark.parametrize("kind,K,E", [("trained", 16421, 98101), ("trained", 70000, 24001), ("far", 16384, 98337),
                                       ("duplicates", 16384, 98304), ("norms", 16384, 98304), ("near ties", 16384, 98304),
-                                      ("flat", 16384, 98304), ("one cell", 16384, 98304), ("one row", 16384, 98304)])
+                                      ("flat", 16384, 98304), ("one cell", 16384, 98304), ("one row", 16384, 98304),
+                                      ("unused", 16384, 98304), ("unused", 70001, 30001)])
 def test_bounded_search_gives_the_ids_of_the_whole_search(kb, kind, K, E):
     """Not one id differs, whichever edges share a wave and are handed over: equal scores go to the lowest id in both,
     edges of gain 0 to the same shape, and grids that are no numbers or overflow to what the whole search gives."""
