@@ -506,8 +506,9 @@ size_t partial_bytes(const LayerPlan& p, int n_out, int64_t B, int heads_in_grou
 // sized for the largest layer and for one group of heads).
 struct WsLayout {
   size_t hidden = 0;    // one of two ping-pong hidden-activation buffers, [n_heads][B][out]
-  size_t partial = 0;   // i-chunk partial sums
-  size_t partial2 = 0;  // second buffer of per-bucket sums when consecutive bucket layers are chained
+  size_t partial = 0;   // partial sums: of layers 1, 3, .. where a layer hands its sums on (the next one's go to the
+  size_t partial2 = 0;  //   other buffer), else of all / of layers 2, 4, .. where a layer hands its sums on, else empty
+  std::vector<char> handed;   // layer l leaves its partial sums to layer l + 1
   size_t cf = 0;        // matrix-core path: fp16 coefficient fragments, a region per layer (layers after the
   size_t bp = 0;        //   first are prepared beside the first one's work) / partial bias sums, likewise
   std::vector<size_t> cf_off, bp_off;   // start of each layer's region within cf / bp
@@ -799,7 +800,7 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
 kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                          int min_rows, std::vector<LayerPlan>* plans, WsLayout* ws) {
+                          int min_rows, bool hand_on, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -831,7 +832,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
     LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? plans->back().n_chunks : 1, min_rows);
     plans->push_back(p);
     auto grow = [](size_t& dst, size_t v) { if (v > dst) dst = v; };
-    grow(ws->partial, partial_bytes(p, R.out, B, group));
+    grow(l & 1 ? ws->partial2 : ws->partial, partial_bytes(p, R.out, B, group));
     ws->cf_off.push_back(ws->cf);
     ws->bp_off.push_back(ws->bp);
     if (p.mfma) {
@@ -842,24 +843,30 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       grow(ws->u, round_up((size_t)(p.products == 3 ? 2 : 1) * (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16 * 16) * (size_t)B * sizeof(uint2), 256));
     if (l + 1 < n_layers) grow(ws->hidden, round_up((size_t)n_heads * (size_t)B * R.out * sizeof(float), 256));
   }
-  // chained layers hand their partial sums straight on: two buffers, used in turn
-  for (int l = 0; l + 1 < n_layers; ++l)
-    if (chained(*plans, l, n_heads, layers, B)) ws->partial2 = ws->partial;
+  for (int l = 0; l < n_layers; ++l) ws->handed.push_back(hand_on && chained(*plans, l, n_heads, layers, B));
+  if (std::find(ws->handed.begin(), ws->handed.end(), 1) == ws->handed.end()) {      // one buffer does for all
+    ws->partial = std::max(ws->partial, ws->partial2);
+    ws->partial2 = 0;
+  }
   return KAN_OK;
 }
 
-// Finer chunks write more partial sums: a call that fits the library's static scratch only without them is planned
-// without them.
+// Finer chunks write more partial sums, and a layer that hands its sums on keeps a second buffer of them: a call that
+// fits the library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
-  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, plans, ws);
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, plans, ws);
   if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
-  std::vector<LayerPlan> compact;
-  WsLayout compact_ws;
-  st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRowsCompact, &compact, &compact_ws);
-  if (st == KAN_OK && compact_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
-    plans->swap(compact);
-    *ws = compact_ws;
+  const struct { int min_rows; bool hand_on; } smaller[] = {{kMfmaMinRowsCompact, true}, {kMfmaMinRows, false}, {kMfmaMinRowsCompact, false}};
+  for (const auto& o : smaller) {
+    std::vector<LayerPlan> other;
+    WsLayout other_ws;
+    st = plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, &other, &other_ws);
+    if (st == KAN_OK && other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
+      plans->swap(other);
+      *ws = other_ws;
+      break;
+    }
   }
   return st;
 }
@@ -1053,8 +1060,8 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     Chain chain;
     chain.partial = (l & 1) ? w.partial2 : w.partial;
     if (!wl.partial2) chain.partial = w.partial;
-    chain.out = chained(plans, l, n_heads, layers, B);
-    if (chained(plans, l - 1, n_heads, layers, B)) {
+    chain.out = wl.handed[l];
+    if (l > 0 && wl.handed[l - 1]) {
       src = ((l - 1) & 1) ? w.partial2 : w.partial;
       chain.in_parts = plans[l - 1].n_chunks;
       chain.in_part_stride = (long long)B * R.in;

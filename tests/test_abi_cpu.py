@@ -208,6 +208,33 @@ def test_precise_path_switches_and_workspace_sizes():
     assert dense >= 2 * (records + words) and dense < three
 
 
+def _head_ws(L, widths, heads, B, path, **kw):
+    arr = (kb.kan_vq_layer * (heads * (len(widths) - 1)))()
+    for h in range(heads):
+        for l in range(len(widths) - 1):
+            arr[h * (len(widths) - 1) + l] = _desc(n_in=widths[l], n_out=widths[l + 1], K=65536, **kw)
+    return L.kan_vq_workspace_bytes(arr, len(widths) - 1, heads, B, path)
+
+
+@pytest.mark.parametrize("widths,heads,B", [((836, 2396, 17, 914), 25, 31), ((268, 1736, 43), 32, 32), ((1356, 884, 16), 51, 31),
+                                            ((16, 216, 1116, 48), 63, 23), ((1116, 1804, 80), 39, 26),
+                                            ((1536, 332, 548, 144, 1224), 61, 32)])
+def test_calls_whose_sums_fit_the_static_scratch_once_are_planned_to_fit(widths, heads, B):
+    """Precise path, many heads: with the partial sums handed on these need two buffers of up to 27 MiB, more than the
+    32 MiB of the static entry point; one of them and the hidden activations fit."""
+    L = kb.lib()
+    for gb, cb in ((kb.KAN_F16, kb.KAN_I8), (kb.KAN_F32, kb.KAN_I8), (kb.KAN_F32, kb.KAN_F32)):
+        need = _head_ws(L, widths, heads, B, kb.KAN_PATH_GATHER, gb_dtype=gb, cb_dtype=cb)
+        assert 0 < need <= kb.KAN_STATIC_SCRATCH_BYTES, (gb, cb, need)
+
+
+def test_partial_sums_that_are_handed_on_take_the_room_of_their_layer():
+    """Two buffers, each as large as the layers that use it: configuration 3's head at batch 16 writes 32 slices of its
+    first layer and 32 of the second, beside two buffers of hidden activations."""
+    need = _head_ws(kb.lib(), (2048, 1024, 256), 1, 16, kb.KAN_PATH_GATHER, gb_dtype=kb.KAN_F16, cb_dtype=kb.KAN_I8)
+    assert need == 4 * 16 * (32 * 1024 + 32 * 256 + 2 * 1024)
+
+
 def test_assign_argument_errors():
     L = kb.lib()
     F = FAKE

@@ -47,3 +47,18 @@ def test_slices_into_the_next_layer(kb, dims, B):
     y = kb.kan_vq_head_forward([[kb.VQLayer(p) for p in Ps]], to_dev(x), path=kb.KAN_PATH_GATHER)[0].cpu().numpy()
     rep = ko.error_report(y, ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
     assert rep["headline"] <= TOL_FP32, rep
+
+
+def test_call_that_fits_the_static_scratch_only_without_the_hand_over(kb):
+    """63 heads whose partial sums fit the library's 32 MiB once: a reduction between the layers, right results."""
+    B, dims = 23, (16, 216, 1116, 48)
+    Ps = [synth.make_layer(9300 + l, dims[l], dims[l + 1], 4099, cb_dtype="i8", gb_dtype="f16") for l in range(3)]
+    head = [kb.VQLayer(p) for p in Ps]
+    x = synth.make_x(9301, B, dims[0])
+    y = kb.kan_vq_head_forward_static([head] * 63, to_dev(x), path=kb.KAN_PATH_GATHER)
+    kb.kan_prof_begin(16)
+    kb.kan_vq_head_forward_static([head] * 63, to_dev(x), path=kb.KAN_PATH_GATHER)
+    assert "kan_reduce@L2" in kb.kan_prof_end()
+    assert torch.equal(y, y[:1].expand_as(y))
+    rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
+    assert rep["headline"] <= TOL_FP32, rep
