@@ -765,8 +765,9 @@ kan_status check_path(int32_t path) {
 // Layer l leaves its partial sums to layer l+1 (one group of heads only: the buffers are
 // sized for one group).  Consumers: the bucket kernel (after a bucket layer), the basis
 // preparation of the matrix-core path (after any layer that splits its inputs), the fused
-// kernel on tiles of 32 samples (after any such layer: see fused_takes_slices) and the
-// vector-ALU kernel at batch 1.
+// kernel on tiles of 32 samples (after any such layer: see fused_takes_slices; on the precise
+// path fifty heads of 256-1280-128 at batch 4 / 16 take 136.7 / 139.8 us so, 138.8 / 145.0 with a
+// reduction launch), the wave-by-wave kernel and the vector-ALU kernel at batch 1.
 bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, int64_t B);
 
 bool chained(const std::vector<LayerPlan>& plans, int l, int n_heads, const kan_vq_layer* layers, int64_t B) {
@@ -776,8 +777,7 @@ bool chained(const std::vector<LayerPlan>& plans, int l, int n_heads, const kan_
     return plans[l].n_chunks <= kFusedChainMaxParts && layers[l + 1].in % 4 == 0 && plans[l + 1].n_jt <= 16 &&
            B * plans[l + 1].rows_per_chunk <= kFusedWaveChainFloats &&
            (long long)plans[l].n_chunks * B * (plans[l + 1].rows_per_chunk / 4) <= 32 * 256;
-  if (plans[l + 1].kind == kPlanFused32) return false;
-  if (plans[l + 1].kind == kPlanFused16)
+  if (plans[l + 1].kind == kPlanFused16 || plans[l + 1].kind == kPlanFused32)
     return fused_takes_slices(plans[l], plans[l + 1], layers[l + 1].in, B);
   // the vector-ALU kernel at batch 1: the threads that share a row of the basis table split the
   // slices; few output tiles (each adds the slices again)

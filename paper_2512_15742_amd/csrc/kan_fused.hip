@@ -69,7 +69,7 @@ constexpr int LDF = 84;                // fp32 tile: row stride in floats (336 B
 template <typename IdxT, typename GbT, typename CbT, bool F32, int MBLK, bool STAGE, bool T16 = false, bool CH = false>
 __global__ __launch_bounds__(kThreads, 2) void kan_fused_kernel(const FusedArgs a) {
   static_assert(!T16 || (F32 && MBLK == 1), "16-sample tiles: fp32 operands only");
-  static_assert(!CH || (MBLK == 1 && !F32), "chained input: 32-sample tiles of fp16 operands only");
+  static_assert(!CH || MBLK == 1, "chained input: 32-sample tiles only");
   constexpr int BM = 32 * MBLK;
   constexpr int NPAIR = MBLK;          // (sample, input) pairs per thread and step
   // The precise path comes in two forms: fp32 operands for 32-sample tiles (one row block: the 40 fp32
@@ -839,9 +839,16 @@ hipError_t launch_variant(const FusedArgs& a, bool f32, int mblk, bool stage_ok,
   if (mblk != 1) return hipErrorInvalidValue;
   const bool stage = stage_ok && sizeof(GbT) <= 2;
   const unsigned lds = 32u * (unsigned)a.rows_per_chunk * 4u;       // the chunk's inputs of the tile's 32 sample rows
-  if (f32) return hipErrorInvalidValue;      // (fp32 operands on slices: kan_fused_wave.hip)
-  if (stage) hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, false, 1, true, false, true>), grid, dim3(kThreads), lds, s, a);
-  else hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, false, 1, false, false, true>), grid, dim3(kThreads), lds, s, a);
+  if (f32 && a.B <= 16) {                    // 16-sample tiles
+    if (stage) hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, true, 1, true, true, true>), grid, dim3(kThreads), lds, s, a);
+    else hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, true, 1, false, true, true>), grid, dim3(kThreads), lds, s, a);
+  } else if (f32) {
+    if (stage) hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, true, 1, true, false, true>), grid, dim3(kThreads), lds, s, a);
+    else hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, true, 1, false, false, true>), grid, dim3(kThreads), lds, s, a);
+  } else {
+    if (stage) hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, false, 1, true, false, true>), grid, dim3(kThreads), lds, s, a);
+    else hipLaunchKernelGGL((kan_fused_kernel<IdxT, GbT, CbT, false, 1, false, false, true>), grid, dim3(kThreads), lds, s, a);
+  }
   return hipGetLastError();
 }
 #else

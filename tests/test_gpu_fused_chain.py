@@ -215,3 +215,19 @@ def test_random_heads(kb, dims, cb, gb, idx, K, B, seed):
         y_chain, _ = check_head_layer_by_layer(kb, Ls, Ps, x, path, tol)
         assert np.abs(y - y_chain).max() <= 2 * tol * max(np.abs(y_chain).max(), 1e-30)
         assert np.array_equal(y, kb.kan_vq_head_forward([Ls], xd, path=path)[0].cpu().numpy())
+
+
+@pytest.mark.parametrize("B", [3, 16, 20])
+@pytest.mark.parametrize("cb,gb,out", [("i8", "f16", 128), ("f16", "f16", 123), ("f32", "f32", 128)])
+def test_large_precise_launches(kb, B, cb, gb, out):
+    """Launches of more than 6 * 2^20 edges take tiles of 128 outputs, on 16 samples and on 32: the second layer of
+    fifty heads adds the slices of the first itself.  (The heads share one set of parameters: equal outputs.)"""
+    Ps = _head(8600, (256, 1280, out), 3001, cb=cb, gb=gb)
+    heads = [gpu_layers(Ps)] * 50
+    x = synth.make_x(8601 + B, B, 256)
+    rec = _launches(kb, heads, to_dev(x), kb.KAN_PATH_GATHER)
+    assert "kan_reduce@L1" not in rec and "kan_fused_f32@L2" in rec, rec
+    y = kb.kan_vq_head_forward(heads, to_dev(x), path=kb.KAN_PATH_GATHER)
+    assert torch.equal(y, y[:1].expand_as(y))
+    rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
+    assert rep["headline"] <= TOL_FP32, rep
