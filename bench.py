@@ -305,7 +305,7 @@ def roofline_of(kt, lps, layer_edges, layer_meta, B, facts, workload, extra_para
     traffic, tsrc = traffic_of(facts, workload, B, dom)
     if B > 64:
         flops = edges * (B * FLOP_PER_EDGE_EVAL + FLOP_PER_EDGE_RECON)
-        peak = PEAK_F16_MFMA_TFLOPS if (is_mfma and family != "kan_fused_f32") else PEAK_FP32_VECTOR_TFLOPS
+        peak = PEAK_F16_MFMA_TFLOPS if (is_mfma and family not in ("kan_fused_f32", "kan_fused_wave")) else PEAK_FP32_VECTOR_TFLOPS
         roof = {"bound": "mfma" if is_mfma else "alu", "achieved": flops / avg_s / 1e12, "peak": peak, "unit": "TFLOP/s"}
     else:
         nbytes = per_launch(layer_meta, dom, lps[dom])

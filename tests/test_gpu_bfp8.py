@@ -57,7 +57,7 @@ def test_bfp8_every_kernel_family(kb, gb, n_in, n_out, B):
         y = kb.kan_vq_layer_forward(L, to_dev(x), path=path).cpu().numpy()
         rep = ko.error_report(y, y_ref, A)
         assert rep["headline"] <= tol and rep["strict"] <= tol, (path, kb.kan_vq_planned_kernel(L, B, 1, path), rep)
-    expect = {1: "kan_gather_bt1", 5: "kan_fused_f32", 33: "kan_fused_f32", 64: "kan_fused_f32", 300: "kan_mfma_split"}[B]
+    expect = {1: "kan_gather_bt1", 5: "kan_fused_wave", 33: "kan_fused_f32", 64: "kan_fused_f32", 300: "kan_mfma_split"}[B]
     assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_GATHER) == expect
 
 

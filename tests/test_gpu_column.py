@@ -80,7 +80,7 @@ def test_column_limits_fall_back_to_bucket(kb):
         L = kb.VQLayer(P).prepare()
         assert [kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_GATHER) for B in (1, 2, 3, 4)] == expect, (n_in, n_out)
     L = kb.VQLayer(synth.make_layer(5, 64, 64, 1000, cb_dtype="i8", gb_dtype="f16")).prepare()
-    assert kb.kan_vq_planned_kernel(L, 5, 1, kb.KAN_PATH_GATHER) == "kan_fused_f32"
+    assert kb.kan_vq_planned_kernel(L, 5, 1, kb.KAN_PATH_GATHER) == "kan_fused_wave"
 
 
 @pytest.mark.parametrize("dist", ["zipf", "zipf-sorted"])
