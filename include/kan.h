@@ -156,7 +156,7 @@ kan_status kan_pli_basis(const float* x, int64_t n, uint8_t* index, float* w, vo
  * form it for either rule (sections 4.1 / 4.3 and App. A.1): start[n] = first entry (cubic rule:
  * the interval index 0..6; two-tap rule: min(k, 6), the taps 1 - u, u sitting at offset k - start,
  * the other two weights 0) and w[n][0..3].  variant 0: the routine of the vector-ALU and bucket
- * kernels (what kan_bspline_basis / kan_pli_basis run); variant 1: the routine of the fused kernel
+ * kernels and of the dense baseline up to 16 samples (what kan_bspline_basis / kan_pli_basis run); variant 1: the routine of the fused kernel
  * and of the basis preparation (index by one fp64 fma and truncation, which is exact, weights in
  * fp32).  Both must give the same start for every fp32 x; parity/debug entry point.
  * x, start, w: device; w 16-byte aligned.                                                        */
@@ -165,7 +165,13 @@ kan_status kan_basis_window(const float* x, int64_t n, int32_t rule, int32_t var
 
 /* Bytes of workspace kan_vq_layer_forward / kan_vq_head_forward need for these
  * descriptors (host array [n_heads][n_layers]), batch B and path.  Returns 0
- * when none is needed and (size_t)-1 when the arguments are invalid.            */
+ * when none is needed and (size_t)-1 when the arguments are invalid.  The figure
+ * belongs to this build of the library (ask for it, do not store it): a large part
+ * of it are the partial sums of layers that are cut into chunks of inputs, up to 32
+ * of them where a layer alone would leave the GPU idle (at batch 1024 20 MiB for a
+ * 73 -> 2072 layer on the fp16 path).  A call whose figure would pass
+ * KAN_STATIC_SCRATCH_BYTES is planned with fewer chunks, or with a reduction between
+ * its layers, where that makes it fit.                                              */
 size_t kan_vq_workspace_bytes(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads,
                               int64_t B, int32_t path);
 
@@ -178,8 +184,8 @@ kan_status kan_vq_layer_forward(const kan_vq_layer* L, const float* x, int64_t B
  * section 4.2): y[b][j] = sum_i sum_m B_m(x_bi) * coef[i][j][m].  G must be 10.
  * coef, x, y and ws are device pointers (ws 256-byte aligned, at least
  * kan_dense_workspace_bytes(in, out, B) bytes, (size_t)-1 for invalid sizes; contents need
- * not survive between calls).  Result within 1e-5 relative at every batch size: up to batch 16 an
- * fp32 FMA kernel, from 17 on the matrix cores on coefficients and basis weights split
+ * not survive between calls).  Result within 1e-5 relative at every batch size: up to batch 16 the
+ * fp32 matrix instruction, from 17 on the fp16 one on coefficients and basis weights split
  * into high and low fp16 parts (hi*hi + hi*lo + lo*hi), as the precise VQ path does.  */
 size_t kan_dense_workspace_bytes(int32_t in, int32_t out, int64_t B);
 kan_status kan_dense_layer_forward(const float* coef, int32_t in, int32_t out, int32_t G,
@@ -273,12 +279,13 @@ kan_status kan_vq_coef_range(const kan_vq_layer* L, float* range, void* stream);
  *   idx[e]  = index of the codebook row nearest (squared Euclidean distance) to the normalised
  *             grid; for an all-constant grid (gain 0) the row of smallest norm.
  * The distance contraction runs on the matrix cores with split fp16 operands (fp32-grade
- * scores, ~1e-6 relative): rows that near to a tie may resolve to either index.
+ * scores, ~1e-6 relative): rows that near to a tie may resolve to either index, equal scores
+ * to the lower one, the same from call to call.
  * codebook: fp32 [K][10]; idx: KAN_U16 (K <= 65536) or KAN_U32 array [in][out]; gain, bias:
  * fp32 [in][out].  ws: kan_vq_assign_workspace_bytes(K) bytes, 256-byte aligned.  All device.
  * With kan_vq_assign_fast_workspace_bytes(in, out, K) bytes (never fewer), large codebooks are searched
- * through cells that bound the distance of their shapes, which leaves most of them out and finds the
- * same rows. */
+ * through cells that bound the distance of their shapes, which leaves most of them out and returns the
+ * same indices. */
 size_t kan_vq_assign_workspace_bytes(int32_t K);
 size_t kan_vq_assign_fast_workspace_bytes(int32_t in, int32_t out, int32_t K);
 kan_status kan_vq_assign(const float* coef, int32_t in, int32_t out, const float* codebook, int32_t K,

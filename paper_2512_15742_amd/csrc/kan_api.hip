@@ -193,7 +193,7 @@ constexpr int64_t kHalfFusedMaxBatch = 64;   // fp16 path: fused kernel up to he
 constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here (both paths) for layers of at least
 constexpr long long kFusedTwoTilesMinEdges = 1ll << 22;    // this many edges whose codeword rows are one gather each
 constexpr long long kFusedMinEdgesForResidency = 1 << 17;   // ... for layers of at least this many edges per head
-constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernel: layers up to here may write partial sums as large as their stream
+constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers up to here may write partial sums four times as large as their stream
 // Precise path, 2 to 32 samples: the wave-by-wave kernel up to this many edges per launch, tiles of 128 outputs with the
 // basis tile in LDS above (there the wait of one step is another's work, and what counts is how little each does:
 // 4096 x 4096 at batch 16 / 31 105 / 125 against 118 / 132 us, fifty heads of 1024-128-21 at batch 16 68.8 against
@@ -341,9 +341,9 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
     if (chunks < want) chunks = want;
   }
   const long long max_by_rows = n_in / 16;                                   // at least two steps each
-  // Partial sums up to a quarter of the parameter stream - up to the whole of it for small layers, whose
-  // launch is a latency chain and not a stream: capped at a quarter, config 3's second layer (262,144 edges) ran
-  // on 48 workgroups at batch 64 and took 17-28 us; with the cap at the stream's size it runs on 128 and takes
+  // Partial sums up to the size of the parameter stream (n_in * bytes_per_edge / 4 B chunks of 4 B bytes per output) -
+  // up to four times that for small layers, whose launch is a latency chain and not a stream: capped at the stream's
+  // size, config 3's second layer (262,144 edges) ran on 48 workgroups at batch 64 and took 17-28 us; with four times it runs on 128 and takes
   // 12.5-14.7 us (the head at batch 32 / 48 / 64: 39.9 / 57.5 / 60.0 against 46.7 / 62.8 / 71.5 us precise, 30.3 /
   // 41.0 / 43.8 against 36.9 / 43.5 / 47.6 us fp16; at batch 32 its chunks also become short enough to take the
   // first layer's partial sums as they are).  Layers of a million edges and more gain nothing from it.
@@ -360,8 +360,8 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 }
 
 // Precise path up to 32 samples: tiles of 64 outputs, the four waves of a workgroup over its inputs.  Two workgroups
-// per CU while a wave keeps two steps, and while the partial sums stay below a quarter of the parameter stream (the
-// whole of it for small layers, as above).
+// per CU while a wave keeps two steps, and while the partial sums stay below the size of the parameter stream (four
+// times that for small layers, as above).
 LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code) {
   LayerPlan p;
   p.mfma = false;
@@ -541,7 +541,7 @@ struct Chain {
   int in_parts = 1;              // slices of the input to add (1: plain x)
   long long in_part_stride = 0;
   int in_tanh = 0;
-  bool out = false;              // leave the per-bucket sums for the next layer (no reduction pass)
+  bool out = false;              // leave the partial sums for the next layer (no reduction pass)
   float* partial = nullptr;      // where this layer's partial sums go (default: w.partial)
   // matrix-core path: stages the head's first launch has already covered
   bool coef_done = false;

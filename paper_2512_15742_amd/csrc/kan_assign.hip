@@ -301,7 +301,7 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 }
 
 // ---- bounded search -------------------------------------------------------------------------------
-// The codebook is cut into cells (the shapes nearest to one of M = K / 32 sampled shapes, the cell's centre c)
+// The codebook is cut into cells (the shapes nearest to one of M = K / 64 sampled shapes, the cell's centre c)
 // and a cell into tiles of 32 shapes sorted by their distance to c.  A tile whose shapes all lie within R of c can be
 // left out for an edge n that knows a shape at distance d already when |n - c| > R + d; in scores (|n| = 1)
 //     n . c - |c|^2 / 2 + R^2 / 2 + R d  <  (1 - d^2) / 2 .
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 //
 // What bounds it: instructions issued.  A wave of the search makes (tiles / 32) bound tests and visits about 250 of
 // 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each one matrix and about ten vector instructions; the
-// counters show every SIMD issuing something nearly all the time, the matrix pipe busy for a quarter of it.  What that
+// counters show the matrix pipe busy for a third of the time and the address units (1 KB of operands per visit) for 62 %.  What that
 // took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
 // scalar code 1057 us, one instruction a visit 1084, more loads in flight 998, tiles listed in LDS and taken in
 // pairs 818, the second instruction in place of vector arithmetic for near scores 761, six waves per SIMD

@@ -108,8 +108,8 @@ __global__ __launch_bounds__(256) void kan_pli_basis_kernel(const float* __restr
 }
 
 // The four-entry window (first entry, four weights) of either rule as the forward kernels form
-// it: FAST = false through basis_eval / basis_eval_pli (vector-ALU and bucket kernels), FAST =
-// true through basis_fast (fused kernel, basis preparation of the streaming contraction).
+// it: FAST = false through basis_eval / basis_eval_pli (vector-ALU and bucket kernels, dense baseline up to 16 samples),
+// FAST = true through basis_fast (fused kernels, basis preparation of the streaming contraction, small-layer kernel).
 template <bool FAST>
 __global__ __launch_bounds__(256) void kan_basis_window_kernel(const float* __restrict__ x, long long n, int rule,
                                                                uint8_t* __restrict__ start, float* __restrict__ w) {
