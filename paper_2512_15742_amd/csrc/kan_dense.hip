@@ -21,10 +21,10 @@
 // Two forms:
 //   kan_dense_kernel        up to 16 samples, fp32 operands (v_mfma_f32_16x16x4f32: lane group g brings one of
 //                           the four terms).  The lane that needs a weight computes it: lane (g, s) evaluates the
-//                           basis of (sample s, input 4g + t) and spreads the four weights over ten registers.  Weights in fp64, rounded once
-//                           to fp32 (error 3.0e-8 against 1.3e-7 with fp32 polynomials; behind the
-//                           stream they cost 0.1-0.2 us: 2048 x 512 at batch 16 14.2 -> 14.4 us back to
-//                           back, 4096 x 1024 38.0 -> 38.4).
+//                           basis of (sample s, input 4g + t) and spreads the four weights over ten registers.
+//                           Weights in fp64, rounded once to fp32 (error 3.0e-8 against 1.3e-7 with fp32
+//                           polynomials; behind the stream they cost less than 0.2 us: 2048 x 512 at batch
+//                           16 14.2 -> 14.3 us back to back, 4096 x 1024 38.0 -> 38.15).
 //                           No LDS, no barrier before the sums of the four waves (spread over the inputs) meet.
 //   kan_dense_split_kernel  17 samples and more, operands in high and low fp16 parts (v_mfma_f32_16x16x32_f16,
 //                           three products: 22 significant bits), tiles of 32 or 64 samples.  The weights of a
@@ -65,6 +65,20 @@ __device__ __forceinline__ void load_grids(const float* col, long long row_strid
   }
 }
 
+// Span and weights of basis_eval (evaluated in fp64, rounded once) in half its instructions: t = (7x + 7) / 2 and the
+// local coordinate are exact in fp64, and the polynomials are written for fma.
+__device__ __forceinline__ BasisW basis_fp64(float xf) {
+  const double t = fma((double)fminf(fmaxf(xf, -1.0f), 1.0f), 3.5, 3.5);
+  BasisW r;
+  r.span = min((int)t, kSpans - 1);
+  const double u = t - (double)r.span, om = 1.0 - u, u2 = u * u;
+  r.w0 = (float)(om * om * (om * (1.0 / 6.0)));
+  r.w1 = (float)fma(u2, fma(u, 0.5, -1.0), 2.0 / 3.0);
+  r.w2 = (float)fma(u, fma(u, fma(u, -0.5, 0.5), 0.5), 1.0 / 6.0);
+  r.w3 = (float)(u2 * (u * (1.0 / 6.0)));
+  return r;
+}
+
 // The four weights at their places among ten, zeros elsewhere.
 __device__ __forceinline__ void spread_weights(const BasisW& w, float (&v)[kG]) {
 #pragma unroll
@@ -103,7 +117,7 @@ __global__ __launch_bounds__(256, 2) void kan_dense_kernel(const DenseArgs a) {
   auto step = [&](int i0, int s) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      BasisW w = basis_eval(xs[s][t]);
+      BasisW w = basis_fp64(xs[s][t]);
       if (i0 + 4 * g + t >= i_end) w = {0.f, 0.f, 0.f, 0.f, 0};
       float v[kG];
       spread_weights(w, v);
