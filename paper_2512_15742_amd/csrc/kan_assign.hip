@@ -44,8 +44,8 @@ __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
 }
 
 // Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) the norm term is minus infinity,
-// so that the row never wins, whatever the norms of the shapes.  Both searches take these, and the products in this order: a score has the same bits in
-// either.
+// so that the row never wins, whatever the norms of the shapes.  Both searches take these, and the products in this
+// order: a score has the same bits in either.
 __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
   h16x8 v;
   float row[kG], nrm = 0.f;
@@ -159,7 +159,6 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
   auto edge_at = [&](long long at) { return LIST ? (long long)a.list[at] : at; };
   // One workgroup's share: the edges from e_wg on, LIST: of these the tiles with their byte set in `tiles`.
   auto serve = [&](long long e_wg, uint32_t tiles) {
-
     // ---- step 1: bias = mean, gain = norm of the centred grid, n = centred / gain ------------
     for (int q = tid; q < kEdges; q += kThreads) {
       const long long at = e_wg + q, e = edge_at(min(at, E - 1));
@@ -324,10 +323,10 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 // whole search alone and 471 against 292 for K = 16,384, 2^18 edges (a few waves left behind there were one chain
 // through all tiles, 340 us); now 553 and 252.
 //
-// What bounds it: instructions issued.  A wave of the search makes (tiles / 32) bound tests and visits about 250 of
-// 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each one matrix and about ten vector instructions; the
-// counters show the matrix pipe busy for a third of the time and the address units (1 KB of operands per visit) for 62 %.  What that
-// took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
+// What bounds it: instructions issued and operands.  A wave of the search makes (tiles / 32) bound tests and visits
+// about 250 of 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each 1 KB of operands, one matrix and about ten
+// vector instructions; the counters show the address units busy for 62 % of the time, the matrix pipe for a third.
+// What that took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
 // scalar code 1057 us, one instruction a visit 1084, more loads in flight 998, tiles listed in LDS and taken in
 // pairs 818, the second instruction in place of vector arithmetic for near scores 761, six waves per SIMD
 // 690; cells of 64 instead of 32 shapes (the choice of the cells 154 -> 87 us).  The whole search takes 3.8 ms.
@@ -336,7 +335,7 @@ constexpr int kCellShapes = 64;                   // shapes per cell on average
 constexpr int kCellMaxTiles = 16384;              // (a wave marks the tiles it has visited in LDS)
 constexpr float kRestShare = 0.9f, kMeanFactor = 1.0f;          // (0.6 / 0.7: K = 8,192, unrelated grids 1153 / 873 us)
 constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
-constexpr int kRestWorkgroups = 1024;             // of the whole search behind it: as many as are resident
+constexpr int kRestWorkgroups = 1024;             // of the whole search behind it: twice what is resident
 constexpr int kAhead = 2;                         // tiles in flight per wave
 constexpr int kSortThreads = 1024, kSortGroups = 64;
 constexpr int kBuildChunk = 1024;                 // members of a cell that are sorted together
@@ -784,7 +783,7 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     float nn = 0.f;
 #pragma unroll
     for (int m = 0; m < kG; ++m) nn = fmaf(n[m], n[m], nn);
-    unit = nn <= 1.000003f;      // longer ones (squares in the subnormal range, below 1e-38, lose bits): the bounds do not hold
+    unit = nn <= 1.000003f;      // (longer: squares in the subnormal range, below 1e-38, lose bits; the bounds do not hold)
     _Float16 hi[kG], lo[kG];
 #pragma unroll
     for (int m = 0; m < kG; ++m) split_h(n[m], hi[m], lo[m]);
