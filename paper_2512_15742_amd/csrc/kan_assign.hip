@@ -76,9 +76,7 @@ __device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long 
 // Centroid-side operands in MFMA A-fragment order: record [(tile * 2 + kstep) * 64 + lane]
 // holds slots kstep*16 + (lane/32)*8 .. +8 of centroid tile*32 + (lane & 31).
 __global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __restrict__ cb, int K, int n_tiles,
-                                                              const uint32_t* __restrict__ any,
                                                               uint4* __restrict__ out) {
-  if (any && *any == 0) return;
   const long long rec = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (rec >= (long long)n_tiles * 2 * 64) return;
   const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
@@ -131,10 +129,11 @@ struct AssignArgs {
   const float* coef;        // [E][10]
   const uint4* cent;        // prepared centroid operands
   long long E;
-  // LIST: the edges in the order of the bounded search, and of every 32 whether they are left (their gains and biases are
-  // there already)
+  // LIST: behind the bounded search, on its tiles.  The edges in its order, and of every 32 whether they are left (their
+  // gains and biases are there already); the number of tiles and the shape of every row
   const uint32_t* list;
   const uint8_t* left;      // [4 * ceil(E / 128)]
+  const uint32_t *tiles, *ids;
   int n_tiles;              // ceil(K / 32)
   void* idx;
   float* gain;
@@ -202,9 +201,10 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
     }
 
     // ---- step 3: stream the centroid tiles (two tiles in flight) -----------------------------------
+    const int n_tiles = LIST ? (int)*a.tiles : a.n_tiles;
     const uint4* cp = a.cent + lane;
     auto load_tile = [&](int t, uint4 (&fa)[2]) {
-      const int tc = t < a.n_tiles ? t : a.n_tiles - 1;        // past the end: a harmless re-read
+      const int tc = t < n_tiles ? t : n_tiles - 1;        // past the end: a harmless re-read
       fa[0] = cp[(long long)(tc * 2) * 64];
       fa[1] = cp[(long long)(tc * 2 + 1) * 64];
     };
@@ -221,8 +221,14 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
         const float m = max_of(acc);
         // A new best is rare (the t-th tile improves a lane's running maximum with probability
         // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
-        // it the lowest register, keeps a tie.
-        if (m > best[nb]) {
+        // it the lowest register, keeps a tie.  (LIST: the lowest id, whatever tile it lies in.)
+        if constexpr (LIST) {
+          if (m >= best[nb]) {
+            const int r = row_of(acc, m), id = (int)a.ids[t * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
+            if (m > best[nb] || (uint32_t)id < (uint32_t)best_tile[nb]) best_tile[nb] = id;
+            best[nb] = m;
+          }
+        } else if (m > best[nb]) {
           best[nb] = m;
           best_tile[nb] = t;
           best_row[nb] = row_of(acc, m);
@@ -233,10 +239,10 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
     const int t0 = SPLIT > 1 ? wave : 0;
     load_tile(t0, fa0);
     load_tile(t0 + SPLIT, fa1);
-    for (int t = t0; t < a.n_tiles; t += 2 * SPLIT) {
+    for (int t = t0; t < n_tiles; t += 2 * SPLIT) {
       score_tile(t, fa0);
       load_tile(t + 2 * SPLIT, fa0);
-      if (t + SPLIT < a.n_tiles) score_tile(t + SPLIT, fa1);
+      if (t + SPLIT < n_tiles) score_tile(t + SPLIT, fa1);
       load_tile(t + 3 * SPLIT, fa1);
     }
 
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
     for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
       const int r = best_row[nb];
       // D layout of the 32x32 MFMA: register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4
-      int id = best_tile[nb] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      int id = LIST ? best_tile[nb] : best_tile[nb] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
       float sc = best[nb];
       const float sc_o = __shfl_xor(sc, 32, kWave);
       const int id_o = __shfl_xor(id, 32, kWave);
@@ -346,7 +352,7 @@ struct CellLayout {
   int tiles_max;
   int groups[2];           // workgroups of the sort: over the shapes, over the edges
   long long chunk[2];      // items per workgroup
-  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, left, any, whole, bytes;
+  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, left, bytes;
 };
 
 size_t centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(uint4); }
@@ -381,8 +387,6 @@ CellLayout cell_layout(long long E, int K) {
   g.wg_least = take((size_t)((K + kEdgesPerWg - 1) / kEdgesPerWg) * 8);
   g.least = take(4);
   g.left = take((size_t)((E + 127) / 128) * 4);
-  g.any = take(4);
-  g.whole = take(centroid_bytes(K));
   g.bytes = at;
   return g;
 }
@@ -405,7 +409,6 @@ struct CellArgs {
   uint32_t* first_tile;          // [M + 1]
   unsigned long long* wg_least;
   uint8_t* left;                 // [4 * ceil(E / 128)] waves whose edges are left to the whole search
-  uint32_t* any;                 // some are
   uint32_t* least;               // shape of the smallest norm: the nearest to an edge of gain 0
   void* idx;
   float *gain, *bias;
@@ -621,7 +624,6 @@ __global__ __launch_bounds__(kSortThreads) void kan_cell_scan_kernel(const CellA
   }
   if (tid == 0) {
     *a.least = (uint32_t)least;
-    *a.any = 0;
   }
 }
 
@@ -812,10 +814,7 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     near = best - slack;
   };
   auto leave = [&] {                             // to the whole search
-    if (lane == 0) {
-      a.left[wg * 4 + wave] = 1;
-      *a.any = 1;
-    }
+    if (lane == 0) a.left[wg * 4 + wave] = 1;
   };
 
   // (1) own cells, both instructions of every tile
@@ -1040,23 +1039,6 @@ int recon_blocks(long long E) {
 }
 
 namespace {
-AssignArgs whole_args(const float* coef, long long E, const float* cb, int K, void* idx, float* gain, float* bias,
-                      void* centroids, const uint32_t* any, hipStream_t s) {
-  AssignArgs a;
-  a.coef = coef;
-  a.cent = (const uint4*)centroids;
-  a.E = E;
-  a.list = nullptr;
-  a.left = nullptr;
-  a.n_tiles = (K + 31) / 32;
-  a.idx = idx;
-  a.gain = gain;
-  a.bias = bias;
-  const long long recs = (long long)a.n_tiles * 2 * 64;
-  hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, a.n_tiles, any,
-                     (uint4*)centroids);
-  return a;
-}
 dim3 split_grid(long long E) { return dim3((unsigned)((E + kEdgeTilesPerWave * 32 - 1) / (kEdgeTilesPerWave * 32))); }
 }  // namespace
 
@@ -1103,7 +1085,6 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   a.first_tile = (uint32_t*)(w + g.first_tile);
   a.wg_least = (unsigned long long*)(w + g.wg_least);
   a.left = (uint8_t*)(w + g.left);
-  a.any = (uint32_t*)(w + g.any);
   a.least = (uint32_t*)(w + g.least);
   a.idx = idx;
   a.gain = gain;
@@ -1121,9 +1102,15 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   const dim3 grid((unsigned)((E + 127) / 128));
   if (idx_u32) hipLaunchKernelGGL(kan_assign_bounded_kernel<uint32_t>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(kan_assign_bounded_kernel<uint16_t>, grid, dim3(256), 0, s, a);
-  AssignArgs rest = whole_args(coef, E, cb, K, idx, gain, bias, w + g.whole, a.any, s);
+  AssignArgs rest = {};
+  rest.coef = coef;
+  rest.cent = a.frag;
+  rest.E = E;
   rest.list = a.sorted[1];
   rest.left = a.left;
+  rest.tiles = a.first_tile + g.M;
+  rest.ids = a.ids;
+  rest.idx = idx;
   const dim3 rest_grid((unsigned)std::min<long long>((E + 127) / 128, kRestWorkgroups));
   if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
   else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
@@ -1132,7 +1119,16 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
 
 hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx, float* gain,
                          float* bias, void* ws, hipStream_t s) {
-  const AssignArgs a = whole_args(coef, E, cb, K, idx, gain, bias, ws, nullptr, s);
+  AssignArgs a = {};
+  a.coef = coef;
+  a.cent = (const uint4*)ws;
+  a.E = E;
+  a.n_tiles = (K + 31) / 32;
+  a.idx = idx;
+  a.gain = gain;
+  a.bias = bias;
+  const long long recs = (long long)a.n_tiles * 2 * 64;
+  hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, a.n_tiles, (uint4*)ws);
   const dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg));
   if (E <= kSplitMaxEdges) {
     if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, false>), split_grid(E), dim3(8 * kWave), 0, s, a);
