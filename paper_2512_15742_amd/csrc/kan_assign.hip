@@ -331,7 +331,7 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 //
 // What bounds it: instructions issued and operands.  A wave of the search makes (tiles / 32) bound tests and visits
 // about 250 of 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each 1 KB of operands, one matrix and about ten
-// vector instructions; the counters show the address units busy for 62 % of the time, the matrix pipe for a third.
+// vector instructions; the counters show the address units busy for 65 % of the time, the matrix pipe for a third.
 // What that took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
 // scalar code 1057 us, one instruction a visit 1084, more loads in flight 998, tiles listed in LDS and taken in
 // pairs 818, the second instruction in place of vector arithmetic for near scores 761, six waves per SIMD
