@@ -82,14 +82,19 @@ typedef enum kan_dtype {
  *                    33 coefficients and basis weights split into high and low fp16 parts,
  *                    three products, fp32-grade sums); from batch 65 (129 for layers of
  *                    2^22 edges or more whose codebook is not fp32): the kernels of the fp16
- *                    path on such split operands.  Prepared layers (see kan_vq_prepare),
+ *                    path on such split operands (layers of a million edges and more, heads
+ *                    of a launch together, up to batch 768: a kernel that gathers and
+ *                    dequantises its own coefficients for tiles of 128 or 256 samples).
+ *                    Prepared layers (see kan_vq_prepare),
  *                    batch <= 4 (<= 3 for layers of 2^23 edges or more): codebook buckets
  *                    in LDS.
  *   KAN_PATH_MFMA    fp16 operands on the matrix cores, fp32 accumulation; ~3e-4
  *                    relative per layer (bound 2e-2).  Batch <= 64 (128 for those large
  *                    layers): fused gather + MFMA kernel; above: coefficients dequantised
  *                    once per call into the workspace in matrix-core operand order, then a
- *                    streaming contraction.
+ *                    streaming contraction; layers of a million edges and more between batch
+ *                    65 and 512 (1024 from 2^22 edges): coefficients dequantised by the
+ *                    contraction itself for tiles of up to 512 samples.
  *   KAN_PATH_AUTO    the precise path below batch 32, the fp16 path from there on.   */
 typedef enum kan_path { KAN_PATH_AUTO = 0, KAN_PATH_GATHER = 1, KAN_PATH_MFMA = 2 } kan_path;
 

@@ -35,6 +35,8 @@ UNITS = [
     ("kan_api.hip", "kan_api.o", []),
     ("kan_misc.hip", "kan_misc.o", []),
     ("kan_mfma.hip", "kan_mfma.o", []),
+    ("kan_wide.hip", "kan_wide.o", []),
+    ("kan_wide.hip", "kan_wide_u32.o", ["-DKAN_WIDE_U32=1"]),
     ("kan_tail.hip", "kan_tail.o", []),
     ("kan_fused.hip", "kan_fused.o", []),
     ("kan_fused.hip", "kan_fused_chained.o", ["-DKAN_FUSED_CH=1"]),

@@ -114,6 +114,7 @@ struct LayerPlan {
   int n_jt, n_bt, n_chunks, rows_per_chunk;
   int tile_n = 0;              // matrix-core path: outputs per workgroup tile (128: four waves, 256: eight)
   int kind;          // PlanKind
+  bool wide = false; // kPlanMfma whose workgroups dequantise their own coefficients (kan_wide.hip): cfg.bt samples x tile_n outputs
   bool mfma;         // kind == kPlanMfma (coefficient + basis preparation, streaming contraction) or kPlanTail (coefficient preparation, one launch)
   int products = 1;  // 3: both operands in high and low fp16 parts, hi*hi + hi*lo + lo*hi (three passes inside the kernel)
   const char* name;
@@ -270,6 +271,60 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
   return p;
 }
 
+// Contraction whose workgroups gather and dequantise their own coefficients (kan_wide.hip): tiles of 64 outputs by 128,
+// 256 or 512 samples (256 at most for split operands).  A row of tiles gathers every edge once more, the streaming form
+// writes and reads 20 (40) bytes per edge once; times of a layer in us, streaming form (fused kernel's two tiles: *) /
+// this one:
+//                        batch 128      256         512          768           1024          1536
+//   256 x 256   fp16   16.2 / 15.6   15.9 / 16.9   17.8 / 20.3
+//   2048 x 256  fp16   20.5 / 20.5   23.7 / 24.4   28.9 / 27.3   30.3 / 35.5
+//   2048 x 512  fp16   27.8 / 23.9   30.7 / 24.9   34.5 / 33.3   42.7 / 43.8   45.6 / 49.7
+//   2048 x 1024 fp16   37.0 / 27.4   43.3 / 30.6   50.6 / 45.7   64.1 / 65.6   65.0 / 61.7
+//   4096 x 1024 fp16   57.7*/ 39.2   69.8 / 44.4   90.6 / 74.0    117 / 113     109 / 105     152 / 152
+//   4096 x 4096 fp16    176*/ 111     216 / 124     272 / 170     376 / 305     378 / 313     590 / 529
+//   2048 x 512  split  37.4 / 30.6   43.0 / 33.0   56.7 / 47.3   80.0 / 62.5   85.7 / 77.1
+//   2048 x 1024 split  59.9 / 37.1   70.7 / 44.3   98.7 / 69.7    136 / 100     125 / 124
+//   4096 x 1024 split  88.9*/ 55.5    135 / 70.0    200 / 121     266 / 184     226 / 232     333 / 413
+//   4096 x 4096 split   312*/ 169     431 / 212     575 / 400     873 / 687     875 / 792    1501 / 1397
+// and with ten heads of 2048-256-21 at batch 128 114 / 61 (fp16), 206 / 87 (split).
+constexpr long long kWideMinEdges = 1ll << 20;        // over the heads of a launch
+constexpr int64_t kWideMinBatch = 65, kWideMaxBatchHalf = 512, kWideMaxBatchHalfLarge = 1024, kWideMaxBatchSplit = 768;
+constexpr long long kWideLargeEdges = 1ll << 22;      // ... for kWideMaxBatchHalfLarge
+
+// Turns plan p of such a layer into one for that kernel where it is the faster one.
+bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool split3) {
+  const long long edges = (long long)n_in * n_out * n_heads;
+  if (B < kWideMinBatch || edges < kWideMinEdges || !wide_takes(n_in, n_out, B)) return false;
+  if (B > (split3 ? kWideMaxBatchSplit : (edges >= kWideLargeEdges ? kWideMaxBatchHalfLarge : kWideMaxBatchHalf))) return false;
+  const int n_jt = (n_out + kWideTileN - 1) / kWideTileN;
+  if ((long long)n_jt * kWideTileN * 2 > 3ll * n_out) return false;        // (tiles half empty)
+  const int tile = B <= 128 ? 128 : (B <= 256 || split3 ? 256 : 512), n_bt = (int)((B + tile - 1) / tile);
+  // Chunks of inputs: the fewest rounds of one workgroup per CU.  In units of a step (about 2 us): what a workgroup takes
+  // outside its steps is about five, the partial sums cost 8 bytes per chunk, sample and output at 4 TB/s.
+  const long long base = (long long)n_heads * n_jt * n_bt, steps = (n_in + 15) / 16;
+  long long best = 1;
+  double best_cost = 0.0;
+  for (long long c = 1; c <= kMaxChainedSlices && (c == 1 || c * 2 <= steps); ++c) {
+    const double rounds = (double)((base * c + 255) / 256);
+    const double cost = rounds * ((double)((steps + c - 1) / c) + 5.0) + (c > 1 ? 1e-6 * (double)(c * n_heads * B * n_out) : 0.0);
+    if (c == 1 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+  }
+  p.kind = kPlanMfma;
+  p.mfma = true;
+  p.wide = true;
+  p.products = split3 ? 3 : 1;
+  p.cfg.bt = tile;
+  p.tile_n = kWideTileN;
+  p.n_jt = n_jt;
+  p.n_bt = n_bt;
+  p.rows_per_chunk = (int)((steps + best - 1) / best) * 16;
+  p.n_chunks = (n_in + p.rows_per_chunk - 1) / p.rows_per_chunk;
+  return true;
+}
+
 // Small layers take one launch (kan_tail.hip) in place of basis words, contraction and reduction.  A workgroup
 // evaluates the basis of all inputs for its 32 samples and reads the records of its outputs, so the line is where
 // that takes longer than the launches it saves: kTailMaxIn inputs (416-32 at batch 1166 17.9 -> 14.6 us, 475-52-13 at
@@ -284,13 +339,16 @@ constexpr long long kTailSlicedInputs = 4096, kTailSlicedInputsManyTiles = 2048;
 
 // x_parts: slices the layer's input may come in.
 LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3,
-                      int x_parts, int min_rows) {
+                      int x_parts, int min_rows, bool wide) {
   LayerPlan p = plan_mfma(n_in, n_out, B, n_heads, idx_u32, gb_kind, code, split3, min_rows);
   const long long n_bt = (B + 31) / 32;
   const int tile_n = split3 || n_out <= 32 || (n_out + 31) / 32 * n_bt * n_heads <= 256 ? 32 : 64;
   const long long n_jt = (n_out + tile_n - 1) / tile_n;
-  if (n_in > kTailMaxIn || (long long)n_in * n_out > kTailMaxEdges || n_jt * n_bt * n_heads > kTailMaxWorkgroups) return p;
-  if (x_parts > 1 && (long long)x_parts * n_in > (n_jt > 2 ? kTailSlicedInputsManyTiles : kTailSlicedInputs)) return p;
+  if (n_in > kTailMaxIn || (long long)n_in * n_out > kTailMaxEdges || n_jt * n_bt * n_heads > kTailMaxWorkgroups ||
+      (x_parts > 1 && (long long)x_parts * n_in > (n_jt > 2 ? kTailSlicedInputsManyTiles : kTailSlicedInputs))) {
+    if (wide) make_wide(p, n_in, n_out, B, n_heads, split3);
+    return p;
+  }
   p.kind = kPlanTail;
   p.cfg.bt = 32;
   p.tile_n = tile_n;
@@ -466,7 +524,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) keep the fused kernel up to
 //     kFusedTwoTilesMaxBatch on either path.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
-                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows) {
+                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
   const bool half_path = path == KAN_PATH_MFMA || (path == KAN_PATH_AUTO && B >= kAutoMfmaBatch);
@@ -480,15 +538,23 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   if (half_path) {
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
-    if (B <= fused_max) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false);
-    return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, false, x_parts, min_rows);
+    if (B <= fused_max) {
+      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false);
+      if (wide) make_wide(p, L.in, L.out, B, n_heads, false);
+      return p;
+    }
+    return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, false, x_parts, min_rows, wide);
   }
   if (prepared_ok && B <= bucket_max_batch((long long)L.in * L.out))
     return column_ok && (long long)L.in * L.out * B <= kColumnMaxWork ? plan_column(L, B) : plan_bucket(L, B, n_heads);
   // large batches: the fp16 machinery with both operands split into high and low parts
-  if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows);
+  if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide);
   const long long edges = (long long)L.in * L.out;
-  if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) return plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
+  if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) {
+    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
+    if (wide) make_wide(p, L.in, L.out, B, n_heads, true);
+    return p;
+  }
   if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code);
   return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok);
 }
@@ -574,6 +640,51 @@ struct BasisBufs {
   uint2* u_lo;
   long long u_stride;
 };
+
+// The same for a layer whose workgroups dequantise their own coefficients: pairs 0..3 lie where the other form keeps
+// its words, pair 4 (a quarter of their size) in the layer's region of the records.
+RotWords rot_words(const LayerPlan& p, const GatherArgs& a, int heads, bool x_shared, const WsPtrs& w) {
+  const long long steps = (a.n_in + 15) / 16, n = x_shared ? 1 : heads;
+  RotWords r;
+  r.W = (uint4*)w.u;
+  r.Z = w.cf;
+  r.W_lo = p.products == 3 ? r.W + n * steps * 8 * a.B : nullptr;
+  r.Z_lo = p.products == 3 ? r.Z + n * steps * 2 * a.B : nullptr;
+  r.w_head_stride = x_shared ? 0 : steps * 8 * a.B;
+  r.z_head_stride = x_shared ? 0 : steps * 2 * a.B;
+  return r;
+}
+kan_status run_wide(const LayerPlan& p, const GatherArgs& a, int heads, bool x_shared, float* dst, long long dst_head_stride,
+                    long long dst_chunk_stride, int apply_tanh, const WsPtrs& w, const Chain& chain, hipStream_t s) {
+  const RotWords r = rot_words(p, a, heads, x_shared, w);
+  if (!chain.basis_done) {
+    const kan_status st = run("kan_prep_basis", s, [&] {
+      return launch_prep_rot(a.x, a.x_head_stride, chain.in_parts, chain.in_part_stride, chain.in_tanh, r, a.n_in, a.B,
+                             x_shared ? 1 : heads, a.rule, s);
+    });
+    if (st != KAN_OK) return st;
+  }
+  WideArgs m;
+  memset(&m, 0, sizeof(m));
+  m.W = r.W;
+  m.Z = r.Z;
+  m.W_lo = r.W_lo;
+  m.Z_lo = r.Z_lo;
+  m.w_head_stride = r.w_head_stride;
+  m.z_head_stride = r.z_head_stride;
+  m.dst = dst;
+  m.dst_head_stride = dst_head_stride;
+  m.dst_chunk_stride = dst_chunk_stride;
+  m.n_in = a.n_in;
+  m.n_out = a.n_out;
+  m.B = a.B;
+  m.rows_per_chunk = p.rows_per_chunk;
+  m.n_jt = p.n_jt;
+  m.apply_tanh = apply_tanh;
+  memcpy(m.h, a.h, sizeof(m.h));
+  dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
+  return run(p.name, s, [&] { return launch_wide(p.cfg, m, p.products == 3, p.cfg.bt, grid, s); });
+}
 kan_status run_prep_basis(const LayerPlan& p, const GatherArgs& a, int heads, bool x_shared, const WsPtrs& w,
                           const Chain& chain, BasisBufs* out, bool launch, hipStream_t s) {
   const long long u_elems = (long long)((a.n_in + 15) / 16 * 16) * a.B;
@@ -597,7 +708,9 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
   const long long dst_chunk_stride = split ? count : 0;
   const int tanh_in_kernel = split ? 0 : apply_tanh;
   kan_status st;
-  if (p.mfma) {
+  if (p.wide) {
+    st = run_wide(p, a, heads, x_shared, dst, dst_head_stride, dst_chunk_stride, tanh_in_kernel, w, chain, s);
+  } else if (p.mfma) {
     PrepCoefArgs pc;
     const bool split3 = p.products == 3;
     st = run_prep_coef(p, a, heads, w, &pc, !chain.coef_done, s);
@@ -800,7 +913,7 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
 kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                          int min_rows, bool hand_on, std::vector<LayerPlan>* plans, WsLayout* ws) {
+                          int min_rows, bool hand_on, bool wide, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -829,13 +942,15 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? plans->back().n_chunks : 1, min_rows);
+    LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? plans->back().n_chunks : 1, min_rows, wide);
     plans->push_back(p);
     auto grow = [](size_t& dst, size_t v) { if (v > dst) dst = v; };
     grow(l & 1 ? ws->partial2 : ws->partial, partial_bytes(p, R.out, B, group));
     ws->cf_off.push_back(ws->cf);
     ws->bp_off.push_back(ws->bp);
-    if (p.mfma) {
+    if (p.wide) {      // (pair 4 of its basis words; pairs 0..3 take the room of the other form's words)
+      ws->cf += round_up((size_t)(p.products == 3 ? 2 : 1) * (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16) * 2 * (size_t)B * sizeof(uint4), 256);
+    } else if (p.mfma) {
       ws->cf += round_up((size_t)(p.products == 3 ? 2 : 1) * group * mfma_cf_records(R.in, R.out) * sizeof(uint4), 256);
       ws->bp += round_up((size_t)group * mfma_bp_floats(R.in, R.out) * sizeof(float), 256);
     }
@@ -851,23 +966,30 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
   return KAN_OK;
 }
 
-// Finer chunks write more partial sums, and a layer that hands its sums on keeps a second buffer of them: a call that
-// fits the library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.
+// Finer chunks write more partial sums, a layer that hands its sums on keeps a second buffer of them: a call that fits the
+// library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.  Basis words
+// take room that the fused kernel does without: a call that would fit without the kernel of kan_wide.hip is planned to
+// fit, with that kernel where possible; one that would not is not slowed down to fit.
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
-  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, plans, ws);
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, plans, ws);
   if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
-  const struct { int min_rows; bool hand_on; } smaller[] = {{kMfmaMinRowsCompact, true}, {kMfmaMinRows, false}, {kMfmaMinRowsCompact, false}};
-  for (const auto& o : smaller) {
-    std::vector<LayerPlan> other;
-    WsLayout other_ws;
-    st = plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, &other, &other_ws);
-    if (st == KAN_OK && other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
-      plans->swap(other);
-      *ws = other_ws;
-      break;
-    }
-  }
+  const struct { int min_rows; bool hand_on; } forms[] = {
+      {kMfmaMinRows, true}, {kMfmaMinRowsCompact, true}, {kMfmaMinRows, false}, {kMfmaMinRowsCompact, false}};
+  std::vector<LayerPlan> other;
+  WsLayout other_ws;
+  auto fits = [&](bool wide) {
+    for (const auto& o : forms)
+      if (plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, wide, &other, &other_ws) == KAN_OK &&
+          other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES)
+        return true;
+    return false;
+  };
+  if (!fits(false)) return st;
+  const bool any_wide = std::any_of(plans->begin(), plans->end(), [](const LayerPlan& p) { return p.wide; });
+  if (any_wide && !fits(true)) (void)fits(false);
+  plans->swap(other);
+  *ws = other_ws;
   return st;
 }
 
@@ -1008,7 +1130,7 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     const LayerPlan& p0 = plans[0];
     for (int l = 0; l < n_layers && ps.n_jobs < kStartJobs; ++l) {
       const LayerPlan& p = plans[l];
-      if (!p.mfma || p.products != p0.products || p.cfg.code != p0.cfg.code || p.cfg.gb_kind != p0.cfg.gb_kind ||
+      if (!p.mfma || p.wide || p.products != p0.products || p.cfg.code != p0.cfg.code || p.cfg.gb_kind != p0.cfg.gb_kind ||
           p.cfg.idx_u32 != p0.cfg.idx_u32)
         continue;
       GatherArgs a;
@@ -1031,6 +1153,8 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     layer_args(0, 0, 1, x, 0, &a0, nullptr);
     BasisBufs bb;
     (void)run_prep_basis(p0, a0, 1, true, w, Chain(), &bb, false, s);
+    ps.rot = p0.wide;
+    if (p0.wide) ps.rw = rot_words(p0, a0, 1, true, w);
     ps.x = x;
     ps.W = w.u;
     ps.W_lo = bb.u_lo;

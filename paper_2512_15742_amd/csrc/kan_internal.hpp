@@ -87,6 +87,13 @@ struct PrepCoefArgs {
   LayerPtrs h[kMaxGroup];
 };
 
+// Basis operand of kan_wide.hip: W[step][4][2][B] and Z[step][2][B] items of 16 bytes, step = input / 16; split form: the
+// low parts beside them (else null).  Head strides in items, 0 when all heads share the input.
+struct RotWords {
+  uint4 *W, *Z, *W_lo, *Z_lo;
+  long long w_head_stride, z_head_stride;
+};
+
 // One launch for all a single head's call can prepare before its first contraction: the
 // coefficient records of up to kStartJobs matrix-core layers of the same storage types, and
 // the basis words of the first layer's input.
@@ -106,6 +113,8 @@ struct PrepStartArgs {
   const float* x;                    // [B][n_in] of the first layer; n_in = 0: no basis words
   uint2* W;
   uint2* W_lo;                       // split form only
+  int rot;                           // write rotated words (kan_wide.hip) instead of W, W_lo
+  RotWords rw;
   int n_in, B, rule;
   int basis_nx;                      // filled by the launcher
 };
@@ -152,6 +161,25 @@ hipError_t launch_prep_basis(const float* x, long long x_head_stride, int x_part
                              int x_tanh, uint2* W, uint2* W_lo, long long w_head_stride, int n_in, int B, int heads,
                              int rule, hipStream_t);
 hipError_t launch_mfma(const MfmaArgs&, int tile_m, int tile_n, dim3 grid, hipStream_t);   // samples (64 | 128) x outputs (128; 256 with 128 samples) per tile
+
+// ---- contraction that dequantises its own coefficients (kan_wide.hip) -----------------------------------------
+constexpr int kWideTileN = 64;        // outputs per workgroup
+constexpr int kWideMaxOut = 1 << 19;  // (a tile of 512 rows of the result is addressed by 32-bit offsets)
+struct WideArgs {
+  const uint4 *W, *Z, *W_lo, *Z_lo;
+  long long w_head_stride, z_head_stride;
+  float* dst;
+  long long dst_head_stride, dst_chunk_stride;
+  int n_in, n_out, B;
+  int rows_per_chunk;          // multiple of 16
+  int n_jt;                    // blockIdx.x = tile of samples * n_jt + output tile
+  int apply_tanh;
+  LayerPtrs h[kMaxGroup];
+};
+bool wide_takes(int n_in, int n_out, int64_t B);       // sizes it can address
+hipError_t launch_wide(const GatherCfg&, const WideArgs&, bool split, int tile_m, dim3 grid, hipStream_t);   // tile_m: 128, 256 or (not split) 512 samples
+hipError_t launch_prep_rot(const float* x, long long x_head_stride, int x_parts, long long x_part_stride, int x_tanh,
+                           const RotWords&, int n_in, int B, int heads, int rule, hipStream_t);
 
 // ---- small layers of the matrix-core path: basis, contraction and sum over all inputs in one launch ----------
 constexpr int kTailMaxIn = 448;       // inputs (those of 32 samples are kept in LDS)

@@ -66,19 +66,6 @@ constexpr int kRowBytes = 208;         // LDS row of the Phi tile: 160 B of weig
 constexpr int kIdxOffset = 160;        // index words of the row: [lane half][S = 0..4] as u16, 16 bytes per lane half
 constexpr int kBufferFlags = 0x00020000;   // buffer resource word 3: raw 32-bit data format, no swizzle
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-// Ten fp32 coefficients as high and low fp16 parts, in pairs (m, m + 5): c = hi + lo / 2048.
-__device__ __forceinline__ void split_pairs(const float (&c)[kG], uint32_t (&hi)[5], uint32_t (&lo)[5]) {
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    hi[m] = flush_h2(pack_h2(c[m], c[m + 5]));
-    lo[m] = flush_h2(pack_h2((c[m] - half_bits_to_float(hi[m] & 0xffffu)) * 2048.0f,
-                             (c[m + 5] - half_bits_to_float(hi[m] >> 16)) * 2048.0f));
-  }
-}
-
 // ---- kan_prep_coef ------------------------------------------------------------------
 // Chat as uint4 records: rec[(((step*5 + S) * 2 + h) * 2 + a) * n_out + j], step = i / 16: the
 // half a (elements 8a .. 8a+7) of the B operand of lane half h in sparse MFMA S of the step,
@@ -301,28 +288,8 @@ __device__ __forceinline__ void prep_basis_block(const float* __restrict__ xh, c
                                                  uint2 (*tile)[33], uint2 (*tile_lo)[33]) {
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;      // 32 x 8
   const int ib = bx * 32, bb = by * 32;
-  // The inputs of the thread's four elements first, every load unconditional (clamped addresses): the
-  // slices of all four are in flight together instead of one element's after the other's arithmetic.
-  const float* xp[4];
   float xs[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    xp[r] = xh + (long long)min(bb + ty + 8 * r, B - 1) * n_in + min(ib + tx, n_in - 1);
-    xs[r] = xp[r][0];
-  }
-  for (int p0 = 1; p0 < x_parts; p0 += 8) {           // eight slices in flight per element, added in order
-    float t[8][4];
-#pragma unroll
-    for (int pp = 0; pp < 8; ++pp) {
-      const long long off = (long long)min(p0 + pp, x_parts - 1) * x_part_stride;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) t[pp][r] = xp[r][off];
-    }
-#pragma unroll
-    for (int pp = 0; pp < 8; ++pp)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) xs[r] += p0 + pp < x_parts ? t[pp][r] : 0.f;
-  }
+  load_block_inputs(xh, x_parts, x_part_stride, n_in, B, bx, by, xs);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int b = bb + ty + 8 * r, i = ib + tx;
@@ -375,8 +342,14 @@ template <typename IdxT, typename GbT, typename CbT, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void kan_prep_start_kernel(const PrepStartArgs a) {
   __shared__ float sb[4][64];
   __shared__ __attribute__((aligned(16))) unsigned char strips[4][kPrepStripBytes];
-  __shared__ uint2 tile[32][33];
-  __shared__ uint2 tile_lo[SPLIT ? 32 : 1][33];
+  union BasisTiles {
+    struct {
+      uint2 tile[32][33], tile_lo[SPLIT ? 32 : 1][33];
+    } words;
+    RotTile rot[SPLIT ? 2 : 1];
+  };
+  __shared__ BasisTiles bt;
+  __shared__ __attribute__((aligned(16))) uint32_t sel[kSpans][8];
   const int blk = blockIdx.x;
   int k = 0;
   while (k < a.n_jobs && blk >= a.first_block[k + 1]) ++k;
@@ -385,9 +358,12 @@ __global__ __launch_bounds__(kThreads) void kan_prep_start_kernel(const PrepStar
     const PrepStartArgs::Job& job = a.job[k];
     prep_coef_block<IdxT, GbT, CbT, SPLIT>(job.h, job.cf, SPLIT ? job.cf_lo : nullptr, job.bp, job.n_in, job.n_out,
                                            rel % job.nx, rel / job.nx, sb, strips);
+  } else if (a.rot) {
+    prep_rot_block(a.x, 1, 0, 0, a.rw, a.n_in, a.B, a.rule, rel % a.basis_nx, rel / a.basis_nx, bt.rot[0],
+                   bt.rot[SPLIT ? 1 : 0], sel);
   } else {
     prep_basis_block(a.x, 1, 0, 0, a.W, SPLIT ? a.W_lo : nullptr, a.n_in, a.B, a.rule, rel % a.basis_nx,
-                     rel / a.basis_nx, tile, SPLIT ? tile_lo : tile);
+                     rel / a.basis_nx, bt.words.tile, SPLIT ? bt.words.tile_lo : bt.words.tile);
   }
 }
 
@@ -892,8 +868,9 @@ hipError_t launch_prep_coef(const GatherCfg& c, const PrepCoefArgs& a, int heads
 }
 
 hipError_t launch_prep_start(const GatherCfg& c, PrepStartArgs& a, bool split, hipStream_t s) {
-  if (c.code == kDense || a.n_jobs < 1 || a.n_jobs > kStartJobs) return hipErrorInvalidValue;
-  if (a.n_in > 0 && (!a.x || !a.W || (split && !a.W_lo))) return hipErrorInvalidValue;
+  if (c.code == kDense || a.n_jobs < 0 || a.n_jobs > kStartJobs) return hipErrorInvalidValue;
+  if (a.n_in > 0 && !a.rot && (!a.x || !a.W || (split && !a.W_lo))) return hipErrorInvalidValue;
+  if (a.n_in > 0 && a.rot && (!a.x || !a.rw.W || !a.rw.Z || (split && (!a.rw.W_lo || !a.rw.Z_lo)))) return hipErrorInvalidValue;
   long long blocks = 0;
   for (int k = 0; k < a.n_jobs; ++k) {
     PrepStartArgs::Job& job = a.job[k];

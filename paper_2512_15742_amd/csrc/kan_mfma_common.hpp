@@ -3,6 +3,7 @@
 #pragma once
 
 #include "kan_device.hpp"
+#include "kan_internal.hpp"
 
 namespace kan {
 
@@ -46,6 +47,16 @@ __device__ __forceinline__ void split_consecutive(const float (&c)[kG], uint32_t
     hi[m] = flush_h2(pack_h2(c[2 * m], c[2 * m + 1]));
     lo[m] = flush_h2(pack_h2((c[2 * m] - half_bits_to_float(hi[m] & 0xffffu)) * 2048.0f,
                              (c[2 * m + 1] - half_bits_to_float(hi[m] >> 16)) * 2048.0f));
+  }
+}
+
+// Ten fp32 coefficients as high and low fp16 parts, in pairs (m, m + 5): c = hi + lo / 2048.
+__device__ __forceinline__ void split_pairs(const float (&c)[kG], uint32_t (&hi)[5], uint32_t (&lo)[5]) {
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    hi[m] = flush_h2(pack_h2(c[m], c[m + 5]));
+    lo[m] = flush_h2(pack_h2((c[m] - half_bits_to_float(hi[m] & 0xffffu)) * 2048.0f,
+                             (c[m + 5] - half_bits_to_float(hi[m] >> 16)) * 2048.0f));
   }
 }
 
@@ -169,6 +180,31 @@ __device__ __forceinline__ void dequant_row(const RawRow<CbT>& r, float g, uint3
   }
 }
 
+// w[m] = fp16 pair (g*coef m, -g*coef m + 5), m = 0..4: the pairs of the sparse operand whose stored values carry
+// "takes the second of the pair" in their sign (kan_wide.hip).
+template <typename CbT>
+__device__ __forceinline__ void dequant_row_pairs(const RawRow<CbT>& r, float g, uint32_t (&w)[5]) {
+  if constexpr (sizeof(CbT) == 1 || kIsBfp8<CbT>) {
+    float gs = g;
+    if constexpr (kIsBfp8<CbT>) gs = g * bfp8_row_scale(r.d);
+    const _Float16 gh = (_Float16)gs;
+    const h16x2 g2 = {gh, -gh}, off = {(_Float16)-1152.0f, (_Float16)-1152.0f};
+    const uint32_t q[5] = {__builtin_amdgcn_perm(r.b, r.a, 0x0c050c00u), __builtin_amdgcn_perm(r.b, r.a, 0x0c060c01u),
+                           __builtin_amdgcn_perm(r.b, r.a, 0x0c070c02u), __builtin_amdgcn_perm(r.d, r.a, 0x0c040c03u),
+                           __builtin_amdgcn_perm(r.d, r.b, 0x0c050c00u)};
+#pragma unroll
+    for (int m = 0; m < 5; ++m)        // 0x6480 ^ byte: the half 1152 + q
+      w[m] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(h16x2, q[m] ^ 0x64806480u) + off) * g2);
+  } else if constexpr (sizeof(CbT) == 2) {
+    auto coef = [&](int m) { return g * half_bits_to_float((r.w[m >> 1] >> (16 * (m & 1))) & 0xffffu); };
+#pragma unroll
+    for (int m = 0; m < 5; ++m) w[m] = pack_h2(coef(m), -coef(m + 5));
+  } else {
+#pragma unroll
+    for (int m = 0; m < 5; ++m) w[m] = pack_h2(g * r.c[m], -(g * r.c[m + 5]));
+  }
+}
+
 // c[m] = g * coef m as fp32 (matrix-core path with fp32 operands).
 template <typename CbT>
 __device__ __forceinline__ void dequant_row_f32(const RawRow<CbT>& r, float g, float (&c)[kG]) {
@@ -258,6 +294,98 @@ __device__ __forceinline__ void fill_sparse_selectors(uint32_t (*sel)[8], int ti
     sel[l][2] = half_sel[4] | 0x0c0c0000u;
     sel[l][3] = (hi[0] | ((2u + hi[1]) << 2)) | ((hi[2] | ((2u + hi[3]) << 2)) << 4) | (hi[4] << 8);
     sel[l][4] = sel[l][5] = sel[l][6] = sel[l][7] = 0;
+  }
+}
+
+// ---- basis operand of a block of 32 samples x 32 inputs (256 threads: 32 x 8) ---------------------------------
+// The inputs of the thread's four elements (sample 32 by + ty + 8 r, input 32 bx + tx): x itself, or (x_parts > 1) the
+// previous layer's partial sums, added here in the order of the slices.  Every load is unconditional (clamped
+// addresses): the slices of all four are in flight together instead of one element's after the other's arithmetic.
+__device__ __forceinline__ void load_block_inputs(const float* __restrict__ xh, const int x_parts, const long long x_part_stride,
+                                                  const int n_in, const int B, const int bx, const int by, float (&xs)[4]) {
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const float* xp[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    xp[r] = xh + (long long)min(by * 32 + ty + 8 * r, B - 1) * n_in + min(bx * 32 + tx, n_in - 1);
+    xs[r] = xp[r][0];
+  }
+  for (int p0 = 1; p0 < x_parts; p0 += 8) {           // eight slices in flight per element, added in order
+    float t[8][4];
+#pragma unroll
+    for (int pp = 0; pp < 8; ++pp) {
+      const long long off = (long long)min(p0 + pp, x_parts - 1) * x_part_stride;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t[pp][r] = xp[r][off];
+    }
+#pragma unroll
+    for (int pp = 0; pp < 8; ++pp)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) xs[r] += p0 + pp < x_parts ? t[pp][r] : 0.f;
+  }
+}
+
+// Rotated words (what kan_wide.hip multiplies): the values of an input's pairs (m, m + 5) in order of m, each with the
+// bit "coefficient m + 5" in its sign.  Input 4 S + 2 a + h of a step of 16: pairs 0..3 (8 bytes) in half h of the
+// 16-byte item W[step][S][a][sample], pair 4 (2 bytes) in place 2 S + h of the item Z[step][a][sample].
+struct RotTile {
+  uint2 w[32][33];
+  uint16_t z[32][34];
+};
+__device__ __forceinline__ void prep_rot_block(const float* __restrict__ xh, const int x_parts, const long long x_part_stride,
+                                               const int x_tanh, const RotWords& out, const int n_in, const int B, const int rule,
+                                               const int bx, const int by, RotTile& hi, RotTile& lo, uint32_t (*sel)[8]) {
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  float xs[4];
+  load_block_inputs(xh, x_parts, x_part_stride, n_in, B, bx, by, xs);
+  fill_sparse_selectors(sel, threadIdx.x);
+  __syncthreads();
+  const bool split = out.W_lo != nullptr;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int s = ty + 8 * r;
+    const bool live = by * 32 + s < B && bx * 32 + tx < n_in;      // inputs past the last one: zeros
+    float xv = xs[r];
+    if (x_tanh) xv = tanhf(xv);
+    const BasisW bw = basis_fast(xv, rule);
+    const uint4 sl = *(const uint4*)&sel[bw.span][0];
+    const uint32_t s0 = ((sl.w & 1u) << 15) | ((sl.w & 4u) << 29), s1 = ((sl.w & 16u) << 11) | ((sl.w & 64u) << 25);
+    const uint32_t sz = (sl.w & 256u) << 7;
+    auto place = [&](uint32_t w01, uint32_t w23, RotTile& t) {
+      t.w[s][tx] = live ? make_uint2(__builtin_amdgcn_perm(w23, w01, sl.x) | s0, __builtin_amdgcn_perm(w23, w01, sl.y) | s1)
+                        : make_uint2(0u, 0u);
+      t.z[s][tx] = live ? (uint16_t)(__builtin_amdgcn_perm(w23, w01, sl.z) | sz) : (uint16_t)0;
+    };
+    if (split) {
+      uint32_t h01, h23, l01, l23;
+      split_weights(bw.w0, bw.w1, h01, l01);
+      split_weights(bw.w2, bw.w3, h23, l23);
+      place(h01, h23, hi);
+      place(l01, l23, lo);
+    } else {
+      place(pack_h2(bw.w0, bw.w1), pack_h2(bw.w2, bw.w3), hi);
+    }
+  }
+  __syncthreads();
+  const int n_steps = (n_in + 15) / 16;
+  for (int it = threadIdx.x; it < 32 * 20; it += 256) {            // 16-byte items: 2 steps x 2 halves x 5, 32 samples each
+    const int s = it & 31, rest = it >> 5, q = rest % 5, a = (rest / 5) & 1, s2 = rest / 10;
+    const int b = by * 32 + s, step = bx * 2 + s2;
+    if (b >= B || step >= n_steps) continue;
+    auto write = [&](const RotTile& t, uint4* W, uint4* Z) {
+      const int i0 = 16 * s2 + 2 * a;
+      if (q < 4) {
+        const uint2 e0 = t.w[s][i0 + 4 * q], e1 = t.w[s][i0 + 4 * q + 1];
+        W[((long long)(step * 4 + q) * 2 + a) * B + b] = make_uint4(e0.x, e0.y, e1.x, e1.y);
+      } else {
+        uint32_t z[4];
+#pragma unroll
+        for (int S = 0; S < 4; ++S) z[S] = (uint32_t)t.z[s][i0 + 4 * S] | ((uint32_t)t.z[s][i0 + 4 * S + 1] << 16);
+        Z[((long long)step * 2 + a) * B + b] = make_uint4(z[0], z[1], z[2], z[3]);
+      }
+    };
+    write(hi, out.W, out.Z);
+    if (split) write(lo, out.W_lo, out.Z_lo);
   }
 }
 

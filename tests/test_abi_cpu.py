@@ -305,3 +305,13 @@ def test_planner_accepts_every_shape_and_names_a_known_kernel():
             ws = L.kan_vq_workspace_bytes(arr, 1, heads, B, path)
             assert ws != kb.SIZE_INVALID and ws % 256 == 0, (n_in, n_out, B, heads, path, ws)
     assert {b"kan_gather_bt1", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16", b"kan_mfma", b"kan_mfma_split"} <= seen
+
+
+@pytest.mark.parametrize("widths,B", [((65536, 64), 128), ((16384, 256), 96), ((4096, 4096), 128), ((4096, 1024), 100)])
+def test_calls_that_fit_the_static_scratch_without_basis_words_still_fit(widths, B):
+    """Batch 65 to 128 on large layers: the fused kernel's plan needs partial sums only, the kernel that dequantises its own
+    coefficients basis words too; a plan with them must not push such a call past the array."""
+    L = kb.lib()
+    for path in (kb.KAN_PATH_GATHER, kb.KAN_PATH_MFMA):
+        need = _head_ws(L, widths, 1, B, path, gb_dtype=kb.KAN_F16, cb_dtype=kb.KAN_I8)
+        assert 0 < need <= kb.KAN_STATIC_SCRATCH_BYTES, need
