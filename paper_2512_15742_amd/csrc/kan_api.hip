@@ -115,6 +115,8 @@ struct LayerPlan {
   int tile_n = 0;              // matrix-core path: outputs per workgroup tile (128: four waves, 256: eight)
   int kind;          // PlanKind
   bool wide = false; // kPlanMfma whose workgroups dequantise their own coefficients (kan_wide.hip): cfg.bt samples x tile_n outputs
+  bool stream = false;   // kPlanMfma on tiles of 256 x 256 with both operands copied to LDS (kan_stream.hip)
+  bool rot() const { return wide || stream; }      // basis words in the rotated form
   bool mfma;         // kind == kPlanMfma (coefficient + basis preparation, streaming contraction) or kPlanTail (coefficient preparation, one launch)
   int products = 1;  // 3: both operands in high and low fp16 parts, hi*hi + hi*lo + lo*hi (three passes inside the kernel)
   const char* name;
@@ -325,6 +327,46 @@ bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool s
   return true;
 }
 
+// Large contractions on tiles of 256 x 256 with both operands copied to LDS by the memory pipeline (kan_stream.hip), in
+// place of the tiles of kan_mfma.hip.  The line is the work, in tiles times steps of 16 inputs: a workgroup is alone on its
+// CU and its partial sums are 256 KB.  Layer times in us, kan_mfma.hip / this:
+//                        batch 1024      1536         2048         3072         4096         8192
+//   1024 x 512  fp16                                 41 / 46      49 / 56      58 / 66      98 / 105   (256 .. 4,096 tile-steps)
+//   2048 x 1024 fp16     66 / 78      84 / 86      98 / 101     135 / 128    162 / 158    279 / 274   (2,048 .. 16,384)
+//   4096 x 1024 fp16                 155 / 150    182 / 172     254 / 231    317 / 290    572 / 519   (6,144 at 1536)
+//   512 x 4096  fp16                  79 / 79      80 / 85      123 / 104    139 / 123    256 / 220   (6,144 at 3072)
+//   4096 x 4096 fp16                 597 / 469    600 / 518     992 / 765   1076 / 864   1965 / 1589
+//   2048 x 1024 split   136 / 160    176 / 176    211 / 205     319 / 283                             (6,144 at 3072)
+//   4096 x 4096 split   886 / 766   1511 / 1123  1494 / 1287   2639 / 1973
+constexpr long long kStreamMinTileSteps = 6144;
+constexpr int kStreamMinOut = 513;                  // (two tiles across: 1024 x 512 is slower up to batch 8192)
+
+bool make_stream(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool split3) {
+  if (n_out < kStreamMinOut || !stream_takes(n_out, B)) return false;
+  const int n_jt = (n_out + kStreamTile - 1) / kStreamTile, n_bt = (int)((B + kStreamTile - 1) / kStreamTile);
+  if ((long long)n_jt * kStreamTile * 8 > 9ll * n_out) return false;            // (tiles an eighth empty)
+  if ((long long)n_jt * n_bt * n_heads * ((n_in + 15) / 16) < kStreamMinTileSteps) return false;
+  const long long base = (long long)n_heads * n_jt * n_bt, steps = (n_in + 15) / 16;
+  long long best = 1;
+  double best_cost = 0.0;
+  for (long long c = 1; c <= kMaxChainedSlices && (c == 1 || c * 4 <= steps); ++c) {
+    const double rounds = (double)((base * c + 255) / 256);
+    const double cost = rounds * ((double)((steps + c - 1) / c) + 5.0) + (c > 1 ? 1e-6 * (double)(c * n_heads * B * n_out) : 0.0);
+    if (c == 1 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+  }
+  p.stream = true;
+  p.cfg.bt = kStreamTile;
+  p.tile_n = kStreamTile;
+  p.n_jt = n_jt;
+  p.n_bt = n_bt;
+  p.rows_per_chunk = (int)(((steps + best - 1) / best * 16 + kMfmaPrepRows - 1) / kMfmaPrepRows * kMfmaPrepRows);
+  p.n_chunks = (n_in + p.rows_per_chunk - 1) / p.rows_per_chunk;
+  return true;
+}
+
 // Small layers take one launch (kan_tail.hip) in place of basis words, contraction and reduction.  A workgroup
 // evaluates the basis of all inputs for its 32 samples and reads the records of its outputs, so the line is where
 // that takes longer than the launches it saves: kTailMaxIn inputs (416-32 at batch 1166 17.9 -> 14.6 us, 475-52-13 at
@@ -346,7 +388,7 @@ LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
   const long long n_jt = (n_out + tile_n - 1) / tile_n;
   if (n_in > kTailMaxIn || (long long)n_in * n_out > kTailMaxEdges || n_jt * n_bt * n_heads > kTailMaxWorkgroups ||
       (x_parts > 1 && (long long)x_parts * n_in > (n_jt > 2 ? kTailSlicedInputsManyTiles : kTailSlicedInputs))) {
-    if (wide) make_wide(p, n_in, n_out, B, n_heads, split3);
+    if (wide && !make_wide(p, n_in, n_out, B, n_heads, split3)) make_stream(p, n_in, n_out, B, n_heads, split3);
     return p;
   }
   p.kind = kPlanTail;
@@ -627,6 +669,7 @@ kan_status run_prep_coef(const LayerPlan& p, const GatherArgs& a, int heads, con
   pc.bp_head_stride = (long long)mfma_bp_floats(a.n_in, a.n_out);
   pc.n_in = a.n_in;
   pc.n_out = a.n_out;
+  pc.rot = p.stream;
   memcpy(pc.h, a.h, sizeof(pc.h));
   if (!launch) return KAN_OK;
   if (p.cfg.code == kDense)
@@ -641,37 +684,34 @@ struct BasisBufs {
   long long u_stride;
 };
 
-// The same for a layer whose workgroups dequantise their own coefficients: pairs 0..3 lie where the other form keeps
-// its words, pair 4 (a quarter of their size) in the layer's region of the records.
+// The same in the rotated form (kan_wide.hip, kan_stream.hip).
 RotWords rot_words(const LayerPlan& p, const GatherArgs& a, int heads, bool x_shared, const WsPtrs& w) {
-  const long long steps = (a.n_in + 15) / 16, n = x_shared ? 1 : heads;
+  const long long items = (long long)((a.n_in + 15) / 16) * 10 * (p.stream ? rot_rows(a.B) : a.B);
   RotWords r;
   r.W = (uint4*)w.u;
-  r.Z = w.cf;
-  r.W_lo = p.products == 3 ? r.W + n * steps * 8 * a.B : nullptr;
-  r.Z_lo = p.products == 3 ? r.Z + n * steps * 2 * a.B : nullptr;
-  r.w_head_stride = x_shared ? 0 : steps * 8 * a.B;
-  r.z_head_stride = x_shared ? 0 : steps * 2 * a.B;
+  r.W_lo = p.products == 3 ? r.W + (x_shared ? 1 : heads) * items : nullptr;
+  r.w_head_stride = x_shared ? 0 : items;
+  r.P = p.stream ? (uint16_t*)((uint4*)w.u + (p.products == 3 ? 2 : 1) * (x_shared ? 1 : heads) * items) : nullptr;
+  r.p_head_stride = x_shared ? 0 : (long long)((a.n_in + 15) / 16) * 10 * rot_rows(a.B);
   return r;
+}
+kan_status run_prep_rot(const RotWords& r, const GatherArgs& a, int heads, bool x_shared, const Chain& chain, hipStream_t s) {
+  if (chain.basis_done) return KAN_OK;
+  return run("kan_prep_basis", s, [&] {
+    return launch_prep_rot(a.x, a.x_head_stride, chain.in_parts, chain.in_part_stride, chain.in_tanh, r, a.n_in, a.B,
+                           x_shared ? 1 : heads, a.rule, s);
+  });
 }
 kan_status run_wide(const LayerPlan& p, const GatherArgs& a, int heads, bool x_shared, float* dst, long long dst_head_stride,
                     long long dst_chunk_stride, int apply_tanh, const WsPtrs& w, const Chain& chain, hipStream_t s) {
   const RotWords r = rot_words(p, a, heads, x_shared, w);
-  if (!chain.basis_done) {
-    const kan_status st = run("kan_prep_basis", s, [&] {
-      return launch_prep_rot(a.x, a.x_head_stride, chain.in_parts, chain.in_part_stride, chain.in_tanh, r, a.n_in, a.B,
-                             x_shared ? 1 : heads, a.rule, s);
-    });
-    if (st != KAN_OK) return st;
-  }
+  const kan_status st = run_prep_rot(r, a, heads, x_shared, chain, s);
+  if (st != KAN_OK) return st;
   WideArgs m;
   memset(&m, 0, sizeof(m));
   m.W = r.W;
-  m.Z = r.Z;
   m.W_lo = r.W_lo;
-  m.Z_lo = r.Z_lo;
   m.w_head_stride = r.w_head_stride;
-  m.z_head_stride = r.z_head_stride;
   m.dst = dst;
   m.dst_head_stride = dst_head_stride;
   m.dst_chunk_stride = dst_chunk_stride;
@@ -707,6 +747,11 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
   const long long dst_head_stride = split ? count * p.n_chunks : final_head_stride;
   const long long dst_chunk_stride = split ? count : 0;
   const int tanh_in_kernel = split ? 0 : apply_tanh;
+  auto reduce = [&] {
+    return run("kan_reduce", s, [&] {
+      return launch_reduce(partial, dst_head_stride, count, p.n_chunks, final_dst, final_head_stride, count, heads, apply_tanh, s);
+    });
+  };
   kan_status st;
   if (p.wide) {
     st = run_wide(p, a, heads, x_shared, dst, dst_head_stride, dst_chunk_stride, tanh_in_kernel, w, chain, s);
@@ -739,6 +784,36 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
       t.rule = a.rule;
       for (int h = 0; h < heads; ++h) t.scale[h] = p.cfg.code == kCbI8 ? a.h[h].scale : 1.0f;
       return run(p.name, s, [&] { return launch_tail(t, split3, p.tile_n, dim3((unsigned)(p.n_jt * p.n_bt), 1, (unsigned)heads), s); });
+    }
+    if (p.stream) {
+      const RotWords r = rot_words(p, a, heads, x_shared, w);
+      st = run_prep_rot(r, a, heads, x_shared, chain, s);
+      if (st != KAN_OK) return st;
+      StreamArgs m;
+      memset(&m, 0, sizeof(m));
+      m.cf = pc.cf;
+      m.cf_lo = pc.cf_lo;
+      m.cf_head_stride = pc.cf_head_stride;
+      m.W = r.W;
+      m.W_lo = r.W_lo;
+      m.w_head_stride = r.w_head_stride;
+      m.P = r.P;
+      m.p_head_stride = r.p_head_stride;
+      m.bias_partial = pc.bias_partial;
+      m.bp_head_stride = pc.bp_head_stride;
+      m.dst = dst;
+      m.dst_head_stride = dst_head_stride;
+      m.dst_chunk_stride = dst_chunk_stride;
+      m.n_in = a.n_in;
+      m.n_out = a.n_out;
+      m.B = a.B;
+      m.rows_per_chunk = p.rows_per_chunk;
+      m.n_jt = p.n_jt;
+      m.apply_tanh = tanh_in_kernel;
+      for (int h = 0; h < heads; ++h) m.scale[h] = p.cfg.code == kCbI8 ? a.h[h].scale : 1.0f;
+      dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
+      st = run(p.name, s, [&] { return launch_stream(m, split3, grid, s); });
+      return st != KAN_OK || !split || chain.out ? st : reduce();
     }
     BasisBufs bb;
     st = run_prep_basis(p, a, heads, x_shared, w, chain, &bb, !chain.basis_done, s);
@@ -863,11 +938,7 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
     st = run(p.name, s, [&] { return launch_gather(p.cfg, a, grid, s); });
   }
-  if (st != KAN_OK || !split || chain.out) return st;
-  return run("kan_reduce", s, [&] {
-    return launch_reduce(partial, dst_head_stride, count, p.n_chunks, final_dst, final_head_stride, count,
-                         heads, apply_tanh, s);
-  });
+  return st != KAN_OK || !split || chain.out ? st : reduce();
 }
 
 kan_status check_path(int32_t path) {
@@ -948,14 +1019,15 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
     grow(l & 1 ? ws->partial2 : ws->partial, partial_bytes(p, R.out, B, group));
     ws->cf_off.push_back(ws->cf);
     ws->bp_off.push_back(ws->bp);
-    if (p.wide) {      // (pair 4 of its basis words; pairs 0..3 take the room of the other form's words)
-      ws->cf += round_up((size_t)(p.products == 3 ? 2 : 1) * (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16) * 2 * (size_t)B * sizeof(uint4), 256);
-    } else if (p.mfma) {
+    if (p.mfma && !p.wide) {
       ws->cf += round_up((size_t)(p.products == 3 ? 2 : 1) * group * mfma_cf_records(R.in, R.out) * sizeof(uint4), 256);
       ws->bp += round_up((size_t)group * mfma_bp_floats(R.in, R.out) * sizeof(float), 256);
     }
-    if (p.kind == kPlanMfma)
-      grow(ws->u, round_up((size_t)(p.products == 3 ? 2 : 1) * (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16 * 16) * (size_t)B * sizeof(uint2), 256));
+    if (p.kind == kPlanMfma) {
+      const size_t rows = (size_t)(l == 0 ? 1 : group) * (size_t)((R.in + 15) / 16), parts = p.products == 3 ? 2 : 1;
+      if (p.stream) grow(ws->u, round_up(rows * 10 * (size_t)rot_rows(B) * (parts * sizeof(uint4) + sizeof(uint16_t)), 256));
+      else grow(ws->u, round_up(parts * rows * (p.wide ? 10 * sizeof(uint4) : 16 * sizeof(uint2)) * (size_t)B, 256));
+    }
     if (l + 1 < n_layers) grow(ws->hidden, round_up((size_t)n_heads * (size_t)B * R.out * sizeof(float), 256));
   }
   for (int l = 0; l < n_layers; ++l) ws->handed.push_back(hand_on && chained(*plans, l, n_heads, layers, B));
@@ -1130,7 +1202,7 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     const LayerPlan& p0 = plans[0];
     for (int l = 0; l < n_layers && ps.n_jobs < kStartJobs; ++l) {
       const LayerPlan& p = plans[l];
-      if (!p.mfma || p.wide || p.products != p0.products || p.cfg.code != p0.cfg.code || p.cfg.gb_kind != p0.cfg.gb_kind ||
+      if (!p.mfma || p.wide || p.stream != p0.stream || p.products != p0.products || p.cfg.code != p0.cfg.code || p.cfg.gb_kind != p0.cfg.gb_kind ||
           p.cfg.idx_u32 != p0.cfg.idx_u32)
         continue;
       GatherArgs a;
@@ -1153,8 +1225,9 @@ kan_status head_forward(const kan_vq_layer* layers, int32_t n_layers, int32_t n_
     layer_args(0, 0, 1, x, 0, &a0, nullptr);
     BasisBufs bb;
     (void)run_prep_basis(p0, a0, 1, true, w, Chain(), &bb, false, s);
-    ps.rot = p0.wide;
-    if (p0.wide) ps.rw = rot_words(p0, a0, 1, true, w);
+    ps.rot = p0.rot();
+    ps.rot_coef = p0.stream;
+    if (p0.rot()) ps.rw = rot_words(p0, a0, 1, true, w);
     ps.x = x;
     ps.W = w.u;
     ps.W_lo = bb.u_lo;

@@ -84,15 +84,23 @@ struct PrepCoefArgs {
   float* bias_partial;         // [head][ceil(n_in / 32)][n_out]
   long long bp_head_stride;    // in floats
   int n_in, n_out;
+  int rot;                     // records as kan_stream.hip takes them (prep_coef_block)
   LayerPtrs h[kMaxGroup];
 };
 
-// Basis operand of kan_wide.hip: W[step][4][2][B] and Z[step][2][B] items of 16 bytes, step = input / 16; split form: the
-// low parts beside them (else null).  Head strides in items, 0 when all heads share the input.
+// Basis operand of kan_wide.hip and kan_stream.hip: 16-byte items W[step][5][2][row], step = input / 16; split form: the
+// low parts beside them (else null).  kan_wide.hip: row = sample.  kan_stream.hip: also the position bits of every item,
+// P[step][5][2][sample] (else null), rot_rows(B) rows of which sample b's items have rot_row(b): the four samples 4 l .. 4 l
+// + 3 of a run of 128 are those that lane l multiplies, so that their position bits are one 8-byte read.  Head strides in
+// items and halfwords, 0 when all heads share the input.
 struct RotWords {
-  uint4 *W, *Z, *W_lo, *Z_lo;
-  long long w_head_stride, z_head_stride;
+  uint4 *W, *W_lo;
+  long long w_head_stride;
+  uint16_t* P;
+  long long p_head_stride;
 };
+constexpr long long rot_rows(long long B) { return (B + 255) / 256 * 256; }
+constexpr long long rot_row(long long b) { return (b & ~127ll) + (b & 3) * 32 + ((b & 127) >> 2); }
 
 // One launch for all a single head's call can prepare before its first contraction: the
 // coefficient records of up to kStartJobs matrix-core layers of the same storage types, and
@@ -113,7 +121,8 @@ struct PrepStartArgs {
   const float* x;                    // [B][n_in] of the first layer; n_in = 0: no basis words
   uint2* W;
   uint2* W_lo;                       // split form only
-  int rot;                           // write rotated words (kan_wide.hip) instead of W, W_lo
+  int rot;                           // write rotated words instead of W, W_lo
+  int rot_coef;                      // the jobs' records as PrepCoefArgs::rot (only with rot)
   RotWords rw;
   int n_in, B, rule;
   int basis_nx;                      // filled by the launcher
@@ -162,12 +171,34 @@ hipError_t launch_prep_basis(const float* x, long long x_head_stride, int x_part
                              int rule, hipStream_t);
 hipError_t launch_mfma(const MfmaArgs&, int tile_m, int tile_n, dim3 grid, hipStream_t);   // samples (64 | 128) x outputs (128; 256 with 128 samples) per tile
 
+// ---- streaming contraction of large batches (kan_stream.hip): tiles of 256 samples x 256 outputs --------------
+constexpr int kStreamTile = 256;
+struct StreamArgs {
+  const uint4 *cf, *cf_lo;     // records of kan_prep_coef with `rot`, cf_lo: split form
+  long long cf_head_stride;
+  const uint4 *W, *W_lo;       // RotWords
+  long long w_head_stride;
+  const uint16_t* P;
+  long long p_head_stride;
+  const float* bias_partial;
+  long long bp_head_stride;
+  float* dst;
+  long long dst_head_stride, dst_chunk_stride;
+  int n_in, n_out, B;
+  int rows_per_chunk;          // multiple of kMfmaPrepRows
+  int n_jt;
+  int apply_tanh;
+  float scale[kMaxGroup];
+};
+bool stream_takes(int n_out, int64_t B);
+hipError_t launch_stream(const StreamArgs&, bool split, dim3 grid, hipStream_t);
+
 // ---- contraction that dequantises its own coefficients (kan_wide.hip) -----------------------------------------
 constexpr int kWideTileN = 64;        // outputs per workgroup
-constexpr int kWideMaxOut = 1 << 19;  // (a tile of 512 rows of the result is addressed by 32-bit offsets)
+constexpr int kWideMaxOut = 1 << 19;  // (a tile of 512 rows of the result is addressed by 32-bit offsets; kan_stream.hip: of 256)
 struct WideArgs {
-  const uint4 *W, *Z, *W_lo, *Z_lo;
-  long long w_head_stride, z_head_stride;
+  const uint4 *W, *W_lo;       // RotWords
+  long long w_head_stride;
   float* dst;
   long long dst_head_stride, dst_chunk_stride;
   int n_in, n_out, B;

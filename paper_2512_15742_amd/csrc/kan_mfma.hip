@@ -76,6 +76,8 @@ constexpr int kBufferFlags = 0x00020000;   // buffer resource word 3: raw 32-bit
 // A workgroup covers 64 output columns x 32 input rows: each of its 4 waves takes 8 rows
 // (half a step; lanes along the columns), so all loads of an edge's chain (metadata, then
 // codeword) are in flight at once across many small waves.
+// ROT: the form that kan_stream.hip takes: coefficients 5..9 negated, input 4 S + 2 a + h of a step in record (S, h, a), its
+// pair (4, 9) in word 2 (S % 2) + h of record (4, S / 2, a): the order of the rotated basis words.
 // SPLIT: fp32-grade operands for the precise path at large batch: every coefficient c (fp32) is
 // written as hi = fp16(c) into cf and as lo = fp16((c - hi) * 2048) into cf_lo (hi + lo / 2048
 // carries 22 bits of c; the factor keeps the low parts out of the fp16 subnormals).
@@ -103,7 +105,7 @@ __device__ __forceinline__ void prep_wide_store(unsigned char* strip, int lane, 
   for (int u = 0; u < (E + 1) / 2; ++u) *(u32x4*)(strip + ((lane + 64 * u) & (32 * E - 1)) * 16) = v[u];
 }
 
-template <typename IdxT, typename GbT, typename CbT, bool SPLIT>
+template <typename IdxT, typename GbT, typename CbT, bool SPLIT, bool ROT>
 __device__ __forceinline__ void prep_coef_block(const LayerPtrs& hp, uint4* __restrict__ cf, uint4* __restrict__ cf_lo,
                                                 float* __restrict__ bp, const int n_in, const int n_out, const int bx,
                                                 const int by, float (*sb)[64], unsigned char (*strips)[kPrepStripBytes]) {
@@ -179,36 +181,67 @@ __device__ __forceinline__ void prep_coef_block(const LayerPtrs& hp, uint4* __re
     for (int r = 0; r < 8; ++r) load_row<CbT>(cb, id[r], raw[r]);
 #pragma unroll
     for (int r = 0; r < 8; ++r) align_row<CbT>(raw[r], row_odd<CbT>(cb, id[r]));
+    if constexpr (ROT) {
+      uint32_t tail[2][4], tail_lo[2][4];                   // [a][2 (S % 2) + h]
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const long long S = 2 * wh + q;
-      uint32_t tail[4], tail_lo[4];
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {                       // ii = 8 wh + 4 q + t: h = t / 2, a = t % 2
-        const long long rec = (((step * 5 + S) * 2 + (t >> 1)) * 2 + (t & 1)) * n_out + j;
-        if constexpr (SPLIT) {
-          float c[kG];
-          dequant_row_f32<CbT>(raw[4 * q + t], g[4 * q + t], c);
+        for (int t = 0; t < 4; ++t) {                       // input 4 S + t: a = t / 2, h = t % 2
+          const int ha = t >> 1, h = t & 1;
+          const long long rec = (((step * 5 + 2 * wh + q) * 2 + h) * 2 + ha) * n_out + j;
           uint32_t hi[5], lo[5];
-          split_pairs(c, hi, lo);
+          if constexpr (SPLIT) {
+            float c[kG];
+            dequant_row_f32<CbT>(raw[4 * q + t], g[4 * q + t], c);
+#pragma unroll
+            for (int m = 5; m < kG; ++m) c[m] = -c[m];
+            split_pairs(c, hi, lo);
+            cf_lo[rec] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            tail_lo[ha][2 * q + h] = lo[4];
+          } else {
+            dequant_row_pairs<CbT>(raw[4 * q + t], g[4 * q + t], hi);
+          }
           cf[rec] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-          cf_lo[rec] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-          tail[t] = hi[4];
-          tail_lo[t] = lo[4];
-        } else {
-          uint32_t w[5];
-          dequant_row<CbT>(raw[4 * q + t], g[4 * q + t], w);   // (c0,c1) (c2,c3) (c4,c5) (c6,c7) (c8,c9)
-          const uint32_t p0 = __builtin_amdgcn_perm(w[2], w[0], 0x07060100u);   // (c0, c5)
-          const uint32_t p1 = __builtin_amdgcn_perm(w[3], w[0], 0x05040302u);   // (c1, c6)
-          const uint32_t p2 = __builtin_amdgcn_perm(w[3], w[1], 0x07060100u);   // (c2, c7)
-          const uint32_t p3 = __builtin_amdgcn_perm(w[4], w[1], 0x05040302u);   // (c3, c8)
-          tail[t] = __builtin_amdgcn_perm(w[4], w[2], 0x07060100u);             // (c4, c9)
-          cf[rec] = make_uint4(p0, p1, p2, p3);
+          tail[ha][2 * q + h] = hi[4];
         }
+#pragma unroll
+      for (int ha = 0; ha < 2; ++ha) {
+        const long long rec = (((step * 5 + 4) * 2 + wh) * 2 + ha) * n_out + j;
+        cf[rec] = make_uint4(tail[ha][0], tail[ha][1], tail[ha][2], tail[ha][3]);
+        if constexpr (SPLIT) cf_lo[rec] = make_uint4(tail_lo[ha][0], tail_lo[ha][1], tail_lo[ha][2], tail_lo[ha][3]);
       }
-      const long long trec = (((step * 5 + 4) * 2 + wh) * 2 + q) * n_out + j;
-      cf[trec] = make_uint4(tail[0], tail[1], tail[2], tail[3]);
-      if constexpr (SPLIT) cf_lo[trec] = make_uint4(tail_lo[0], tail_lo[1], tail_lo[2], tail_lo[3]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const long long S = 2 * wh + q;
+        uint32_t tail[4], tail_lo[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {                       // ii = 8 wh + 4 q + t: h = t / 2, a = t % 2
+          const long long rec = (((step * 5 + S) * 2 + (t >> 1)) * 2 + (t & 1)) * n_out + j;
+          if constexpr (SPLIT) {
+            float c[kG];
+            dequant_row_f32<CbT>(raw[4 * q + t], g[4 * q + t], c);
+            uint32_t hi[5], lo[5];
+            split_pairs(c, hi, lo);
+            cf[rec] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            cf_lo[rec] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            tail[t] = hi[4];
+            tail_lo[t] = lo[4];
+          } else {
+            uint32_t w[5];
+            dequant_row<CbT>(raw[4 * q + t], g[4 * q + t], w);   // (c0,c1) (c2,c3) (c4,c5) (c6,c7) (c8,c9)
+            const uint32_t p0 = __builtin_amdgcn_perm(w[2], w[0], 0x07060100u);   // (c0, c5)
+            const uint32_t p1 = __builtin_amdgcn_perm(w[3], w[0], 0x05040302u);   // (c1, c6)
+            const uint32_t p2 = __builtin_amdgcn_perm(w[3], w[1], 0x07060100u);   // (c2, c7)
+            const uint32_t p3 = __builtin_amdgcn_perm(w[4], w[1], 0x05040302u);   // (c3, c8)
+            tail[t] = __builtin_amdgcn_perm(w[4], w[2], 0x07060100u);             // (c4, c9)
+            cf[rec] = make_uint4(p0, p1, p2, p3);
+          }
+        }
+        const long long trec = (((step * 5 + 4) * 2 + wh) * 2 + q) * n_out + j;
+        cf[trec] = make_uint4(tail[0], tail[1], tail[2], tail[3]);
+        if constexpr (SPLIT) cf_lo[trec] = make_uint4(tail_lo[0], tail_lo[1], tail_lo[2], tail_lo[3]);
+      }
     }
   }
   sb[wave][lane] = bs;
@@ -217,12 +250,12 @@ __device__ __forceinline__ void prep_coef_block(const LayerPtrs& hp, uint4* __re
     bp[(long long)by * n_out + j] = (sb[0][lane] + sb[1][lane]) + (sb[2][lane] + sb[3][lane]);
 }
 
-template <typename IdxT, typename GbT, typename CbT, bool SPLIT>
+template <typename IdxT, typename GbT, typename CbT, bool SPLIT, bool ROT>
 __global__ __launch_bounds__(kThreads) void kan_prep_coef_kernel(const PrepCoefArgs a) {
   __shared__ float sb[4][64];
   __shared__ __attribute__((aligned(16))) unsigned char strips[4][kPrepStripBytes];
   const int head = blockIdx.z;
-  prep_coef_block<IdxT, GbT, CbT, SPLIT>(a.h[head], a.cf + (long long)head * a.cf_head_stride,
+  prep_coef_block<IdxT, GbT, CbT, SPLIT, ROT>(a.h[head], a.cf + (long long)head * a.cf_head_stride,
                                          SPLIT ? a.cf_lo + (long long)head * a.cf_head_stride : nullptr,
                                          a.bias_partial + (long long)head * a.bp_head_stride, a.n_in, a.n_out,
                                          blockIdx.x, blockIdx.y, sb, strips);
@@ -338,32 +371,32 @@ __global__ __launch_bounds__(256) void kan_prep_basis_kernel(const float* __rest
 // the basis words of the first layer's input.  The small grids of the later layers and the
 // basis pass fill the tail of the first layer's coefficient pass instead of running as
 // launches of their own behind it.  Blocks are numbered job after job, the largest first.
-template <typename IdxT, typename GbT, typename CbT, bool SPLIT>
+// ROT_COEF, ROT_BASIS: the forms that kan_stream.hip (both) and kan_wide.hip (basis words) take.  They are kernels of their
+// own: with both forms of the records in one, small layers paid 1.8 us for the longer code (1000 x 333 at batch 500 12.4 ->
+// 14.2 us).  The strips and the basis tiles of the plain form have room of their own, which keeps it at four workgroups per
+// CU: with eight, whose reads and writes then do not overlap, config 3 at batch 1024 takes 31.6 us, with four or five
+// 29.7-30.1, with two 32.9.
+template <typename IdxT, typename GbT, typename CbT, bool SPLIT, bool ROT_COEF, bool ROT_BASIS>
 __global__ __launch_bounds__(kThreads) void kan_prep_start_kernel(const PrepStartArgs a) {
   __shared__ float sb[4][64];
   __shared__ __attribute__((aligned(16))) unsigned char strips[4][kPrepStripBytes];
-  union BasisTiles {
-    struct {
-      uint2 tile[32][33], tile_lo[SPLIT ? 32 : 1][33];
-    } words;
-    RotTile rot[SPLIT ? 2 : 1];
-  };
-  __shared__ BasisTiles bt;
-  __shared__ __attribute__((aligned(16))) uint32_t sel[kSpans][8];
   const int blk = blockIdx.x;
   int k = 0;
   while (k < a.n_jobs && blk >= a.first_block[k + 1]) ++k;
   const int rel = blk - a.first_block[k];
   if (k < a.n_jobs) {
     const PrepStartArgs::Job& job = a.job[k];
-    prep_coef_block<IdxT, GbT, CbT, SPLIT>(job.h, job.cf, SPLIT ? job.cf_lo : nullptr, job.bp, job.n_in, job.n_out,
-                                           rel % job.nx, rel / job.nx, sb, strips);
-  } else if (a.rot) {
-    prep_rot_block(a.x, 1, 0, 0, a.rw, a.n_in, a.B, a.rule, rel % a.basis_nx, rel / a.basis_nx, bt.rot[0],
-                   bt.rot[SPLIT ? 1 : 0], sel);
+    prep_coef_block<IdxT, GbT, CbT, SPLIT, ROT_COEF>(job.h, job.cf, SPLIT ? job.cf_lo : nullptr, job.bp, job.n_in, job.n_out,
+                                                     rel % job.nx, rel / job.nx, sb, strips);
+  } else if constexpr (ROT_BASIS) {
+    __shared__ RotTile tile[SPLIT ? 2 : 1];
+    __shared__ __attribute__((aligned(16))) uint32_t sel[kSpans][8];
+    prep_rot_block(a.x, 1, 0, 0, a.rw, a.n_in, a.B, a.rule, rel % a.basis_nx, rel / a.basis_nx, tile[0], tile[SPLIT ? 1 : 0], sel);
   } else {
+    __shared__ uint2 tile[32][33];
+    __shared__ uint2 tile_lo[SPLIT ? 32 : 1][33];
     prep_basis_block(a.x, 1, 0, 0, a.W, SPLIT ? a.W_lo : nullptr, a.n_in, a.B, a.rule, rel % a.basis_nx,
-                     rel / a.basis_nx, bt.words.tile, SPLIT ? bt.words.tile_lo : bt.words.tile);
+                     rel / a.basis_nx, tile, SPLIT ? tile_lo : tile);
   }
 }
 
@@ -845,16 +878,21 @@ hipError_t prep_types(const GatherCfg& c, F&& launch) {
 template <typename IdxT, bool SPLIT>
 hipError_t prep_coef_types(const GatherCfg& c, const PrepCoefArgs& a, dim3 grid, hipStream_t s) {
   return prep_types(c, [&](auto gb, auto cb) {
-    hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, typename decltype(gb)::type, typename decltype(cb)::type, SPLIT>), grid,
-                       dim3(kThreads), 0, s, a);
+    typedef typename decltype(gb)::type GbT;
+    typedef typename decltype(cb)::type CbT;
+    if (a.rot) hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, GbT, CbT, SPLIT, true>), grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, GbT, CbT, SPLIT, false>), grid, dim3(kThreads), 0, s, a);
   });
 }
 
 template <typename IdxT, bool SPLIT>
 hipError_t prep_start_types(const GatherCfg& c, const PrepStartArgs& a, dim3 grid, hipStream_t s) {
   return prep_types(c, [&](auto gb, auto cb) {
-    hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, typename decltype(gb)::type, typename decltype(cb)::type, SPLIT>), grid,
-                       dim3(kThreads), 0, s, a);
+    typedef typename decltype(gb)::type GbT;
+    typedef typename decltype(cb)::type CbT;
+    if (a.rot_coef) hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, true, true>), grid, dim3(kThreads), 0, s, a);
+    else if (a.rot) hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, true>), grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, false>), grid, dim3(kThreads), 0, s, a);
   });
 }
 
@@ -868,9 +906,9 @@ hipError_t launch_prep_coef(const GatherCfg& c, const PrepCoefArgs& a, int heads
 }
 
 hipError_t launch_prep_start(const GatherCfg& c, PrepStartArgs& a, bool split, hipStream_t s) {
-  if (c.code == kDense || a.n_jobs < 0 || a.n_jobs > kStartJobs) return hipErrorInvalidValue;
+  if (c.code == kDense || a.n_jobs < 0 || a.n_jobs > kStartJobs || (a.rot_coef && !a.rot)) return hipErrorInvalidValue;
   if (a.n_in > 0 && !a.rot && (!a.x || !a.W || (split && !a.W_lo))) return hipErrorInvalidValue;
-  if (a.n_in > 0 && a.rot && (!a.x || !a.rw.W || !a.rw.Z || (split && (!a.rw.W_lo || !a.rw.Z_lo)))) return hipErrorInvalidValue;
+  if (a.n_in > 0 && a.rot && (!a.x || !a.rw.W || (split && !a.rw.W_lo))) return hipErrorInvalidValue;
   long long blocks = 0;
   for (int k = 0; k < a.n_jobs; ++k) {
     PrepStartArgs::Job& job = a.job[k];

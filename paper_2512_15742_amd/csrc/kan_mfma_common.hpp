@@ -180,6 +180,17 @@ __device__ __forceinline__ void dequant_row(const RawRow<CbT>& r, float g, uint3
   }
 }
 
+// Position bits of the four value pairs of an A fragment of rotated words: pair t holds its values' bits in bits 15 and 31
+// of word t, the sparse instruction takes them from bits 4 t and 4 t + 2 (bit 4 t + 3 set: the second value is one of
+// elements 2, 3 of its group).
+__device__ __forceinline__ int rot_positions(const u32x4 v) {
+  uint32_t u = v.w & 0x80008000u;
+  u |= (v.z >> 4) & 0x08000800u;
+  u |= (v.y >> 8) & 0x00800080u;
+  u |= (v.x >> 12) & 0x00080008u;
+  return (int)((u >> 3) | (u >> 17) | 0x8888u);
+}
+
 // w[m] = fp16 pair (g*coef m, -g*coef m + 5), m = 0..4: the pairs of the sparse operand whose stored values carry
 // "takes the second of the pair" in their sign (kan_wide.hip).
 template <typename CbT>
@@ -325,9 +336,9 @@ __device__ __forceinline__ void load_block_inputs(const float* __restrict__ xh, 
   }
 }
 
-// Rotated words (what kan_wide.hip multiplies): the values of an input's pairs (m, m + 5) in order of m, each with the
-// bit "coefficient m + 5" in its sign.  Input 4 S + 2 a + h of a step of 16: pairs 0..3 (8 bytes) in half h of the
-// 16-byte item W[step][S][a][sample], pair 4 (2 bytes) in place 2 S + h of the item Z[step][a][sample].
+// Rotated words (what kan_wide.hip and kan_stream.hip multiply): the values of an input's pairs (m, m + 5) in order of m,
+// each with the bit "coefficient m + 5" in its sign.  Input 4 S + 2 a + h of a step of 16: pairs 0..3 (8 bytes) in half h
+// of the 16-byte item W[step][S][a][sample], pair 4 (2 bytes) in place 2 S + h of the item W[step][4][a][sample].
 struct RotTile {
   uint2 w[32][33];
   uint16_t z[32][34];
@@ -368,24 +379,28 @@ __device__ __forceinline__ void prep_rot_block(const float* __restrict__ xh, con
   }
   __syncthreads();
   const int n_steps = (n_in + 15) / 16;
+  const long long rows = out.P ? rot_rows(B) : B;
   for (int it = threadIdx.x; it < 32 * 20; it += 256) {            // 16-byte items: 2 steps x 2 halves x 5, 32 samples each
     const int s = it & 31, rest = it >> 5, q = rest % 5, a = (rest / 5) & 1, s2 = rest / 10;
     const int b = by * 32 + s, step = bx * 2 + s2;
     if (b >= B || step >= n_steps) continue;
-    auto write = [&](const RotTile& t, uint4* W, uint4* Z) {
+    const long long row = out.P ? rot_row(b) : b, item = ((long long)step * 5 + q) * 2 + a;
+    auto write = [&](const RotTile& t, uint4* W) {
       const int i0 = 16 * s2 + 2 * a;
+      u32x4 v;
       if (q < 4) {
         const uint2 e0 = t.w[s][i0 + 4 * q], e1 = t.w[s][i0 + 4 * q + 1];
-        W[((long long)(step * 4 + q) * 2 + a) * B + b] = make_uint4(e0.x, e0.y, e1.x, e1.y);
+        v = u32x4{e0.x, e0.y, e1.x, e1.y};
       } else {
-        uint32_t z[4];
 #pragma unroll
-        for (int S = 0; S < 4; ++S) z[S] = (uint32_t)t.z[s][i0 + 4 * S] | ((uint32_t)t.z[s][i0 + 4 * S + 1] << 16);
-        Z[((long long)step * 2 + a) * B + b] = make_uint4(z[0], z[1], z[2], z[3]);
+        for (int S = 0; S < 4; ++S) v[S] = (uint32_t)t.z[s][i0 + 4 * S] | ((uint32_t)t.z[s][i0 + 4 * S + 1] << 16);
       }
+      *(u32x4*)(W + item * rows + row) = v;
+      return v;
     };
-    write(hi, out.W, out.Z);
-    if (split) write(lo, out.W_lo, out.Z_lo);
+    const u32x4 v = write(hi, out.W);
+    if (out.P) out.P[item * rows + b] = (uint16_t)rot_positions(v);
+    if (split) write(lo, out.W_lo);
   }
 }
 

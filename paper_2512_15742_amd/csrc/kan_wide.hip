@@ -94,35 +94,22 @@ __global__ __launch_bounds__(kThreads, 2) void kan_wide_kernel(const WideArgs a)
     a_off[rb] = ((uint32_t)lh * (uint32_t)B + (uint32_t)min(b0 + (wm * RB + rb) * 32 + ln, B - 1)) * 16u;
   const uint32_t plane_bytes = 2u * (uint32_t)B * 16u;          // both halves of a record plane
   const char* const Wm = (const char*)(a.W + (long long)head * a.w_head_stride);
-  const char* const Zm = (const char*)(a.Z + (long long)head * a.z_head_stride);
   const char* const Wl = SPLIT ? (const char*)(a.W_lo + (long long)head * a.w_head_stride) : nullptr;
-  const char* const Zl = SPLIT ? (const char*)(a.Z_lo + (long long)head * a.z_head_stride) : nullptr;
   struct AFrag {
     u32x4 h[RB][5];
     u32x4 l[SPLIT ? RB : 1][5];
   };
   auto load_a = [&](int k, int S, AFrag& f) {                     // fragments of group S of step k
     const int step = step0 + min(k, n_steps - 1);                 // past the end: the last step again
-    auto part = [&](const char* W, const char* Z, u32x4 (&v)[RB][5]) {
-      const char* const p = S < 4 ? W + (size_t)(step * 4 + S) * plane_bytes : Z + (size_t)step * plane_bytes;
+    auto part = [&](const char* W, u32x4 (&v)[RB][5]) {
+      const char* const p = W + (size_t)(step * 5 + S) * plane_bytes;
       const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)plane_bytes, kBufferFlags);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) v[rb][S] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)a_off[rb], 0, 0);
     };
-    part(Wm, Zm, f.h);
-    if constexpr (SPLIT) part(Wl, Zl, f.l);
+    part(Wm, f.h);
+    if constexpr (SPLIT) part(Wl, f.l);
   };
-  // Position bits of the four value pairs of a fragment: pair t holds its values' bits in bits 15 and 31 of word t,
-  // the instruction takes them from bits 4 t and 4 t + 2 (bit 4 t + 3 set: the second value is one of coefficients
-  // 2, 3 of its group).
-  auto positions = [](const u32x4 v) {
-    uint32_t u = v.w & 0x80008000u;
-    u |= (v.z >> 4) & 0x08000800u;
-    u |= (v.y >> 8) & 0x00800080u;
-    u |= (v.x >> 12) & 0x00080008u;
-    return (int)((u >> 3) | (u >> 17) | 0x8888u);
-  };
-
   // ---- edges: inputs 2 wave, 2 wave + 1 of every step, column j0 + lane
   const bool j_ok = j0 + lane < n_out;
   struct MetaRaw {
@@ -268,7 +255,7 @@ __global__ __launch_bounds__(kThreads, 2) void kan_wide_kernel(const WideArgs a)
       if (S < 4) read_b(S + 1, bf[(S + 1) & 1]);
       int ix[RB];
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) ix[rb] = positions(f.h[rb][S]);
+      for (int rb = 0; rb < RB; ++rb) ix[rb] = rot_positions(f.h[rb][S]);
       __builtin_amdgcn_sched_barrier(0);
       const BFrag& o = bf[S & 1];
 #pragma unroll
@@ -417,11 +404,8 @@ __global__ __launch_bounds__(256) void kan_prep_rot_kernel(const float* __restri
   __shared__ __attribute__((aligned(16))) uint32_t sel[kSpans][8];
   const int head = blockIdx.z;
   w.W += (long long)head * w.w_head_stride;
-  w.Z += (long long)head * w.z_head_stride;
-  if (w.W_lo) {
-    w.W_lo += (long long)head * w.w_head_stride;
-    w.Z_lo += (long long)head * w.z_head_stride;
-  }
+  if (w.W_lo) w.W_lo += (long long)head * w.w_head_stride;
+  if (w.P) w.P += (long long)head * w.p_head_stride;
   prep_rot_block(x + (long long)head * x_head_stride, x_parts, x_part_stride, x_tanh, w, n_in, B, rule, blockIdx.x, blockIdx.y,
                  hi, lo, sel);
 }
@@ -443,14 +427,14 @@ bool wide_takes(int n_in, int n_out, int64_t B) {
 
 hipError_t launch_wide(const GatherCfg& c, const WideArgs& a, bool split, int tile_m, dim3 grid, hipStream_t s) {
   if (c.code == kDense || a.B < 1 || !wide_takes(a.n_in, a.n_out, a.B) || a.rows_per_chunk < IT || a.rows_per_chunk % IT != 0 ||
-      !a.W || !a.Z || (split && (!a.W_lo || !a.Z_lo)) || (long long)a.n_jt * BN < a.n_out)
+      !a.W || (split && !a.W_lo) || (long long)a.n_jt * BN < a.n_out)
     return hipErrorInvalidValue;
   return c.idx_u32 ? launch_wide_u32(c, a, split, tile_m, grid, s) : launch_types<uint16_t>(c, a, split, tile_m, grid, s);
 }
 
 hipError_t launch_prep_rot(const float* x, long long x_head_stride, int x_parts, long long x_part_stride, int x_tanh,
                            const RotWords& w, int n_in, int B, int heads, int rule, hipStream_t s) {
-  if (x_parts < 1 || !w.W || !w.Z || (w.W_lo && !w.Z_lo)) return hipErrorInvalidValue;
+  if (x_parts < 1 || !w.W) return hipErrorInvalidValue;
   dim3 grid((n_in + 31) / 32, (B + 31) / 32, heads);
   hipLaunchKernelGGL(kan_prep_rot_kernel, grid, dim3(256), 0, s, x, x_head_stride, x_parts, x_part_stride, x_tanh, w, n_in, B, rule);
   return hipGetLastError();

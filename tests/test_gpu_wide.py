@@ -1,6 +1,7 @@
-"""Contraction that dequantises its own coefficients (kan_wide.hip): edges of its tiles of samples and outputs, odd and
+"""Kernels on rotated basis words: the contraction that dequantises its own coefficients (kan_wide.hip): edges of its tiles of samples and outputs, odd and
 ragged steps, every storage type, per-edge arrays that start anywhere, both rules, slices of a previous layer and
-several heads, against the oracle; codebook rows that no edge uses."""
+several heads, against the oracle; codebook rows that no edge uses.  The streaming contraction on tiles of 256 x 256
+(kan_stream.hip): odd and ragged steps, tiles that the samples or outputs do not fill, chunks, slices, several heads."""
 import numpy as np
 import pytest
 
@@ -95,3 +96,32 @@ def test_unused_codebook_rows_do_not_reach_the_result(kb):
     x = synth.make_x(9951, 100, 1033)
     for path in (kb.KAN_PATH_MFMA, kb.KAN_PATH_GATHER):
         assert torch.isfinite(kb.kan_vq_layer_forward(kb.VQLayer(P), to_dev(x), path=path)).all()
+
+
+@pytest.mark.parametrize("n_in,n_out,B,t", [(1033, 1021, 6100, 0), (4100, 1000, 1400, 2), (4111, 1023, 1300, 8), (200, 4095, 7700, 1),
+                                            (12300, 520, 1025, 3)])
+def test_stream_edges_of_tiles_and_steps(kb, n_in, n_out, B, t):
+    cb, gb, idx = TYPES[t]
+    P = synth.make_layer(9600 + n_in, n_in, n_out, 70000 if idx == "u32" else 4099, cb_dtype=cb, gb_dtype=gb, idx_dtype=idx)
+    x = np.random.default_rng(B + n_in).uniform(-1.1, 1.1, size=(B, n_in)).astype(np.float32)
+    x[0, 0], x[-1, -1] = 1.0, -1.0
+    rows = np.unique(np.r_[0, 31, 255, 256, B // 2, B - 1])
+    for path, tol in ((kb.KAN_PATH_MFMA, TOL_HALF), (kb.KAN_PATH_GATHER, TOL_FP32)):
+        y = kb.kan_vq_layer_forward(kb.VQLayer(P), to_dev(x), path=path).cpu().numpy()
+        check(y, x, P, tol, rows)
+
+
+@pytest.mark.parametrize("heads", [1, 3])
+def test_stream_slices_and_heads(kb, heads):
+    """A layer that cuts its inputs into chunks in front, its slices added by the basis pass; hidden rows of several heads."""
+    dims, B = (300, 1090, 1020, 40), 6100
+    Ps = [[synth.make_layer(9650 + 10 * h + l, dims[l], dims[l + 1], 4099, cb_dtype="i8", gb_dtype="f16") for l in range(3)]
+          for h in range(heads)]
+    x = synth.make_x(9651, B, dims[0])
+    hs = [[kb.VQLayer(p) for p in head] for head in Ps]
+    rows = np.r_[0, 255, 256, B // 2, B - 1]
+    for path, tol in ((kb.KAN_PATH_MFMA, TOL_HALF), (kb.KAN_PATH_GATHER, TOL_FP32)):
+        y = kb.kan_vq_head_forward(hs, to_dev(x), path=path).cpu().numpy()
+        for h in range(heads):
+            rep = ko.error_report(y[h][rows], ko.vq_head_forward(x[rows], [p.as_dict() for p in Ps[h]]))
+            assert np.isfinite(y).all() and rep["headline"] <= tol * 3, (path, h, rep)
