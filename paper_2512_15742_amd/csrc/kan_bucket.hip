@@ -12,14 +12,17 @@
 // well, and streams its block of the bucket's edges.
 //
 // Inside a bucket the edges are ordered by output j, then input i.  A workgroup owns the
-// block of edges of a run of outputs, reads it flat (thread t holds 8 consecutive edges per
-// pass: 16-byte loads whose addresses depend on nothing but the block's first edge), puts the
-// per-edge products into LDS and then sums every segment (the edges of one output) with one
-// wave in a fixed order; the per-bucket sums are added by the fixed-order reduction kernel
-// or by the next bucket layer itself: no atomics on this path, reproducible bits.  (The one
-// exception is the side path for non-finite products - a codeword holding Inf or NaN that an
-// edge refers to - which counts and places such products with LDS atomics; finite data never
-// takes it, and its results are non-finite whatever the order.)
+// block of edges of a run of outputs and reads it flat, 512 edges per wave and pass (a lane holds
+// 8 consecutive ones: 16-byte loads whose addresses depend on nothing but the block's bounds); a
+// wave turns its products of a pass into running sums, and what a segment (the edges of one
+// output) has of them is the difference at its two ends.  Two ways: blocks of up to 17 passes
+// (batch 1 to 2 on a layer of two million edges) keep the running sums of all of them and add after one barrier;
+// in larger blocks each of the 16 waves takes a sixteenth of the passes and adds pass by pass
+// without any barrier.  A segment that reaches into several waves' runs is put
+// together at the end in the order of the waves, the per-bucket sums are added by the fixed-order
+// reduction kernel or by the next bucket layer itself: reproducible bits.  (The one exception is
+// the side path for non-finite products - a codeword holding Inf or NaN that an edge refers to -
+// whose results are non-finite whatever the order.)
 // The bias of an edge needs no lookup at all: the four bases sum to 1 on [-1,1], so
 // sum_i bias_ij is a per-output constant computed at preparation time.
 //
@@ -37,8 +40,7 @@ namespace {
 
 constexpr int kWaves = kBucketThreads / kWave;     // 16
 constexpr int kEpt = 8;                            // consecutive edges per thread and pass
-constexpr int kPass = kBucketThreads * kEpt;       // 8192 edges per workgroup and pass
-constexpr int kBadMax = 32;                        // non-finite products of a pass that are placed one by one
+constexpr int kPass = kWave * kEpt;                // 512 edges per wave and pass
 
 // Raw records of one pass: edges e0 .. e0 + 7 of the thread (16-byte loads; the eight gains
 // are 32 bytes as fp32 - two loads -, 16 as fp16, 8 as byte codes).  GK is the GbKind.
@@ -81,15 +83,6 @@ __device__ __forceinline__ float dpp_add(float v) {
   return v + __int_as_float(moved);
 }
 
-// Sum over a row of 16 lanes, delivered in every lane of the row.
-__device__ __forceinline__ float row_sum(float v) {
-  v = dpp_add<0xB1, 0xf>(v);
-  v = dpp_add<0x4E, 0xf>(v);
-  v = dpp_add<0x141, 0xf>(v);
-  v = dpp_add<0x140, 0xf>(v);
-  return v;
-}
-
 __device__ __forceinline__ float wave_sum_to_last_lane(float v) {
   v = dpp_add<0xB1, 0xf>(v);       // quad_perm [1,0,3,2]: neighbours
   v = dpp_add<0x4E, 0xf>(v);       // quad_perm [2,3,0,1]: every lane holds its quad's sum
@@ -116,19 +109,16 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   constexpr int kCbPerThread = (kCbBytes / 16 + kBucketThreads - 1) / kBucketThreads;   // 16-byte units per thread
   __shared__ __attribute__((aligned(16))) uint32_t cb[kCbBytes / 4 + 8];   // + 16 bytes read-ahead, + 16 spare
   __shared__ float4 bas[MAXIN];             // {w0, w1, w2, span as integer bits}; w3 = 1 - w0 - w1 - w2
-  __shared__ __attribute__((aligned(16))) float prod[kPass];   // per-edge products of the current pass
-  __shared__ float res[kBucketMaxJw];       // sums of this workgroup's segments
+  __shared__ __attribute__((aligned(16))) float prod[kWaves + 1][kPass];   // running sums of the products of a wave's pass (and of a 17th)
+  __shared__ float res[kBucketMaxJw];           // sums of this workgroup's segments: what the wave in whose run a segment begins has of it ...
   __shared__ uint32_t segl[kBucketMaxJw + 1];   // first edge of every segment of the block (+ end)
-  __shared__ int seg_first[2];                  // first segment that reaches into the pass (by pass parity)
-  __shared__ float wave_total[kWaves];          // prefix mode: the sum of each wave's 512 products of the pass
-  __shared__ int bad_n[2];                      // prefix mode: non-finite products of the pass (by pass parity) ...
-  __shared__ uint32_t bad_pos[kBadMax];         // ... their edges ...
-  __shared__ float bad_val[kBadMax];            // ... and values: they are added to their own segment only
+  __shared__ __attribute__((aligned(16))) float head_sum[kWaves];            // ... and what each wave has of the segment that began before its run
+  __shared__ __attribute__((aligned(16))) int head_seg[kWaves];              // (-1: none did)
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int head = blockIdx.z, b = blockIdx.y;
-  const BucketHead H = a.h[head];
+  const int hd = blockIdx.z, b = blockIdx.y;
+  const BucketHead H = a.h[hd];
   const char* prep = (const char*)H.prepared;
   // the block of this workgroup: outputs [j0, j1) of one bucket, edges [blk_lo, blk_hi)
   const uint32_t* __restrict__ ent = (const uint32_t*)(prep + a.off_blk) + (size_t)blockIdx.x * kBucketEntryWords;
@@ -152,7 +142,7 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   //          (fixed order) and squashed ----------------------------------------------------
   float xv[kXPerThread];
   {
-    const float* xr = a.x + (long long)head * a.x_head_stride + (long long)b * a.n_in;
+    const float* xr = a.x + (long long)hd * a.x_head_stride + (long long)b * a.n_in;
     int xi[kXPerThread];
 #pragma unroll
     for (int r = 0; r < kXPerThread; ++r) {
@@ -225,16 +215,23 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
     }
   }
   // ---- (4) records (their addresses need the block's bounds, two dependent scalar loads that
-  //          have had the basis evaluation above to arrive).  Pass p covers edges
-  //          [base + p * 8192, + 8192), base = blk_lo rounded down to a multiple of 8, so that
-  //          every thread's group of 8 is 16-byte aligned.
-  //          Groups past the block re-read its last group; the arrays are padded, so a group
-  //          that straddles the end of the last block stays inside the buffer. -----------------
+  //          have had the basis evaluation above to arrive).  A wave's run is a number of whole
+  //          passes from blk_lo rounded down to a multiple of 8, so that every lane's group of 8
+  //          is 16-byte aligned: dealt out evenly, except that the first wave takes the last of
+  //          17 (blocks end where a segment does, so those of a chip filled with blocks of 16
+  //          passes are a little more or a little less).  Groups past the block re-read its last
+  //          group; the arrays are padded, so a group that straddles the end of the last block
+  //          stays inside the buffer. ----------------------------------------------------------------
   const uint32_t base = blk_lo & ~7u;
   const uint32_t last_group = blk_hi > 0u ? (blk_hi - 1u) & ~7u : 0u;
-  const int n_pass = blk_hi > blk_lo ? (int)((blk_hi - base + kPass - 1) / kPass) : 0;
+  const uint32_t n_edges = blk_hi > blk_lo ? blk_hi - base : 0u, passes = (n_edges + kPass - 1u) / kPass;
+  const bool one_pass = passes <= (uint32_t)kWaves + 1u;
+  const uint32_t first = one_pass ? (uint32_t)wave : (uint32_t)wave * passes / kWaves;
+  const uint32_t w_lo = base + min(first * (uint32_t)kPass, n_edges);
+  const uint32_t w_hi = one_pass ? base + n_edges : base + min((uint32_t)(wave + 1) * passes / kWaves * (uint32_t)kPass, n_edges);
+  const int n_pass = (int)((w_hi - w_lo + kPass - 1u) / kPass);
   auto load_pass = [&](PassRegs<GK>& c, int p) {
-    const uint32_t e0 = min(base + (uint32_t)p * kPass + (uint32_t)tid * kEpt, last_group);
+    const uint32_t e0 = min(w_lo + (uint32_t)p * kPass + (uint32_t)lane * kEpt, last_group);
     c.i = __builtin_nontemporal_load((const u32x4*)(pi + e0));
     c.q = __builtin_nontemporal_load((const u32x4*)(pq + e0));
     if constexpr (GK == kGbQ8) c.g0 = __builtin_nontemporal_load((const u32x2*)(pg + (size_t)e0 * kGainBytes));
@@ -243,7 +240,7 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   };
   PassRegs<GK> A, B;
   load_pass(A, 0);
-  load_pass(B, 1);
+  load_pass(B, one_pass ? kWaves : 1);
 
   __builtin_amdgcn_sched_barrier(0);
 
@@ -257,21 +254,25 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   segl[min(tid, njw)] = sv0;
   segl[min(tid + kBucketThreads, njw)] = sv1;
   for (int t = tid; t < njw; t += kBucketThreads) res[t] = 0.f;
-  if (tid < 2) bad_n[tid] = 0;
+  if (lane == 0) head_sum[wave] = 0.f;
   __syncthreads();
 
-  // Segment sums, two ways.  Long segments (more than 512 edges on the block's average): a whole
-  // wave adds one segment's products.  Shorter ones: the products of a pass are turned into
-  // running sums over each wave's 512 edges (eight per thread, then a scan across the lanes),
-  // and a segment's sum is the difference of the running sums at its two ends, plus whole
-  // waves in between: one thread per segment, three dependent LDS reads instead of a chain
-  // per group of lanes.  Both ways add in a fixed order.
-  const uint32_t avg_len_x = blk_hi - blk_lo;                               // compared with len * njw: uniform
-  const bool use_prefix = avg_len_x <= 512u * (uint32_t)njw;
-  // products of the thread's 8 edges of pass p -> prod
-  auto products = [&](const PassRegs<GK>& c, int p) {
-    // edge e belongs to the block iff blk_lo <= e < blk_hi, i.e. (e - blk_lo) < (blk_hi - blk_lo) unsigned
-    const uint32_t rel0 = base + (uint32_t)p * kPass + (uint32_t)tid * kEpt - blk_lo, len = blk_hi - blk_lo;
+  // No barrier from here to the end of the passes: the waves drift apart, and one's LDS reads, arithmetic and waits for
+  // records run beside another's.  (With passes of 8,192 edges for the whole workgroup and two barriers each, the sums in
+  // between cost 0.8 us a pass: 4096 x 4096, K = 262,144, batch 2 61.4 -> 53.6 us.)
+  int seg_now = 0, head = -1;      // set by find_segment: the wave's first segment not ended, and if it began before the run
+  static_assert(kBucketMaxJw <= kWave * 16, "two rounds find a segment");
+  const uint32_t start = max(w_lo, blk_lo);
+  const uint32_t sixteenth = segl[min((lane + 1) * 16, njw)];
+  auto find_segment = [&] {        // (rounds of 64 and 16 lanes over at most 1024; behind the first products, whose LDS reads take longer)
+    seg_now = 16 * (int)__popcll(__ballot((lane + 1) * 16 <= njw && sixteenth <= start));
+    seg_now += (int)__popcll(__ballot(lane < 16 && seg_now + lane < njw && segl[min(seg_now + lane + 1, njw)] <= start));
+    head = seg_now < njw && segl[min(seg_now, njw)] < start ? seg_now : -1;
+  };
+  // running sums of the products of the lane's 8 edges of pass p -> strip
+  auto products = [&](const PassRegs<GK>& c, int p, float* strip) {
+    // edge e belongs to the wave's run iff blk_lo <= e < w_hi, i.e. (e - blk_lo) < (w_hi - blk_lo) unsigned
+    const uint32_t rel0 = w_lo + (uint32_t)p * kPass + (uint32_t)lane * kEpt - blk_lo, len = w_hi - blk_lo;
     float pr[kEpt];
 #pragma unroll
     for (int u = 0; u < kEpt; ++u) pr[u] = 0.f;
@@ -323,128 +324,126 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
       pr[u] = (rel0 + (uint32_t)u < len) ? gain_of<GK>(c, u, qp) * s : 0.f;
     }
     }
-    if (use_prefix) {
-      float run[kEpt];                    // running sums of the thread's eight products
-      run[0] = pr[0];
+    float sums[kEpt];                     // running sums of the lane's eight products
+    sums[0] = pr[0];
 #pragma unroll
-      for (int u = 1; u < kEpt; ++u) run[u] = run[u - 1] + pr[u];
-      // A running sum would carry a non-finite product (a codeword with an Inf or NaN that an
-      // edge does refer to) into the segments behind it: such products are set aside.  The
-      // thread's total is finite iff all its eight products are.
-      if (!__builtin_isfinite(run[kEpt - 1])) {
-        float keep = 0.f;
+    for (int u = 1; u < kEpt; ++u) sums[u] = sums[u - 1] + pr[u];
+    // A running sum would carry a non-finite product (a codeword with an Inf or NaN that an
+    // edge does refer to) into the segments behind it: such products go to their own segment
+    // only.  The lane's total is finite iff all its eight products are.
+    if (!__builtin_isfinite(sums[kEpt - 1])) {
+      float keep = 0.f;
 #pragma unroll
-        for (int u = 0; u < kEpt; ++u) {
-          if (__builtin_isfinite(pr[u])) {
-            keep += pr[u];
-          } else {
-            const int k = atomicAdd(&bad_n[p & 1], 1);
-            if (k < kBadMax) {
-              bad_pos[k] = base + (uint32_t)p * kPass + (uint32_t)tid * kEpt + (uint32_t)u;
-              bad_val[k] = pr[u];
-            }
-          }
-          run[u] = keep;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kEpt; ++u) pr[u] = run[u];
-      float v = pr[kEpt - 1];            // inclusive scan of the threads' totals over the wave
-      v = dpp_add<0x111, 0xf>(v);        // row_shr 1, 2, 4, 8: within rows of 16 lanes
-      v = dpp_add<0x112, 0xf>(v);
-      v = dpp_add<0x114, 0xf>(v);
-      v = dpp_add<0x118, 0xf>(v);
-      v = dpp_add<0x142, 0xa>(v);        // row_bcast 15: rows 1 and 3 add the total of the row before
-      v = dpp_add<0x143, 0xc>(v);        // row_bcast 31: rows 2 and 3 add the total of the first half
-      const float before = __shfl_up(v, 1, 64);
-      const float ex = lane == 0 ? 0.f : before;
-#pragma unroll
-      for (int u = 0; u < kEpt; ++u) pr[u] += ex;
-      if (lane == kWave - 1) wave_total[wave] = v;
-    }
-    ((float4*)prod)[tid * 2] = make_float4(pr[0], pr[1], pr[2], pr[3]);
-    ((float4*)prod)[tid * 2 + 1] = make_float4(pr[4], pr[5], pr[6], pr[7]);
-    // The first segment that ends after the start of the pass: thread t answers for segment t
-    // (exactly one does), so that the sums below visit only the segments of the pass and a
-    // block of 1024 short segments does not walk all of them in every pass.
-    const uint32_t pa = base + (uint32_t)p * kPass;
-    if (tid < njw && segl[tid + 1] > pa && (tid == 0 || segl[tid] <= pa)) seg_first[p & 1] = tid;
-  };
-
-  auto segment_sums = [&](int p) {
-    const uint32_t pa = base + (uint32_t)p * kPass;        // prod[n] is edge pa + n
-    if (use_prefix) {
-      for (int jj = seg_first[p & 1] + tid; jj < njw; jj += kBucketThreads) {
-        const uint32_t s0 = segl[jj], s1 = segl[jj + 1];
-        if (s0 >= pa + (uint32_t)kPass) break;             // in order: the rest lies behind the pass
-        const uint32_t lo = max(s0, pa) - pa, hi = min(s1, pa + (uint32_t)kPass) - pa;
-        if (lo < hi) {
-          const int wl = (int)(lo >> 9), wh = (int)((hi - 1) >> 9);       // 512 products per wave
-          float sum = prod[hi - 1];
-          for (int w = wh - 1; w >= wl; --w) sum += wave_total[w];        // whole waves, and the first wave's total
-          if (lo & 511u) sum -= prod[lo - 1];
-          res[jj] += sum;
-        }
-      }
-      const int nb = bad_n[p & 1];                          // (uniform; almost always 0)
-      if (nb > 0) {
-        __syncthreads();                                    // the sums above are in res
-        if (nb > kBadMax) {                                 // too many to place: the whole block is not a number
-          for (int t = tid; t < njw; t += kBucketThreads) res[t] = __builtin_nanf("");
-        } else if (tid < nb) {
-          const uint32_t e = bad_pos[tid];                  // its segment: segl[jj] <= e < segl[jj + 1]
+      for (int u = 0; u < kEpt; ++u) {
+        if (__builtin_isfinite(pr[u])) {
+          keep += pr[u];
+        } else {
+          const uint32_t e = rel0 + (uint32_t)u + blk_lo;     // its segment: segl[jj] <= e < segl[jj + 1]
           int lo_j = 0, hi_j = njw;
           while (hi_j - lo_j > 1) {
             const int mid = (lo_j + hi_j) >> 1;
             if (segl[mid] <= e) lo_j = mid; else hi_j = mid;
           }
-          atomicAdd(&res[lo_j], bad_val[tid]);
+          atomicAdd(&res[lo_j], pr[u]);
         }
-        __syncthreads();
-        if (tid == 0) bad_n[p & 1] = 0;                     // next written two passes on, behind two barriers
+        sums[u] = keep;
       }
-      return;
     }
-    // a whole wave per segment; wave w takes segments w, w + 16, ... of the pass
-    constexpr int group_shift = 6;
-    const int glanes = 1 << group_shift, per_wave = kWave >> group_shift;
-    const int grp = lane >> group_shift, gl = lane & (glanes - 1);
-    for (int jj = seg_first[p & 1] + wave * per_wave + grp; jj < njw; jj += kWaves * per_wave) {
-      const uint32_t s0 = segl[jj], s1 = segl[jj + 1];
-      if (s0 >= pa + (uint32_t)kPass) break;               // in order: the rest lies behind the pass (the groups of a wave leave one by one)
-      const uint32_t lo = max(s0, pa), hi = min(s1, pa + (uint32_t)kPass);
-      float acc = 0.f;
-      for (uint32_t e = lo + (uint32_t)gl; e < hi; e += (uint32_t)glanes) acc += prod[e - pa];
-      acc = row_sum(acc);                                   // every lane: the sum of its row of 16
-      if (group_shift >= 5) acc = dpp_add<0x142, 0xa>(acc); // rows 1 and 3: the sum of their half wave
-      if (group_shift == 6) acc = dpp_add<0x143, 0xc>(acc); // row 3: the sum of the wave
-      if (gl == glanes - 1 && lo < hi) res[jj] += acc;
-    }
+    float v = sums[kEpt - 1];            // inclusive scan of the lanes' totals over the wave
+    v = dpp_add<0x111, 0xf>(v);          // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);          // row_bcast 15: rows 1 and 3 add the total of the row before
+    v = dpp_add<0x143, 0xc>(v);          // row_bcast 31: rows 2 and 3 add the total of the first half
+    const float before = __shfl_up(v, 1, 64);
+    const float ex = lane == 0 ? 0.f : before;
+    ((float4*)strip)[lane * 2] = make_float4(sums[0] + ex, sums[1] + ex, sums[2] + ex, sums[3] + ex);
+    ((float4*)strip)[lane * 2 + 1] = make_float4(sums[4] + ex, sums[5] + ex, sums[6] + ex, sums[7] + ex);
   };
 
-  // two passes are always in flight: a slot is refilled as soon as it has been consumed
-  // (after the last pass the refills are harmless re-reads)
-  for (int p = 0; p < n_pass; p += 2) {
-    products(A, p);
-    load_pass(A, p + 2);
-    __syncthreads();
-    segment_sums(p);
-    __syncthreads();
-    if (p + 1 >= n_pass) break;
-    products(B, p + 1);
-    load_pass(B, p + 3);
-    __syncthreads();
-    segment_sums(p + 1);
-    __syncthreads();
+  // What the segments have of pass p, a lane per segment; the bounds of the first 64 are read ahead of the products.
+  auto pass = [&](const PassRegs<GK>& c, int p) {
+    float* const strip = prod[wave];
+    const uint32_t pa = w_lo + (uint32_t)p * kPass, pe = min(pa + (uint32_t)kPass, w_hi);
+    uint32_t s0 = segl[min(seg_now + lane, njw)], s1 = segl[min(seg_now + lane + 1, njw)];
+    products(c, p, strip);
+    if (p == 0) {
+      find_segment();
+      s0 = segl[min(seg_now + lane, njw)];
+      s1 = segl[min(seg_now + lane + 1, njw)];
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (;;) {
+      const int jj = seg_now + lane;
+      const uint32_t lo = max(s0, pa), hi = min(s1, pe);
+      if (jj < njw && lo < hi) {
+        const float upto = strip[hi - 1 - pa], from = strip[lo > pa ? lo - 1 - pa : 0];
+        // (one wave adds to an element, in the order of its passes)
+        atomicAdd(jj == head ? &head_sum[wave] : &res[jj], lo > pa ? upto - from : upto);
+      }
+      const int ended = (int)__popcll(__ballot(jj < njw && s1 <= pe));
+      seg_now += ended;
+      if (ended < kWave) break;
+      s0 = segl[min(seg_now + lane, njw)];
+      s1 = segl[min(seg_now + lane + 1, njw)];
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  if (one_pass) {
+    // The strips lie behind one another, so a thread can take a segment's sum from the strips of all waves, without the
+    // search for the segments of a run: 1500 x 1100, K = 20,000, batch 1 (segments of 500 edges, a wave's run) 13.1 -> 11.5 us;
+    // 2048 x 1024 x 256 at batch 1, whose first layer's blocks are 16 passes and a little, 13.8 -> 12.0 with the 17th strip.
+    if (n_pass > 0) products(A, 0, prod[wave]);
+    if (n_pass > kWaves) products(B, kWaves, prod[kWaves]);
+  } else {
+    // two passes are always in flight: a slot is refilled as soon as it has been consumed
+    // (after the last pass the refills are harmless re-reads)
+    for (int p = 0; p < n_pass; p += 2) {
+      pass(A, p);
+      load_pass(A, p + 2);
+      if (p + 1 >= n_pass) break;
+      pass(B, p + 1);
+      load_pass(B, p + 3);
+    }
+    if (lane == 0) head_seg[wave] = head;
   }
+  __syncthreads();
+  // what the waves have of segments that began before their runs, in the order of the waves
+  if (!one_pass && wave == 0) {
+    const int seg_of = lane < kWaves ? head_seg[lane] : -1;
+    float sum = head_sum[lane & (kWaves - 1)];
+    const int other = __shfl_up(seg_of, 1, 64);
+    const bool first = lane == 0 || seg_of != other;
+    if (__ballot(seg_of >= 0 && !first) != 0) {  // a segment that takes up whole runs
+      const int own = __float_as_int(sum);
+      sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w)
+        sum += seg_of == __builtin_amdgcn_readlane(seg_of, w) ? __int_as_float(__builtin_amdgcn_readlane(own, w)) : 0.f;
+    }
+    if (seg_of >= 0 && first) res[seg_of] += sum;
+  }
+  if (!one_pass && njw > kWave) __syncthreads();  // (else the same wave reads them)
+  // a segment's sum where the passes are at most 17
+  auto sum_of_strips = [&](int t) {
+    const float* const flat = prod[0];
+    const uint32_t lo = max(segl[t], base) - base, hi = segl[t + 1] - base;
+    if (lo >= hi) return 0.f;
+    float sum = flat[hi - 1];
+    for (uint32_t w = lo / kPass; w < (hi - 1) / kPass; ++w) sum += prod[w][kPass - 1];
+    return lo % kPass ? sum - flat[lo - 1] : sum;
+  };
 
   // ---- segment sums -> memory (coalesced): scale, bias sum (first bucket only), activation ----
-  float* dst = a.dst + (long long)head * a.dst_head_stride + (long long)bucket * a.dst_chunk_stride +
+  float* dst = a.dst + (long long)hd * a.dst_head_stride + (long long)bucket * a.dst_chunk_stride +
                (long long)b * a.n_out;
   const float* bias_sum = (const float*)(prep + a.off_bias);
   const float scale = CODE == kCbI8 ? H.scale : 1.0f;
   for (int t = tid; t < njw; t += kBucketThreads) {
-    float v = scale * res[t] + (bucket == 0 ? bias_sum[j0 + t] : 0.0f);
+    const float sum = res[t] + (one_pass ? sum_of_strips(t) : 0.f);
+    float v = scale * sum + (bucket == 0 ? bias_sum[j0 + t] : 0.0f);
     if (a.apply_tanh && a.n_buckets == 1) v = tanhf(v);
     dst[j0 + t] = v;
   }

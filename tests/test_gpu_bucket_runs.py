@@ -1,0 +1,69 @@
+"""The two ways the bucket kernel adds its segments: blocks of up to 17 passes of 512 edges (one strip of running sums
+per pass) and larger ones (a run of passes per wave), against the float64 oracle with the bound of the other fp32 kernels."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle import kan_oracle as ko
+from paper_2512_15742_amd import synth
+
+from kan_testlib import TOL_FP32, gpu_layers, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _forward(P, x):
+    from paper_2512_15742_amd import binding as kb
+    (L,) = [L.prepare() for L in gpu_layers([P])]
+    L.use_prepared(True)
+    L.keep_on_bucket_kernel(True)
+    assert kb.kan_vq_planned_kernel(L, len(x), 1, kb.KAN_PATH_GATHER) == "kan_bucket"
+    first, again = (kb.kan_vq_head_forward([[L]], to_dev(x), path=kb.KAN_PATH_GATHER)[0].cpu().numpy() for _ in range(2))
+    assert np.array_equal(first, again, equal_nan=True)              # whatever the waves' timing
+    return first
+
+
+# One bucket and batch 4: 64 blocks per sample, so a block holds n_in * n_out / 64 edges, rounded to whole outputs.
+@pytest.mark.parametrize("n_in,n_out", [
+    (512, 1024),       # 8192 edges: 16 passes exactly
+    (513, 1024),       # 8208 from unaligned starts: the 17th pass
+    (512, 1088),       # 8704: 17 passes exactly
+    (515, 1088),       # 8755: runs of one and two passes
+    (4096, 150),       # segments of 8 passes: over several whole runs
+    (16, 40000),       # 625 short segments per block
+    (3, 200000),       # 1024 outputs per block, the most there are: runs of hundreds of segments
+])
+@pytest.mark.parametrize("cb,gb", [("i8", "f16"), ("f32", "f32")])
+@pytest.mark.parametrize("skew", [False, True])
+def test_segments_of_a_block(n_in, n_out, cb, gb, skew):
+    rows = (8192 if cb == "i8" else 2048) // (2 if n_in > 2048 else 1)
+    P = synth.make_layer(n_in + n_out, n_in, n_out, 3 * rows if skew else rows, cb_dtype=cb, gb_dtype=gb)
+    if skew:           # outputs that own whole stretches of a bucket, and as many that have no edge in it
+        third = n_out // 3
+        P.idx[:, :third] %= rows
+        P.idx[:, 2 * third:] = P.idx[:, 2 * third:] % rows + 2 * rows
+    x = synth.make_x(9, 4, n_in)
+    y_ref, A = ko.vq_layer_forward(x, **P.as_dict(), return_abs=True)
+    rep = ko.error_report(_forward(P, x), y_ref, A)
+    # "strict" divides by the terms of the output alone; the sum of a short segment is a difference of running sums over
+    # up to 512 edges, whose rounding is in proportion to the terms of all of them
+    assert rep["headline"] <= TOL_FP32 and rep["strict"] <= TOL_FP32 * max(1.0, 512 / n_in), rep
+
+
+@pytest.mark.parametrize("n_in,n_out", [(513, 1024), (600, 1200)])
+def test_a_non_finite_codeword_stays_with_its_outputs(n_in, n_out):
+    P = synth.make_layer(3, n_in, n_out, 2048, cb_dtype="f32", gb_dtype="f32")
+    P.idx[P.idx == 7] = 8
+    hit = np.zeros(n_out, dtype=bool)
+    hit[[0, n_out // 2, n_out - 1]] = True
+    P.idx[[[0], [n_in // 2], [n_in - 1]], np.flatnonzero(hit)] = 7
+    cb = P.codebook.copy()
+    cb[7] = np.inf
+    x = synth.make_x(4, 4, n_in)
+    y = _forward(dataclasses.replace(P, codebook=cb), x)
+    y_ref = ko.vq_layer_forward(x, **P.as_dict())
+    assert not np.isfinite(y[:, hit]).any()
+    assert ko.error_report(y[:, ~hit], y_ref[:, ~hit])["headline"] <= TOL_FP32
