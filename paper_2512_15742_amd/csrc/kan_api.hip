@@ -122,6 +122,7 @@ struct LayerPlan {
   const char* name;
 };
 
+constexpr int kCUs = 256;
 constexpr int kTargetWorkgroups = 512;    // two workgroups of 4 waves per CU
 constexpr int kEnoughWorkgroups = 384;
 
@@ -459,10 +460,20 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
   return p;
 }
 
-// Precise path up to 32 samples: tiles of 64 outputs, the four waves of a workgroup over its inputs.  Two workgroups
-// per CU while a wave keeps two steps, and while the partial sums stay below the size of the parameter stream (four
-// times that for small layers, as above).
-LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code) {
+// Precise path up to 32 samples: tiles of 64 outputs, the four waves of a workgroup over its inputs.  The chunk's
+// steps of 16 inputs are chosen by what they cost, in steps of a busy CU (1 us, its address units bound): the fullest
+// CU's workgroups times their steps (a lone workgroup's step takes as long as 1.75: latencies without a neighbour
+// behind them), and the partial sums, written here and read by the next layer or the reduction.  Filling the chip with
+// at least 512 workgroups of two steps or more, as before, left one CU with three workgroups of ten steps where
+// 520 were launched (ten heads of 2048-256-21 at batch 4 / 16 / 32: 54.6 / 55.5 / 75 us, now 41.6 / 46.0 / 59.3;
+// twenty of 1024-128-50 at 16 38.7 -> 30.5), and small layers with a second step that takes longer than
+// the slices it saves (64-32 at batch 16 7.5 -> 6.5, 1000-333-21 24.3 -> 20.9, 2048-1024-256 at batch 4 28.2 -> 26.7).
+// Not more chunks than the next layer takes as they are, unless two steps each would be too many already; chunks of a
+// single step for up to kFusedWaveStepBytes of partial sums, beyond which a caller's workspace would grow with them.
+// (Eight waves to a workgroup for half the slices: 2048-1024-256 at batch 16 30.2 against 28.6 us.)
+// compact: the smaller partial sums of the former rule, for calls that fit the static scratch only so.
+constexpr long long kFusedWaveStepBytes = 512 * 1024;
+LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool compact) {
   LayerPlan p;
   p.mfma = false;
   p.kind = kPlanFusedWave;
@@ -472,16 +483,25 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   p.n_bt = 1;
   const int bytes_per_edge = (idx_u32 ? 4 : 2) + 2 * gb_bytes(gb_kind);
   const long long base = (long long)n_heads * p.n_jt;
-  long long chunks = (kTargetWorkgroups + base - 1) / base;
-  const long long max_by_rows = n_in / (2 * kFusedWaveStep);
+  const int steps = (n_in + kFusedWaveStep - 1) / kFusedWaveStep;
+  // partial sums up to the size of the parameter stream (four times that for small layers, as above)
   const long long max_by_bytes =
       (long long)n_in * bytes_per_edge / ((long long)n_in * n_out <= kFusedSmallLayerEdges ? B : 4 * B);
-  if (chunks > max_by_rows) chunks = max_by_rows;
-  if (chunks > max_by_bytes) chunks = max_by_bytes;
-  if (chunks < 1) chunks = 1;
-  const int rows = (int)((n_in + chunks - 1) / chunks);
-  p.rows_per_chunk = (rows + kFusedWaveStep - 1) / kFusedWaveStep * kFusedWaveStep;
-  p.n_chunks = (n_in + p.rows_per_chunk - 1) / p.rows_per_chunk;
+  long long max_by_count = steps > 2 * kFusedChainMaxParts ? steps : kFusedChainMaxParts;
+  if ((long long)steps * n_heads * B * n_out * 4 > kFusedWaveStepBytes) max_by_count = std::min<long long>(max_by_count, (steps + 1) / 2);
+  if (compact) max_by_count = std::min<long long>(n_in / (2 * kFusedWaveStep), (kTargetWorkgroups + base - 1) / base);
+  const long long most = std::max(1ll, std::min({max_by_count, max_by_bytes, (long long)steps}));
+  double least = 0;
+  for (int per_cu = 1; per_cu <= 8; ++per_cu) {          // the fewest steps with at most so many workgroups on a CU
+    const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, 1, most);
+    const int per = (int)((steps + want - 1) / want), chunks = (steps + per - 1) / per;
+    const long long wgs = base * chunks;
+    const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B);
+    if (least > 0 && cost >= least) continue;
+    least = cost;
+    p.rows_per_chunk = per * kFusedWaveStep;
+    p.n_chunks = chunks;
+  }
   return p;
 }
 
@@ -597,7 +617,7 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true);
     return p;
   }
-  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code);
+  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows);
   return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok);
 }
 

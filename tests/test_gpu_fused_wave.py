@@ -62,3 +62,18 @@ def test_call_that_fits_the_static_scratch_only_without_the_hand_over(kb):
     assert torch.equal(y, y[:1].expand_as(y))
     rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
     assert rep["headline"] <= TOL_FP32, rep
+
+
+@pytest.mark.parametrize("dims,heads", [((64, 32, 8), 1),            # chunks of a single step, handed on and reduced
+                                        ((2080, 40, 21), 1),         # more steps than slices may be handed on
+                                        ((2048, 256, 21), 10),       # several workgroups per CU and several steps each
+                                        ((333, 100, 10), 7)])
+@pytest.mark.parametrize("B", [4, 16, 32])
+def test_chunks_of_heads(kb, dims, heads, B):
+    Ps = [[synth.make_layer(9400 + 3 * h + l, dims[l], dims[l + 1], 521, cb_dtype="i8", gb_dtype="f16") for l in range(2)]
+          for h in range(heads)]
+    x = synth.make_x(9500 + B, B, dims[0])
+    y = kb.kan_vq_head_forward([[kb.VQLayer(p) for p in P] for P in Ps], to_dev(x), path=kb.KAN_PATH_GATHER).cpu().numpy()
+    for h in (0, heads - 1):
+        rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
+        assert rep["headline"] <= TOL_FP32, rep
