@@ -406,7 +406,8 @@ LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
 // of 128.  With one batch tile every edge is gathered once and the work is bound by the
 // gather rate of the CUs' address units, so every CU should be busy: i is split while the
 // partial sums stay below the size of the parameter stream.
-LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool f32) {
+// compact: the smaller partial sums of the first count of chunks, for calls that fit the static scratch only so.
+LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool f32, bool compact) {
   LayerPlan p;
   p.mfma = false;
   p.kind = f32 ? kPlanFused32 : kPlanFused16;
@@ -436,12 +437,17 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
   // codebooks stay in its L2: at least kFusedMinWgsPerHead workgroups per head.
   // (layers whose whole codebook traffic is small gain nothing from it: their workgroups would
   // only get shorter)
+  long long resident = 1;
   if (n_heads > 1 && (long long)n_in * n_out >= kFusedMinEdgesForResidency) {
     const long long per_head = (long long)p.n_jt * p.n_bt;
-    const long long want = (kFusedMinWgsPerHead + per_head - 1) / per_head;
-    if (chunks < want) chunks = want;
+    resident = (kFusedMinWgsPerHead + per_head - 1) / per_head;
+    if (chunks < resident) chunks = resident;
   }
-  const long long max_by_rows = n_in / 16;                                   // at least two steps each
+  // At least two steps each; the precise form, whose steps are longer, takes single ones while the matrix-core kernels
+  // still take that many slices as they are (500-128-64-10 at batch 37 43.5 -> 37 us; in the fp16 form 4096 x 64 at
+  // batch 24 loses, 11.4 -> 13.4).
+  long long max_by_rows = compact ? n_in / 16 : (n_in + 15) / 16;
+  if (f32 && !compact) max_by_rows = std::max(max_by_rows, std::min<long long>((n_in + 7) / 8, kMaxChainedSlices));
   // Partial sums up to the size of the parameter stream (n_in * bytes_per_edge / 4 B chunks of 4 B bytes per output) -
   // up to four times that for small layers, whose launch is a latency chain and not a stream: capped at the stream's
   // size, config 3's second layer (262,144 edges) ran on 48 workgroups at batch 64 and took 17-28 us; with four times it runs on 128 and takes
@@ -453,10 +459,28 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
   if (chunks > max_by_rows) chunks = max_by_rows;
   if (chunks > max_by_bytes) chunks = max_by_bytes;
   if (chunks < 1) chunks = 1;
-  int rows = (int)((n_in + chunks - 1) / chunks);
-  rows = (rows + 7) / 8 * 8;
-  p.rows_per_chunk = rows;
-  p.n_chunks = (n_in + rows - 1) / rows;
+  // A few workgroups more than the CUs hold in whole rounds: the fullest CU then has a round of long chunks for itself
+  // (ten heads of 2048-256-21 at batch 64 on 260 workgroups of 20 steps: 72.6 us fp16, 105.4 precise; on 500 of 11 59.1
+  // and 86.4).  Cost as for the wave-by-wave kernel below: steps on the fullest CU, and the partial sums.
+  const int steps = (n_in + 7) / 8;
+  const auto cost_of = [&](int per) {
+    const long long wgs = base * ((steps + per - 1) / per);
+    return per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.5) + 1.28e-4 * (double)(wgs * p.cfg.bt);
+  };
+  int per = (int)((steps + chunks - 1) / chunks);
+  const long long wgs = base * ((steps + per - 1) / per), rounds = (wgs + kCUs - 1) / kCUs;
+  if (!compact && rounds > 1 && rounds * kCUs * 8 > wgs * 9) {
+    const int planned = per;
+    const long long most = std::min(max_by_rows, max_by_bytes);
+    for (long long r = rounds - 1; r <= 2 * rounds; ++r) {
+      const long long want = r * kCUs / base;
+      if (want < resident || want > most) continue;
+      const int other = (int)((steps + want - 1) / want);
+      if (cost_of(other) < cost_of(per) && cost_of(other) < 0.9 * cost_of(planned)) per = other;
+    }
+  }
+  p.rows_per_chunk = 8 * per;
+  p.n_chunks = (steps + per - 1) / per;
   return p;
 }
 
@@ -601,7 +625,7 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
     if (B <= fused_max) {
-      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false);
+      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows);
       if (wide) make_wide(p, L.in, L.out, B, n_heads, false);
       return p;
     }
@@ -613,7 +637,7 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide);
   const long long edges = (long long)L.in * L.out;
   if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) {
-    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true);
+    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows);
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true);
     return p;
   }
