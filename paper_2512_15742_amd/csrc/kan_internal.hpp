@@ -121,11 +121,11 @@ struct PrepStartArgs {
   const float* x;                    // [B][n_in] of the first layer; n_in = 0: no basis words
   uint2* W;
   uint2* W_lo;                       // split form only
+  int n_in, B, rule;
+  int basis_nx;                      // filled by the launcher
   int rot;                           // write rotated words instead of W, W_lo
   int rot_coef;                      // the jobs' records as PrepCoefArgs::rot (only with rot)
   RotWords rw;
-  int n_in, B, rule;
-  int basis_nx;                      // filled by the launcher
 };
 
 struct MfmaArgs {
