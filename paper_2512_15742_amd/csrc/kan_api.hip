@@ -607,8 +607,10 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   fp16 path (KAN_PATH_MFMA, and AUTO from batch 32): up to kHalfFusedMaxBatch the fused
 //     kernel with fp16 operands, above that coefficient/basis preparation + the streaming
 //     contraction (small layers, on either path: coefficient preparation + one launch, plan_matrix);
-//   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) keep the fused kernel up to
-//     kFusedTwoTilesMaxBatch on either path.
+//   from batch 65, layers of a million edges and more: the contraction that gathers and dequantises its own
+//     coefficients (make_wide), large products the one on tiles of 256 x 256 (make_stream), either path;
+//   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) would keep the fused kernel up to
+//     kFusedTwoTilesMaxBatch on either path; its plan is what they report, make_wide what they run.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
                   bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true) {
   const int code = code_of(L);
@@ -619,6 +621,8 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   // 96-128: 288-290 -> 210-213 us on the fp16 path, 587 -> 474-478 us precise; 4096 x 1024: 60.8 -> 57.2 and
   // 103 -> 90-95 us; a 2048 x 1024 layer gains at batch 96 and loses at 128, config 3's head 57.5 -> 61.0 us,
   // fp32 rows - three loads per gather - lose: config 2 at batch 128 32.4 -> 35.7 us; at batch 192 all lose).
+  // make_wide takes such launches over in turn (4096 x 4096 at batch 128 176 -> 111 us); the plan of two tiles is left
+  // for calls that fit the static scratch only without its basis words.
   const bool two_tiles = (long long)L.in * L.out >= kFusedTwoTilesMinEdges && code != kCbF32;
   const int64_t fused_max = two_tiles ? kFusedTwoTilesMaxBatch : kHalfFusedMaxBatch;
   if (half_path) {
