@@ -446,7 +446,9 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
   // At least two steps each; the precise form, whose steps are longer, takes single ones while the matrix-core kernels
   // still take that many slices as they are (500-128-64-10 at batch 37 43.5 -> 37 us; in the fp16 form 4096 x 64 at
   // batch 24 loses, 11.4 -> 13.4).
-  long long max_by_rows = compact ? n_in / 16 : (n_in + 15) / 16;
+  // (rounded down, which leaves chunks of three steps, where a reduction follows: 1000-333-21 fp16 at batch 37 26.4 us, 26.6
+  // with more slices; 22.7 against 26.2 at batch 24, whose next layer adds them itself)
+  long long max_by_rows = compact || (!f32 && p.cfg.bt == 64) ? n_in / 16 : (n_in + 15) / 16;
   if (f32 && !compact) max_by_rows = std::max(max_by_rows, std::min<long long>((n_in + 7) / 8, kMaxChainedSlices));
   // Partial sums up to the size of the parameter stream (n_in * bytes_per_edge / 4 B chunks of 4 B bytes per output) -
   // up to four times that for small layers, whose launch is a latency chain and not a stream: capped at the stream's

@@ -35,7 +35,16 @@ __global__ __launch_bounds__(256) void kan_reduce_kernel(const float* __restrict
         s2 += __builtin_nontemporal_load(p + (long long)(c + 2 * CG) * chunk_stride + n);
         s3 += __builtin_nontemporal_load(p + (long long)(c + 3 * CG) * chunk_stride + n);
       }
-      for (; c < n_chunks; c += CG) s0 += __builtin_nontemporal_load(p + (long long)c * chunk_stride + n);
+      // what is left of the fours: all loads in flight (past the last chunk: the last one, not added).  One by one in a loop,
+      // two chunks a thread (32 slices of 4,096 outputs) were two memory latencies: 2048-1024-256 at batch 16 28.6 -> 28.2 us,
+      // 1000-333-21 at 37, whose two reductions have 42 and 14 slices, 26.4 -> 24.8.
+      if (c < n_chunks) {
+        float t[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) t[i] = __builtin_nontemporal_load(p + (long long)min(c + i * CG, n_chunks - 1) * chunk_stride + n);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s0 += c + i * CG < n_chunks ? t[i] : 0.f;
+      }
     }
     float s = (s0 + s1) + (s2 + s3);
     if constexpr (CG > 1) {
