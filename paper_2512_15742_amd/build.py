@@ -35,6 +35,7 @@ UNITS = [
     ("kan_api.hip", "kan_api.o", []),
     ("kan_misc.hip", "kan_misc.o", []),
     ("kan_mfma.hip", "kan_mfma.o", []),
+    ("kan_mfma.hip", "kan_prep_rot.o", ["-DKAN_PREP_ROT=1"]),
     ("kan_stream.hip", "kan_stream.o", []),
     ("kan_wide.hip", "kan_wide.o", []),
     ("kan_wide.hip", "kan_wide_u32.o", ["-DKAN_WIDE_U32=1"]),

@@ -55,6 +55,13 @@
 #include "kan_internal.hpp"
 #include "kan_mfma_common.hpp"
 
+// 1: this translation unit holds the preparation kernels of the rotated forms (kan_wide.hip, kan_stream.hip), nothing else.
+// A code object of their own: among the kernels here they put the ones that a head at batch 1024 launches in turn further
+// apart, 85.7-90.2 us against 86.9-91.2.
+#ifndef KAN_PREP_ROT
+#define KAN_PREP_ROT 0
+#endif
+
 namespace kan {
 namespace {
 
@@ -265,6 +272,7 @@ __global__ __launch_bounds__(kThreads) void kan_prep_coef_kernel(const PrepCoefA
 // The dense baseline at large batch: its fp32 coefficients coef[i][j][10] in the split form,
 // in the record order of kan_prep_coef (same grid: 64 columns x 32 rows per workgroup, a wave
 // takes 8 rows).  No bias sums: the contraction is launched without them.
+#if !KAN_PREP_ROT
 __global__ __launch_bounds__(kThreads) void kan_prep_dense_kernel(const float* __restrict__ coef, uint4* __restrict__ cf,
                                                                   uint4* __restrict__ cf_lo, int n_in, int n_out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -306,6 +314,7 @@ __global__ __launch_bounds__(kThreads) void kan_prep_dense_kernel(const float* _
     cf_lo[trec] = make_uint4(tail_lo[0], tail_lo[1], tail_lo[2], tail_lo[3]);
   }
 }
+#endif
 
 // ---- kan_prep_basis -----------------------------------------------------------------
 // An input's basis word for a sample = { half2(w0, w1), half2(w2, w3) } with span bit 0, 1, 2 in
@@ -353,6 +362,7 @@ __device__ __forceinline__ void prep_basis_block(const float* __restrict__ xh, c
   }
 }
 
+#if !KAN_PREP_ROT
 __global__ __launch_bounds__(256) void kan_prep_basis_kernel(const float* __restrict__ x, long long x_head_stride,
                                                              int x_parts, long long x_part_stride, int x_tanh,
                                                              uint2* __restrict__ W, uint2* __restrict__ W_lo,
@@ -364,6 +374,7 @@ __global__ __launch_bounds__(256) void kan_prep_basis_kernel(const float* __rest
                    W + (long long)head * w_head_stride, W_lo ? W_lo + (long long)head * w_head_stride : nullptr, n_in, B,
                    rule, blockIdx.x, blockIdx.y, tile, tile_lo);
 }
+#endif
 
 // ---- kan_prep_start -----------------------------------------------------------------
 // Everything a single head's call can prepare before its first contraction, in one launch:
@@ -880,8 +891,7 @@ hipError_t prep_coef_types(const GatherCfg& c, const PrepCoefArgs& a, dim3 grid,
   return prep_types(c, [&](auto gb, auto cb) {
     typedef typename decltype(gb)::type GbT;
     typedef typename decltype(cb)::type CbT;
-    if (a.rot) hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, GbT, CbT, SPLIT, true>), grid, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, GbT, CbT, SPLIT, false>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((kan_prep_coef_kernel<IdxT, GbT, CbT, SPLIT, KAN_PREP_ROT>), grid, dim3(kThreads), 0, s, a);
   });
 }
 
@@ -890,19 +900,41 @@ hipError_t prep_start_types(const GatherCfg& c, const PrepStartArgs& a, dim3 gri
   return prep_types(c, [&](auto gb, auto cb) {
     typedef typename decltype(gb)::type GbT;
     typedef typename decltype(cb)::type CbT;
+#if KAN_PREP_ROT
     if (a.rot_coef) hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, true, true>), grid, dim3(kThreads), 0, s, a);
-    else if (a.rot) hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, true>), grid, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, false>), grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, true>), grid, dim3(kThreads), 0, s, a);
+#else
+    hipLaunchKernelGGL((kan_prep_start_kernel<IdxT, GbT, CbT, SPLIT, false, false>), grid, dim3(kThreads), 0, s, a);
+#endif
   });
+}
+
+hipError_t prep_coef_of(const GatherCfg& c, const PrepCoefArgs& a, dim3 grid, hipStream_t s) {
+  if (a.cf_lo) return c.idx_u32 ? prep_coef_types<uint32_t, true>(c, a, grid, s) : prep_coef_types<uint16_t, true>(c, a, grid, s);
+  return c.idx_u32 ? prep_coef_types<uint32_t, false>(c, a, grid, s) : prep_coef_types<uint16_t, false>(c, a, grid, s);
+}
+
+hipError_t prep_start_of(const GatherCfg& c, const PrepStartArgs& a, bool split, dim3 grid, hipStream_t s) {
+  if (split) return c.idx_u32 ? prep_start_types<uint32_t, true>(c, a, grid, s) : prep_start_types<uint16_t, true>(c, a, grid, s);
+  return c.idx_u32 ? prep_start_types<uint32_t, false>(c, a, grid, s) : prep_start_types<uint16_t, false>(c, a, grid, s);
 }
 
 }  // namespace
 
+#if KAN_PREP_ROT
+hipError_t launch_prep_coef_rot(const GatherCfg& c, const PrepCoefArgs& a, dim3 grid, hipStream_t s) { return prep_coef_of(c, a, grid, s); }
+hipError_t launch_prep_start_rot(const GatherCfg& c, const PrepStartArgs& a, bool split, dim3 grid, hipStream_t s) {
+  return prep_start_of(c, a, split, grid, s);
+}
+#else
+// with rotated words, as checked below
+hipError_t launch_prep_coef_rot(const GatherCfg& c, const PrepCoefArgs& a, dim3 grid, hipStream_t s);
+hipError_t launch_prep_start_rot(const GatherCfg& c, const PrepStartArgs& a, bool split, dim3 grid, hipStream_t s);
+
 hipError_t launch_prep_coef(const GatherCfg& c, const PrepCoefArgs& a, int heads, hipStream_t s) {
   if (c.code == kDense) return hipErrorInvalidValue;
   dim3 grid((a.n_out + 63) / 64, (a.n_in + kMfmaPrepRows - 1) / kMfmaPrepRows, heads);
-  if (a.cf_lo) return c.idx_u32 ? prep_coef_types<uint32_t, true>(c, a, grid, s) : prep_coef_types<uint16_t, true>(c, a, grid, s);
-  return c.idx_u32 ? prep_coef_types<uint32_t, false>(c, a, grid, s) : prep_coef_types<uint16_t, false>(c, a, grid, s);
+  return a.rot ? launch_prep_coef_rot(c, a, grid, s) : prep_coef_of(c, a, grid, s);
 }
 
 hipError_t launch_prep_start(const GatherCfg& c, PrepStartArgs& a, bool split, hipStream_t s) {
@@ -922,8 +954,7 @@ hipError_t launch_prep_start(const GatherCfg& c, PrepStartArgs& a, bool split, h
   blocks += (long long)a.basis_nx * ((a.B + 31) / 32);
   if (blocks != prep_start_blocks(a) || blocks > kPrepStartMaxBlocks) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, 1, 1);
-  if (split) return c.idx_u32 ? prep_start_types<uint32_t, true>(c, a, grid, s) : prep_start_types<uint16_t, true>(c, a, grid, s);
-  return c.idx_u32 ? prep_start_types<uint32_t, false>(c, a, grid, s) : prep_start_types<uint16_t, false>(c, a, grid, s);
+  return a.rot ? launch_prep_start_rot(c, a, split, grid, s) : prep_start_of(c, a, split, grid, s);
 }
 
 hipError_t launch_prep_dense(const float* coef, uint4* cf, uint4* cf_lo, int n_in, int n_out, hipStream_t s) {
@@ -971,5 +1002,7 @@ hipError_t launch_mfma(const MfmaArgs& a, int tile_m, int tile_n, dim3 grid, hip
   }
   return hipGetLastError();
 }
+
+#endif
 
 }  // namespace kan
