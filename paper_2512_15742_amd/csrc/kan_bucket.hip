@@ -14,15 +14,16 @@
 // Inside a bucket the edges are ordered by output j, then input i.  A workgroup owns the
 // block of edges of a run of outputs and reads it flat, 512 edges per wave and pass (a lane holds
 // 8 consecutive ones: 16-byte loads whose addresses depend on nothing but the block's bounds); a
-// wave turns its products of a pass into running sums, and what a segment (the edges of one
-// output) has of them is the difference at its two ends.  Two ways: blocks of up to 17 passes
+// wave turns its products of a pass into running sums that start anew with every segment (the edges
+// of one output), so what a segment has of the pass stands at its last edge and holds nothing of its
+// neighbours: neither their rounding nor their overflow, infinities and NaN.  (As differences of running
+// sums over the whole pass, an output next to one of a thousand times its terms was off by 5e-6 to 2e-5
+// of its own.)  Two ways: blocks of up to 17 passes
 // (batch 1 to 2 on a layer of two million edges) keep the running sums of all of them and add after one barrier;
 // in larger blocks each of the 16 waves takes a sixteenth of the passes and adds pass by pass
 // without any barrier.  A segment that reaches into several waves' runs is put
 // together at the end in the order of the waves, the per-bucket sums are added by the fixed-order
-// reduction kernel or by the next bucket layer itself: reproducible bits.  (The one exception is
-// the side path for non-finite products - a codeword holding Inf or NaN that an edge refers to -
-// whose results are non-finite whatever the order.)
+// reduction kernel or by the next bucket layer itself: reproducible bits.
 // The bias of an edge needs no lookup at all: the four bases sum to 1 on [-1,1], so
 // sum_i bias_ij is a per-output constant computed at preparation time.
 //
@@ -83,6 +84,14 @@ __device__ __forceinline__ float dpp_add(float v) {
   return v + __int_as_float(moved);
 }
 
+__device__ __forceinline__ float masked(float v, uint32_t m) { return __uint_as_float(__float_as_uint(v) & m); }
+
+// What another lane holds; 0 where there is no such lane.
+template <int CTRL>
+__device__ __forceinline__ float dpp_moved(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
 __device__ __forceinline__ float wave_sum_to_last_lane(float v) {
   v = dpp_add<0xB1, 0xf>(v);       // quad_perm [1,0,3,2]: neighbours
   v = dpp_add<0x4E, 0xf>(v);       // quad_perm [2,3,0,1]: every lane holds its quad's sum
@@ -106,14 +115,19 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   // block-floating-point rows (a power of two of them per bucket: 4096 or 2048)
   constexpr int kCbStride = CODE == kCbBfp8 ? kCbBytes / 20 * 12 : kCbBytes;
   constexpr int kXPerThread = MAXIN / kBucketThreads;
+  constexpr int kWindow = CODE == kCbF32 ? 4 : (CODE == kCbF16 ? 3 : 2);      // dwords that hold four entries of a row
+  constexpr int kWinWords = CODE == kCbBfp8 ? 3 : kWindow;
   constexpr int kCbPerThread = (kCbBytes / 16 + kBucketThreads - 1) / kBucketThreads;   // 16-byte units per thread
   __shared__ __attribute__((aligned(16))) uint32_t cb[kCbBytes / 4 + 8];   // + 16 bytes read-ahead, + 16 spare
   __shared__ float4 bas[MAXIN];             // {w0, w1, w2, span as integer bits}; w3 = 1 - w0 - w1 - w2
-  __shared__ __attribute__((aligned(16))) float prod[kWaves + 1][kPass];   // running sums of the products of a wave's pass (and of a 17th)
+  // running sums of the products of a wave's pass (and of a 17th): of each lane's eight, and at the end of each lane of all before it
+  __shared__ __attribute__((aligned(16))) float prod[kWaves + 1][kPass];
+  __shared__ float upto[kWaves + 1][kWave];
   __shared__ float res[kBucketMaxJw];           // sums of this workgroup's segments: what the wave in whose run a segment begins has of it ...
   __shared__ uint32_t segl[kBucketMaxJw + 1];   // first edge of every segment of the block (+ end)
   __shared__ __attribute__((aligned(16))) float head_sum[kWaves];            // ... and what each wave has of the segment that began before its run
   __shared__ __attribute__((aligned(16))) int head_seg[kWaves];              // (-1: none did)
+  __shared__ uint32_t starts[kWaves + 1][kPass / 32];                        // a bit per edge of prod: the first of its segment
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -133,6 +147,11 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   constexpr int kGainBytes = gb_bytes(GK);
   const Q8Params qp = {H.gain_log2_lo, H.gain_log2_step, 0.f};
 
+  // No segment starts yet.  The barrier waits beside the scalar loads above, which everything below needs (behind the
+  // vector loads the waves would wait until the address units have taken the last wave's, 0.4 us).
+  if (tid < (kWaves + 1) * (kPass / 32)) starts[0][tid] = 0u;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
 
   // Loads are issued in the order their data is needed (they return in order): the inputs
   // of the sample, the codebook bucket, the segment table; then, after the basis table has
@@ -253,6 +272,8 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   }
   segl[min(tid, njw)] = sv0;
   segl[min(tid + kBucketThreads, njw)] = sv1;
+  static_assert(kBucketMaxJw <= kBucketThreads, "a thread per segment");
+  if (one_pass && tid < njw && sv0 < blk_hi) atomicOr(&starts[0][(sv0 - base) >> 5], 1u << ((sv0 - base) & 31u));
   for (int t = tid; t < njw; t += kBucketThreads) res[t] = 0.f;
   if (lane == 0) head_sum[wave] = 0.f;
   __syncthreads();
@@ -264,129 +285,136 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   static_assert(kBucketMaxJw <= kWave * 16, "two rounds find a segment");
   const uint32_t start = max(w_lo, blk_lo);
   const uint32_t sixteenth = segl[min((lane + 1) * 16, njw)];
-  auto find_segment = [&] {        // (rounds of 64 and 16 lanes over at most 1024; behind the first products, whose LDS reads take longer)
-    seg_now = 16 * (int)__popcll(__ballot((lane + 1) * 16 <= njw && sixteenth <= start));
-    seg_now += (int)__popcll(__ballot(lane < 16 && seg_now + lane < njw && segl[min(seg_now + lane + 1, njw)] <= start));
+  auto find_segment = [&] {        // (rounds of 64 and 16 lanes over at most 1024)
+    seg_now = 16 * (int)__popcll(__builtin_amdgcn_ballot_w64((lane + 1) * 16 <= njw && sixteenth <= start));
+    seg_now += (int)__popcll(__builtin_amdgcn_ballot_w64(lane < 16 && seg_now + lane < njw && segl[min(seg_now + lane + 1, njw)] <= start));
     head = seg_now < njw && segl[min(seg_now, njw)] < start ? seg_now : -1;
   };
-  // running sums of the products of the lane's 8 edges of pass p -> strip
-  auto products = [&](const PassRegs<GK>& c, int p, float* strip) {
-    // edge e belongs to the wave's run iff blk_lo <= e < w_hi, i.e. (e - blk_lo) < (w_hi - blk_lo) unsigned
-    const uint32_t rel0 = w_lo + (uint32_t)p * kPass + (uint32_t)lane * kEpt - blk_lo, len = w_hi - blk_lo;
-    float pr[kEpt];
+  const int lanes_to_row = lane & 16 ? (lane & 15) + 1 : kWave, lanes_to_half = lane & 32 ? lane - 31 : kWave;
+  // Running sums of the products of the lane's 8 edges, anew from every segment's first edge (bit u of f: the lane's edge
+  // u is one) -> prod[strip], and of all the lanes' up to this one's last edge, anew likewise -> upto[strip].  Edges outside the block (groups that straddle its ends, re-read groups) are looked up like the
+  // others: what they give, numbers or not, stands in front of the block's first segment or behind its last.
+  auto products = [&](const PassRegs<GK>& c, const uint32_t f, const int strip) {
+    float4 w[kEpt];
+    uint32_t at[kEpt], win[kEpt][kWinWords];
+    auto read_basis = [&](int u0) {
 #pragma unroll
-    for (int u = 0; u < kEpt; ++u) pr[u] = 0.f;
-    // Groups wholly outside the block (past its end in the last pass) skip the lookups.  The
-    // group holds an edge of the block iff rel0 + u < len for some u in 0..7; rel0 is "negative"
-    // (wrapped, -7..-1) only for the group that straddles the block's start, and adding 7 to
-    // both sides covers that case as well.
-    if (rel0 + (uint32_t)(kEpt - 1) < len + (uint32_t)(kEpt - 1)) {
+      for (int u = u0; u < u0 + kEpt / 2; ++u) w[u] = bas[u16_of(c.i, u)];
+    };
+    auto read_window = [&](int u0) {
 #pragma unroll
-    for (int u = 0; u < kEpt; ++u) {
-      const float4 w = bas[u16_of(c.i, u)];
-      const uint32_t at = u16_of(c.q, u) * (CODE == kCbBfp8 ? 12u : 10u) + __float_as_uint(w.w);
-      float c0, c1, c2, c3;
-      if constexpr (CODE == kCbI8 || CODE == kCbBfp8) {
-        // bytes at .. at+3 of the bucket: two aligned dwords, funnel-shifted; q + 128 as
-        // unsigned bytes (the differences below do not see the offset)
-        const uint32_t lo = cb[at >> 2], hi = cb[(at >> 2) + 1];
-        const uint32_t win = __builtin_amdgcn_alignbyte(hi, lo, at & 3u) ^ 0x80808080u;
-        c0 = (float)(win & 0xffu);
-        c1 = (float)((win >> 8) & 0xffu);
-        c2 = (float)((win >> 16) & 0xffu);
-        c3 = (float)(win >> 24);
-      } else if constexpr (CODE == kCbF16) {
-        // halves at .. at+3 of the bucket (8 bytes from byte 2 * at): three aligned dwords,
-        // funnel-shifted by 0 or 2 bytes
-        const uint32_t d = at >> 1, sh = (at & 1u) * 2u;
-        const uint32_t w0 = __builtin_amdgcn_alignbyte(cb[d + 1], cb[d], sh);
-        const uint32_t w1 = __builtin_amdgcn_alignbyte(cb[d + 2], cb[d + 1], sh);
-        c0 = half_bits_to_float(w0 & 0xffffu);
-        c1 = half_bits_to_float(w0 >> 16);
-        c2 = half_bits_to_float(w1 & 0xffffu);
-        c3 = half_bits_to_float(w1 >> 16);
-      } else {
-        const float* cf = (const float*)cb;
-        c0 = cf[at];
-        c1 = cf[at + 1];
-        c2 = cf[at + 2];
-        c3 = cf[at + 3];
+      for (int u = u0; u < u0 + kEpt / 2; ++u) {
+        at[u] = u16_of(c.q, u) * (CODE == kCbBfp8 ? 12u : 10u) + __float_as_uint(w[u].w);
+        // bytes at .. at+3 (halves at .. at+3, floats at .. at+3) of the bucket lie in two (three, four) aligned dwords
+        const uint32_t d = CODE == kCbF32 ? at[u] : (CODE == kCbF16 ? at[u] >> 1 : at[u] >> 2);
+#pragma unroll
+        for (int n = 0; n < kWindow; ++n) win[u][n] = cb[d + n];
+        if constexpr (CODE == kCbBfp8) win[u][2] = cb[u16_of(c.q, u) * 3u + 2u];      // the row's own power of two
       }
-      // sum_k w_k c_k with w3 = 1 - w0 - w1 - w2 (the bases sum to 1)
-      float s = (CODE == kCbI8 || CODE == kCbBfp8) ? c3 - 128.0f : c3;
-      s = fmaf(w.z, c2 - c3, s);
-      s = fmaf(w.y, c1 - c3, s);
-      s = fmaf(w.x, c0 - c3, s);
-      if constexpr (CODE == kCbBfp8) s *= bfp8_row_scale(cb[u16_of(c.q, u) * 3u + 2u]);     // the row's own power of two
-      // Edges outside the block (groups that straddle its ends, re-read groups) contribute
-      // an exact zero rather than gain * s, so that a non-finite codeword which no edge of
-      // the block refers to cannot reach a sum.
-      pr[u] = (rel0 + (uint32_t)u < len) ? gain_of<GK>(c, u, qp) * s : 0.f;
-    }
-    }
-    float sums[kEpt];                     // running sums of the lane's eight products
-    sums[0] = pr[0];
+    };
+    float sums[kEpt];
+    auto add_products = [&](int u0) {
 #pragma unroll
-    for (int u = 1; u < kEpt; ++u) sums[u] = sums[u - 1] + pr[u];
-    // A running sum would carry a non-finite product (a codeword with an Inf or NaN that an
-    // edge does refer to) into the segments behind it: such products go to their own segment
-    // only.  The lane's total is finite iff all its eight products are.
-    if (!__builtin_isfinite(sums[kEpt - 1])) {
-      float keep = 0.f;
-#pragma unroll
-      for (int u = 0; u < kEpt; ++u) {
-        if (__builtin_isfinite(pr[u])) {
-          keep += pr[u];
+      for (int u = u0; u < u0 + kEpt / 2; ++u) {
+        float c0, c1, c2, c3;
+        if constexpr (CODE == kCbI8 || CODE == kCbBfp8) {
+          // funnel-shifted; q + 128 as unsigned bytes (the differences below do not see the offset)
+          const uint32_t v = __builtin_amdgcn_alignbyte(win[u][1], win[u][0], at[u] & 3u) ^ 0x80808080u;
+          c0 = (float)(v & 0xffu);
+          c1 = (float)((v >> 8) & 0xffu);
+          c2 = (float)((v >> 16) & 0xffu);
+          c3 = (float)(v >> 24);
+        } else if constexpr (CODE == kCbF16) {
+          const uint32_t sh = (at[u] & 1u) * 2u;        // funnel-shifted by 0 or 2 bytes
+          const uint32_t w0 = __builtin_amdgcn_alignbyte(win[u][1], win[u][0], sh);
+          const uint32_t w1 = __builtin_amdgcn_alignbyte(win[u][2], win[u][1], sh);
+          c0 = half_bits_to_float(w0 & 0xffffu);
+          c1 = half_bits_to_float(w0 >> 16);
+          c2 = half_bits_to_float(w1 & 0xffffu);
+          c3 = half_bits_to_float(w1 >> 16);
         } else {
-          const uint32_t e = rel0 + (uint32_t)u + blk_lo;     // its segment: segl[jj] <= e < segl[jj + 1]
-          int lo_j = 0, hi_j = njw;
-          while (hi_j - lo_j > 1) {
-            const int mid = (lo_j + hi_j) >> 1;
-            if (segl[mid] <= e) lo_j = mid; else hi_j = mid;
-          }
-          atomicAdd(&res[lo_j], pr[u]);
+          c0 = __uint_as_float(win[u][0]);
+          c1 = __uint_as_float(win[u][1]);
+          c2 = __uint_as_float(win[u][2]);
+          c3 = __uint_as_float(win[u][3]);
         }
-        sums[u] = keep;
+        // sum_k w_k c_k with w3 = 1 - w0 - w1 - w2 (the bases sum to 1)
+        float s = (CODE == kCbI8 || CODE == kCbBfp8) ? c3 - 128.0f : c3;
+        s = fmaf(w[u].z, c2 - c3, s);
+        s = fmaf(w[u].y, c1 - c3, s);
+        s = fmaf(w[u].x, c0 - c3, s);
+        if constexpr (CODE == kCbBfp8) s *= bfp8_row_scale(win[u][2]);
+        const uint32_t go = (uint32_t)__builtin_amdgcn_sbfe((int)~f, u, 1);      // all ones unless the edge starts a segment
+        sums[u] = u > 0 ? fmaf(gain_of<GK>(c, u, qp), s, masked(sums[u - 1], go)) : gain_of<GK>(c, u, qp) * s;
       }
-    }
-    float v = sums[kEpt - 1];            // inclusive scan of the lanes' totals over the wave
-    v = dpp_add<0x111, 0xf>(v);          // row_shr 1, 2, 4, 8: within rows of 16 lanes
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);          // row_bcast 15: rows 1 and 3 add the total of the row before
-    v = dpp_add<0x143, 0xc>(v);          // row_bcast 31: rows 2 and 3 add the total of the first half
-    const float before = __shfl_up(v, 1, 64);
-    const float ex = lane == 0 ? 0.f : before;
-    ((float4*)strip)[lane * 2] = make_float4(sums[0] + ex, sums[1] + ex, sums[2] + ex, sums[3] + ex);
-    ((float4*)strip)[lane * 2 + 1] = make_float4(sums[4] + ex, sums[5] + ex, sums[6] + ex, sums[7] + ex);
+    };
+    // Four edges' reads are in flight beside four edges' arithmetic.  Left to itself the compiler made it an LDS round trip
+    // per edge (2048 x 1024 at batch 1 10.0 against 9.6 us); two trips for all eight, or two or one edge at a time, are
+    // slower by 1-4 %.
+    read_basis(0);
+    __builtin_amdgcn_sched_barrier(0);
+    read_window(0);
+    read_basis(kEpt / 2);
+    __builtin_amdgcn_sched_barrier(0);
+    add_products(0);
+    read_window(kEpt / 2);
+    add_products(kEpt / 2);
+    // Inclusive scan of the lanes' last sums over the wave.  A lane in which a segment starts takes nothing from the lanes
+    // before it; `open` is how many lanes back the nearest such lane is (this one: 0; none among 32: 32).
+    float v = sums[kEpt - 1];
+    const uint32_t back = (uint32_t)((__builtin_amdgcn_ballot_w64(f != 0u) << (kWave - 1 - lane)) >> 32);
+    const int open = back != 0u ? __builtin_clz(back) : 32;
+    auto add = [&](float moved, int lanes) { v += open >= lanes ? moved : 0.f; };
+    add(dpp_moved<0x111>(v), 1);         // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    add(dpp_moved<0x112>(v), 2);
+    add(dpp_moved<0x114>(v), 4);
+    add(dpp_moved<0x118>(v), 8);
+    add(dpp_moved<0x142>(v), lanes_to_row);      // row_bcast 15: rows 1 and 3 add the sum of the row before
+    add(dpp_moved<0x143>(v), lanes_to_half);     // row_bcast 31: rows 2 and 3 add the sum of the first half
+    upto[strip][lane] = v;
+    ((float4*)prod[strip])[lane * 2] = make_float4(sums[0], sums[1], sums[2], sums[3]);
+    ((float4*)prod[strip])[lane * 2 + 1] = make_float4(sums[4], sums[5], sums[6], sums[7]);
   };
+  // What the segment of edges [lo, hi) of that strip has.
+  auto piece = [&](const int strip, uint32_t lo, uint32_t hi) {
+    const uint32_t l = (hi - 1u) / kEpt;
+    const float own = prod[strip][hi - 1u], before = upto[strip][l > 0u ? l - 1u : 0u];
+    return lo < l * kEpt ? own + before : own;
+  };
+  auto starts_of_lane = [&](int strip) { return (uint32_t)((const uint8_t*)starts[strip])[lane]; };
 
-  // What the segments have of pass p, a lane per segment; the bounds of the first 64 are read ahead of the products.
-  auto pass = [&](const PassRegs<GK>& c, int p) {
-    float* const strip = prod[wave];
+  // What the segments have of pass p, a lane per segment; the bounds of the first 64 are read ahead.
+  uint32_t s0 = 0u, s1 = 0u;
+  auto read_bounds = [&] {
+    s0 = segl[min(seg_now + lane, njw)];
+    s1 = segl[min(seg_now + lane + 1, njw)];
+  };
+  auto pass = [&](PassRegs<GK>& c, int p) {
+    uint32_t* const st = starts[wave];
     const uint32_t pa = w_lo + (uint32_t)p * kPass, pe = min(pa + (uint32_t)kPass, w_hi);
-    uint32_t s0 = segl[min(seg_now + lane, njw)], s1 = segl[min(seg_now + lane + 1, njw)];
-    products(c, p, strip);
-    if (p == 0) {
-      find_segment();
-      s0 = segl[min(seg_now + lane, njw)];
-      s1 = segl[min(seg_now + lane + 1, njw)];
+    if (lane < kPass / 32) st[lane] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t from = s0;
+    for (int jj = seg_now + lane;;) {          // (64 segments that start before the pass ends: there may be more)
+      const bool before_end = jj < njw && from < pe;
+      if (before_end && from > pa) atomicOr(&st[(from - pa) >> 5], 1u << ((from - pa) & 31u));
+      if (__popcll(__builtin_amdgcn_ballot_w64(before_end)) < kWave) break;
+      jj += kWave;
+      from = segl[min(jj, njw)];
     }
+    __builtin_amdgcn_wave_barrier();
+    products(c, starts_of_lane(wave), wave);
+    load_pass(c, p + 2);
     __builtin_amdgcn_wave_barrier();
     for (;;) {
       const int jj = seg_now + lane;
       const uint32_t lo = max(s0, pa), hi = min(s1, pe);
-      if (jj < njw && lo < hi) {
-        const float upto = strip[hi - 1 - pa], from = strip[lo > pa ? lo - 1 - pa : 0];
-        // (one wave adds to an element, in the order of its passes)
-        atomicAdd(jj == head ? &head_sum[wave] : &res[jj], lo > pa ? upto - from : upto);
-      }
-      const int ended = (int)__popcll(__ballot(jj < njw && s1 <= pe));
+      // (one wave adds to an element, in the order of its passes)
+      if (jj < njw && lo < hi) atomicAdd(jj == head ? &head_sum[wave] : &res[jj], piece(wave, lo - pa, hi - pa));
+      const int ended = (int)__popcll(__builtin_amdgcn_ballot_w64(jj < njw && s1 <= pe));
       seg_now += ended;
+      read_bounds();
       if (ended < kWave) break;
-      s0 = segl[min(seg_now + lane, njw)];
-      s1 = segl[min(seg_now + lane + 1, njw)];
     }
     __builtin_amdgcn_wave_barrier();
   };
@@ -395,17 +423,17 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
     // The strips lie behind one another, so a thread can take a segment's sum from the strips of all waves, without the
     // search for the segments of a run: 1500 x 1100, K = 20,000, batch 1 (segments of 500 edges, a wave's run) 13.1 -> 11.5 us;
     // 2048 x 1024 x 256 at batch 1, whose first layer's blocks are 16 passes and a little, 13.8 -> 12.0 with the 17th strip.
-    if (n_pass > 0) products(A, 0, prod[wave]);
-    if (n_pass > kWaves) products(B, kWaves, prod[kWaves]);
+    if (n_pass > 0) products(A, starts_of_lane(wave), wave);
+    if (n_pass > kWaves) products(B, starts_of_lane(kWaves), kWaves);
   } else {
     // two passes are always in flight: a slot is refilled as soon as it has been consumed
     // (after the last pass the refills are harmless re-reads)
+    find_segment();
+    read_bounds();
     for (int p = 0; p < n_pass; p += 2) {
       pass(A, p);
-      load_pass(A, p + 2);
       if (p + 1 >= n_pass) break;
       pass(B, p + 1);
-      load_pass(B, p + 3);
     }
     if (lane == 0) head_seg[wave] = head;
   }
@@ -416,7 +444,7 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
     float sum = head_sum[lane & (kWaves - 1)];
     const int other = __shfl_up(seg_of, 1, 64);
     const bool first = lane == 0 || seg_of != other;
-    if (__ballot(seg_of >= 0 && !first) != 0) {  // a segment that takes up whole runs
+    if (__builtin_amdgcn_ballot_w64(seg_of >= 0 && !first) != 0) {  // a segment that takes up whole runs
       const int own = __float_as_int(sum);
       sum = 0.f;
 #pragma unroll
@@ -428,12 +456,12 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   if (!one_pass && njw > kWave) __syncthreads();  // (else the same wave reads them)
   // a segment's sum where the passes are at most 17
   auto sum_of_strips = [&](int t) {
-    const float* const flat = prod[0];
-    const uint32_t lo = max(segl[t], base) - base, hi = segl[t + 1] - base;
+    const uint32_t lo = segl[t] - base, hi = segl[t + 1] - base;
     if (lo >= hi) return 0.f;
-    float sum = flat[hi - 1];
-    for (uint32_t w = lo / kPass; w < (hi - 1) / kPass; ++w) sum += prod[w][kPass - 1];
-    return lo % kPass ? sum - flat[lo - 1] : sum;
+    const uint32_t last = (hi - 1u) / kPass, at = last * kPass;
+    float sum = piece((int)last, max(lo, at) - at, hi - at);
+    for (uint32_t w = lo / kPass; w < last; ++w) sum += upto[w][kWave - 1];
+    return sum;
   };
 
   // ---- segment sums -> memory (coalesced): scale, bias sum (first bucket only), activation ----
@@ -677,12 +705,12 @@ __global__ __launch_bounds__(256) void kan_prepare_fill_kernel(const IdxT* __res
         tgo[(size_t)j * n_in + i0 + r] = tg[r * kPrepareCols + c];
       }
       const uint32_t b = min(id >> rows_shift, (uint32_t)(n_buckets - 1));
-      unsigned long long todo = __ballot(live);
+      unsigned long long todo = __builtin_amdgcn_ballot_w64(live);
       uint32_t pos = 0;
       while (todo) {                                         // one round per bucket present among the 64 rows
         const int first = __ffsll((long long)todo) - 1;
         const uint32_t kb = __shfl(b, first);
-        const unsigned long long same = __ballot(live && b == kb) & todo;
+        const unsigned long long same = __builtin_amdgcn_ballot_w64(live && b == kb) & todo;
         const uint32_t start = wbase[kb];
         if (live && b == kb) pos = start + (uint32_t)__popcll(same & lt);
         __builtin_amdgcn_wave_barrier();
