@@ -407,7 +407,11 @@ LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
 // gather rate of the CUs' address units, so every CU should be busy: i is split while the
 // partial sums stay below the size of the parameter stream.
 // compact: the smaller partial sums of the first count of chunks, for calls that fit the static scratch only so.
-LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool f32, bool compact) {
+// reduced: nobody but a launch of kan_reduce adds the slices (the last layer, or one whose successor does not take them).
+// The launch and its pass over the sums are then part of what a cut costs; in the units of cost_of below:
+constexpr double kFusedReduceSteps = 1.0, kFusedReduceStepsHalf = 2.8;
+LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool f32, bool compact,
+                     bool reduced) {
   LayerPlan p;
   p.mfma = false;
   p.kind = f32 ? kPlanFused32 : kPlanFused16;
@@ -443,9 +447,9 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
     resident = (kFusedMinWgsPerHead + per_head - 1) / per_head;
     if (chunks < resident) chunks = resident;
   }
-  // At least two steps each; the precise form, whose steps are longer, takes single ones while the matrix-core kernels
-  // still take that many slices as they are (500-128-64-10 at batch 37 43.5 -> 37 us; in the fp16 form 4096 x 64 at
-  // batch 24 loses, 11.4 -> 13.4).
+  // At least two steps each; the precise form, whose steps are longer, takes single ones up to kMaxChainedSlices of
+  // them, with a reduction behind them too (500-128-64-10 at batch 37, every layer reduced, 43.5 -> 37 us; in the fp16
+  // form 4096 x 64 at batch 24 loses, 11.4 -> 13.4).
   // (rounded down, which leaves chunks of three steps, where a reduction follows: 1000-333-21 fp16 at batch 37 26.4 us, 26.6
   // with more slices; 22.7 against 26.2 at batch 24, whose next layer adds them itself)
   long long max_by_rows = compact || (!f32 && p.cfg.bt == 64) ? n_in / 16 : (n_in + 15) / 16;
@@ -470,9 +474,9 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
     return per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.5) + 1.28e-4 * (double)(wgs * p.cfg.bt);
   };
   int per = (int)((steps + chunks - 1) / chunks);
+  const int planned = per;
   const long long wgs = base * ((steps + per - 1) / per), rounds = (wgs + kCUs - 1) / kCUs;
   if (!compact && rounds > 1 && rounds * kCUs * 8 > wgs * 9) {
-    const int planned = per;
     const long long most = std::min(max_by_rows, max_by_bytes);
     for (long long r = rounds - 1; r <= 2 * rounds; ++r) {
       const long long want = r * kCUs / base;
@@ -480,6 +484,17 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
       const int other = (int)((steps + want - 1) / want);
       if (cost_of(other) < cost_of(per) && cost_of(other) < 0.9 * cost_of(planned)) per = other;
     }
+  }
+  // A cut that only a reduction launch undoes, against none (whole us, one chunk / cut):
+  //   precise  24 x 21 at batch 37 10.9 / 7.9,  26 x 684, 12 heads, at 34 14.5 / 12.5,  25 x 217, 8 heads, at 40 14.3 / 11.5,
+  //            31 x 3724, 7 heads, at 48 15.8 / 21.3,  21 x 303, 39 heads, at 54 12.1 / 15.7,  73 x 1749, 21 heads, at 45 45.9 / 49.9
+  //   fp16     24 x 128 at 16 5.3 / 6.1,  25 x 727 at 31 7.4 / 6.9,  31 x 327, 35 heads, at 30 8.0 / 9.1,
+  //            30 x 3297, 8 heads, at 10 8.0 / 9.9,  147 x 866, 46 heads, at 36 37.5 / 44.4
+  if (!compact && reduced && resident == 1 && per < steps) {
+    const auto sums = [&](int q) { return 1.28e-4 * (double)(n_heads * (long long)p.n_jt * ((steps + q - 1) / q) * B); };
+    const auto work = [&](int q) { return q * std::max((double)((base * ((steps + q - 1) / q) + kCUs - 1) / kCUs), 1.5); };
+    const double whole = work(steps) + sums(steps), cut = work(per) + 2 * sums(per) + (f32 ? kFusedReduceSteps : kFusedReduceStepsHalf);
+    if (cut >= (planned == steps ? 0.9 : 1.0) * whole) per = steps;       // (0.9: as for the choice of rounds above)
   }
   p.rows_per_chunk = 8 * per;
   p.n_chunks = (steps + per - 1) / per;
@@ -498,8 +513,15 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // single step for up to kFusedWaveStepBytes of partial sums, beyond which a caller's workspace would grow with them.
 // (Eight waves to a workgroup for half the slices: 2048-1024-256 at batch 16 30.2 against 28.6 us.)
 // compact: the smaller partial sums of the former rule, for calls that fit the static scratch only so.
+// reduced: nobody but a launch of kan_reduce adds the slices (as in plan_fused).  The launch takes about 2.7 us, in units
+// of the cost above: 3.3 where a CU has one workgroup, of 16 samples at most, 2.0 with the longer steps of more samples, 1.3
+// where one chunk is several rounds of workgroups.  One chunk / cut, us: 32 x 128 at batch 4 / 16 / 31 4.7 / 5.4, 4.8 / 5.7,
+// 6.6 / 6.8, 48 x 128 6.3 / 5.5, 6.5 / 5.7, 9.2 / 6.8; several heads: 34 x 387, 13 of them, at 16 7.2 / 8.0; 38 x 1139, 8, at 4
+// 6.9 / 7.8; 48 x 512, 20, at 16 6.8 / 9.6; 64 x 669, 21, at 8 8.0 / 9.9; 82 x 2736, 19, at 24 46.0 / 47.2; 72 x 385, 47, at 5
+// 14.9 / 13.9; 97 x 1650, 13, at 8 19.0 / 18.0.
 constexpr long long kFusedWaveStepBytes = 512 * 1024;
-LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool compact) {
+LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool compact,
+                          bool reduced) {
   LayerPlan p;
   p.mfma = false;
   p.kind = kPlanFusedWave;
@@ -517,12 +539,14 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   if ((long long)steps * n_heads * B * n_out * 4 > kFusedWaveStepBytes) max_by_count = std::min<long long>(max_by_count, (steps + 1) / 2);
   if (compact) max_by_count = std::min<long long>(n_in / (2 * kFusedWaveStep), (kTargetWorkgroups + base - 1) / base);
   const long long most = std::max(1ll, std::min({max_by_count, max_by_bytes, (long long)steps}));
+  const double reduction = !reduced ? 0.0 : (base > kCUs ? 1.3 : (B > 16 ? 2.0 : 3.3));
   double least = 0;
-  for (int per_cu = 1; per_cu <= 8; ++per_cu) {          // the fewest steps with at most so many workgroups on a CU
+  for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
     const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, 1, most);
     const int per = (int)((steps + want - 1) / want), chunks = (steps + per - 1) / per;
     const long long wgs = base * chunks;
-    const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B);
+    const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B) +
+                        (chunks > 1 ? reduction : 0.0);
     if (least > 0 && cost >= least) continue;
     least = cost;
     p.rows_per_chunk = per * kFusedWaveStep;
@@ -614,7 +638,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) would keep the fused kernel up to
 //     kFusedTwoTilesMaxBatch on either path; its plan is what they report, make_wide what they run.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
-                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true) {
+                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
   const bool half_path = path == KAN_PATH_MFMA || (path == KAN_PATH_AUTO && B >= kAutoMfmaBatch);
@@ -631,7 +655,7 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
     if (B <= fused_max) {
-      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows);
+      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
       if (wide) make_wide(p, L.in, L.out, B, n_heads, false);
       return p;
     }
@@ -643,11 +667,11 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide);
   const long long edges = (long long)L.in * L.out;
   if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) {
-    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows);
+    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true);
     return p;
   }
-  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows);
+  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows, reduced);
   return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok);
 }
 
@@ -1055,7 +1079,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
   *ws = WsLayout();
   ws->n_layers = n_layers;
   plans->clear();
-  for (int l = 0; l < n_layers; ++l) {
+  auto plan_of = [&](int l, bool reduced) {
     const kan_vq_layer& R = layers[l];
     bool vec_ok = true, prepared_ok = true, column_ok = true;
     for (int h = 0; h < n_heads; ++h) {
@@ -1063,8 +1087,22 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    LayerPlan p = plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? plans->back().n_chunks : 1, min_rows, wide);
-    plans->push_back(p);
+    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced);
+  };
+  for (int l = 0; l < n_layers; ++l) plans->push_back(plan_of(l, false));
+  // Layers whose slices a reduction launch adds, where that is known: whole where that is faster, unless the layer
+  // would then no longer take its predecessor's slices.
+  auto hands_on = [&](int l) { return hand_on && chained(*plans, l, n_heads, layers, B); };
+  for (int l = n_layers - 1; l >= 0; --l) {
+    if ((*plans)[l].n_chunks <= 1 || hands_on(l)) continue;
+    const LayerPlan cut = (*plans)[l];
+    const bool takes = hands_on(l - 1);
+    (*plans)[l] = plan_of(l, true);
+    if (takes && !hands_on(l - 1)) (*plans)[l] = cut;
+  }
+  for (int l = 0; l < n_layers; ++l) {
+    const kan_vq_layer& R = layers[l];
+    const LayerPlan& p = (*plans)[l];
     auto grow = [](size_t& dst, size_t v) { if (v > dst) dst = v; };
     grow(l & 1 ? ws->partial2 : ws->partial, partial_bytes(p, R.out, B, group));
     ws->cf_off.push_back(ws->cf);
@@ -1080,7 +1118,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
     }
     if (l + 1 < n_layers) grow(ws->hidden, round_up((size_t)n_heads * (size_t)B * R.out * sizeof(float), 256));
   }
-  for (int l = 0; l < n_layers; ++l) ws->handed.push_back(hand_on && chained(*plans, l, n_heads, layers, B));
+  for (int l = 0; l < n_layers; ++l) ws->handed.push_back(hands_on(l));
   if (std::find(ws->handed.begin(), ws->handed.end(), 1) == ws->handed.end()) {      // one buffer does for all
     ws->partial = std::max(ws->partial, ws->partial2);
     ws->partial2 = 0;
