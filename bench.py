@@ -289,7 +289,7 @@ def sweep(kb, torch, synth):
         vq_rows("config5 4096->4096 K=262144 " + variant, [ps], x, both[1:], 3)
 
 
-MAIN_KERNELS = ("kan_gather", "kan_mfma", "kan_fused", "kan_bucket", "kan_column")
+MAIN_KERNELS = ("kan_gather", "kan_mfma", "kan_wide", "kan_stream", "kan_fused", "kan_bucket", "kan_column")
 
 
 def roofline_of(kt, lps, layer_edges, layer_meta, B, facts, workload, extra_param_bytes=0):
@@ -301,7 +301,7 @@ def roofline_of(kt, lps, layer_edges, layer_meta, B, facts, workload, extra_para
     avg_s = kt[dom]["avg_us"] * 1e-6
     edges = per_launch(layer_edges, dom, lps[dom])
     family = dom.split("@")[0]
-    is_mfma = family.startswith(("kan_mfma", "kan_fused"))
+    is_mfma = family.startswith(("kan_mfma", "kan_wide", "kan_stream", "kan_fused"))
     traffic, tsrc = traffic_of(facts, workload, B, dom)
     if B > 64:
         flops = edges * (B * FLOP_PER_EDGE_EVAL + FLOP_PER_EDGE_RECON)
@@ -528,7 +528,7 @@ def config3_legs(kb, torch, synth, args, path, facts, with_cpu):
 
 
 def dtype_of(r):
-    return "f16" if r["roofline"]["kernel"].startswith(("kan_mfma@", "kan_fused_f16")) else "f32"
+    return "f16" if r["roofline"]["kernel"].startswith(("kan_mfma@", "kan_wide@", "kan_stream@", "kan_fused_f16")) else "f32"
 
 
 def main():

@@ -80,21 +80,23 @@ typedef enum kan_dtype {
  *                    codeword-window gather per edge on the vector ALUs; from batch 2:
  *                    fused gather + matrix-core kernel (fp32 operands up to batch 32; from
  *                    33 coefficients and basis weights split into high and low fp16 parts,
- *                    three products, fp32-grade sums); from batch 65 (129 for layers of
- *                    2^22 edges or more whose codebook is not fp32): the kernels of the fp16
- *                    path on such split operands (layers of a million edges and more, heads
- *                    of a launch together, up to batch 768: a kernel that gathers and
- *                    dequantises its own coefficients for tiles of 128 or 256 samples).
- *                    Prepared layers (see kan_vq_prepare),
+ *                    three products, fp32-grade sums); from batch 65: the kernels of the
+ *                    fp16 path on such split operands (layers of a million edges and more,
+ *                    heads of a launch together, up to batch 768: a kernel that gathers and
+ *                    dequantises its own coefficients for tiles of 128 or 256 samples; large
+ *                    products: tiles of 256 x 256).  Prepared layers (see kan_vq_prepare),
  *                    batch <= 4 (<= 3 for layers of 2^23 edges or more): codebook buckets
  *                    in LDS.
  *   KAN_PATH_MFMA    fp16 operands on the matrix cores, fp32 accumulation; ~3e-4
- *                    relative per layer (bound 2e-2).  Batch <= 64 (128 for those large
- *                    layers): fused gather + MFMA kernel; above: coefficients dequantised
- *                    once per call into the workspace in matrix-core operand order, then a
- *                    streaming contraction; layers of a million edges and more between batch
- *                    65 and 512 (1024 from 2^22 edges): coefficients dequantised by the
- *                    contraction itself for tiles of up to 512 samples.
+ *                    relative per layer (bound 2e-2).  Batch <= 64: fused gather + MFMA
+ *                    kernel; above: coefficients dequantised once per call into the workspace
+ *                    in matrix-core operand order, then a streaming contraction (large
+ *                    products: on tiles of 256 x 256); layers of a million edges and more
+ *                    between batch 65 and 512 (1024 from 2^22 edges): coefficients dequantised
+ *                    by the contraction itself for tiles of up to 512 samples.
+ *                    Either path, batch 65 to 128, layers of 2^22 edges or more whose codebook
+ *                    is not fp32: the kernel of batch 64 again where it fits the static
+ *                    scratch and the others, which need room for basis values, do not.
  *   KAN_PATH_AUTO    the precise path below batch 32, the fp16 path from there on.   */
 typedef enum kan_path { KAN_PATH_AUTO = 0, KAN_PATH_GATHER = 1, KAN_PATH_MFMA = 2 } kan_path;
 
@@ -325,7 +327,8 @@ kan_status kan_prof_begin(int32_t max_launches);
 kan_status kan_prof_end(kan_prof_record* out, int32_t cap, int32_t* n_out);
 
 const char* kan_status_string(int32_t status);
-/* Name of the kernel family the dispatcher would pick (for reports). */
+/* Name of the kernel family that a call of n_heads such layers runs (for reports); in a head of
+ * several layers the static scratch may decide otherwise.                                     */
 const char* kan_vq_planned_kernel(const kan_vq_layer* L, int64_t B, int32_t n_heads, int32_t path);
 const char* kan_dense_planned_kernel(int32_t in, int32_t out, int64_t B);
 

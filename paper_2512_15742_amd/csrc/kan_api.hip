@@ -318,6 +318,7 @@ bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool s
   p.kind = kPlanMfma;
   p.mfma = true;
   p.wide = true;
+  p.name = split3 ? "kan_wide_split" : "kan_wide";
   p.products = split3 ? 3 : 1;
   p.cfg.bt = tile;
   p.tile_n = kWideTileN;
@@ -359,6 +360,7 @@ bool make_stream(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool
     }
   }
   p.stream = true;
+  p.name = split3 ? "kan_stream_split" : "kan_stream";
   p.cfg.bt = kStreamTile;
   p.tile_n = kStreamTile;
   p.n_jt = n_jt;
@@ -635,8 +637,8 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //     contraction (small layers, on either path: coefficient preparation + one launch, plan_matrix);
 //   from batch 65, layers of a million edges and more: the contraction that gathers and dequantises its own
 //     coefficients (make_wide), large products the one on tiles of 256 x 256 (make_stream), either path;
-//   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) would keep the fused kernel up to
-//     kFusedTwoTilesMaxBatch on either path; its plan is what they report, make_wide what they run.
+//   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) keep the fused kernel up to
+//     kFusedTwoTilesMaxBatch on either path where make_wide does not take them.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
                   bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true) {
   const int code = code_of(L);
@@ -1128,8 +1130,11 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 
 // Finer chunks write more partial sums, a layer that hands its sums on keeps a second buffer of them: a call that fits the
 // library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.  Basis words
-// take room that the fused kernel does without: a call that would fit without the kernel of kan_wide.hip is planned to
-// fit, with that kernel where possible; one that would not is not slowed down to fit.
+// take room that the fused kernel does without, rotated ones of whole tiles of 256 samples more than those of kan_mfma.hip: a
+// call that would fit without the kernels of kan_wide.hip and kan_stream.hip is planned to fit, with the former where
+// possible; one that would not is not slowed down to fit.  The same plan serves callers who bring a workspace of their own:
+// what it needs does not depend on the entry point (65536 x 64 at batch 128: two tiles of the fused kernel in 8 MB; 200 x
+// 4095 at 7700: kan_mfma in 28.6 MB, kan_stream would take 34).
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
   kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, plans, ws);
@@ -1584,8 +1589,13 @@ kan_status kan_vq_coef_range(const kan_vq_layer* L, float* range, void* stream) 
 
 const char* kan_vq_planned_kernel(const kan_vq_layer* L, int64_t B, int32_t n_heads, int32_t path) {
   if (validate_layer(L) != KAN_OK || check_path(path) != KAN_OK || B < 1 || n_heads < 1) return "invalid";
-  return plan_vq(*L, B, n_heads < kMaxGroup ? n_heads : kMaxGroup, layer_vec_ok(*L), layer_prepared_ok(*L), path, layer_column_ok(*L))
-      .name;
+  // as a call of such layers is planned, its scratch included (a group of heads is as good as all of them)
+  const int group = n_heads < kMaxGroup ? n_heads : kMaxGroup;
+  const std::vector<kan_vq_layer> heads((size_t)group, *L);
+  std::vector<LayerPlan> plans;
+  WsLayout ws;
+  if (plan_head(heads.data(), 1, group, std::min<int64_t>(B, kMaxBatch), path, &plans, &ws) != KAN_OK) return "invalid";
+  return plans[0].name;
 }
 
 const char* kan_dense_planned_kernel(int32_t in, int32_t out, int64_t B) {

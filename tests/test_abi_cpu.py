@@ -193,8 +193,11 @@ def test_precise_path_switches_and_workspace_sizes():
     L = kb.lib()
     d = _desc(n_in=2048, n_out=1024, K=65536)
     assert L.kan_vq_planned_kernel(C.byref(d), 64, 1, kb.KAN_PATH_GATHER) == b"kan_fused_f32"
-    assert L.kan_vq_planned_kernel(C.byref(d), 65, 1, kb.KAN_PATH_GATHER) == b"kan_mfma_split"
-    assert L.kan_vq_planned_kernel(C.byref(d), 65, 1, kb.KAN_PATH_MFMA) == b"kan_mfma"
+    assert L.kan_vq_planned_kernel(C.byref(d), 65, 1, kb.KAN_PATH_GATHER) == b"kan_wide_split"      # a million edges and more
+    assert L.kan_vq_planned_kernel(C.byref(d), 65, 1, kb.KAN_PATH_MFMA) == b"kan_wide"
+    small = _desc(n_in=1024, n_out=512, K=65536)
+    assert L.kan_vq_planned_kernel(C.byref(small), 65, 1, kb.KAN_PATH_GATHER) == b"kan_mfma_split"
+    assert L.kan_vq_planned_kernel(C.byref(small), 65, 1, kb.KAN_PATH_MFMA) == b"kan_mfma"
     assert L.kan_dense_planned_kernel(2048, 1024, 16) == b"kan_dense"
     assert L.kan_dense_planned_kernel(2048, 1024, 17) == b"kan_dense_split"
     assert L.kan_dense_planned_kernel(2048, 1024, 0) == b"invalid"
@@ -283,7 +286,7 @@ def test_planner_accepts_every_shape_and_names_a_known_kernel():
     L = kb.lib()
     rng = np.random.default_rng(20251127)
     known = {b"kan_gather_bt1", b"kan_gather_bt4", b"kan_gather_bt16", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16",
-             b"kan_mfma", b"kan_mfma_split", b"kan_bucket"}
+             b"kan_mfma", b"kan_mfma_split", b"kan_wide", b"kan_wide_split", b"kan_stream", b"kan_stream_split", b"kan_bucket"}
     kinds = [(kb.KAN_F32, kb.KAN_F32), (kb.KAN_I8, kb.KAN_F16), (kb.KAN_I8, kb.KAN_F32), (kb.KAN_F16, kb.KAN_F16),
              (kb.KAN_I8, kb.KAN_Q8)]
     seen = set()
@@ -304,7 +307,22 @@ def test_planner_accepts_every_shape_and_names_a_known_kernel():
             arr = (kb.kan_vq_layer * heads)(*([d] * heads))
             ws = L.kan_vq_workspace_bytes(arr, 1, heads, B, path)
             assert ws != kb.SIZE_INVALID and ws % 256 == 0, (n_in, n_out, B, heads, path, ws)
-    assert {b"kan_gather_bt1", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16", b"kan_mfma", b"kan_mfma_split"} <= seen
+    assert {b"kan_gather_bt1", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16", b"kan_mfma", b"kan_mfma_split",
+            b"kan_wide", b"kan_wide_split", b"kan_stream", b"kan_stream_split"} <= seen
+
+
+def test_the_reported_kernel_is_that_of_the_planned_call():
+    """The kernels on rotated basis words under names of their own, and a call that leaves them for room in the static
+    scratch under the name of what it runs."""
+    L = kb.lib()
+    for n_in, n_out, B, half, precise in (
+            (2048, 1024, 512, b"kan_wide", b"kan_wide_split"), (2048, 1024, 1024, b"kan_mfma", b"kan_mfma_split"),
+            (4096, 1024, 128, b"kan_wide", b"kan_wide_split"), (4096, 4096, 8192, b"kan_stream", b"kan_stream_split"),
+            (65536, 64, 128, b"kan_fused_f16", b"kan_fused_f32"),           # 84 MB of basis words
+            (200, 4095, 7700, b"kan_mfma", b"kan_stream_split")):           # 35.7 MB with rotated words, 30.0 without
+        d = _desc(n_in=n_in, n_out=n_out, K=65536, cb_dtype=kb.KAN_I8, gb_dtype=kb.KAN_F16)
+        assert L.kan_vq_planned_kernel(C.byref(d), B, 1, kb.KAN_PATH_MFMA) == half, (n_in, n_out, B)
+        assert L.kan_vq_planned_kernel(C.byref(d), B, 1, kb.KAN_PATH_GATHER) == precise, (n_in, n_out, B)
 
 
 @pytest.mark.parametrize("widths,B", [((65536, 64), 128), ((16384, 256), 96), ((4096, 4096), 128), ((4096, 1024), 100)])

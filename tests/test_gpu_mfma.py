@@ -122,7 +122,7 @@ def test_mfma_config3_head(kb, B):
     print("config3 mfma", B, rep)
     assert rep["headline"] <= TOL_MFMA, rep
     # the automatic dispatcher takes the same path at these batch sizes
-    assert kb.kan_vq_planned_kernel(Ls[0], B, 1, kb.KAN_PATH_AUTO) == "kan_mfma"
+    assert kb.kan_vq_planned_kernel(Ls[0], B, 1, kb.KAN_PATH_AUTO) == {256: "kan_wide", 4096: "kan_stream"}.get(B, "kan_mfma")
     y_auto = kb.kan_vq_head_forward([Ls], to_dev(x), path=kb.KAN_PATH_AUTO)[0]
     assert np.array_equal(y_auto.cpu().numpy(), y)
 
@@ -266,7 +266,7 @@ def test_profiled_launches_are_keyed_by_layer(kb):
     for _ in range(3):
         kb.kan_vq_head_forward([Ls], xd, path=kb.KAN_PATH_MFMA)
     rec = kb.kan_prof_end()
-    assert set(rec) == {"kan_prep_start", "kan_mfma@L1", "kan_prep_basis@L2", "kan_mfma@L2", "kan_reduce@L2"}, rec
+    assert set(rec) == {"kan_prep_start", "kan_wide@L1", "kan_prep_basis@L2", "kan_mfma@L2", "kan_reduce@L2"}, rec
     assert all(v["launches"] == 3 and v["total_ms"] > 0 for v in rec.values()), rec
     # outside a head call nothing carries a layer
     kb.kan_prof_begin(8)
@@ -275,21 +275,23 @@ def test_profiled_launches_are_keyed_by_layer(kb):
 
 
 @pytest.mark.parametrize("B", [100, 128, 129])
-def test_large_layer_keeps_the_fused_kernel_for_two_batch_tiles(kb, B):
-    """A layer of 2^22 edges (Int8 rows): up to batch 128 both paths gather every row once per tile of 64
-    samples instead of preparing records; from 129 the streaming kernels take over.  Sampled outputs of
-    both tiles against the oracle, and the ragged second tile."""
-    P = synth.make_layer(610, 4096, 1024, 65536, cb_dtype="i8", gb_dtype="f16")
+@pytest.mark.parametrize("n_in,n_out,fits", [(4096, 1024, True), (65536, 64, False)])
+def test_large_layer_keeps_the_fused_kernel_for_two_batch_tiles(kb, n_in, n_out, fits, B):
+    """Layers of 2^22 edges (Int8 rows) whose basis words do not fit the static scratch: up to batch 128 both paths gather
+    every row once per tile of 64 samples instead of preparing records or basis words.  Others, and from 129 on, take the
+    kernel that dequantises its own coefficients.  Sampled outputs of both tiles against the oracle, and the ragged
+    second tile."""
+    P = synth.make_layer(610, n_in, n_out, 65536, cb_dtype="i8", gb_dtype="f16")
     L = kb.VQLayer(P)
-    x = synth.make_x(611, B, 4096, "uniform")
+    x = synth.make_x(611, B, n_in, "uniform")
     xd = to_dev(x)
-    for path, tol, fused, streaming in ((kb.KAN_PATH_MFMA, TOL_MFMA, "kan_fused_f16", "kan_mfma"),
-                                        (kb.KAN_PATH_GATHER, TOL_FP32, "kan_fused_f32", "kan_mfma_split")):
-        assert kb.kan_vq_planned_kernel(L, B, 1, path) == (fused if B <= 128 else streaming)
+    for path, tol, fused, wide in ((kb.KAN_PATH_MFMA, TOL_MFMA, "kan_fused_f16", "kan_wide"),
+                                   (kb.KAN_PATH_GATHER, TOL_FP32, "kan_fused_f32", "kan_wide_split")):
+        assert kb.kan_vq_planned_kernel(L, B, 1, path) == (wide if fits or B > 128 else fused)
         y = kb.kan_vq_layer_forward(L, xd, path=path).cpu().numpy()
         assert np.isfinite(y).all()
         check_layer_output(y, x, P, tol, n_samples=96, seed=B, full=False)
     small = kb.VQLayer(synth.make_layer(612, 2048, 1024, 65536, cb_dtype="i8", gb_dtype="f16"))
-    assert kb.kan_vq_planned_kernel(small, 100, 1, kb.KAN_PATH_MFMA) == "kan_mfma"
+    assert kb.kan_vq_planned_kernel(small, 100, 1, kb.KAN_PATH_MFMA) == "kan_wide"
     wide_rows = kb.VQLayer(synth.make_layer(613, 4096, 1024, 65536, cb_dtype="f32", gb_dtype="f32"))
-    assert kb.kan_vq_planned_kernel(wide_rows, 100, 1, kb.KAN_PATH_GATHER) == "kan_mfma_split"
+    assert kb.kan_vq_planned_kernel(wide_rows, 100, 1, kb.KAN_PATH_GATHER) == "kan_wide_split"

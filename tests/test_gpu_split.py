@@ -148,7 +148,7 @@ def test_split_three_layer_head(kb, B, n_heads):
 def test_split_config2_and_config3(kb, B):
     (P,), x = synth.config2(B)
     L = kb.VQLayer(P)
-    assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_GATHER) == "kan_mfma_split"
+    assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_GATHER) == ("kan_wide_split" if B == 256 else "kan_mfma_split")
     y = kb.kan_vq_layer_forward(L, to_dev(x), path=kb.KAN_PATH_GATHER).cpu().numpy()
     check_layer_output(y, x, P, TOL_FP32, n_samples=96, full=False, seed=B)
     Ps, x3 = synth.config3(B)
@@ -204,7 +204,7 @@ def test_split_config5_sampled(kb):
     three-pass form: sampled outputs and whole rows against the oracle at the fp32 bound."""
     (P,), x = synth.config5("i8")
     L = kb.VQLayer(P)
-    assert kb.kan_vq_planned_kernel(L, x.shape[0], 1, kb.KAN_PATH_GATHER) == "kan_mfma_split"
+    assert kb.kan_vq_planned_kernel(L, x.shape[0], 1, kb.KAN_PATH_GATHER) == "kan_stream_split"
     y = kb.kan_vq_layer_forward(L, to_dev(x), path=kb.KAN_PATH_GATHER).cpu().numpy()
     assert np.isfinite(y).all()
     rep = check_layer_output(y, x, P, TOL_FP32, n_samples=64, full=False, seed=55)
