@@ -1091,11 +1091,17 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
     }
     return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced);
   };
-  for (int l = 0; l < n_layers; ++l) plans->push_back(plan_of(l, false));
-  // Layers whose slices a reduction launch adds, where that is known: whole where that is faster, unless the layer
-  // would then no longer take its predecessor's slices.
+  const int last = n_layers - 1;
+  for (int l = 0; l <= last; ++l) plans->push_back(plan_of(l, l == last));
+  // Layers whose slices a reduction launch adds - the last one, others once the plans behind them are known - are whole
+  // where that is faster, unless they would then no longer take their predecessor's slices.
   auto hands_on = [&](int l) { return hand_on && chained(*plans, l, n_heads, layers, B); };
-  for (int l = n_layers - 1; l >= 0; --l) {
+  if ((*plans)[last].n_chunks == 1 && last > 0 && (*plans)[last - 1].n_chunks > 1 && !hands_on(last - 1)) {
+    const LayerPlan whole = (*plans)[last];
+    (*plans)[last] = plan_of(last, false);
+    if (!hands_on(last - 1)) (*plans)[last] = whole;
+  }
+  for (int l = last - 1; l >= 0; --l) {
     if ((*plans)[l].n_chunks <= 1 || hands_on(l)) continue;
     const LayerPlan cut = (*plans)[l];
     const bool takes = hands_on(l - 1);
