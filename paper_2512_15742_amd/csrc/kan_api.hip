@@ -289,7 +289,12 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
 //   2048 x 1024 split  59.9 / 37.1   70.7 / 44.3   98.7 / 69.7    136 / 100     125 / 124
 //   4096 x 1024 split  88.9*/ 55.5    135 / 70.0    200 / 121     266 / 184     226 / 232     333 / 413
 //   4096 x 4096 split   312*/ 169     431 / 212     575 / 400     873 / 687     875 / 792    1501 / 1397
-// and with ten heads of 2048-256-21 at batch 128 114 / 61 (fp16), 206 / 87 (split).
+// and with ten heads of 2048-256-21 at batch 128 114 / 61 (fp16), 206 / 87 (split).  The lines are drawn through this table,
+// where one size gains and the next loses on their far side.  A second run, with the parameters in the caches, puts the kernel
+// ahead beyond them too.  Streaming form / this / kan_stream.hip at batch 640, 768, 896, 1024: 2048 x 1024 fp16
+// 59.4 / 54.8 / 56.0, 64.0 / 56.3 / 58.5, 66.8 / 58.6 / 65.3, 65.0 / 61.7 / 68.6.  Streaming form / this at batch 128, 256, 512,
+// 768, split operands, Int8 rows: 1024 x 512 29.3 / 26.4, 31.0 / 28.0, 36.7 / 34.8, 47.2 / 40.8, 512 x 512 25.4 / 18.4,
+// 27.5 / 22.7, 30.5 / 28.3, 34.7 / 33.3, 2048 x 256 32.1 / 26.1, 33.0 / 34.5, 41.0 / 35.5, 50.6 / 44.5.
 constexpr long long kWideMinEdges = 1ll << 20;        // over the heads of a launch
 constexpr int64_t kWideMinBatch = 65, kWideMaxBatchHalf = 512, kWideMaxBatchHalfLarge = 1024, kWideMaxBatchSplit = 768;
 constexpr long long kWideLargeEdges = 1ll << 22;      // ... for kWideMaxBatchHalfLarge
@@ -510,7 +515,8 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // at least 512 workgroups of two steps or more, as before, left one CU with three workgroups of ten steps where
 // 520 were launched (ten heads of 2048-256-21 at batch 4 / 16 / 32: 54.6 / 55.5 / 75 us, now 41.6 / 46.0 / 59.3;
 // twenty of 1024-128-50 at 16 38.7 -> 30.5), and small layers with a second step that takes longer than
-// the slices it saves (64-32 at batch 16 7.5 -> 6.5, 1000-333-21 24.3 -> 20.9, 2048-1024-256 at batch 4 28.2 -> 26.7).
+// the slices it saves (64-32 at batch 16 7.5 -> 6.5 on the GPU - the call is bound by the host, 9.6 before and after -,
+// 1000-333-21 24.3 -> 20.9, 2048-1024-256 at batch 4 28.2 -> 26.7).
 // Not more chunks than the next layer takes as they are, unless two steps each would be too many already; chunks of a
 // single step for up to kFusedWaveStepBytes of partial sums, beyond which a caller's workspace would grow with them.
 // (Eight waves to a workgroup for half the slices: 2048-1024-256 at batch 16 30.2 against 28.6 us.)

@@ -56,8 +56,8 @@
 #include "kan_mfma_common.hpp"
 
 // 1: this translation unit holds the preparation kernels of the rotated forms (kan_wide.hip, kan_stream.hip), nothing else.
-// A code object of their own: among the kernels here they put the ones that a head at batch 1024 launches in turn further
-// apart, 85.7-90.2 us against 86.9-91.2.
+// A unit of their own: the two halves compile side by side.  (A head at batch 1024 took 85.7-90.2 us over the runs with
+// them apart, 86.9-91.2 with all in one: no difference that these ranges show.)
 #ifndef KAN_PREP_ROT
 #define KAN_PREP_ROT 0
 #endif

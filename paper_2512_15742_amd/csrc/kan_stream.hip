@@ -11,9 +11,10 @@
 // through a ring of six slots; one barrier per group.  Wave (wm, wn) of 2 x 4 owns 128 x 64 results: 4 + 4 fragment
 // reads of 1 KB per 8 MFMAs.
 //
-// What bounds it is power: 4096 x 4096 at batch 8192 takes 1.35 ms (tiles of 128 x 256 with the basis tile built in
-// LDS by the waves, kan_mfma.hip: 1.73), in which the matrix pipe is busy 67 % of 2.0 M clocks, at 1.5 GHz where the
-// card does 2.4 unloaded: 1.0 of the 1.3 PFLOP/s that a large dense product reaches here.  What each part costs there:
+// What bounds it is most likely power: 4096 x 4096 at batch 8192 takes 1.34-1.45 ms over the cards (tiles of 128 x 256 with
+// the basis tile built in LDS by the waves, kan_mfma.hip: 1.73).  On a card where it took 1.44 the counters read 2.12 M
+// clocks, 1.47 GHz (the preparation launch in front ran at 2.16), the matrix pipe busy for 58 % of them (60.5 where it took
+// 1.39), LDS 31 %: 1.0 of the 1.3 PFLOP/s that a large dense product reaches here.  What each part costs there:
 // without the copies 1.07 ms (with position bits computed for free), without copies and LDS reads 0.93.  Position bits
 // computed from the fragments' signs instead of read (40 vector instructions per 8 MFMAs) 1.49; reads, copies and MFMAs
 // in blocks instead of in turn 1.56; planes padded by half a bank row: no change (the counters show no conflicts).
