@@ -24,6 +24,7 @@
 // finds the same shapes from a small part of the scores.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kan_device.hpp"
 #include "kan_internal.hpp"
@@ -43,17 +44,14 @@ __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
   lo = (_Float16)(v - (float)hi);
 }
 
-// Slots s0 .. s0+7 of a shape's operand.  Without a shape (rows past the last one) the norm term is minus infinity,
+// Slots s0 .. s0+7 of a shape's operand.  Without a shape (its row is zeros then) (rows past the last one) the norm term is minus infinity,
 // so that the row never wins, whatever the norms of the shapes.  Both searches take these, and the products in this
 // order: a score has the same bits in either.
-__device__ __forceinline__ uint4 shape_slots(const float* __restrict__ cb, long long c, bool there, int s0) {
+__device__ __forceinline__ uint4 shape_slots(const float (&row)[kG], bool there, int s0) {
   h16x8 v;
-  float row[kG], nrm = 0.f;
+  float nrm = 0.f;
 #pragma unroll
-  for (int m = 0; m < kG; ++m) {
-    row[m] = there ? cb[c * kG + m] : 0.f;
-    nrm = fmaf(row[m], row[m], nrm);
-  }
+  for (int m = 0; m < kG; ++m) nrm = fmaf(row[m], row[m], nrm);
   const float half_norm = there ? -0.5f * nrm : -INFINITY;
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
@@ -81,7 +79,10 @@ __global__ __launch_bounds__(256) void kan_assign_prep_kernel(const float* __res
   if (rec >= (long long)n_tiles * 2 * 64) return;
   const int lane = (int)(rec & 63), ks = (int)((rec >> 6) & 1);
   const int c = (int)(rec >> 7) * 32 + (lane & 31);
-  out[rec] = shape_slots(cb, c, c < K, ks * 16 + (lane >> 5) * 8);
+  float row[kG];
+#pragma unroll
+  for (int m = 0; m < kG; ++m) row[m] = c < K ? cb[(long long)c * kG + m] : 0.f;
+  out[rec] = shape_slots(row, c < K, ks * 16 + (lane >> 5) * 8);
 }
 
 // Step 1 of an edge: bias = mean, gain = norm of the centred grid, direction = centred / gain.
@@ -125,15 +126,29 @@ __device__ __forceinline__ int row_of(const f32x16& v, float m) {
   return r_best;
 }
 
+// The bounded search's tiles are four groups of eight shapes: a lane's registers 4 g .. 4 g + 3 are its rows of group g,
+// rows 4 (lane / 32) .. of its eight, and these lie by id.  found(g, row among the four, score) for every group whose best
+// score is at least `best`, which it may raise: equal scores of several groups are all reported.
+constexpr int kGroupShapes = 8;
+constexpr int kGroupRecords = kGroupShapes * 4;            // [instruction][half of a wave][shape] records of 16 bytes
+template <typename Found>
+__device__ __forceinline__ void for_groups_with(const f32x16& v, const float& best, Found found) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float a = v[4 * g], b = v[4 * g + 1], c = v[4 * g + 2], d = v[4 * g + 3], m = fmaxf(max3(a, b, c), d);
+    if (m >= best) found(g, a == m ? 0 : (b == m ? 1 : (c == m ? 2 : 3)), m);
+  }
+}
+
 struct AssignArgs {
   const float* coef;        // [E][10]
   const uint4* cent;        // prepared centroid operands
   long long E;
-  // LIST: behind the bounded search, on its tiles.  The edges in its order, and of every 32 whether they are left (their
-  // gains and biases are there already); the number of tiles and the shape of every row
+  // LIST: behind the bounded search, on its groups of eight shapes, four to a tile.  The edges in its order, and of every 32
+  // whether they are left (their gains and biases are there already); the number of groups and the shape of every row
   const uint32_t* list;
   const uint8_t* left;      // [4 * ceil(E / 128)]
-  const uint32_t *tiles, *ids;
+  const uint32_t *groups, *ids;
   int n_tiles;              // ceil(K / 32)
   void* idx;
   float* gain;
@@ -201,12 +216,12 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
     }
 
     // ---- step 3: stream the centroid tiles (two tiles in flight) -----------------------------------
-    const int n_tiles = LIST ? (int)*a.tiles : a.n_tiles;
-    const uint4* cp = a.cent + lane;
+    const int n_tiles = LIST ? ((int)*a.groups + 3) / 4 : a.n_tiles;
+    const uint4* cp = a.cent + (LIST ? ((lane & 31) >> 3) * kGroupRecords + (lane >> 5) * kGroupShapes + (lane & 7) : lane);
     auto load_tile = [&](int t, uint4 (&fa)[2]) {
       const int tc = t < n_tiles ? t : n_tiles - 1;        // past the end: a harmless re-read
       fa[0] = cp[(long long)(tc * 2) * 64];
-      fa[1] = cp[(long long)(tc * 2 + 1) * 64];
+      fa[1] = cp[(long long)(tc * 2) * 64 + (LIST ? kGroupRecords / 2 : 64)];
     };
     f32x16 zero;
 #pragma unroll
@@ -223,11 +238,12 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
         // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
         // it the lowest register, keeps a tie.  (LIST: the lowest id, whatever tile it lies in.)
         if constexpr (LIST) {
-          if (m >= best[nb]) {
-            const int r = row_of(acc, m), id = (int)a.ids[t * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
-            if (m > best[nb] || (uint32_t)id < (uint32_t)best_tile[nb]) best_tile[nb] = id;
-            best[nb] = m;
-          }
+          if (m >= best[nb])
+            for_groups_with(acc, best[nb], [&](int g, int r, float mg) {
+              const int id = (int)a.ids[t * 32 + g * kGroupShapes + 4 * (lane >> 5) + r];
+              if (mg > best[nb] || (uint32_t)id < (uint32_t)best_tile[nb]) best_tile[nb] = id;
+              best[nb] = mg;
+            });
         } else if (m > best[nb]) {
           best[nb] = m;
           best_tile[nb] = t;
@@ -306,53 +322,64 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
 }
 
 // ---- bounded search -------------------------------------------------------------------------------
-// The codebook is cut into cells (the shapes nearest to one of M = K / 64 sampled shapes, the cell's centre c)
-// and a cell into tiles of 32 shapes sorted by their distance to c.  A tile whose shapes all lie within R of c can be
-// left out for an edge n that knows a shape at distance d already when |n - c| > R + d; in scores (|n| = 1)
+// The codebook is cut into cells (the shapes nearest to one of M = K / 64 sampled shapes, the cell's centre) and a cell
+// into groups of eight shapes that lie close together.  Shapes that all lie within R of a point c can be left out for an
+// edge n that knows a shape at distance d already when |n - c| > R + d; in scores (|n| = 1)
 //     n . c - |c|^2 / 2 + R^2 / 2 + R d  <  (1 - d^2) / 2 .
-// The left side is a product of an edge's vector (n, 1, d) with a tile's vector (c, (R^2 - |c|^2) / 2, R), so one
-// v_mfma_f32_32x32x16_f16 tests 32 edges against 32 tiles, the right side included; what the fp16 operands
-// round away is covered by a margin.  The edges are sorted by their nearest centre, so that the 32 of a wave ask for
-// about the same tiles, and a wave scores every tile that any of its edges asks for:
-//     (1) the tiles of the edges' own cells: seven of ten edges with 5 % noise find their shape here;
-//     (2) the tiles within R + min(d, the wave's mean d): finds nearly all of the others, whose d of step 1 alone
-//         would ask for a large part of the codebook;
-//     (3) where an edge is left with a larger d: what that one still asks for.
-// The scores are those of the whole search, bit for bit, no tile that can hold the best one is left out and equal
+// The left side is a product of an edge's vector (n, 1, d) with the ball's vector (c, (R^2 - |c|^2) / 2, R), so one
+// v_mfma_f32_32x32x16_f16 tests 32 edges against 32 balls, the right side included; what the fp16 operands
+// round away is covered by a margin.  The cells are tested first, then the groups of those that any edge of the wave asks
+// for; four groups that any edge asks for make up a tile of the search, wherever they lie.  The edges are sorted by their
+// nearest centre and the side of it that they lie on, so that the 32 of a wave ask for about the same groups:
+//     (1) the groups of the edges' own cells: seven of ten edges with 5 % noise find their shape here;
+//     (2) those within R + min(d, what a typical edge of the wave has): finds nearly all of the others, whose d of
+//         step 1 alone would ask for a large part of the codebook;
+//     (3) where an edge is left with a larger d than it asked at: what that one still asks for.
+// The scores are those of the whole search, bit for bit, no group that can hold the best one is left out and equal
 // scores go to the lowest id: the result is the whole search's, whichever edges share a wave (the sort places them in
-// no particular order) and whichever of them are handed over: a wave that would visit more than kRestShare of the tiles
+// no particular order) and whichever of them are handed over: a wave that would visit more than kRestShare of the groups
 // in (2) or in (3) leaves its edges to the whole search.  A visit costs about what a tile costs there, so that is worth
 // it only for edges that ask for nearly everything (vectors that the bounds do not hold for, codebooks of one shape):
-// grids that fit their codebook poorly ask for less, and stay.  With 25 % noise or unrelated grids, 2^20 edges: 234 of
-// 330 tiles for K = 8,192, 356 of 630 for 16,384, 636 of 2,500 for 65,536.  With 0.7 of the tiles for both steps
-// together and the left edges compacted by one counter, unrelated grids took 1003 us for K = 8,192 against 528 of the
-// whole search alone and 471 against 292 for K = 16,384, 2^18 edges (a few waves left behind there were one chain
-// through all tiles, 340 us); now 553 and 252.
+// grids that fit their codebook poorly ask for less, and stay.
 //
-// What bounds it: instructions issued and operands.  A wave of the search makes (tiles / 32) bound tests and visits
-// about 250 of 2,500 tiles (65,536 shapes, 5 % noise; 15 % noise: 600), each 1 KB of operands, one matrix and about ten
-// vector instructions; the counters show the address units busy for 65 % of the time, the matrix pipe for a third.
-// What that took, 2048 x 512 edges against 65,536 shapes: two instructions a visit and tiles picked from bit masks by
-// scalar code 1057 us, one instruction a visit 1084, more loads in flight 998, tiles listed in LDS and taken in
-// pairs 818, the second instruction in place of vector arithmetic for near scores 761, six waves per SIMD
-// 690; cells of 64 instead of 32 shapes (the choice of the cells 154 -> 87 us).  The whole search takes 3.8 ms.
+// What bounds it: instruction issue (vector instructions for 60 % of the time) and operands (the address units 66 % busy).
+// A wave makes about 47 tests of 32 cells, 38 of 32 groups, and visits 68 tiles of four groups, each with one matrix, one
+// 1 KB load and some 15 vector instructions (65,536 shapes, 5 % noise).  Groups of eight in place of tiles of 32 shapes around the
+// cell's centre took 258 visits down to 92 at 101 tests in place of 80; the sides of the centre to the figures above;
+// resources of the loads that were not known to be the same for the wave had cost a loop around every load.
+// 2048 x 512 edges against 65,536 shapes, the whole call: 737 -> 480 us (the kernel 650 -> 400); 2 % / 15 % noise / unrelated
+// grids 545 / 1290 / 1332 -> 332 / 885 / 908.  The whole search takes 3.7 ms.
 
 constexpr int kCellShapes = 64;                   // shapes per cell on average
-constexpr int kCellMaxTiles = 16384;              // (a wave marks the tiles it has visited in LDS)
-constexpr float kRestShare = 0.9f, kMeanFactor = 1.0f;          // (0.6 / 0.7: K = 8,192, unrelated grids 1153 / 873 us)
+constexpr int kCellMaxGroups = 49152;             // (listed in 16 bits)
+constexpr float kRestShare = 0.9f;                // (0.6 / 0.7: K = 8,192, unrelated grids 1153 / 873 us)
+// Step (2): edges within kFound of the mean of those below the wave's mean have found their shape where that is well below
+// the mean of all; the others ask at kAsk of it.  Where edges are not apart like that, all ask at kPoor of the mean at most:
+// nearly none is left for (3), which would test the cells again and visit most groups once more.
+constexpr float kFound = 1.8f, kAsk = 1.5f, kApart = 1.3f, kPoor = 1.2f;
+
 constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
 constexpr int kRestWorkgroups = 1024;             // of the whole search behind it: twice what is resident
 constexpr int kAhead = 2;                         // tiles in flight per wave
-constexpr int kSortThreads = 1024, kSortGroups = 64;
-constexpr int kBuildChunk = 1024;                 // members of a cell that are sorted together
+// Lists of a wave in LDS: cells that may hold a best shape (of 32 words of cells), a window of their groups, groups to visit
+constexpr int kListCells = 1024, kListGroups = 640, kListVisits = 1024;
+constexpr int kPadGroups = 8;                     // groups without shapes behind the last one (a tile may reach past it)
+constexpr int kSortThreads = 1024, kSortGroups = 128;
+// Edges of a cell are sorted by the side of its centre they lie on along kMaxSub directions as well, so that a wave's 32 lie
+// closer together: 49 + 71 in place of 57 + 94 tiles tested and visited a wave (65,536 shapes, 5 % noise).
+constexpr int kMaxSub = 3, kMaxBins = 8192;       // (bins are counted in LDS)
+constexpr int kBuildThreads = 512;
+constexpr int kBuildChunk = 512;                  // members of a cell that are grouped together, a power of two
 
 // Where the pieces of the search lie in the workspace.
 struct CellLayout {
   int M;                   // cells, a multiple of 32
-  int tiles_max;
+  int sub;                 // log2 of the parts of a cell that the edges are sorted by
+  int bins[2];             // of the sort, one for edges without direction included
+  int groups_max;
   int groups[2];           // workgroups of the sort: over the shapes, over the edges
   long long chunk[2];      // items per workgroup
-  size_t centres, frag, ids, bound, member, perm, key[2], hist[2], total[2], first[2], first_tile, wg_least, least, left, bytes;
+  size_t centres, frag, ids, cell_bound, bound, member, perm, key[2], hist[2], total[2], first[2], first_group, wg_least, least, left, bytes;
 };
 
 size_t centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(uint4); }
@@ -360,7 +387,11 @@ size_t centroid_bytes(int K) { return (size_t)((K + 31) / 32) * 2 * 64 * sizeof(
 CellLayout cell_layout(long long E, int K) {
   CellLayout g;
   g.M = (K / kCellShapes + 31) / 32 * 32;
-  g.tiles_max = (K + 31) / 32 + g.M;
+  g.sub = 0;
+  while (g.sub < kMaxSub && (g.M << (g.sub + 1)) <= kMaxBins) ++g.sub;
+  g.bins[0] = g.M + 1;
+  g.bins[1] = (g.M << g.sub) + 1;
+  g.groups_max = (K + kGroupShapes - 1) / kGroupShapes + g.M;
   size_t at = 0;
   auto take = [&](size_t bytes) {
     const size_t here = at;
@@ -368,9 +399,10 @@ CellLayout cell_layout(long long E, int K) {
     return here;
   };
   g.centres = take((size_t)g.M * 2 * sizeof(uint4));
-  g.frag = take((size_t)g.tiles_max * 2 * 64 * sizeof(uint4));
-  g.ids = take((size_t)g.tiles_max * 32 * 4);
-  g.bound = take((size_t)((g.tiles_max + 31) / 32) * 64 * sizeof(uint4));
+  g.frag = take((size_t)(g.groups_max + kPadGroups) * kGroupRecords * sizeof(uint4));
+  g.ids = take((size_t)(g.groups_max + kPadGroups) * kGroupShapes * 4);
+  g.cell_bound = take((size_t)g.M * 2 * sizeof(uint4));
+  g.bound = take((size_t)g.groups_max * 2 * sizeof(uint4));
   g.member = take((size_t)K * 4);
   g.perm = take((size_t)E * 4);
   for (int p = 0; p < 2; ++p) {
@@ -379,11 +411,11 @@ CellLayout cell_layout(long long E, int K) {
     g.groups[p] = (int)(groups < kSortGroups ? groups : kSortGroups);
     g.chunk[p] = (n + g.groups[p] - 1) / g.groups[p];
     g.key[p] = take((size_t)n * 2);
-    g.hist[p] = take((size_t)g.groups[p] * (g.M + 1) * 4);
-    g.total[p] = take((size_t)(g.M + 1) * 4);
-    g.first[p] = take((size_t)(g.M + 1) * 4);
+    g.hist[p] = take((size_t)g.groups[p] * g.bins[p] * 4);
+    g.total[p] = take((size_t)g.bins[p] * 4);
+    g.first[p] = take((size_t)g.bins[p] * 4);
   }
-  g.first_tile = take((size_t)(g.M + 1) * 4);
+  g.first_group = take((size_t)(g.M + 1) * 4);
   g.wg_least = take((size_t)((K + kEdgesPerWg - 1) / kEdgesPerWg) * 8);
   g.least = take(4);
   g.left = take((size_t)((E + 127) / 128) * 4);
@@ -395,24 +427,59 @@ struct CellArgs {
   const float* coef;
   const float* cb;
   long long E;
-  int K, M;
+  int K, M, sub;
+  int bins[2];
   int shape_wgs;                 // kan_cells_kernel: workgroups over the shapes, in front of those over the edges
   int groups[2];
   long long chunk[2];
   uint4* centres;                // operands of the centres
-  uint4* frag;                   // operands of the tiles
-  uint32_t* ids;                 // shape of every tile row
-  uint4* bound;                  // bound operands of the tiles
+  uint4* frag;                   // operands of the groups, kGroupRecords each
+  uint32_t* ids;                 // shape of every group row
+  uint4* cell_bound;             // bound operands of the cells, 32 to a matrix operand
+  uint4* bound;                  // bound operands of the groups, two records each
   uint32_t* sorted[2];           // shapes, edges in the order of their cells
-  uint16_t* key[2];              // cell of every shape, edge (M: an edge without direction)
+  uint16_t* key[2];              // bin of every shape (its cell), edge (its cell's part; the last one: an edge without direction)
   uint32_t *hist[2], *total[2], *first[2];
-  uint32_t* first_tile;          // [M + 1]
+  uint32_t* first_group;         // [M + 1]
   unsigned long long* wg_least;
   uint8_t* left;                 // [4 * ceil(E / 128)] waves whose edges are left to the whole search
   uint32_t* least;               // shape of the smallest norm: the nearest to an edge of gain 0
   void* idx;
   float *gain, *bias;
 };
+
+// Over the 64 lanes, for all of them: moves within rows of 16, then of the rows' results (an LDS permute for each step is a
+// round trip).
+template <typename Op>
+__device__ __forceinline__ float wave_fold(float v, float none, Op op) {
+  auto moved = [&](auto ctrl, auto rows) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), ctrl.value, rows.value, 0xf, false));
+  };
+  using std::integral_constant;
+  v = op(v, moved(integral_constant<int, 0x111>(), integral_constant<int, 0xf>()));
+  v = op(v, moved(integral_constant<int, 0x112>(), integral_constant<int, 0xf>()));
+  v = op(v, moved(integral_constant<int, 0x114>(), integral_constant<int, 0xf>()));
+  v = op(v, moved(integral_constant<int, 0x118>(), integral_constant<int, 0xf>()));
+  v = op(v, moved(integral_constant<int, 0x142>(), integral_constant<int, 0xa>()));
+  v = op(v, moved(integral_constant<int, 0x143>(), integral_constant<int, 0xc>()));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_total(float v) {
+  return wave_fold(v, 0.f, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_most(float v) {       // v >= -1
+  return wave_fold(v, -1.f, [](float a, float b) { return fmaxf(a, b); });
+}
+
+__device__ __forceinline__ int sums_up_to(int v) {          // of the lanes up to this one
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
 
 // A row's sixteen slots as the two halves of a wave hold them.
 __device__ __forceinline__ uint4 pack_slots(const float (&v)[8]) {
@@ -434,20 +501,28 @@ __device__ __forceinline__ const float* centre_row(const CellArgs& a, int m) {
 __global__ __launch_bounds__(256) void kan_cell_centres_kernel(const CellArgs a) {
   const int rec = blockIdx.x * 256 + threadIdx.x;
   if (rec >= a.M * 2) return;
-  const float* c = centre_row(a, (rec >> 6) * 32 + (rec & 31));
-  float nrm = 0.f;
+  const float* row = centre_row(a, (rec >> 6) * 32 + (rec & 31));
+  float c[kG], nrm = 0.f;
 #pragma unroll
-  for (int k = 0; k < kG; ++k) nrm = fmaf(c[k], c[k], nrm);
-  const float hn = -0.5f * nrm, hi = fp16_of(hn);
+  for (int k = 0; k < kG; ++k) {
+    c[k] = row[k];
+    nrm = fmaf(c[k], c[k], nrm);
+  }
+  // (beyond fp16, or no number: a centre that nothing is near)
+  const bool fits = nrm < 1.19e5f;
+#pragma unroll
+  for (int k = 0; k < kG; ++k) c[k] = fits ? c[k] : 0.f;
+  const float hn = fits ? -0.5f * nrm : -6e4f, hi = fp16_of(hn);
   const float v0[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
   const float v1[8] = {c[8], c[9], hi, hn - hi, 0.f, 0.f, 0.f, 0.f};
   a.centres[rec] = (rec & 32) ? pack_slots(v1) : pack_slots(v0);
 }
 
-// Nearest centre of every shape and every edge; gains and biases of the edges.  Any cell is a valid one, so the
-// choice is cheap: the maxima of four rows each, the group's number in the low two bits of the mantissa, one running
-// maximum - sixteen vector instructions per 32 x 32 scores - and the four rows of the winning group
-// are told apart at the end.
+// Nearest centre of every shape and every edge, and on which side of it an edge lies; gains and biases of the edges.  Any
+// cell is a valid one, so the choice is cheap: the maxima of four rows each, the group's number in the low two bits of the
+// mantissa, one running maximum - sixteen vector instructions per 32 x 32 scores - and the four rows of the winning
+// group are told apart at the end.  Four is added to the scores, so that those that matter are positive and compare as
+// integers (floating-point maxima of two operands cost an instruction each to quiet what may be no number).
 __global__ __launch_bounds__(kAssignThreads, 4) void kan_cells_kernel(const CellArgs a) {
   __shared__ uint4 sB[kEdgesPerWg * 2];
   __shared__ uint8_t s_flat[kEdgesPerWg];
@@ -493,18 +568,17 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_cells_kernel(const Cell
   if (shapes && tid == 0) a.wg_least[blockIdx.x] = s_least;
 
   h16x8 fb[kEdgeTilesPerWave];
-  float best[kEdgeTilesPerWave];
-  int best_tile[kEdgeTilesPerWave];
+  int best[kEdgeTilesPerWave], best_tile[kEdgeTilesPerWave];
 #pragma unroll
   for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
     const int q = (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
     fb[nb] = __builtin_bit_cast(h16x8, sB[q * 2 + (lane >> 5)]);
-    best[nb] = -3.0e38f;
+    best[nb] = 0;
     best_tile[nb] = 0;
   }
-  f32x16 zero;
+  f32x16 four;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  for (int r = 0; r < 16; ++r) four[r] = 4.f;
   const uint4* cp = a.centres + lane;
   const int n_tiles = a.M / 32;
   uint4 next = cp[0];
@@ -513,141 +587,246 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_cells_kernel(const Cell
     next = cp[min(t + 1, n_tiles - 1) * 64];
 #pragma unroll
     for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-      f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fb[nb], zero, 0, 0, 0);
-      float m = best[nb];
+      const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fb[nb], four, 0, 0, 0);
+      int m = best[nb];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float v = fmaxf(max3(acc[q], acc[q + 4], acc[q + 8]), acc[q + 12]);
-        m = fmaxf(m, __uint_as_float((__float_as_uint(v) & ~3u) | (uint32_t)q));
+        auto bits = [&](int r) { return __float_as_int(acc[r]); };
+        const int v = max(max(max(bits(q), bits(q + 4)), bits(q + 8)), bits(q + 12));
+        m = max(m, (v & ~3) | q);
       }
       best_tile[nb] = m > best[nb] ? t : best_tile[nb];
       best[nb] = m;
     }
   }
+  typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
+  auto dot = [](const h16x8& u, const h16x8& v) {
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) sum = __builtin_amdgcn_fdot2(h16x2{u[k], u[k + 1]}, h16x2{v[k], v[k + 1]}, sum, false);
+    return sum;
+  };
+  const int half = lane >> 5;
+  // the directions of the parts: orthogonal, of sum 0 as the shapes are
+  h16x8 way[kMaxSub];
+  {
+    constexpr signed char kWay[kMaxSub][kG] = {{1, 1, 1, 1, 1, -1, -1, -1, -1, -1}, {1, -1, 1, -1, 0, 1, -1, 1, -1, 0}, {1, 1, -1, -1, 0, 0, 1, 1, -1, -1}};
+#pragma unroll
+    for (int b = 0; b < kMaxSub; ++b)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) way[b][k] = (_Float16)(float)(half ? (k < 2 ? kWay[b][8 + k] : 0) : kWay[b][k]);
+  }
 #pragma unroll
   for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-    const float sc_o = __shfl_xor(best[nb], 32, kWave);
-    const int tile_o = __shfl_xor(best_tile[nb], 32, kWave);
-    const bool other = sc_o > best[nb] || (sc_o == best[nb] && lane >= 32);
-    const int grp = (int)(__float_as_uint(other ? sc_o : best[nb]) & 3u), tile = other ? tile_o : best_tile[nb];
-    const int row0 = tile * 32 + 4 * ((lane >> 5) ^ (int)other) + grp;          // rows row0 + 8 k
+    const int best_o = __shfl_xor(best[nb], 32, kWave), tile_o = __shfl_xor(best_tile[nb], 32, kWave);
+    const bool other = best_o > best[nb] || (best_o == best[nb] && half);
+    const int grp = (other ? best_o : best[nb]) & 3, tile = other ? tile_o : best_tile[nb];
+    const int row0 = 4 * (half ^ (int)other) + grp;                // of the tile: rows row0 + 8 k
     const int q = (wave * kEdgeTilesPerWave + nb) * 32 + (lane & 31);
-    // this half's two of the four rows
-    float top = -3.0e38f;
+    // this half's eight slots of the four
+    const uint4* rec = a.centres + tile * 64 + half * 32 + row0;
+    h16x8 row[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) row[k] = __builtin_bit_cast(h16x8, rec[8 * k]);
+    h16x8 near = row[0];
     int id = row0;
+    float top = 0.f;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int m = row0 + 8 * (2 * (lane >> 5) + k);
-      const float* c = centre_row(a, m);
-      const _Float16* v = (const _Float16*)(sB + q * 2);
-      float dot = 0.f, nrm = 0.f;
-#pragma unroll
-      for (int z = 0; z < kG; ++z) {
-        dot = fmaf((float)v[z], c[z], dot);
-        nrm = fmaf(c[z], c[z], nrm);
+    for (int k = 0; k < 4; ++k) {
+      float sc = dot(fb[nb], row[k]);
+      sc += __shfl_xor(sc, 32, kWave);
+      if (k == 0 || sc > top) {
+        top = sc;
+        near = row[k];
+        id = row0 + 8 * k;
       }
-      dot -= 0.5f * nrm;
-      id = dot > top ? m : id;
-      top = fmaxf(top, dot);
     }
-    const float top_o = __shfl_xor(top, 32, kWave);
-    const int id_o = __shfl_xor(id, 32, kWave);
-    if (top_o > top) id = id_o;
-    if (lane < 32 && first + q < n) key[first + q] = (uint16_t)(s_flat[q] ? a.M : id);
+    int bin = tile * 32 + id;
+    if (!shapes) {
+      const h16x8 off = fb[nb] - near;
+#pragma unroll
+      for (int b = 0; b < kMaxSub; ++b) {
+        float side = dot(off, way[b]);
+        side += __shfl_xor(side, 32, kWave);
+        if (b < a.sub) bin = 2 * bin + (side > 0.f);
+      }
+      if (s_flat[q]) bin = a.M << a.sub;
+    }
+    if (lane < 32 && first + q < n) key[first + q] = (uint16_t)bin;
   }
 }
 
-// Counting sort of shapes (blockIdx.y = 0) and edges (1) by cell, in chunks: cells counted per chunk, added up over the
-// chunks, over the cells, items put in their places.  No order is kept within a cell of a chunk.
+// Counting sort of shapes (blockIdx.y = 0) and edges (1) by bin, in chunks: bins counted per chunk, added up over the
+// chunks, over the bins, items put in their places.  No order is kept within a bin of a chunk.
 __global__ __launch_bounds__(kSortThreads) void kan_cell_count_kernel(const CellArgs a) {
   extern __shared__ uint32_t h[];
   const int p = blockIdx.y, g = blockIdx.x;
   if (g >= a.groups[p]) return;
-  for (int m = threadIdx.x; m <= a.M; m += kSortThreads) h[m] = 0;
+  const int bins = a.bins[p];
+  for (int m = threadIdx.x; m < bins; m += kSortThreads) h[m] = 0;
   __syncthreads();
   const long long n = p ? a.E : a.K, begin = g * a.chunk[p], end = min(n, begin + a.chunk[p]);
   for (long long i = begin + threadIdx.x; i < end; i += kSortThreads) atomicAdd(&h[a.key[p][i]], 1u);
   __syncthreads();
-  for (int m = threadIdx.x; m <= a.M; m += kSortThreads) a.hist[p][(long long)g * (a.M + 1) + m] = h[m];
+  for (int m = threadIdx.x; m < bins; m += kSortThreads) a.hist[p][(long long)g * bins + m] = h[m];
 }
 
+// A bin's counts of the chunks become running sums: a thread per bin and quarter of the chunks.
 __global__ __launch_bounds__(256) void kan_cell_chunks_kernel(const CellArgs a) {
-  const int p = blockIdx.y, m = blockIdx.x * 256 + threadIdx.x;
-  if (m > a.M) return;
-  uint32_t* h = a.hist[p] + m;
-  uint32_t sum = 0;
-  for (int g0 = 0; g0 < a.groups[p]; g0 += 16) {
-    uint32_t v[16];
+  constexpr int kQuarter = kSortGroups / 4;
+  __shared__ uint32_t of_quarter[4][64];
+  const int p = blockIdx.y, col = threadIdx.x & 63, quarter = threadIdx.x >> 6, m = blockIdx.x * 64 + col;
+  const int bins = a.bins[p], groups = a.groups[p];
+  const bool there = m < bins;
+  uint32_t* h = a.hist[p] + min(m, bins - 1);
+  uint32_t v[kQuarter], sum = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = g0 + k < a.groups[p] ? h[(long long)(g0 + k) * (a.M + 1)] : 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-      if (g0 + k < a.groups[p]) {
-        h[(long long)(g0 + k) * (a.M + 1)] = sum;
-        sum += v[k];
-      }
+  for (int k = 0; k < kQuarter; ++k) {
+    const int g = quarter * kQuarter + k;
+    v[k] = there && g < groups ? h[(long long)g * bins] : 0u;
   }
-  a.total[p][m] = sum;
+#pragma unroll
+  for (int k = 0; k < kQuarter; ++k) sum += v[k];
+  of_quarter[quarter][col] = sum;
+  __syncthreads();
+  uint32_t run = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) run += q < quarter ? of_quarter[q][col] : 0u;
+#pragma unroll
+  for (int k = 0; k < kQuarter; ++k) {
+    const int g = quarter * kQuarter + k;
+    if (there && g < groups) h[(long long)g * bins] = run;
+    run += v[k];
+  }
+  if (there && quarter == 3) a.total[p][m] = run;
 }
 
-// One workgroup: running sums over the cells (shapes, tiles, edges) and the shape of the smallest norm.
+// One workgroup: running sums over the bins (shapes, groups, edges) and the shape of the smallest norm.
 __global__ __launch_bounds__(kSortThreads) void kan_cell_scan_kernel(const CellArgs a) {
-  __shared__ uint32_t part[kSortThreads];
+  constexpr int kPer = kMaxBins / kSortThreads + 1;         // bins of a thread
+  __shared__ int of_wave[3][kSortThreads / kWave];
   __shared__ unsigned long long least;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) least = ~0ull;
+  uint32_t n[2][kPer];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int m = tid * kPer + k;
+      n[p][k] = m < a.bins[p] ? a.total[p][m] : 0u;
+    }
+  auto groups_of = [](uint32_t shapes) { return (shapes + kGroupShapes - 1) / kGroupShapes; };
+  uint32_t own[3] = {0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    own[0] += n[0][k];
+    own[1] += groups_of(n[0][k]);
+    own[2] += n[1][k];
+  }
+  uint32_t run[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int upto = sums_up_to((int)own[q]);
+    if (lane == kWave - 1) of_wave[q][wave] = upto;
+    run[q] = (uint32_t)upto - own[q];
+  }
   __syncthreads();
   unsigned long long l = ~0ull;
   for (int k = tid; k < a.shape_wgs; k += kSortThreads) l = min(l, a.wg_least[k]);
-  atomicMin(&least, l);
-  const int per = (a.M + 1 + kSortThreads - 1) / kSortThreads, m0 = tid * per, m1 = min(a.M + 1, m0 + per);
-  for (int pass = 0; pass < 3; ++pass) {       // shapes, tiles, edges
-    const uint32_t* total = a.total[pass == 2 ? 1 : 0];
-    uint32_t* out = pass == 1 ? a.first_tile : a.first[pass == 2 ? 1 : 0];
-    auto item = [&](int m) { return pass == 1 ? (total[m] + 31) / 32 : total[m]; };
-    uint32_t sum = 0;
-    for (int m = m0; m < m1; ++m) sum += item(m);
-    __syncthreads();
-    part[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < kSortThreads; o <<= 1) {
-      const uint32_t v = tid >= o ? part[tid - o] : 0;
-      __syncthreads();
-      part[tid] += v;
-      __syncthreads();
+  if (l != ~0ull) atomicMin(&least, l);
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    for (int w = 0; w < wave; ++w) run[q] += (uint32_t)of_wave[q][w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int m = tid * kPer + k;
+    if (m < a.bins[0]) {
+      a.first[0][m] = run[0];
+      a.first_group[m] = run[1];
     }
-    uint32_t run = part[tid] - sum;
-    for (int m = m0; m < m1; ++m) {
-      out[m] = run;
-      run += item(m);
-    }
+    if (m < a.bins[1]) a.first[1][m] = run[2];
+    run[0] += n[0][k];
+    run[1] += groups_of(n[0][k]);
+    run[2] += n[1][k];
   }
-  if (tid == 0) {
-    *a.least = (uint32_t)least;
-  }
+  __syncthreads();
+  if (tid == 0) *a.least = (uint32_t)least;
 }
 
 __global__ __launch_bounds__(kSortThreads) void kan_cell_place_kernel(const CellArgs a) {
   extern __shared__ uint32_t at[];
   const int p = blockIdx.y, g = blockIdx.x;
   if (g >= a.groups[p]) return;
-  for (int m = threadIdx.x; m <= a.M; m += kSortThreads)
-    at[m] = a.first[p][m] + a.hist[p][(long long)g * (a.M + 1) + m];
+  const int bins = a.bins[p];
+  for (int m = threadIdx.x; m < bins; m += kSortThreads) at[m] = a.first[p][m] + a.hist[p][(long long)g * bins + m];
   __syncthreads();
   const long long n = p ? a.E : a.K, begin = g * a.chunk[p], end = min(n, begin + a.chunk[p]);
   for (long long i = begin + threadIdx.x; i < end; i += kSortThreads)
     a.sorted[p][atomicAdd(&at[a.key[p][i]], 1u)] = (uint32_t)i;
 }
 
-// Tiles of one cell: members sorted by distance to the centre (then by id), operands of the search and of the bound.
+// Bound operands of a ball of radius R (squared: far) around c: an edge asks for it, or not (see the head of this search).
+__device__ __forceinline__ void ball_operands(const float (&c)[kG], float far, bool empty, uint4& lower, uint4& upper) {
+  float cn = 0.f;
+#pragma unroll
+  for (int k = 0; k < kG; ++k) cn = fmaf(c[k], c[k], cn);
+  const float R = fp16_up(sqrtf(far) * 1.00001f);
+  // (fp16 operands: n and c are off by 2^-11 of themselves each, or flushed below 6e-5)
+  float cst = 0.5f * (R * R - cn) + 1.5e-3f * sqrtf(cn) + 1e-4f;
+  const bool fits = cn < 1e5f && R < 300.f && fabsf(cst) < 6e4f;
+  if (!fits) cst = 6e4f;                          // beyond fp16, or no number: always asked for
+  if (empty) cst = -6e4f;                         // never
+  const float hi = fp16_of(cst), Rf = empty ? 0.f : (fits ? R : 300.f);
+  const bool zero = empty || !fits;
+  const float v0[8] = {zero ? 0.f : c[0], zero ? 0.f : c[1], zero ? 0.f : c[2], zero ? 0.f : c[3],
+                       zero ? 0.f : c[4], zero ? 0.f : c[5], zero ? 0.f : c[6], zero ? 0.f : c[7]};
+  const float v1[8] = {zero ? 0.f : c[8], zero ? 0.f : c[9], hi, cst - hi, Rf, 1.f, 1.f, 0.f};
+  lower = pack_slots(v0);
+  upper = pack_slots(v1);
+}
+
+// Part `at` of a chunk of n members after `level` halvings: [lo, hi), halved between whole groups while it is more than one.
+__device__ __forceinline__ void part_of(int n, int level, int at, int& lo, int& hi) {
+  lo = 0;
+  hi = n;
+  for (int l = level - 1; l >= 0; --l) {
+    const int groups = (hi - lo + kGroupShapes - 1) / kGroupShapes, cut = lo + groups / 2 * kGroupShapes;
+    if (groups < 2) {
+      if ((at >> l) & 1) lo = hi;                  // (one group stays whole, in the first of the two)
+    } else if ((at >> l) & 1) {
+      lo = cut;
+    } else {
+      hi = cut;
+    }
+  }
+}
+// The same for the part that holds position i.
+__device__ __forceinline__ void part_around(int n, int level, int i, int& lo, int& hi) {
+  lo = 0;
+  hi = n;
+  for (int l = 0; l < level; ++l) {
+    const int groups = (hi - lo + kGroupShapes - 1) / kGroupShapes, cut = lo + groups / 2 * kGroupShapes;
+    if (groups < 2) return;
+    if (i >= cut) lo = cut;
+    else hi = cut;
+  }
+}
+
+// Groups of one cell: its members are halved along the direction in which they spread most until eight are left (two
+// steps of the power iteration from the member farthest from the mean; exact directions: 59 in place of 63 tiles a wave, the
+// longest axis: 77), the operands of the search and the bounds of groups and cell are written.
 // The first M workgroups take the first kBuildChunk members of a cell each.  Shapes that coincide (the unused rows of a
 // trained codebook) all fall into one cell: the workgroups behind start at every kBuildChunk-th shape in the order of
 // the cells and take the further chunk of its cell that begins there or next (one workgroup for the whole cell: with
 // 30 % of 65,536 rows unused 658 us, now 35).
-__global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
-  __shared__ unsigned long long sorted[kBuildChunk];       // {squared distance to the centre, id}
-  __shared__ uint32_t row_id[kBuildChunk];                 // a tile's rows by id
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(kBuildThreads) void kan_cell_build_kernel(const CellArgs a) {
+  __shared__ float x[kG][kBuildChunk];                     // the members' shapes
+  __shared__ uint32_t id[kBuildChunk];
+  __shared__ uint16_t order[2][kBuildChunk];               // members in the order of the parts
+  __shared__ __attribute__((aligned(16))) uint32_t spot[kBuildChunk + 4];       // where along its part's direction the member at a position lies
+  __shared__ uint32_t farthest;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int m = blockIdx.x, n0 = 0;
   if (m >= a.M) {
     const uint32_t at = (uint32_t)(m - a.M) * kBuildChunk;
@@ -660,85 +839,181 @@ __global__ __launch_bounds__(256) void kan_cell_build_kernel(const CellArgs a) {
     n0 = (int)((at - a.first[0][m] + kBuildChunk - 1) / kBuildChunk) * kBuildChunk;
     if (n0 == 0) return;
   }
-  const float* cr = centre_row(a, m);
-  float c[kG], cn = 0.f;
-#pragma unroll
-  for (int k = 0; k < kG; ++k) {
-    c[k] = cr[k];
-    cn = fmaf(c[k], c[k], cn);
-  }
   const int n = (int)a.total[0][m];
   const uint32_t* member = a.sorted[0] + a.first[0][m];
-  if (n0 < n) {
-    const int nc = min(kBuildChunk, n - n0), tile0 = (int)a.first_tile[m] + n0 / 32, tiles = (nc + 31) / 32;
-    int full = 32;
-    while (full < nc) full <<= 1;
-    for (int i = tid; i < full; i += 256) {
-      if (i >= nc) {
-        sorted[i] = ~0ull;
-        continue;
-      }
+  const int nc = min(kBuildChunk, n - n0), groups = (nc + kGroupShapes - 1) / kGroupShapes;
+  if (nc > 0) {
+    for (int i = tid; i < nc; i += kBuildThreads) {
       const uint32_t k = member[n0 + i];
+      id[i] = k;
+      order[0][i] = (uint16_t)i;
+#pragma unroll
+      for (int q = 0; q < kG; ++q) x[q][i] = a.cb[(long long)k * kG + q];
+    }
+    __syncthreads();
+    if (tid < 4) spot[nc + tid] = ~0u;
+    int now = 0, levels = 0;
+    while ((1 << levels) < groups) ++levels;
+    for (int level = 0; level < levels; ++level) {
+      // every member's place along its part's direction, a wave per part
+      for (int p = wave; p < (1 << level); p += kBuildThreads / kWave) {
+        int lo, hi;
+        part_of(nc, level, p, lo, hi);
+        if (hi - lo <= kGroupShapes) continue;             // (the same for the whole wave)
+        float mean[kG], v[kG];
+#pragma unroll
+        for (int q = 0; q < kG; ++q) mean[q] = 0.f;
+        for (int i = lo + lane; i < hi; i += 64) {
+          const int t = order[now][i];
+#pragma unroll
+          for (int q = 0; q < kG; ++q) mean[q] += x[q][t];
+        }
+        const float inv = 1.0f / (float)(hi - lo);
+#pragma unroll
+        for (int q = 0; q < kG; ++q) mean[q] = wave_total(mean[q]) * inv;
+        float top = -1.f;
+        int who = lo;
+        for (int i = lo + lane; i < hi; i += 64) {
+          const int t = order[now][i];
+          float d2 = 0.f;
+#pragma unroll
+          for (int q = 0; q < kG; ++q) d2 = fmaf(x[q][t] - mean[q], x[q][t] - mean[q], d2);
+          if (d2 > top) {
+            top = d2;
+            who = i;
+          }
+        }
+        const unsigned long long most = __ballot(top == wave_most(top));       // (0 for a part of no numbers)
+        const int t0 = order[now][__builtin_amdgcn_readlane(who, most ? __ffsll(most) - 1 : 0)];
+#pragma unroll
+        for (int q = 0; q < kG; ++q) v[q] = x[q][t0] - mean[q];
+        for (int step = 0; step < 2; ++step) {
+          float w[kG], big = 0.f;
+#pragma unroll
+          for (int q = 0; q < kG; ++q) w[q] = 0.f;
+          for (int i = lo + lane; i < hi; i += 64) {
+            const int t = order[now][i];
+            float dot = 0.f;
+#pragma unroll
+            for (int q = 0; q < kG; ++q) dot = fmaf(x[q][t] - mean[q], v[q], dot);
+#pragma unroll
+            for (int q = 0; q < kG; ++q) w[q] = fmaf(x[q][t] - mean[q], dot, w[q]);
+          }
+#pragma unroll
+          for (int q = 0; q < kG; ++q) {
+            v[q] = wave_total(w[q]);
+            big = fmaxf(big, fabsf(v[q]));
+          }
+          const float by = big > 0.f ? 1.0f / big : 0.f;
+#pragma unroll
+          for (int q = 0; q < kG; ++q) v[q] *= by;
+        }
+        for (int i = lo + lane; i < hi; i += 64) {
+          const int t = order[now][i];
+          float dot = 0.f;
+#pragma unroll
+          for (int q = 0; q < kG; ++q) dot = fmaf(x[q][t] - mean[q], v[q], dot);
+          const uint32_t bits = __float_as_uint(dot);      // in the order of the numbers; what is none has a place as well
+          spot[i] = ((bits >> 31 ? ~bits : bits | 0x80000000u) & ~(kBuildChunk - 1u)) | (uint32_t)i;      // (no two alike)
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < nc; i += kBuildThreads) {
+        int lo, hi, at;
+        part_around(nc, level, i, lo, hi);
+        at = i;
+        if (hi - lo > kGroupShapes) {
+          const uint32_t mine = spot[i];
+          at = lo;
+          for (int j = lo; j < hi; j += 4) {               // (parts begin and, but the last, end at whole groups)
+            const uint4 o = *(const uint4*)&spot[j];
+            at += (int)(o.x < mine) + (int)(o.y < mine) + (int)(o.z < mine) + (int)(o.w < mine);
+          }
+        }
+        order[now ^ 1][at] = order[now][i];
+      }
+      now ^= 1;
+      __syncthreads();
+    }
+    // Within a group by id: of equal scores a lane keeps the first row, which is then the lowest id, as in the whole search.
+    // A thread per row (spot: the member there).
+    for (int i = tid; i < nc; i += kBuildThreads) {
+      const int t = order[now][i], g = i & ~(kGroupShapes - 1);
+      const uint32_t k = id[t];
+      int at = g;
+      for (int j = g; j < min(g + kGroupShapes, nc); ++j) at += id[order[now][j]] < k;
+      spot[at] = (uint32_t)t;
+    }
+    __syncthreads();
+    const int group0 = (int)a.first_group[m] + n0 / kGroupShapes;
+    for (int rec = tid; rec < groups * kGroupRecords; rec += kBuildThreads) {      // [group][shape][instruction, half]
+      const int row = rec >> 2, part = rec & 3, r = row & (kGroupShapes - 1), g = group0 + row / kGroupShapes;
+      const bool there = row < nc;
+      const int t = there ? (int)spot[row] : 0;
+      float shape[kG];
+#pragma unroll
+      for (int q = 0; q < kG; ++q) shape[q] = there ? x[q][t] : 0.f;
+      a.frag[(long long)g * kGroupRecords + part * kGroupShapes + r] = shape_slots(shape, there, (part >> 1) * 16 + (part & 1) * 8);
+      if (part == 0) a.ids[g * kGroupShapes + r] = there ? id[t] : 0xffffffffu;
+    }
+    for (int row = tid; row < (groups * kGroupShapes + 63) / 64 * 64; row += kBuildThreads) {       // (whole waves: eight lanes a group)
+      const bool there = row < nc;
+      const int t = there ? (int)spot[row] : 0;
+      const float share = 1.0f / (float)max(1, min(kGroupShapes, nc - (row & ~(kGroupShapes - 1))));
+      float c[kG], d2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < kG; ++q) {
+        c[q] = there ? x[q][t] : 0.f;
+#pragma unroll
+        for (int o = 1; o < kGroupShapes; o <<= 1) c[q] += __shfl_xor(c[q], o, kWave);
+        c[q] *= share;
+        const float d = there ? x[q][t] - c[q] : 0.f;
+        d2 = fmaf(d, d, d2);
+      }
+      if (!(d2 >= 0.f)) d2 = 3.0e38f;             // (a row that is no number: its group is never left out)
+#pragma unroll
+      for (int o = 1; o < kGroupShapes; o <<= 1) d2 = fmaxf(d2, __shfl_xor(d2, o, kWave));
+      uint4 rec[2];
+      ball_operands(c, d2, false, rec[0], rec[1]);
+      if ((row & (kGroupShapes - 1)) == 0 && there) {
+        a.bound[(long long)(group0 + row / kGroupShapes) * 2] = rec[0];
+        a.bound[(long long)(group0 + row / kGroupShapes) * 2 + 1] = rec[1];
+      }
+    }
+  }
+  if (n0 == 0) {                                  // the cell: the ball around its centre
+    if (tid == 0) farthest = 0u;
+    __syncthreads();
+    const float* cr = centre_row(a, m);
+    float c[kG];
+#pragma unroll
+    for (int k = 0; k < kG; ++k) c[k] = cr[k];
+    float far = 0.f;
+    for (int i = tid; i < n; i += kBuildThreads) {
+      const float* s = a.cb + (long long)member[i] * kG;
       float d2 = 0.f;
 #pragma unroll
       for (int q = 0; q < kG; ++q) {
-        const float d = a.cb[(long long)k * kG + q] - c[q];
+        const float d = (i < nc ? x[q][i] : s[q]) - c[q];
         d2 = fmaf(d, d, d2);
       }
-      if (!(d2 >= 0.f)) d2 = 3.0e38f;           // (a row that is no number sorts last and is never skipped)
-      sorted[i] = ((unsigned long long)__float_as_uint(d2) << 32) | k;
+      if (!(d2 >= 0.f)) d2 = 3.0e38f;
+      far = fmaxf(far, d2);
     }
+    atomicMax(&farthest, __float_as_uint(far));
     __syncthreads();
-    for (int size = 2; size <= full; size <<= 1)           // bitonic
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        for (int i = tid; i < full / 2; i += 256) {
-          const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-          const unsigned long long u = sorted[lo], v = sorted[hi];
-          if ((u > v) == ((lo & size) == 0)) {
-            sorted[lo] = v;
-            sorted[hi] = u;
-          }
-        }
-        __syncthreads();
-      }
-    // Within a tile by id: of equal scores a lane keeps the first row, which is then the lowest id, as in the whole search.
-    for (int i = tid; i < nc; i += 256) {
-      const uint32_t id = (uint32_t)sorted[i];
-      int at = i & ~31;
-#pragma unroll
-      for (int o = 0; o < 32; ++o) at += (uint32_t)sorted[(i & ~31) + o] < id;      // (past the last one: the largest id)
-      row_id[at] = id;
-    }
-    __syncthreads();
-    for (int rec = tid; rec < tiles * 128; rec += 256) {
-      const int row = rec >> 2, part = rec & 3, ks = part >> 1, half = part & 1;       // (a row's four records)
-      const int tile = tile0 + (row >> 5), r = row & 31;
-      const uint32_t k = row < nc ? row_id[row] : 0xffffffffu;
-      a.frag[((long long)tile * 2 + ks) * 64 + half * 32 + r] = shape_slots(a.cb, k, row < nc, ks * 16 + half * 8);
-      if (part == 0) a.ids[tile * 32 + r] = k;
-    }
-    for (int t = tid; t < tiles; t += 256) {
-      const float far = __uint_as_float((uint32_t)(sorted[min(nc, t * 32 + 32) - 1] >> 32));
-      const float R = fp16_up(sqrtf(far) * 1.00001f);
-      // (fp16 operands: n and c are off by 2^-11 of themselves each, or flushed below 6e-5)
-      float cst = 0.5f * (R * R - cn) + 1.5e-3f * sqrtf(cn) + 1e-4f;
-      if (!(cn < 1e5f) || !(R < 300.f) || !(fabsf(cst) < 6e4f)) cst = 6e4f;      // beyond fp16: always visited
-      const float hi = fp16_of(cst), Rf = R < 300.f ? R : 300.f;
-      const float v0[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
-      const float v1[8] = {c[8], c[9], hi, cst - hi, Rf, 1.f, 1.f, 0.f};
-      uint4* rec = a.bound + (long long)((tile0 + t) >> 5) * 64 + ((tile0 + t) & 31);
-      rec[0] = pack_slots(v0);
-      rec[32] = pack_slots(v1);
+    if (tid == 0) {
+      uint4* rec = a.cell_bound + (long long)(m >> 5) * 64 + (m & 31);
+      ball_operands(c, __uint_as_float(farthest), n == 0, rec[0], rec[32]);
     }
   }
-  if (blockIdx.x == 0 && tid < 32) {             // rows of the last bound operand past the last tile: never visited
-    const int T = (int)a.first_tile[a.M], t = (T & ~31) + tid;
-    if (t >= T && (T & 31)) {
-      const float v0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const float v1[8] = {0.f, 0.f, -6e4f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      uint4* rec = a.bound + (long long)(t >> 5) * 64 + (t & 31);
-      rec[0] = pack_slots(v0);
-      rec[32] = pack_slots(v1);
+  if (blockIdx.x == 0) {                          // groups without shapes behind the last one
+    const int T = (int)a.first_group[a.M];
+    for (int rec = tid; rec < kPadGroups * kGroupRecords; rec += kBuildThreads) {
+      const int part = (rec / kGroupShapes) & 3;
+      const float none[kG] = {};
+      a.frag[(long long)T * kGroupRecords + rec] = shape_slots(none, false, (part >> 1) * 16 + (part & 1) * 8);
+      if (rec < kPadGroups * kGroupShapes) a.ids[T * kGroupShapes + rec] = 0xffffffffu;
     }
   }
 }
@@ -756,10 +1031,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, size_
 
 template <typename IdxT>
 __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellArgs a) {
-  __shared__ uint32_t s_seen[4][kCellMaxTiles / 32];       // tiles visited, a row per wave
-  __shared__ uint16_t s_list[4][64 * 32 + 2 * kAhead];     // tiles to visit
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  // runs of consecutive workgroups on one XCD (workgroups go to the eight in turn): neighbours ask for the same tiles
+  // A wave's lists.  Only the wave itself reads them: LDS serves its accesses in order, and order() keeps the compiler to it.
+  __shared__ uint16_t s_cells[4][kListCells], s_window[4][kListGroups + 64 * kAhead], s_visits[4][kListVisits + 16 * kAhead];
+  auto order = [] { asm volatile("" ::: "memory"); };
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
+  // runs of consecutive workgroups on one XCD (workgroups go to the eight in turn): neighbours ask for the same groups
   const unsigned W = gridDim.x, xcd = blockIdx.x & 7u, q8 = W >> 3, r8 = W & 7u;
   const long long wg = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
   const long long pos = (wg * 4 + wave) * 32 + (lane & 31);
@@ -767,13 +1043,14 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
     if (lane == 0) a.left[wg * 4 + wave] = 0;
     return;
   }
-  volatile uint32_t* seen = s_seen[wave];
-  volatile uint16_t* list = s_list[wave];
-  const int T = (int)a.first_tile[a.M], words = (T + 31) / 32, most = (int)(kRestShare * T);
-  for (int w = lane; w < words; w += 64) seen[w] = 0;
+  uint16_t* const cells = s_cells[wave];
+  uint16_t* const window = s_window[wave];
+  uint16_t* const visits = s_visits[wave];
+  auto first_group = [&](int cell) { return __builtin_amdgcn_readfirstlane((int)a.first_group[cell]); };     // (for the whole wave)
+  const int T = first_group(a.M), words = a.M / 32, most = (int)(kRestShare * T);
 
   const uint32_t e = a.sorted[1][min(pos, a.E - 1)];
-  const int key = a.key[1][e];
+  const int key = a.key[1][e] >> a.sub;           // its cell
   const bool there = pos < a.E, live = there && key < a.M;
 
   // edge operands of the search (see the head of the file) and of the bound
@@ -804,39 +1081,54 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 
   float best = -3.0e38f;
-  uint32_t best_id = 0;
-  auto id_of = [&](int t, int r) { return a.ids[t * 32 + 8 * (r >> 2) + 4 * half + (r & 3)]; };
+  int best_row = -1;             // where in the groups' rows the best shape lies
   // The first product of a shape that can win reaches `near` = best - slack (see first_product_slack).
   float slack = 0.f, near = 0.f;
-  auto take = [&](float sc, uint32_t id) {       // (equal scores: the lower id)
-    if (sc > best || (sc == best && id < best_id)) best_id = id;
+  auto take = [&](float sc, int row) {           // (equal scores: the lower id)
+    if (sc > best || (sc == best && a.ids[row] < a.ids[max(best_row, 0)])) best_row = row;
     best = fmaxf(best, sc);
     near = best - slack;
   };
   auto leave = [&] {                             // to the whole search
     if (lane == 0) a.left[wg * 4 + wave] = 1;
   };
+  const __amdgpu_buffer_rsrc_t cell_rsrc = buffer_of(a.cell_bound, (size_t)a.M * 32);
+  const __amdgpu_buffer_rsrc_t bound_rsrc = buffer_of(a.bound, (size_t)T * 32);
+  const __amdgpu_buffer_rsrc_t frag_rsrc = buffer_of(a.frag, (size_t)(T + kPadGroups) * kGroupRecords * 16);
+  auto load = [&](const __amdgpu_buffer_rsrc_t& rsrc, int lane_at, int at) {
+    return __builtin_bit_cast(h16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_at, at, 0));
+  };
+  // A tile of the search: four groups, a lane's rows are those of group g (its own argument)
+  const int row_at = (half * kGroupShapes + (lane & (kGroupShapes - 1))) * 16;
+  auto load_rows = [&](int g, int instruction) {
+    return load(frag_rsrc, g * (kGroupRecords * 16) + row_at, instruction * (kGroupRecords * 8));
+  };
+  // (g: the tile's four groups, the same for the whole wave.  Read from lanes inside the branch, the registers of the lanes
+  // that are switched off there would not need to hold them.)
+  auto take_tile = [&](const f32x16& acc, const int (&g)[4]) {
+    for_groups_with(acc, best, [&](int q, int r, float m) { take(m, g[q] * kGroupShapes + 4 * half + r); });
+  };
 
   // (1) own cells, both instructions of every tile
-  int visits = 0;
-  bool pending = live;
-  for (unsigned long long w; (w = __ballot(pending)) != 0;) {
-    const int cell = __builtin_amdgcn_readlane(key, __ffsll(w) - 1);
-    pending = pending && key != cell;
-    const int t0 = (int)a.first_tile[cell], t1 = (int)a.first_tile[cell + 1];
-    visits += t1 - t0;
-    if (visits > most) {
+  int visited = 0;
+  unsigned long long firsts = 0;                 // a lane of every own cell
+  for (unsigned long long w = __ballot(live); w != 0;) {
+    const int first = __ffsll(w) - 1, cell = __builtin_amdgcn_readlane(key, first);
+    firsts |= 1ull << first;
+    w &= ~__ballot(key == cell);
+    const int g0 = first_group(cell), g1 = first_group(cell + 1);
+    visited += g1 - g0;
+    if (visited > most) {
       leave();
       return;
     }
-    for (int t = t0; t < t1; ++t) {
-      const h16x8 f0 = __builtin_bit_cast(h16x8, (a.frag + (long long)t * 128)[lane]);
-      const h16x8 f1 = __builtin_bit_cast(h16x8, (a.frag + (long long)t * 128 + 64)[lane]);
+    for (int t = g0; t < g1; t += 4) {           // (past the cell's last group: the next cell's, or one without shapes)
+      const int g = t + ((lane & 31) >> 3);
+      const h16x8 f0 = load_rows(g, 0), f1 = load_rows(g, 1);
       f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f0, fb[0], zero, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f1, fb[1], acc, 0, 0, 0);
-      const float m = max_of(acc);
-      if (m >= best) take(m, id_of(t, row_of(acc, m)));
-      if (lane == 0) seen[t >> 5] = seen[t >> 5] | (1u << (t & 31));
+      const int four[4] = {t, t + 1, t + 2, t + 3};
+      take_tile(acc, four);
     }
   }
 
@@ -844,27 +1136,52 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
   // they agree on the better shape first.
   auto distance = [&] {
     const float sc_o = __shfl_xor(best, 32, kWave);
-    take(sc_o, (uint32_t)__shfl_xor((int)best_id, 32, kWave));
+    const int row_o = __shfl_xor(best_row, 32, kWave);
+    if (row_o >= 0) take(sc_o, row_o);
     float dist = live ? sqrtf(fmaxf(0.f, 1.0f - 2.0f * best) + 4e-6f) : 0.f;
     if (live && !unit) dist = 2.0f * kFar;       // (every tile: the wave goes to the whole search)
     slack = live ? first_product_slack(dist) : -INFINITY;      // (an edge without direction asks for nothing)
     near = best - slack;
     return dist;
   };
-  const __amdgpu_buffer_rsrc_t bound_rsrc = buffer_of(a.bound, (size_t)((T + 31) / 32) * 1024);
-  const __amdgpu_buffer_rsrc_t frag_rsrc = buffer_of(a.frag, (size_t)T * 2048);
-  auto load = [&](const __amdgpu_buffer_rsrc_t& rsrc, int at) {
-    return __builtin_bit_cast(h16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, at, 0));
+  // The groups listed so far.  A tile whose first product comes near the best score gets the second instruction.
+  int n_visits = 0;
+  auto visit = [&] {
+    // (to whole tiles and pairs of them: the last group again; what is loaded ahead of that is not used)
+    order();
+    const uint16_t last = visits[n_visits - 1];
+    if (lane < 4 * kAhead) visits[n_visits + lane] = last;
+    order();
+    const uint16_t* at = visits + ((lane & 31) >> 3);
+    auto examine = [&](int g, const f32x16& first) {
+      int four[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) four[q] = __builtin_amdgcn_readlane(g, q * kGroupShapes);
+      take_tile(__builtin_amdgcn_mfma_f32_32x32x16_f16(load_rows(g, 1), fb[1], first, 0, 0, 0), four);
+    };
+    int g[kAhead];
+    h16x8 f[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      g[k] = at[4 * k];
+      f[k] = load_rows(g[k], 0);
+    }
+    for (int i = 0; i < n_visits; i += 4 * kAhead) {
+      at += 4 * kAhead;
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[k], fb[0], zero, 0, 0, 0);
+        const int u = g[k];
+        g[k] = at[4 * k];
+        f[k] = load_rows(g[k], 0);
+        if (__ballot(max_of(acc) >= near)) examine(u, acc);
+      }
+    }
+    order();
+    n_visits = 0;
   };
-  // A tile whose first product comes near the best score gets the second instruction.
-  auto examine = [&](int t, const f32x16& first) {
-    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(load(frag_rsrc, t * 2048 + 1024), fb[1], first, 0, 0, 0);
-    const float m = max_of(acc);
-    if (m >= best) take(m, id_of(t, row_of(acc, m)));
-  };
-  // Every tile not visited yet that an edge with its bit in `who` asks for at distance d.  False: too many.
-  // (An instruction of any kind takes its wave's SIMD an issue slot: tiles are listed first, so that a visit is a
-  // lane read, a load, a matrix instruction and the maxima of a pair of tiles.)
+  // Every group that an edge with its bit in `who` asks for at distance d: of the cells that it asks for but the own ones,
+  // a lane a cell, then of their groups.  False: too many.
   auto search = [&](bool who, float d) -> bool {
     int asked = 0;
     const bool far = d > kFar;                   // (no shape known yet, or beyond fp16: every tile)
@@ -875,107 +1192,103 @@ __global__ __launch_bounds__(256, 6) void kan_assign_bounded_kernel(const CellAr
       fe[5] = (_Float16)-thr_hi;
       fe[6] = (_Float16)(thr_hi - thr);
     }
-    for (int w0 = 0; w0 < words; w0 += 64) {
-      const int w1 = min(words, w0 + 64);
-      uint32_t mine = 0;                         // lane w: the tiles of word w0 + w
+    // bit c: an edge (the rows) asks for the ball of column c
+    auto asks = [&](const h16x8& ball) {
+      const unsigned long long any = __ballot(!(max_of(__builtin_amdgcn_mfma_f32_32x32x16_f16(fe, ball, zero, 0, 0, 0)) <= 0.f));
+      return (uint32_t)any | (uint32_t)(any >> 32);
+    };
+    for (int w0 = 0; w0 < words; w0 += kListCells / 32) {
+      const int w1 = min(words - w0, kListCells / 32);
+      int mine = 0;                              // lane w: the cells of word w0 + w
       h16x8 f[kAhead];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) f[k] = load(bound_rsrc, min(w0 + k, words - 1) * 1024);
-      for (int w = 0; w < w1 - w0; w += kAhead) {        // (past the last word: that one again, struck out below)
+      for (int k = 0; k < kAhead; ++k) f[k] = load(cell_rsrc, lane * 16, (w0 + min(k, w1 - 1)) * 1024);
+      for (int w = 0; w < w1; w += kAhead) {     // (past the last word: that one again, struck out below)
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
-          // rows: edges, columns: tiles
-          const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fe, f[k], zero, 0, 0, 0);
-          f[k] = load(bound_rsrc, min(w0 + w + k + kAhead, words - 1) * 1024);
-          const unsigned long long any = __ballot(!(max_of(acc) <= 0.f));
-          mine = lane == w + k ? (uint32_t)any | (uint32_t)(any >> 32) : mine;
+          const int any = (int)asks(f[k]);
+          f[k] = load(cell_rsrc, lane * 16, (w0 + min(w + k + kAhead, w1 - 1)) * 1024);
+          mine = lane == w + k ? any : mine;
         }
       }
-      if (w0 + lane < w1) {
-        const uint32_t before = seen[w0 + lane];
-        mine &= ~before;
-        seen[w0 + lane] = before | mine;
-      } else {
-        mine = 0;
+      if (lane >= w1) mine = 0;
+      for (unsigned long long w = firsts; w != 0; w &= w - 1) {
+        const int cell = __builtin_amdgcn_readlane(key, __ffsll(w) - 1);
+        if (lane == (cell >> 5) - w0) mine &= ~(1 << (cell & 31));
       }
-      // the list of these tiles
-      int upto = __popc(mine);
-      const int own = upto;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(upto, o, kWave);
-        upto += lane >= o ? v : 0;
-      }
-      const int count = __builtin_amdgcn_readlane(upto, 63);
-      asked += count;
-      if (asked > most) return false;
-      if (count == 0) continue;
-      int last = 0;
-      for (int at = upto - own; mine; ++at) {
-        last = (w0 + lane) * 32 + __ffs(mine) - 1;
+      const int own = __popc(mine), cells_to = sums_up_to(own), n_cells = __builtin_amdgcn_readlane(cells_to, 63);
+      order();
+      for (int at = cells_to - own; mine; ++at) {
+        cells[at] = (uint16_t)((w0 + lane) * 32 + __ffs(mine) - 1);
         mine &= mine - 1;
-        list[at] = (uint16_t)last;
       }
-      const unsigned long long some = __ballot(own != 0);
-      last = __builtin_amdgcn_readlane(last, 63 - __clzll(some));
-      if (lane < 2 * kAhead) list[count + lane] = (uint16_t)last;      // (to whole groups, and one ahead: the last again)
-      for (int i0 = 0; i0 < count; i0 += 64) {
-        const int tiles = list[min(i0 + lane, count)];
-        auto tile = [&](int i) { return __builtin_amdgcn_readlane(tiles, i); };
-        int t[kAhead];
-        const int n_here = min(64, count - i0);
+      order();
+      for (int c0 = 0; c0 < n_cells; c0 += 64) {
+        const bool one = c0 + lane < n_cells;
+        const int cell = one ? cells[c0 + lane] : 0, g0 = (int)a.first_group[cell];
+        const int ng = one ? (int)a.first_group[cell + 1] - g0 : 0, to = sums_up_to(ng), from = to - ng;
+        const int total = __builtin_amdgcn_readlane(to, 63);
+        for (int v0 = 0; v0 < total; v0 += kListGroups) {
+          const int n = min(total - v0, kListGroups);
+          order();
+          for (int j = max(0, v0 - from); j < min(ng, v0 + kListGroups - from); ++j) window[from + j - v0] = (uint16_t)(g0 + j);
+          order();
+          int g[kAhead];
+          const uint16_t* at = window + (lane & 31);
+          auto load_ball = [&](int i) { return load(bound_rsrc, i * 32 + half * 16, 0); };
+          // (past the last one: whatever stands there, struck out below)
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
-          t[k] = tile(k);
-          f[k] = load(frag_rsrc, t[k] * 2048);
-        }
-        for (int i = 0; i < n_here; i += kAhead) {
+          for (int k = 0; k < kAhead; ++k) {
+            g[k] = at[32 * k];
+            f[k] = load_ball(g[k]);
+          }
+          for (int i = 0; i < n; i += 32 * kAhead) {
+            at += 32 * kAhead;
 #pragma unroll
-          for (int k = 0; k < kAhead; k += 2) {
-            const f32x16 acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[k], fb[0], zero, 0, 0, 0);
-            const f32x16 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[k + 1], fb[0], zero, 0, 0, 0);
-            const int u0 = t[k], u1 = t[k + 1];
-            t[k] = tile(min(i + k + kAhead, 63));
-            t[k + 1] = tile(min(i + k + 1 + kAhead, 63));
-            f[k] = load(frag_rsrc, t[k] * 2048);
-            f[k + 1] = load(frag_rsrc, t[k + 1] * 2048);
-            const float m0 = max_of(acc0), m1 = max_of(acc1);
-            if (__ballot(fmaxf(m0, m1) >= near)) {
-              if (__ballot(m0 >= near)) examine(u0, acc0);
-              if (__ballot(m1 >= near)) examine(u1, acc1);
+            for (int k = 0; k < kAhead; ++k) {
+              const int group = g[k], rest = n - i - 32 * k;
+              const uint32_t ones = asks(f[k]) & (rest >= 32 ? ~0u : (rest > 0 ? (1u << rest) - 1u : 0u));
+              g[k] = at[32 * k];
+              f[k] = load_ball(g[k]);
+              if (lane < 32 && ((ones >> lane) & 1u)) visits[__builtin_amdgcn_mbcnt_lo(ones, n_visits)] = (uint16_t)group;
+              n_visits += __popc(ones);
+              asked += __popc(ones);
             }
           }
+          if (asked > most) return false;
+          const bool last = v0 + kListGroups >= total && c0 + 64 >= n_cells;       // (no empty cell is asked for)
+          if (n_visits > (last ? 0 : kListVisits - kListGroups)) visit();
         }
       }
     }
     return true;
   };
 
-  float d = distance();
-  const bool in = live && d <= kFar;
-  float sum = in ? d : 0.f, cnt = in ? 1.f : 0.f;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    sum += __shfl_xor(sum, o, kWave);
-    cnt += __shfl_xor(cnt, o, kWave);
+  float d = distance(), asked_at;
+  {
+    auto mean_of = [&](bool which) {
+      const int n = __popcll(__ballot(which));
+      return n > 0 ? wave_total(which ? d : 0.f) / (float)n : 2.0f * kFar;
+    };
+    const float mean = mean_of(live && d <= kFar), low = mean_of(live && d <= mean);
+    // the edges that have found their shape: their own distance, and the others what those would ask for
+    const bool apart = kFound * low < kApart * mean;
+    asked_at = !apart ? fminf(d, kPoor * mean) : (d <= kFound * low ? d : fminf(d, kAsk * low));
   }
-  const float mean = cnt > 0.f ? kMeanFactor * sum / cnt : 2.0f * kFar;
-  bool done = search(live, fminf(d, mean));      // (2)
-  if (done) {
+  bool who = live;
+  for (int step = 2; step <= 3 && __ballot(who); ++step) {
+    if (!search(who, step == 2 ? asked_at : d)) {
+      leave();
+      return;
+    }
     d = distance();
-    const bool left = live && d > mean;
-    if (__ballot(left)) done = search(left, d);  // (3)
+    who = live && d > asked_at;
   }
-  if (!done) {
-    leave();
-    return;
-  }
-  (void)distance();
   if (lane == 0) a.left[wg * 4 + wave] = 0;
-  // (an edge without direction: the shape of the smallest norm; one that is no number has no scores and keeps row 0)
+  // (an edge without direction: the shape of the smallest norm; one that is no number has no scores and gets row 0)
   if (lane < 32 && there) {
-    if (!live) best_id = a.gain[e] == a.gain[e] ? *a.least : 0u;
-    ((IdxT*)a.idx)[e] = (IdxT)best_id;
+    const uint32_t id = live ? (best_row >= 0 ? a.ids[best_row] : 0u) : (a.gain[e] == a.gain[e] ? *a.least : 0u);
+    ((IdxT*)a.idx)[e] = (IdxT)id;
   }
 }
 
@@ -1045,15 +1358,16 @@ dim3 split_grid(long long E) { return dim3((unsigned)((E + kEdgeTilesPerWave * 3
 // The bounded search pays where its cells, launches and bound tests are small next to the scores they save, for grids
 // that fit their codebook and at little loss for those that do not.  Bounded search with 2 % / 5 % / 15 % noise per
 // coefficient / unrelated grids against the whole search (which does not care), us:
-//     K = 65,536   2^20 edges  545 / 779 / 1290 / 1332  against 3820      2^16 edges  128 / 167 / 224 / 226  against 312
-//     K = 32,768   2^17 edges  110 / 148 / 203 / 212  against 313
-//     K = 16,384   2^20 edges  300 / 420 / 688 / 732  against 1024        2^18 edges  132 / 167 / 238 / 252  against 296
-//                  2^17 edges  98 / 126 / 160 / 165  against 173          98,304 edges  94 / 112 / 141 / 146  against 132
-//     K = 8,192    2^20 edges  252 / 335 / 522 / 553  against 547
-// (K = 8,192 and 2^18 edges with 5 % noise 249 against 195; K = 262,144 and 2^20 edges 1.9 against 14.9 ms).
+//     K = 65,536   2^20 edges  332 / 491 / 885 / 908  against 3631      2^15 edges  119 / 159 / 225 / 218  against 190
+//     K = 32,768   2^17 edges  105 / 130 / 193 / 192  against 316       2^16 edges  98 / 121 / 173 / 169  against 175
+//     K = 16,384   2^20 edges  203 / 286 / 552 / 561  against 988       2^18 edges  102 / 131 / 210 / 216  against 291
+//                  2^17 edges  85 / 103 / 152 / 154  against 168        2^16 edges  81 / 99 / 141 / 137  against 100
+//     K = 8,192    2^20 edges  184 / 243 / 445 / 443  against 530       2^19 edges  124 / 159 / 266 / 263  against 285
+//                  2^18 edges  96 / 117 / 178 / 177  against 164
+//     K = 4,096    2^20 edges  168 / 211 / 355 / 362  against 290
 bool assign_bounded_ok(long long E, int K) {
   const long long work = E * K;
-  return (work >= (3ll << 29) && K >= 16384 || work >= (1ll << 33) && K >= 8192) && cell_layout(1, K).tiles_max <= kCellMaxTiles;
+  return (work >= (3ll << 29) && K >= 16384 || work >= (1ll << 32) && K >= 8192) && cell_layout(1, K).groups_max <= kCellMaxGroups;
 }
 size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
 
@@ -1067,14 +1381,17 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   a.E = E;
   a.K = K;
   a.M = g.M;
+  a.sub = g.sub;
   a.shape_wgs = (K + kEdgesPerWg - 1) / kEdgesPerWg;
   a.centres = (uint4*)(w + g.centres);
   a.frag = (uint4*)(w + g.frag);
   a.ids = (uint32_t*)(w + g.ids);
+  a.cell_bound = (uint4*)(w + g.cell_bound);
   a.bound = (uint4*)(w + g.bound);
   a.sorted[0] = (uint32_t*)(w + g.member);
   a.sorted[1] = (uint32_t*)(w + g.perm);
   for (int p = 0; p < 2; ++p) {
+    a.bins[p] = g.bins[p];
     a.groups[p] = g.groups[p];
     a.chunk[p] = g.chunk[p];
     a.key[p] = (uint16_t*)(w + g.key[p]);
@@ -1082,7 +1399,7 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
     a.total[p] = (uint32_t*)(w + g.total[p]);
     a.first[p] = (uint32_t*)(w + g.first[p]);
   }
-  a.first_tile = (uint32_t*)(w + g.first_tile);
+  a.first_group = (uint32_t*)(w + g.first_group);
   a.wg_least = (unsigned long long*)(w + g.wg_least);
   a.left = (uint8_t*)(w + g.left);
   a.least = (uint32_t*)(w + g.least);
@@ -1091,14 +1408,14 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   a.bias = bias;
   const unsigned edge_wgs = (unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg);
   const dim3 sort_grid((unsigned)(g.groups[0] > g.groups[1] ? g.groups[0] : g.groups[1]), 2);
-  const size_t cells_lds = (size_t)(g.M + 1) * 4;
+  const size_t cells_lds = (size_t)g.bins[1] * 4;
   hipLaunchKernelGGL(kan_cell_centres_kernel, dim3((unsigned)((g.M * 2 + 255) / 256)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(kan_cells_kernel, dim3((unsigned)a.shape_wgs + edge_wgs), dim3(kAssignThreads), 0, s, a);
   hipLaunchKernelGGL(kan_cell_count_kernel, sort_grid, dim3(kSortThreads), cells_lds, s, a);
-  hipLaunchKernelGGL(kan_cell_chunks_kernel, dim3((unsigned)(g.M / 256 + 1), 2), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(kan_cell_chunks_kernel, dim3((unsigned)((g.bins[1] + 63) / 64), 2), dim3(256), 0, s, a);
   hipLaunchKernelGGL(kan_cell_scan_kernel, dim3(1), dim3(kSortThreads), 0, s, a);
   hipLaunchKernelGGL(kan_cell_place_kernel, sort_grid, dim3(kSortThreads), cells_lds, s, a);
-  hipLaunchKernelGGL(kan_cell_build_kernel, dim3((unsigned)(g.M + (K + kBuildChunk - 1) / kBuildChunk)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(kan_cell_build_kernel, dim3((unsigned)(g.M + (K + kBuildChunk - 1) / kBuildChunk)), dim3(kBuildThreads), 0, s, a);
   const dim3 grid((unsigned)((E + 127) / 128));
   if (idx_u32) hipLaunchKernelGGL(kan_assign_bounded_kernel<uint32_t>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(kan_assign_bounded_kernel<uint16_t>, grid, dim3(256), 0, s, a);
@@ -1108,7 +1425,7 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   rest.E = E;
   rest.list = a.sorted[1];
   rest.left = a.left;
-  rest.tiles = a.first_tile + g.M;
+  rest.groups = a.first_group + g.M;
   rest.ids = a.ids;
   rest.idx = idx;
   const dim3 rest_grid((unsigned)std::min<long long>((E + 127) / 128, kRestWorkgroups));

@@ -136,6 +136,8 @@ def _grids(kind, K, E, seed):
     if kind == "near ties":        # pairs of rows 1e-5 apart: scores that differ by less than a millionth
         cb *= 0.97 + torch.rand((K, 1), generator=g, device="cuda") * 0.06
         cb[K // 2:] = cb[:K - K // 2] + 3e-6 * torch.randn((K - K // 2, 10), generator=g, device="cuda")
+    if kind == "clumps":           # cells of some hundred to some thousand shapes, most of them beyond one chunk of 512
+        cb[:K // 2] = cb[torch.randint(0, 5, (K // 2,), generator=g, device="cuda")] + 0.02 * cb[:K // 2]
     k = torch.randint(0, K, (E, 1), generator=g, device="cuda")
     if kind == "one cell":
         k[:] = 5
@@ -144,6 +146,10 @@ def _grids(kind, K, E, seed):
     coef = gain * (cb[k] + noise) + 0.01 * torch.randn((E, 1, 1), generator=g, device="cuda")
     if kind == "flat":
         coef[::3] = 0.0
+    if kind == "no numbers":       # among the shapes that become centres of cells as well as between them
+        cb[::64 * 7] = float("nan")
+        cb[32::64 * 5] = float("inf")
+        cb[::64 * 11] = 1e6
     return coef.contiguous(), cb.contiguous()
 
 
@@ -207,7 +213,11 @@ def test_bounded_search_scores_as_well_as_the_whole_search(kb, K, E):
 @pytest.mark.parametrize("kind,K,E", [("trained", 16421, 98101), ("trained", 70000, 24001), ("far", 16384, 98337),
                                       ("duplicates", 16384, 98304), ("norms", 16384, 98304), ("near ties", 16384, 98304),
                                       ("flat", 16384, 98304), ("one cell", 16384, 98304), ("one row", 16384, 98304),
-                                      ("unused", 16384, 98304), ("unused", 70001, 30001)])
+                                      ("unused", 16384, 98304), ("unused", 70001, 30001),
+                                      # parts of a cell: 8 up to 1024 cells, 4, 2, 1 (K / 64 cells, at most 8192 parts)
+                                      ("trained", 65536, 24607), ("trained", 131071, 12301), ("trained", 262144, 6151),
+                                      ("trained", 300000, 5377), ("clumps", 16384, 98304), ("clumps", 65521, 33001),
+                                      ("no numbers", 16384, 98304)])
 def test_bounded_search_gives_the_ids_of_the_whole_search(kb, kind, K, E):
     """Not one id differs, whichever edges share a wave and are handed over: equal scores go to the lowest id in both,
     edges of gain 0 to the same shape, and grids that are no numbers or overflow to what the whole search gives."""
