@@ -115,11 +115,18 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   // block-floating-point rows (a power of two of them per bucket: 4096 or 2048)
   constexpr int kCbStride = CODE == kCbBfp8 ? kCbBytes / 20 * 12 : kCbBytes;
   constexpr int kXPerThread = MAXIN / kBucketThreads;
+  constexpr int kEntryBytes = CODE == kCbF32 ? 4 : (CODE == kCbF16 ? 2 : 1);
+  constexpr int kRowBytes = CODE == kCbBfp8 ? 12 : 10 * kEntryBytes;
   constexpr int kWindow = CODE == kCbF32 ? 4 : (CODE == kCbF16 ? 3 : 2);      // dwords that hold four entries of a row
-  constexpr int kWinWords = CODE == kCbBfp8 ? 3 : kWindow;
   constexpr int kCbPerThread = (kCbBytes / 16 + kBucketThreads - 1) / kBucketThreads;   // 16-byte units per thread
-  __shared__ __attribute__((aligned(16))) uint32_t cb[kCbBytes / 4 + 8];   // + 16 bytes read-ahead, + 16 spare
-  __shared__ float4 bas[MAXIN];             // {w0, w1, w2, span as integer bits}; w3 = 1 - w0 - w1 - w2
+  // The bucket's rows (+ 16 bytes read-ahead, + 16 spare) and the basis table {w0, w1, w2, where in LDS the entry of row 0 lies
+  // that the window begins with}; w3 = 1 - w0 - w1 - w2.  The table lies where the offset field of an LDS instruction (16 bits)
+  // reaches, the rows' address is part of the table: neither lookup takes an addition.
+  constexpr int kCbLds = kCbBytes + 32, kBasLds = MAXIN * 16, kCbAt = kCbLds < kBasLds ? 0 : kBasLds, kBasAt = kCbLds < kBasLds ? kCbLds : 0;
+  static_assert(kBasAt < 65536 && kCbLds % 16 == 0 && kBasLds % 16 == 0, "offset of 16 bits");
+  __shared__ __attribute__((aligned(16))) char tables[kCbLds + kBasLds];
+  char* const cb = tables + kCbAt;
+  float4* const bas = (float4*)(tables + kBasAt);
   // running sums of the products of a wave's pass (and of a 17th): of each lane's eight, and at the end of each lane of all before it
   __shared__ __attribute__((aligned(16))) float prod[kWaves + 1][kPass];
   __shared__ float upto[kWaves + 1][kWave];
@@ -229,7 +236,7 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
         const float xin = a.x_tanh ? tanhf(xv[r]) : xv[r];
         const BasisW w = basis_eval_rule(xin, a.rule);
         // (threads past the last input of the round write entries nobody reads)
-        bas[i] = make_float4(w.w0, w.w1, w.w2, __uint_as_float((uint32_t)w.span));
+        bas[i] = make_float4(w.w0, w.w1, w.w2, __uint_as_float((uint32_t)(kCbAt + w.span * kEntryBytes)));
       }
     }
   }
@@ -295,8 +302,10 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
   // u is one) -> prod[strip], and of all the lanes' up to this one's last edge, anew likewise -> upto[strip].  Edges outside the block (groups that straddle its ends, re-read groups) are looked up like the
   // others: what they give, numbers or not, stands in front of the block's first segment or behind its last.
   auto products = [&](const PassRegs<GK>& c, const uint32_t f, const int strip) {
+    const uint32_t go_on = ~f;
     float4 w[kEpt];
-    uint32_t at[kEpt], win[kEpt][kWinWords];
+    uint32_t at[kEpt], win[kEpt][kWindow];       // a window's first byte, the aligned dwords that hold it
+    uint32_t third[kEpt];                        // block floating point: the row's third dword, with its power of two
     auto read_basis = [&](int u0) {
 #pragma unroll
       for (int u = u0; u < u0 + kEpt / 2; ++u) w[u] = bas[u16_of(c.i, u)];
@@ -304,12 +313,12 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
     auto read_window = [&](int u0) {
 #pragma unroll
       for (int u = u0; u < u0 + kEpt / 2; ++u) {
-        at[u] = u16_of(c.q, u) * (CODE == kCbBfp8 ? 12u : 10u) + __float_as_uint(w[u].w);
-        // bytes at .. at+3 (halves at .. at+3, floats at .. at+3) of the bucket lie in two (three, four) aligned dwords
-        const uint32_t d = CODE == kCbF32 ? at[u] : (CODE == kCbF16 ? at[u] >> 1 : at[u] >> 2);
+        at[u] = u16_of(c.q, u) * (uint32_t)kRowBytes + __float_as_uint(w[u].w);
+        // (LDS serves unaligned reads as well, at less than half the rate: 2048 x 1024 at batch 1 10.0 against 12.3 us)
+        const uint32_t* const d = (const uint32_t*)(tables + (at[u] & ~3u));
 #pragma unroll
-        for (int n = 0; n < kWindow; ++n) win[u][n] = cb[d + n];
-        if constexpr (CODE == kCbBfp8) win[u][2] = cb[u16_of(c.q, u) * 3u + 2u];      // the row's own power of two
+        for (int n = 0; n < kWindow; ++n) win[u][n] = d[n];
+        if constexpr (CODE == kCbBfp8) third[u] = ((const uint32_t*)cb)[u16_of(c.q, u) * 3u + 2u];
       }
     };
     float sums[kEpt];
@@ -318,20 +327,18 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
       for (int u = u0; u < u0 + kEpt / 2; ++u) {
         float c0, c1, c2, c3;
         if constexpr (CODE == kCbI8 || CODE == kCbBfp8) {
-          // funnel-shifted; q + 128 as unsigned bytes (the differences below do not see the offset)
-          const uint32_t v = __builtin_amdgcn_alignbyte(win[u][1], win[u][0], at[u] & 3u) ^ 0x80808080u;
-          c0 = (float)(v & 0xffu);
-          c1 = (float)((v >> 8) & 0xffu);
-          c2 = (float)((v >> 16) & 0xffu);
-          c3 = (float)(v >> 24);
+          const int v = (int)__builtin_amdgcn_alignbyte(win[u][1], win[u][0], at[u]);      // (shifts by its low two bits)
+          c0 = (float)(int8_t)v;
+          c1 = (float)(int8_t)(v >> 8);
+          c2 = (float)(int8_t)(v >> 16);
+          c3 = (float)(int8_t)(v >> 24);
         } else if constexpr (CODE == kCbF16) {
-          const uint32_t sh = (at[u] & 1u) * 2u;        // funnel-shifted by 0 or 2 bytes
-          const uint32_t w0 = __builtin_amdgcn_alignbyte(win[u][1], win[u][0], sh);
-          const uint32_t w1 = __builtin_amdgcn_alignbyte(win[u][2], win[u][1], sh);
-          c0 = half_bits_to_float(w0 & 0xffffu);
-          c1 = half_bits_to_float(w0 >> 16);
-          c2 = half_bits_to_float(w1 & 0xffffu);
-          c3 = half_bits_to_float(w1 >> 16);
+          const uint32_t lo = __builtin_amdgcn_alignbyte(win[u][1], win[u][0], at[u]);
+          const uint32_t hi = __builtin_amdgcn_alignbyte(win[u][2], win[u][1], at[u]);
+          c0 = half_bits_to_float(lo & 0xffffu);
+          c1 = half_bits_to_float(lo >> 16);
+          c2 = half_bits_to_float(hi & 0xffffu);
+          c3 = half_bits_to_float(hi >> 16);
         } else {
           c0 = __uint_as_float(win[u][0]);
           c1 = __uint_as_float(win[u][1]);
@@ -339,12 +346,13 @@ __global__ __launch_bounds__(kBucketThreads) void kan_bucket_kernel(const Bucket
           c3 = __uint_as_float(win[u][3]);
         }
         // sum_k w_k c_k with w3 = 1 - w0 - w1 - w2 (the bases sum to 1)
-        float s = (CODE == kCbI8 || CODE == kCbBfp8) ? c3 - 128.0f : c3;
+        float s = c3;
         s = fmaf(w[u].z, c2 - c3, s);
         s = fmaf(w[u].y, c1 - c3, s);
         s = fmaf(w[u].x, c0 - c3, s);
-        if constexpr (CODE == kCbBfp8) s *= bfp8_row_scale(win[u][2]);
-        const uint32_t go = (uint32_t)__builtin_amdgcn_sbfe((int)~f, u, 1);      // all ones unless the edge starts a segment
+        if constexpr (CODE == kCbBfp8) s *= bfp8_row_scale(third[u]);
+        uint32_t go;                             // all ones unless the edge starts a segment (written as C++, the compiler compares and selects)
+        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(go) : "v"(go_on), "n"(u));
         sums[u] = u > 0 ? fmaf(gain_of<GK>(c, u, qp), s, masked(sums[u - 1], go)) : gain_of<GK>(c, u, qp) * s;
       }
     };
