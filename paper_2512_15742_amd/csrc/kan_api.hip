@@ -290,20 +290,44 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
 //   4096 x 1024 split  88.9*/ 55.5    135 / 70.0    200 / 121     266 / 184     226 / 232     333 / 413
 //   4096 x 4096 split   312*/ 169     431 / 212     575 / 400     873 / 687     875 / 792    1501 / 1397
 // and with ten heads of 2048-256-21 at batch 128 114 / 61 (fp16), 206 / 87 (split).  The lines are drawn through this table,
-// where one size gains and the next loses on their far side.  A second run, with the parameters in the caches, puts the kernel
-// ahead beyond them too.  Streaming form / this / kan_stream.hip at batch 640, 768, 896, 1024: 2048 x 1024 fp16
-// 59.4 / 54.8 / 56.0, 64.0 / 56.3 / 58.5, 66.8 / 58.6 / 65.3, 65.0 / 61.7 / 68.6.  Streaming form / this at batch 128, 256, 512,
-// 768, split operands, Int8 rows: 1024 x 512 29.3 / 26.4, 31.0 / 28.0, 36.7 / 34.8, 47.2 / 40.8, 512 x 512 25.4 / 18.4,
-// 27.5 / 22.7, 30.5 / 28.3, 34.7 / 33.3, 2048 x 256 32.1 / 26.1, 33.0 / 34.5, 41.0 / 35.5, 50.6 / 44.5.
+// where one size gains and the next loses on their far side.
+// Beyond them it is ahead for single heads of one- and two-byte codebook rows (parameters from the memory-side cache):
+//   - batch 513 to 900, more than 512 outputs, fp16, at 520 / 640 / 768 / 900: 1024 x 1024 36.2 / 39.2 / 41.0 / 45.0 against
+//     34.1 / 35.0 / 36.2 / 38.0, 2048 x 1024 58.8 / 62.8 / 67.3 / 66.6 against 52.0 / 53.3 / 55.3 / 58.8, 1500 x 1100
+//     79.9 / 80.5 / 61.0 / 86.0 against 46.5 / 47.6 / 50.3 / 53.1 (kan_mfma.hip pads 1100 outputs to 1280), 1900 x 1100 at 900
+//     101.6 against 62.0; fp32 rows 2048 x 1024 at 1024 74.8 against 75.8;
+//   - up to batch 1024 where the next layer adds the slices (2048-1024-256 at 640 / 1024 83.0 / 90.9 against 79.8 / 87.6);
+//   - layers of 2^18 edges with 512 outputs and more, up to batch 256 fp16 and 768 split: 512 x 512 fp16 at 80 / 256 / 400
+//     16.0 / 17.6 / 20.1 against 14.6 / 16.9 / 20.7, split at 80 / 256 / 700 21.2 / 22.9 / 31.4 against 18.3 / 21.5 / 27.9, 1024 x 512
+//     fp16 at 80 / 256 19.6 / 22.1 against 17.3 / 19.1, split at 256 / 700 30.6 / 45.9 against 24.2 / 37.9, 700 x 900 split at 128 / 512
+//     31.8 / 44.0 against 21.0 / 34.8, 300 x 1000 split at 80 / 700 25.9 / 34.8 against 19.2 / 29.1.  Layers of few outputs
+//     for their inputs lose (2048 x 128 split at 400 29.7 against 32.3, fp16 21.4 against 25.5), smaller ones gain 1 to 5 %;
+//     fp16 ones that take a layer's slices lose, their records being written beside the first layer's (2048-700-512-30 at 250
+//     58.1 against 60.1).
+// Above these batches the sizes disagree again (fp16 at 1536 2048 x 1024 87.6 / 86.3, at 2048 100 / 105.5; 4096 x 1024 at 1200 134 /
+// 141; split at 1536 2048 x 1024 176 / 195).
 constexpr long long kWideMinEdges = 1ll << 20;        // over the heads of a launch
 constexpr int64_t kWideMinBatch = 65, kWideMaxBatchHalf = 512, kWideMaxBatchHalfLarge = 1024, kWideMaxBatchSplit = 768;
 constexpr long long kWideLargeEdges = 1ll << 22;      // ... for kWideMaxBatchHalfLarge
+constexpr int64_t kWideMaxBatchHalfManyOut = 900;     // ... above kWideManyOut outputs
+constexpr int kWideManyOut = 512;
+constexpr long long kWideSmallEdges = 1ll << 18;      // from kWideManyOut outputs on
+constexpr int64_t kWideSmallMaxBatchHalf = 256;
+
+// Largest batch at which that kernel is the faster one, 0: at none.
+int64_t wide_max_batch(int n_in, int n_out, int n_heads, int code, bool split3, int x_parts, bool reduced) {
+  const long long edges = (long long)n_in * n_out * n_heads;
+  const bool beyond = n_heads == 1 && code != kCbF32;
+  if (edges < kWideMinEdges)
+    return !beyond || edges < kWideSmallEdges || n_out < kWideManyOut ? 0 : (split3 ? kWideMaxBatchSplit : (x_parts > 1 ? 0 : kWideSmallMaxBatchHalf));
+  if (split3) return kWideMaxBatchSplit;
+  if (edges >= kWideLargeEdges || (beyond && !reduced)) return kWideMaxBatchHalfLarge;
+  return beyond && n_out > kWideManyOut ? kWideMaxBatchHalfManyOut : kWideMaxBatchHalf;
+}
 
 // Turns plan p of such a layer into one for that kernel where it is the faster one.
-bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool split3) {
-  const long long edges = (long long)n_in * n_out * n_heads;
-  if (B < kWideMinBatch || edges < kWideMinEdges || !wide_takes(n_in, n_out, B)) return false;
-  if (B > (split3 ? kWideMaxBatchSplit : (edges >= kWideLargeEdges ? kWideMaxBatchHalfLarge : kWideMaxBatchHalf))) return false;
+bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool split3, int x_parts, bool reduced) {
+  if (B < kWideMinBatch || B > wide_max_batch(n_in, n_out, n_heads, p.cfg.code, split3, x_parts, reduced) || !wide_takes(n_in, n_out, B)) return false;
   const int n_jt = (n_out + kWideTileN - 1) / kWideTileN;
   if ((long long)n_jt * kWideTileN * 2 > 3ll * n_out) return false;        // (tiles half empty)
   const int tile = B <= 128 ? 128 : (B <= 256 || split3 ? 256 : 512), n_bt = (int)((B + tile - 1) / tile);
@@ -389,14 +413,14 @@ constexpr long long kTailSlicedInputs = 4096, kTailSlicedInputsManyTiles = 2048;
 
 // x_parts: slices the layer's input may come in.
 LayerPlan plan_matrix(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3,
-                      int x_parts, int min_rows, bool wide) {
+                      int x_parts, int min_rows, bool wide, bool reduced) {
   LayerPlan p = plan_mfma(n_in, n_out, B, n_heads, idx_u32, gb_kind, code, split3, min_rows);
   const long long n_bt = (B + 31) / 32;
   const int tile_n = split3 || n_out <= 32 || (n_out + 31) / 32 * n_bt * n_heads <= 256 ? 32 : 64;
   const long long n_jt = (n_out + tile_n - 1) / tile_n;
   if (n_in > kTailMaxIn || (long long)n_in * n_out > kTailMaxEdges || n_jt * n_bt * n_heads > kTailMaxWorkgroups ||
       (x_parts > 1 && (long long)x_parts * n_in > (n_jt > 2 ? kTailSlicedInputsManyTiles : kTailSlicedInputs))) {
-    if (wide && !make_wide(p, n_in, n_out, B, n_heads, split3)) make_stream(p, n_in, n_out, B, n_heads, split3);
+    if (wide && !make_wide(p, n_in, n_out, B, n_heads, split3, x_parts, reduced)) make_stream(p, n_in, n_out, B, n_heads, split3);
     return p;
   }
   p.kind = kPlanTail;
@@ -664,19 +688,19 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // path would write 20 bytes per edge and read them back for no reuse)
     if (B <= fused_max) {
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
-      if (wide) make_wide(p, L.in, L.out, B, n_heads, false);
+      if (wide) make_wide(p, L.in, L.out, B, n_heads, false, x_parts, reduced);
       return p;
     }
-    return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, false, x_parts, min_rows, wide);
+    return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, false, x_parts, min_rows, wide, reduced);
   }
   if (prepared_ok && B <= bucket_max_batch((long long)L.in * L.out))
     return column_ok && (long long)L.in * L.out * B <= kColumnMaxWork ? plan_column(L, B) : plan_bucket(L, B, n_heads);
   // large batches: the fp16 machinery with both operands split into high and low parts
-  if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide);
+  if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide, reduced);
   const long long edges = (long long)L.in * L.out;
   if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) {
     LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);
-    if (wide) make_wide(p, L.in, L.out, B, n_heads, true);
+    if (wide) make_wide(p, L.in, L.out, B, n_heads, true, x_parts, reduced);
     return p;
   }
   if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows, reduced);
