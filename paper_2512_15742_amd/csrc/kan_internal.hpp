@@ -273,8 +273,8 @@ hipError_t launch_fused_wave(const GatherCfg&, const FusedArgs&, dim3 grid, hipS
 
 // ---- bucketed small-batch path (prepared layers) ----------------------------------
 // A prepared layer holds its edges regrouped by codebook bucket (a run of consecutive
-// codewords whose rows fit in LDS) and, inside a bucket, by output j then input i; a
-// segment is the run of edges of one (bucket, j).  Per edge it keeps the input index, the
+// codewords whose rows fit in LDS) and, inside a bucket, by output j then input i (layers of more than kColumnMaxEdges
+// edges: by the LDS banks of the inputs); a segment is the run of edges of one (bucket, j).  Per edge it keeps the input index, the
 // codeword id relative to the bucket and the gain; the biases of an output are summed once
 // (the bases sum to 1, so they do not depend on x).
 constexpr int kBucketMaxIn = 4096;      // the basis table of all inputs lives in LDS beside the bucket

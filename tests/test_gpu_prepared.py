@@ -167,6 +167,28 @@ def test_prepared_layout_bit_exact(kb, n_in, n_out, K, cb, gb, idxd):
     _check_tables(_read_layout.tables, got[0], (P.K + rows - 1) // rows, n_in, n_out)
 
 
+@pytest.mark.parametrize("n_in,n_out,K,cb,gb,idxd", [
+    (1025, 1030, 300, "i8", "f16", "u16"),      # one bucket: segments of 1025 edges, three blocks of the ordering
+    (2048, 513, 65536, "i8", "q8", "u16"),      # segments of about 256
+    (4096, 257, 262144, "i8", "f16", "u32"),    # of about 64
+    (600, 1800, 9000, "f32", "f32", "u16"),     # of about 120, one bucket nearly empty
+])
+def test_large_layers_order_their_segments_by_lds_bank(kb, n_in, n_out, K, cb, gb, idxd):
+    """More than 2^20 edges: the same records in every segment, most of them where sixteen lanes side by side read different
+    banks (input mod 16 = position / 8 mod 16; one in sixteen as they fall), the same bytes every time."""
+    P = synth.make_layer(n_in + K, n_in, n_out, K, cb_dtype=cb, gb_dtype=gb, idx_dtype=idxd)
+    L = kb.VQLayer(P).prepare()
+    got, exp = _read_layout(L.prepared, P), _expected_layout(P)
+    assert np.array_equal(got[0], exp[0])
+    seg_of = np.repeat(np.arange(len(got[0]) - 1), np.diff(got[0].astype(np.int64)))
+    order = np.lexsort((got[2], seg_of))
+    for g, e in zip(got[2:], exp[2:]):
+        assert np.array_equal(g[order], e)
+    assert (got[2] % 16 == np.arange(len(got[2])) // 8 % 16).mean() > 0.4
+    for g, again in zip(got, _read_layout(kb.VQLayer(P).prepare().prepared, P)):
+        assert np.array_equal(g, again)
+
+
 @pytest.mark.parametrize("dist,n_out", [("zipf-sorted", 300), ("zipf", 300), ("zipf-sorted", 2500), ("uniform", 1024)])
 def test_block_tables_balance_skewed_histograms(kb, dist, n_out):
     P = synth.make_layer(91, 700, n_out, 40000, cb_dtype="i8", gb_dtype="f16", idx_dist=dist, zipf_s=1.2)
