@@ -125,13 +125,20 @@ struct LayerPlan {
 constexpr int kCUs = 256;
 constexpr int kTargetWorkgroups = 512;    // two workgroups of 4 waves per CU
 constexpr int kEnoughWorkgroups = 384;
+constexpr long long kFusedMinEdgesForResidency = 1 << 17;   // several heads: workgroups for the sake of L2 from this many edges per head
+constexpr int kGatherMinWgsPerHead = 32, kGatherMinRowsPerHead = 16;
 
 // Geometry for one choice of outputs-per-lane.  The four waves of a workgroup are
 // interleaved along i whenever the layer has rows for them (their sums meet in LDS), so a
 // workgroup spans 64*jpl outputs and parallelism comes from output tiles first; i is split
 // into chunks only as far as the partial sums stay small next to the parameter stream
 // (n_chunks * B * out * 4 bytes <= a quarter of in * out * bytes_per_edge).
-void gather_geometry(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, int jpl, int bytes_per_edge) {
+// head_cb: bytes of a head's codebook where the XCDs take the heads one behind the other (gather_by_head), 0 where they do
+// not.  An XCD holds 128 or 160 workgroups: with one for every 8 KB of the codebook it works on as many heads as its L2 holds
+// codebooks.  Fifty heads of 2048-256-21 at batch 1, Int8, 11 / 32 / 64 workgroups each: 234 / 173 / 165 us, twenty 94 / 83 / 74,
+// of fp32 rows with 11 / 64 / 128 171 / 130 / 109; thirty of 1000-200-60 with 5,000 shapes 9 / 32 / 64 69 / 59 / 64 (chunks of 16
+// inputs there: one pass of the four waves).
+void gather_geometry(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, int jpl, int bytes_per_edge, long long head_cb) {
   p.cfg.jpl = jpl;
   const int lanes_j = (n_out + jpl - 1) / jpl;
   p.cfg.wj = n_in >= 16 ? 1 : (lanes_j > 128 ? 4 : (lanes_j > 64 ? 2 : 1));
@@ -140,21 +147,28 @@ void gather_geometry(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, 
   p.n_bt = (int)((B + p.cfg.bt - 1) / p.cfg.bt);
   const long long base = (long long)n_heads * p.n_jt * p.n_bt;
   long long chunks = (kTargetWorkgroups + base - 1) / (base > 0 ? base : 1);
+  if (head_cb > 0) {
+    const long long want = std::max<long long>(kGatherMinWgsPerHead, head_cb >> 13) / p.n_jt;
+    chunks = std::max(chunks, std::min<long long>(want, n_in / kGatherMinRowsPerHead));
+  }
   const long long max_by_rows = n_in / (wi * 4);
   const long long max_by_bytes = (long long)n_in * bytes_per_edge / (16 * (B > 0 ? B : 1));
   if (chunks > max_by_rows) chunks = max_by_rows;
   if (chunks > max_by_bytes) chunks = max_by_bytes;
   if (chunks < 1) chunks = 1;
   int rows = (int)((n_in + chunks - 1) / chunks);
-  rows = (rows + wi - 1) / wi * wi;
+  const int unit = head_cb > 0 ? kGatherMinRowsPerHead : wi;
+  rows = (rows + unit - 1) / unit * unit;
   p.rows_per_chunk = rows;
   p.n_chunks = (n_in + rows - 1) / rows;
 }
 
-// VQ layers at batch 1.
+// VQ layers at batch 1.  compact: no finer chunks for the sake of L2, for calls that fit the static scratch only so.
 LayerPlan plan_gather(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code,
-                      bool vec_ok) {
+                      bool vec_ok, long long cb_bytes, bool compact) {
   LayerPlan p;
+  const bool by_head = !compact && (long long)n_in * n_out >= kFusedMinEdgesForResidency && gather_by_head(n_heads, cb_bytes);
+  const long long head_cb = by_head ? cb_bytes : 0;
   p.mfma = false;
   p.kind = kPlanGather;
   p.cfg.idx_u32 = idx_u32;
@@ -170,12 +184,12 @@ LayerPlan plan_gather(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, 
   long long best_wgs = -1;
   for (int c = vec_ok ? jpl_max : 1; c >= 1; c >>= 1) {
     if (n_out % c != 0 || (c > 1 && n_out / c < 64)) continue;
-    gather_geometry(p, n_in, n_out, B, n_heads, c, bytes_per_edge);
+    gather_geometry(p, n_in, n_out, B, n_heads, c, bytes_per_edge, head_cb);
     const long long wgs = (long long)n_heads * p.n_jt * p.n_bt * p.n_chunks;
     if (wgs >= kEnoughWorkgroups) { best = c; break; }
     if (wgs > best_wgs) { best = c; best_wgs = wgs; }
   }
-  gather_geometry(p, n_in, n_out, B, n_heads, best, bytes_per_edge);
+  gather_geometry(p, n_in, n_out, B, n_heads, best, bytes_per_edge, head_cb);
   return p;
 }
 
@@ -196,7 +210,6 @@ constexpr int kMfmaMaxSteps = 256;            // steps of 16 inputs per workgrou
 constexpr int64_t kHalfFusedMaxBatch = 64;   // fp16 path: fused kernel up to here, streaming contraction above
 constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here (both paths) for layers of at least
 constexpr long long kFusedTwoTilesMinEdges = 1ll << 22;    // this many edges whose codeword rows are one gather each
-constexpr long long kFusedMinEdgesForResidency = 1 << 17;   // ... for layers of at least this many edges per head
 constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers up to here may write partial sums four times as large as their stream
 // Precise path, 2 to 32 samples: the wave-by-wave kernel up to this many edges per launch, tiles of 128 outputs with the
 // basis tile in LDS above (there the wait of one step is another's work, and what counts is how little each does:
@@ -704,7 +717,8 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     return p;
   }
   if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows, reduced);
-  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok);
+  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, (long long)L.K * cb_row_bytes(code),
+                     min_rows != kMfmaMinRows);
 }
 
 bool layer_vec_ok(const kan_vq_layer& L) {

@@ -43,19 +43,23 @@ __global__ __launch_bounds__(kThreads) void kan_gather_kernel(const GatherArgs a
   const int wi = wave / wj_count;
 
   int head = blockIdx.z, chunk = blockIdx.y, tile = blockIdx.x;
-  if constexpr (SL) {
+  const bool by_head = a.by_head != 0;
+  if (SL || by_head) {
     // Workgroups go to the eight XCDs in turn (linear id mod 8), each with an L2 of its own.  The output
     // tiles of a chunk read the same slices, and a chunk of 16 rows is half a 128-byte line per slice,
     // whose other half the next chunk reads: runs of consecutive (chunk, tile) items per XCD fetch every
     // line once.
+    // Heads whose codebooks together exceed an L2: an XCD takes its heads one behind the other, a few at a time, and a codebook
+    // enters one L2 only (all of them on every XCD: fifty heads of 2048-256-21, Int8, at batch 1 403 us, now 150; twenty of
+    // fp32 rows 224, now 77; line fills from L2 to the vector caches bound it, 170 G/s of the 255 that gathers alone reach).
     const unsigned T = gridDim.x, C = gridDim.y, W = T * C * gridDim.z;
     const unsigned L = blockIdx.x + T * (blockIdx.y + C * blockIdx.z);
     const unsigned xcd = L & 7u, m = L >> 3, q = W >> 3, r = W & 7u;
     const unsigned item = xcd * q + min(xcd, r) + m;          // XCD x owns q + (x < r) items
-    head = (int)(item / (T * C));
+    head = __builtin_amdgcn_readfirstlane((int)(item / (T * C)));
     const unsigned rem = item % (T * C);
-    chunk = (int)(rem / T);
-    tile = (int)(rem % T);
+    chunk = __builtin_amdgcn_readfirstlane((int)(rem / T));
+    tile = __builtin_amdgcn_readfirstlane((int)(rem % T));
   }
   const int jt = tile % a.n_jt;
   const int btile = tile / a.n_jt;
@@ -77,13 +81,12 @@ __global__ __launch_bounds__(kThreads) void kan_gather_kernel(const GatherArgs a
   const float scale = (CODE == kCbI8) ? hp.scale : 1.0f;
 
   {
-    // Warm this XCD's L2 with the codebook before the random gathers start: the workgroups
-    // that share an XCD (linear id mod 8) each stream one slice of it, coalesced.
-    if (a.cb_bytes > 0) {
-      const long long wg = blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z);
-      const long long per_xcd = ((long long)gridDim.x * gridDim.y * gridDim.z + 7) / 8;
-      const long long slice = ((a.cb_bytes + per_xcd - 1) / per_xcd + 4095) / 4096 * 4096;
-      const long long lo = (wg >> 3) * slice, hi = min(lo + slice, a.cb_bytes - 16);
+    // Warm this XCD's L2 with the codebook before the random gathers start: the workgroups that share an XCD (linear
+    // id mod 8; by head: those of the head, which sit on one XCD or two) each stream one slice of it, coalesced.
+    if (a.warm_slice > 0) {
+      const unsigned wg = by_head ? (unsigned)tile + gridDim.x * (unsigned)chunk
+                                  : (blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >> 3;
+      const long long lo = (long long)wg * a.warm_slice, hi = min(lo + a.warm_slice, a.cb_bytes - 16);
       uint32_t v = 0;
       for (long long off = lo + tid * 16; off < hi; off += kThreads * 16) {
         uint4 q;
@@ -167,6 +170,9 @@ __global__ __launch_bounds__(kThreads) void kan_gather_kernel(const GatherArgs a
 #pragma unroll
           for (int p = 0; p < JPL; ++p) raw[q][p] = load_window<CbT>(cb, id[q][p], sp[q]);
         }
+        // (left to itself the compiler uses the first windows before it has asked for the last: 4096 x 4096, fp16 rows, 160 us, now
+        // 144; 1024 x 512 11.0, now 9.8)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < R; ++q) {
           const float live = (r0 + q * wi_count < rows) ? 1.0f : 0.0f;
@@ -277,7 +283,21 @@ hipError_t launch_types(const GatherCfg& c, const GatherArgs& a, dim3 grid, hipS
 
 hipError_t launch_gather(const GatherCfg& c, const GatherArgs& a, dim3 grid, hipStream_t s) {
   if (c.bt != 1 || a.x_parts > kGatherChainMaxParts) return hipErrorInvalidValue;
-  return c.idx_u32 ? launch_types<uint32_t>(c, a, grid, s) : launch_types<uint16_t>(c, a, grid, s);
+  GatherArgs g = a;
+  g.by_head = gather_by_head((int)grid.z, a.cb_bytes);
+  // The codebook is brought into L2 ahead where several heads gather 64 times and more from each of its lines (fifty heads of
+  // 2048-256 150 against 155 us, five 35.0 / 36.8).  With fewer edges the gathers themselves are the faster way: twenty heads
+  // of 1024-128, 25 to a line, 27.1 / 26.1, and second layers of 256 x 21 took 13 to 35 us for their share, now 6 to 10.
+  // One head, whose codebook all eight XCDs read, is the better without at any size: 2048-1024-256 23.7 / 22.7, 1024 x 512
+  // 9.8 / 9.0, 4096 x 4096 144.8 / 139.4.
+  if (grid.z > 1 && (long long)a.n_in * a.n_out * 2 >= a.cb_bytes) {
+    const long long wgs = (long long)grid.x * grid.y;
+    const long long sharers = g.by_head ? wgs : (wgs * grid.z + 7) / 8;
+    g.warm_slice = ((a.cb_bytes + sharers - 1) / sharers + 4095) / 4096 * 4096;
+  } else {
+    g.warm_slice = 0;
+  }
+  return c.idx_u32 ? launch_types<uint32_t>(c, g, grid, s) : launch_types<uint16_t>(c, g, grid, s);
 }
 
 }  // namespace kan

@@ -35,6 +35,10 @@ struct GatherCfg {
   int code;        // CodeKind
 };
 
+// Batch 1: heads whose codebooks together exceed the L2 of an XCD are dealt to the XCDs.
+constexpr long long kL2Bytes = 4ll << 20;
+__host__ __device__ constexpr bool gather_by_head(int n_heads, long long cb_bytes) { return n_heads > 1 && n_heads * cb_bytes > kL2Bytes; }
+
 struct GatherArgs {
   const float* x;              // [heads or 1][B][n_in]
   long long x_head_stride;     // elements between heads; 0 when all heads share x
@@ -45,7 +49,9 @@ struct GatherArgs {
   int rows_per_chunk;          // i-rows per workgroup (multiple of 4/wj)
   int n_jt;                    // j-tiles; blockIdx.x = bt_index * n_jt + jt
   int apply_tanh;              // only honoured when the kernel writes final values
-  long long cb_bytes;          // codebook bytes per head (0: no L2 warm-up of the codebook)
+  long long cb_bytes;          // codebook bytes per head
+  long long warm_slice;        // set by launch_gather: bytes of it that a workgroup brings into its L2
+  int by_head;                 // set by launch_gather: gather_by_head
   int rule;                    // edge function: 0 cubic B-spline, 1 two-tap linear interpolation
   // Chained input: x is the previous layer's partial sums,
   // [head][x_parts][B][n_in]; a workgroup adds the slices of its own rows in a fixed order and

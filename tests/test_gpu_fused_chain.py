@@ -162,6 +162,19 @@ def test_batch1_group_of_heads(kb):
         assert np.isfinite(y[h]).all() and rep["headline"] <= TOL_FP32, (h, rep)
 
 
+@pytest.mark.parametrize("dims,heads,K,cb,gb,idx", [((700, 437, 21), 9, 50000, "i8", "f16", "u16"), ((337, 392, 5), 4, 70000, "f16", "f32", "u32"),
+                                                    ((1025, 128), 3, 40000, "f32", "f32", "u16"), ((17, 130, 3), 66, 7000, "i8", "q8", "u16")])
+def test_batch1_heads_one_behind_the_other(kb, dims, heads, K, cb, gb, idx):
+    """Codebooks of more than 4 MB together: every XCD takes its heads in turn.  Chunks that the inputs do not fill, heads that
+    share an XCD or lie on two, second layers of few edges; 66 heads: a full group, and one whose codebooks fit."""
+    heads_P = [_head(8900 + 10 * h, dims, K, cb=cb, gb=gb, idx=idx) for h in range(heads)]
+    x = synth.make_x(8901, 1, dims[0])
+    y = kb.kan_vq_head_forward([gpu_layers(Ps) for Ps in heads_P], to_dev(x), path=kb.KAN_PATH_GATHER).cpu().numpy()
+    for h, Ps in enumerate(heads_P):
+        rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
+        assert np.isfinite(y[h]).all() and rep["headline"] <= TOL_FP32, (h, rep)
+
+
 @pytest.mark.parametrize("B", [1, 7, 16, 24])
 def test_two_tap_rule_with_handed_over_sums(kb, B):
     """The two-tap rule (linear interpolation between two grid points) through the same hand-over."""
