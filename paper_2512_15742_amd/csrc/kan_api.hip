@@ -221,14 +221,25 @@ constexpr int kFusedMinWgsPerHead = 20;      // fused kernel, several heads: wor
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
 // its second tile of 64 samples (config 3: 97 us at 64, 113 at 80; config 2: 33 and 57).
 constexpr int64_t kSplitMinBatch = 65;
-// Dense baseline: fp32 operands up to 16 samples (one tile of the fp32 instruction), split operands above; one pass
-// over the coefficients per tile of 64 samples up to batch 128, on small layers (which do not fill the chip with the
-// tiles of the streaming form) up to 256, converted records above.  One pass against records: 2048 x 512 at batch
-// 128 / 192 29.7 / 64.1 against 38.8 / 41.7 us, 4096 x 1024 at 128 / 192 107 / 241 against 110 / 137, 500 x 333 at
-// 192 / 256 23.4 / 28.0 against 36.0 / 35.5, 2048 x 64 22.9 / 27.9 against 30.4 / 31.7.
+// Dense baseline: fp32 operands up to 16 samples (one tile of the fp32 instruction), split operands above.  Three forms for
+// these: one pass over the coefficients per tile of 64 samples (kan_dense.hip), the contraction that converts its own
+// coefficients for 128 or 256 samples at a time (kan_wide.hip), converted records (kan_mfma.hip).  Beyond 64 samples
+// the one pass is ahead while a CU has two steps of it (32 inputs x 64 outputs x 64 samples): one pass / kan_wide / records
+//   1024 x 256 at 256 / 300   18.3 / 21.3 / 28.7,  23.2 / 20.7 / 27.5     300 x 64 at 128 / 300   11.3 / 16.2 / -,  11.5 / 19.3 / 24.9
+//   500 x 333 at 128 / 300    12.9 / 16.0 / -,     19.6 / 19.1 / 26.2     256 x 500 at 256        13.8 / 17.8 / 28.5
+//   2048 x 200 at 128 / 160   20.8 / 20.9 / -,     30.2 / 24.2 / 34.6     2048 x 512 at 80        29.4 / 23.2 / -
+// Beyond it kan_wide, for layers of up to a million edges as far as the work goes, for larger ones below batch 1024; kan_wide /
+// records: 2048 x 512 at 256 / 1024 / 2048 / 3000 30.0 / 49.4, 69.4 / 93.7, 122 / 128, 197 / 180; 1024 x 256 at 3000 / 4096
+// 63.3 / 82.5, 79.3 / 84.5; 2048 x 1024 at 256 / 768 / 1300 44.1 / 77.0, 94.1 / 141, 177 / 171; 4096 x 1024 at 128 / 768 / 1300
+// 56.5 / 107, 181 / 282, 344 / 330.  Layers whose tiles of 64 outputs would be half empty (make_wide) keep one pass up to batch 128,
+// small ones up to 256.
 constexpr int64_t kDenseSplitMinBatch = 17;
 constexpr int64_t kDenseOnePassMaxBatch = 128, kDenseOnePassSmallMaxBatch = 256;
 constexpr long long kDenseOnePassSmallEdges = 1ll << 18;
+constexpr long long kDenseOnePassMaxSteps = 512;
+constexpr int64_t kDenseWideMaxBatch = 1024;
+constexpr long long kDenseWideMaxWork = 1ll << 31;      // edges x samples, from kDenseWideMaxBatch on
+constexpr long long kDenseSmallSums = 2ll << 20;        // bytes of partial sums that any layer may write
 constexpr int64_t kAutoMfmaBatch = 32;    // KAN_PATH_AUTO switches to the matrix cores from here (measured crossover 16-32)
 
 LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool split3 = false,
@@ -340,7 +351,9 @@ int64_t wide_max_batch(int n_in, int n_out, int n_heads, int code, bool split3, 
 
 // Turns plan p of such a layer into one for that kernel where it is the faster one.
 bool make_wide(LayerPlan& p, int n_in, int n_out, int64_t B, int n_heads, bool split3, int x_parts, bool reduced) {
-  if (B < kWideMinBatch || B > wide_max_batch(n_in, n_out, n_heads, p.cfg.code, split3, x_parts, reduced) || !wide_takes(n_in, n_out, B)) return false;
+  const bool dense = p.cfg.code == kDense;
+  if (!dense && (B < kWideMinBatch || B > wide_max_batch(n_in, n_out, n_heads, p.cfg.code, split3, x_parts, reduced))) return false;
+  if (!wide_takes(n_in, n_out, B, dense)) return false;
   const int n_jt = (n_out + kWideTileN - 1) / kWideTileN;
   if ((long long)n_jt * kWideTileN * 2 > 3ll * n_out) return false;        // (tiles half empty)
   const int tile = B <= 128 ? 128 : (B <= 256 || split3 ? 256 : 512), n_bt = (int)((B + tile - 1) / tile);
@@ -1446,10 +1459,12 @@ kan_status kan_vq_layer_forward(const kan_vq_layer* L, const float* x, int64_t B
 // split-operand streaming form the precise VQ path uses (a converter of the coefficients in place of gather +
 // dequantise).
 static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
-  if (B > kDenseOnePassMaxBatch && (B > kDenseOnePassSmallMaxBatch || (long long)in * out > kDenseOnePassSmallEdges)) {
+  const long long edges = (long long)in * out;
+  if (B > 64 && (long long)((out + 63) / 64) * ((B + 63) / 64) * ((in + kDenseStep64 - 1) / kDenseStep64) > kDenseOnePassMaxSteps) {
     LayerPlan p = plan_mfma(in, out, B, 1, 0, 0, kDense, true);
+    const bool wide = (B < kDenseWideMaxBatch || B * edges < kDenseWideMaxWork) && make_wide(p, in, out, B, 1, true, 1, true);
     p.name = "kan_dense_split";
-    return p;
+    if (wide || (B > kDenseOnePassMaxBatch && (B > kDenseOnePassSmallMaxBatch || edges > kDenseOnePassSmallEdges))) return p;
   }
   LayerPlan p;
   p.mfma = false;
@@ -1460,10 +1475,12 @@ static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
   p.n_jt = (out + tile_n - 1) / tile_n;
   p.n_bt = (int)((B + p.cfg.bt - 1) / p.cfg.bt);
   // Workgroups for the whole chip (two per CU of four waves, one of eight), while the partial sums stay below a
-  // quarter of the coefficients.
+  // quarter of the coefficients, of small layers, whose launch is a latency chain, below all of them (300 x 64 at batch 64 / 256
+  // 11.1 / 31.3 -> 11.1 / 11.4 us, 100 x 100 at 400 25.1 -> 11.6).
   const long long base = (long long)p.n_jt * p.n_bt, target = p.cfg.bt == 16 ? kTargetWorkgroups : kTargetWorkgroups / 2;
   long long chunks = (target + base - 1) / base;
-  const long long max_by_rows = (in + step - 1) / step, max_by_bytes = (long long)in * 40 / (16 * B);
+  const long long max_by_rows = (in + step - 1) / step, sums = (long long)in * out * 40 / ((long long)in * out <= kFusedSmallLayerEdges ? 1 : 4);
+  const long long max_by_bytes = std::max(sums, kDenseSmallSums) / (4 * B * out);
   if (chunks > max_by_rows) chunks = max_by_rows;
   if (chunks > max_by_bytes) chunks = max_by_bytes;
   if (chunks < 1) chunks = 1;
@@ -1475,8 +1492,8 @@ static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
 
 static void dense_ws(const LayerPlan& p, int32_t in, int32_t out, int64_t B, size_t* partial, size_t* cf, size_t* u) {
   *partial = partial_bytes(p, out, B, 1);
-  *cf = p.mfma ? round_up(2 * mfma_cf_records(in, out) * sizeof(uint4), 256) : 0;
-  *u = p.mfma ? round_up(2 * (size_t)((in + 15) / 16 * 16) * (size_t)B * sizeof(uint2), 256) : 0;
+  *cf = p.mfma && !p.wide ? round_up(2 * mfma_cf_records(in, out) * sizeof(uint4), 256) : 0;
+  *u = !p.mfma ? 0 : round_up(2 * (size_t)((in + 15) / 16) * (size_t)B * (p.wide ? 10 * sizeof(uint4) : 16 * sizeof(uint2)), 256);
 }
 
 size_t kan_dense_workspace_bytes(int32_t in, int32_t out, int64_t B) {

@@ -213,7 +213,7 @@ struct WideArgs {
   int apply_tanh;
   LayerPtrs h[kMaxGroup];
 };
-bool wide_takes(int n_in, int n_out, int64_t B);       // sizes it can address
+bool wide_takes(int n_in, int n_out, int64_t B, bool dense);       // sizes it can address
 hipError_t launch_wide(const GatherCfg&, const WideArgs&, bool split, int tile_m, dim3 grid, hipStream_t);   // tile_m: 128, 256 or (not split) 512 samples
 hipError_t launch_prep_rot(const float* x, long long x_head_stride, int x_parts, long long x_part_stride, int x_tanh,
                            const RotWords&, int n_in, int B, int heads, int rule, hipStream_t);

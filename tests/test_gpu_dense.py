@@ -37,6 +37,25 @@ def test_one_pass_kernels(kb, n_in, n_out, B):
     check_dense_output(y, x, coef, TOL_FP32)
 
 
+@pytest.mark.parametrize("n_in,n_out,B", [(1033, 1021, 65), (2056, 512, 129), (4097, 257, 128), (1640, 640, 257), (300, 1090, 300), (520, 511, 1023),
+                                          (1024, 256, 257), (500, 96, 1400),                # the contraction that converts its own coefficients
+                                          (1024, 256, 256), (300, 64, 1024), (31, 33, 700),  # the last of the one-pass rule, many tiles of it
+                                          (9000, 40, 128), (9000, 33, 200)])                # tiles of 64 outputs half empty: one pass, records
+def test_beyond_one_tile(kb, n_in, n_out, B):
+    rng = np.random.default_rng(n_in + 3 * n_out + B)
+    coef = (rng.standard_normal((n_in, n_out, 10)) * rng.uniform(1e-3, 2.0, (n_in, n_out, 1))).astype(np.float32)
+    tail = coef.copy()
+    tail[:n_in - (n_in % 16 or 16)] = 0                # the last step of 16 inputs alone
+    x = synth.make_x(B, B, n_in)
+    x[0, 0], x[-1, -1] = 1.0, -1.0
+    rows = np.unique(np.r_[0, 31, 63, 64, min(127, B - 1), B // 2, B - 1])
+    check_dense_output(kb.kan_dense_layer_forward(to_dev(coef), to_dev(x)).cpu().numpy()[rows], x[rows], coef, TOL_FP32)
+    # (one edge's sum of four products can cancel to nothing: errors against the largest result, not against its |phi|)
+    y = kb.kan_dense_layer_forward(to_dev(tail), to_dev(x)).cpu().numpy()
+    rep = ko.error_report(y[rows], ko.dense_layer_forward(tail, x[rows]))
+    assert np.isfinite(y).all() and rep["headline"] <= TOL_FP32, rep
+
+
 def test_fp32_operands_have_no_fp16_range(kb):
     """Up to 16 samples the operands stay fp32: coefficients beyond fp16's range on either side."""
     rng = np.random.default_rng(5)
