@@ -906,7 +906,6 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
       t.x_part_stride = chain.in_part_stride;
       t.x_parts = chain.in_parts;
       t.x_tanh = chain.in_tanh;
-      t.vec = a.n_in % 4 == 0 && aligned(a.x, 16);      // (the strides are multiples of n_in)
       t.dst = final_dst;
       t.dst_head_stride = final_head_stride;
       t.n_in = a.n_in;

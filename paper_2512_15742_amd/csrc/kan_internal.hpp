@@ -229,7 +229,6 @@ struct TailArgs {
   const float* x;              // [head or 1][x_parts][B][n_in]: slices to add in order (and squash: x_tanh)
   long long x_head_stride, x_part_stride;
   int x_parts, x_tanh;
-  int vec;                     // 16-byte loads: n_in in fours, x and the slices 16-byte aligned
   float* dst;                  // finished outputs
   long long dst_head_stride;
   int n_in, n_out, B;

@@ -28,40 +28,41 @@ constexpr int IT = 16;                           // inputs per step, as in kan_m
 constexpr int kTailXStride = kTailMaxIn + 1;     // (odd: the 32 rows of a column lie in 32 banks)
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ __forceinline__ void zero(float& v) { v = 0.f; }
-__device__ __forceinline__ void zero(f32x4& v) { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
-__device__ __forceinline__ void put(float* p, float v, int tanh_on) { *p = tanh_on ? tanhf(v) : v; }
-__device__ __forceinline__ void put(float* p, const f32x4& v, int tanh_on) {
-#pragma unroll
-  for (int c = 0; c < 4; ++c) p[c] = tanh_on ? tanhf(v[c]) : v[c];
-}
-
-// The inputs of samples b0 .. b0 + 31 into xs: U items (one or four inputs each) per thread and round, P slices of
-// each in flight, added in slice order.  Loads are unconditional (clamped addresses).
-template <typename V, int U, int P>
+// The inputs of samples b0 .. b0 + 31 into xs: the tile's rows are one run of floats in memory, taken in items of four
+// (wherever rows end), U items per thread and round, P slices of each in flight, added in slice order.  Loads are
+// unconditional (clamped addresses; the last item of the run ends with it and repeats what the one before holds).  A
+// tile of eight slices is two trips to memory that way (single floats, half the slices at a time, where rows are no multiple
+// of four: six; 500-333-21 at batch 128 34.0 -> 29.1 us, 399 x 10 at any batch 19.0 -> 13.5).
+template <int U, int P>
 __device__ __forceinline__ void stage_inputs(const TailArgs& a, const float* x, int b0, float* xs) {
-  constexpr int W = (int)(sizeof(V) / 4);
-  const int per_row = a.n_in / W, items = 32 * per_row;
+  const int n = min(32, a.B - b0) * a.n_in, items = (n + 3) >> 2;
+  const float* const p = x + (long long)b0 * a.n_in;
+  if (n < 4) {                                                          // (a last row of up to three inputs)
+    const int t = threadIdx.x;
+    if (t < n) {
+      float sum = 0.f;
+      for (int q = 0; q < a.x_parts; ++q) sum += p[(long long)q * a.x_part_stride + t];
+      xs[t / a.n_in * kTailXStride + t % a.n_in] = a.x_tanh ? tanhf(sum) : sum;
+    }
+    return;
+  }
   for (int base = threadIdx.x; base < items; base += U * kTailThreads) {
-    const float* p[U];
     int at[U];
-    V sum[U];
+    f32x4 sum[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int item = min(base + u * kTailThreads, items - 1);
-      const int row = item / per_row, col = item - row * per_row;
-      p[u] = x + (long long)min(b0 + row, a.B - 1) * a.n_in + col * W;
-      at[u] = row * kTailXStride + col * W;
-      zero(sum[u]);
+      at[u] = min(4 * (base + u * kTailThreads), n - 4);
+      sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     for (int p0 = 0; p0 < a.x_parts; p0 += P) {
-      V t[P][U];
+      f32x4 t[P][U];
 #pragma unroll
       for (int q = 0; q < P; ++q) {
-        const long long off = (long long)min(p0 + q, a.x_parts - 1) * a.x_part_stride;
+        const float* const slice = p + (long long)min(p0 + q, a.x_parts - 1) * a.x_part_stride;
 #pragma unroll
-        for (int u = 0; u < U; ++u) t[q][u] = *(const V*)(p[u] + off);
+        for (int u = 0; u < U; ++u) t[q][u] = *(const f32x4_a4*)(slice + at[u]);
       }
 #pragma unroll
       for (int q = 0; q < P; ++q) {
@@ -72,8 +73,18 @@ __device__ __forceinline__ void stage_inputs(const TailArgs& a, const float* x, 
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (base + u * kTailThreads < items) put(xs + at[u], sum[u], a.x_tanh);
+    for (int u = 0; u < U; ++u) {
+      if (base + u * kTailThreads >= items) continue;
+      int row = at[u] / a.n_in, col = at[u] - row * a.n_in;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        xs[row * kTailXStride + col] = a.x_tanh ? tanhf(sum[u][c]) : sum[u][c];
+        if (++col == a.n_in) {
+          col = 0;
+          ++row;
+        }
+      }
+    }
   }
 }
 
@@ -131,12 +142,14 @@ __global__ __launch_bounds__(kTailThreads) void kan_tail_kernel(const TailArgs a
   }
   {
     const float* x = a.x + (long long)head * a.x_head_stride;
-    if (a.vec) {
-      if (a.n_in * 8 <= kTailThreads) stage_inputs<f32x4, 1, 8>(a, x, b0, buf);
-      else stage_inputs<f32x4, 4, 4>(a, x, b0, buf);
+    if (a.x_parts == 1) {
+      stage_inputs<8, 1>(a, x, b0, buf);
+    } else if (a.x_parts <= 4) {
+      stage_inputs<4, 4>(a, x, b0, buf);
     } else {
-      stage_inputs<float, 8, 4>(a, x, b0, buf);
+      stage_inputs<3, 8>(a, x, b0, buf);
     }
+    for (int t = tid + (a.B - b0) * n_in; t < 32 * n_in; t += kTailThreads) buf[t / n_in * kTailXStride + t % n_in] = 0.f;   // rows past the last
     const int pad = n_steps * IT - n_in;            // the last step's missing inputs (their coefficients are zeros)
     for (int t = tid; t < 32 * pad; t += kTailThreads) buf[(t / pad) * kTailXStride + n_in + t % pad] = 0.f;
   }
