@@ -291,8 +291,8 @@ kan_status kan_vq_coef_range(const kan_vq_layer* L, float* range, void* stream);
  * codebook: fp32 [K][10]; idx: KAN_U16 (K <= 65536) or KAN_U32 array [in][out]; gain, bias:
  * fp32 [in][out].  ws: kan_vq_assign_workspace_bytes(K) bytes, 256-byte aligned.  All device.
  * With kan_vq_assign_fast_workspace_bytes(in, out, K) bytes (never fewer), large codebooks are searched
- * through cells that bound the distance of their shapes, which leaves most of them out and returns the
- * same indices. */
+ * through cells that bound the distance of their shapes, which leaves most of them out, and few edges by
+ * several workgroups that take a part of the codebook each; both return the same indices. */
 size_t kan_vq_assign_workspace_bytes(int32_t K);
 size_t kan_vq_assign_fast_workspace_bytes(int32_t in, int32_t out, int32_t K);
 kan_status kan_vq_assign(const float* coef, int32_t in, int32_t out, const float* codebook, int32_t K,

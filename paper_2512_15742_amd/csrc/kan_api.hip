@@ -1572,7 +1572,7 @@ size_t kan_vq_assign_fast_workspace_bytes(int32_t in, int32_t out, int32_t K) {
   if (check_assign_shapes(in, out, K, KAN_U32) != KAN_OK) return (size_t)-1;
   const long long E = (long long)in * out;
   const size_t least = kan_vq_assign_workspace_bytes(K);
-  if (!assign_bounded_ok(E, K)) return least;
+  if (!assign_bounded_ok(E, K)) return round_up(assign_whole_bytes(E, K), 256);
   const size_t bounded = round_up(assign_bounded_bytes(E, K), 256);
   return bounded > least ? bounded : least;
 }
@@ -1592,7 +1592,7 @@ kan_status kan_vq_assign(const float* coef, int32_t in, int32_t out, const float
   return run("kan_vq_assign", s, [&] {
     if (bounded)
       return launch_assign_bounded(coef, (long long)in * out, codebook, K, idx_dtype == KAN_U32, idx, gain, bias, ws, s);
-    return launch_assign(coef, (long long)in * out, codebook, K, idx_dtype == KAN_U32, idx, gain, bias, ws, s);
+    return launch_assign(coef, (long long)in * out, codebook, K, idx_dtype == KAN_U32, idx, gain, bias, ws, ws_bytes, s);
   });
 }
 

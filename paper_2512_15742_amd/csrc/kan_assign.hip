@@ -20,7 +20,7 @@
 // resolve to the lower index within a half-wave's rows; which of two half-waves' equal scores
 // wins is decided by index at the end.
 
-// That is the whole search (kan_assign_kernel).  Large codebooks take the bounded search further down, which
+// That is the whole search (kan_assign_whole_kernel, kan_assign_own_kernel).  Large codebooks take the bounded search further down, which
 // finds the same shapes from a small part of the scores.
 
 #include <algorithm>
@@ -36,8 +36,6 @@ namespace {
 constexpr int kAssignThreads = 256;
 constexpr int kEdgeTilesPerWave = 4;                                   // 4 x 32 edges per wave
 constexpr int kEdgesPerWg = (kAssignThreads / kWave) * kEdgeTilesPerWave * 32;   // 512
-constexpr long long kSplitMaxEdges = 1ll << 17;                         // whole search: up to here eight waves share their edges
-constexpr int kSlots = 32;                                             // contraction length
 
 __device__ __forceinline__ void split_h(float v, _Float16& hi, _Float16& lo) {
   hi = (_Float16)v;
@@ -118,12 +116,19 @@ __device__ __forceinline__ float max_of(const f32x16& v) {
   const float m4 = max3(v[12], v[13], v[14]);
   return max3(max3(m0, m1, m2), m3, max3(m4, v[15], -3.0e38f));
 }
-// The first register that holds it.
+// The first register that holds it: of the first three whose maximum it is (25 instructions; one register after the
+// other 45, half of them waits for the condition of the one before).
 __device__ __forceinline__ int row_of(const f32x16& v, float m) {
-  int r_best = 15;
+  float x = v[15], y = v[15];
+  int base = 15;
 #pragma unroll
-  for (int r = 14; r >= 0; --r) r_best = v[r] == m ? r : r_best;
-  return r_best;
+  for (int q = 4; q >= 0; --q) {
+    const bool here = max3(v[3 * q], v[3 * q + 1], v[3 * q + 2]) == m;
+    x = here ? v[3 * q] : x;
+    y = here ? v[3 * q + 1] : y;
+    base = here ? 3 * q : base;
+  }
+  return base + (x == m ? 0 : (y == m ? 1 : (base < 15 ? 2 : 0)));
 }
 
 // The bounded search's tiles are four groups of eight shapes: a lane's registers 4 g .. 4 g + 3 are its rows of group g,
@@ -140,111 +145,278 @@ __device__ __forceinline__ void for_groups_with(const f32x16& v, const float& be
   }
 }
 
-struct AssignArgs {
+// An edge's operand, in pieces of eight slots.
+__device__ __forceinline__ void edge_pieces(const float (&c)[kG], uint4 (&piece)[4]) {
+  _Float16 hi[kG], lo[kG];
+#pragma unroll
+  for (int m = 0; m < kG; ++m) split_h(c[m], hi[m], lo[m]);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    h16x8 v;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int s = n * 8 + t;
+      v[t] = s < 10 ? hi[s] : (s == 10 || s == 31 ? (_Float16)1.0f : (s < 21 ? hi[s - 11] : lo[s - 21]));
+    }
+    piece[n] = __builtin_bit_cast(uint4, v);
+  }
+}
+// An edge's operand in LDS, four pieces of eight slots; edges four apart keep them in another order, so that the sixteen
+// lanes that store or read a piece together meet different banks.
+__device__ __forceinline__ int piece_at(int q, int piece) { return q * 4 + (piece ^ ((q >> 2) & 3)); }
+__device__ __forceinline__ void store_edge(uint4* sB, int q, const float (&c)[kG]) {
+  uint4 piece[4];
+  edge_pieces(c, piece);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) sB[piece_at(q, n)] = piece[n];
+}
+
+// What the second product can add to the score of a shape at distance d or less of an edge (|n| = 1): its norm is at
+// most 1 + d, the low parts are at most 2^-11 of what they complete, on either side of n . C and in |C|^2 / 2.
+constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
+__device__ __forceinline__ float first_product_slack(float d) {
+  const float r = 1.001f + d;
+  return d <= kFar ? fmaf(r, fmaf(r, 2.45e-4f, 9.8e-4f), 1e-5f) : INFINITY;
+}
+
+// ---- whole search ---------------------------------------------------------------------------------
+// Eight waves share 128 edges and take the tiles of shapes in turn; with few edges several workgroups share them as well,
+// each on a part of the codebook, and a second launch takes the best of the parts.  (One workgroup per 128 edges left most of
+// the chip idle: 2^13 edges x 65,536 shapes 171 us, 44 in eight parts; 10,388 x 5,377 24.0 / 16.0, 4,096 x 4,096 19.7 / 11.4.)
+// The waves tell each other through LDS what an edge's best shape reaches at least: a wave's own best starts anew with it, and
+// the row of a new best is a third of the work of a tile (131,072 edges x 4,096 shapes 55 -> 43 us).
+// FILTER: the second product, half of the matrix work, only for tiles whose first one comes near that (first_product_slack):
+// after the first hundreds of tiles that is rare.  65,536 edges x 65,536 shapes 281 -> 217 us, 98,304 x 16,384 113 -> 97; with
+// 169 or 128 tiles a part it loses (10,388 x 5,377 15.4 -> 16.9, 131,072 x 4,096 48 -> 51).
+// Bound: matrix and vector instructions, at clocks that the matrix instructions lower; the loads are one tile of 2 KB for four of edges.
+constexpr int kWholeWaves = 8, kWholeEdges = kEdgeTilesPerWave * 32;
+
+// The two half-waves hold different rows of the same edge, the waves different tiles: the better score, of equal ones the
+// lower id.
+__device__ __forceinline__ void keep_better(float sc, int id, int q, float* s_best, int* s_id) {
+  const float sc_o = __shfl_xor(sc, 32, kWave);
+  const int id_o = __shfl_xor(id, 32, kWave);
+  if (sc_o > sc || (sc_o == sc && id_o < id)) {
+    id = id_o;
+    sc = sc_o;
+  }
+  if ((threadIdx.x & 63) < 32) {
+    s_best[q] = sc;
+    s_id[q] = id;
+  }
+}
+__device__ __forceinline__ uint2 best_of_waves(const float (&s_best)[kWholeWaves][kWholeEdges], const int (&s_id)[kWholeWaves][kWholeEdges], int q) {
+  float sc = s_best[0][q];
+  int id = s_id[0][q];
+#pragma unroll
+  for (int w = 1; w < kWholeWaves; ++w) {
+    const float o = s_best[w][q];
+    const int io = s_id[w][q];
+    if (o > sc || (o == sc && io < id)) {
+      sc = o;
+      id = io;
+    }
+  }
+  return make_uint2(__float_as_uint(sc), (uint32_t)id);
+}
+// Row r of a lane's sixteen is row 8 (r / 4) + 4 (lane / 32) + r % 4 of its tile.
+__device__ __forceinline__ int shape_of(int tile, int r, int half) { return tile * 32 + 8 * (r >> 2) + 4 * half + (r & 3); }
+
+struct WholeArgs {
   const float* coef;        // [E][10]
   const uint4* cent;        // prepared centroid operands
   long long E;
-  // LIST: behind the bounded search, on its groups of eight shapes, four to a tile.  The edges in its order, and of every 32
-  // whether they are left (their gains and biases are there already); the number of groups and the shape of every row
-  const uint32_t* list;
-  const uint8_t* left;      // [4 * ceil(E / 128)]
-  const uint32_t *groups, *ids;
-  int n_tiles;              // ceil(K / 32)
+  int n_tiles, parts, part_tiles;
+  uint2* found;             // [parts][E] score and shape of every part; parts = 1: not used
   void* idx;
-  float* gain;
-  float* bias;
+  float *gain, *bias;
 };
 
-// SPLIT = 1: four waves with 128 edges of their own each.  SPLIT > 1: that many waves share 128 edges and take the
-// centroid tiles in turn: with few edges a wave's chain of tiles is what takes the time (K = 4,096 and 2^11 / 2^16 /
-// 2^17 edges 21 / 34 / 58 us with eight waves against 85 / 89 / 91 us, with 2^18 edges 104 against 107, above it loses).
-template <typename IdxT, int SPLIT, bool LIST>
-__global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void kan_assign_kernel(const AssignArgs a) {
-  static_assert(!LIST || SPLIT > 1, "a workgroup's edges are four tiles of the list");
-  constexpr int kThreads = SPLIT > 1 ? SPLIT * kWave : kAssignThreads;
-  constexpr int kEdges = SPLIT > 1 ? kEdgeTilesPerWave * 32 : kEdgesPerWg;
-  // edge-side operands of the workgroup's edges: [edge][32 slots] fp16
-  __shared__ __attribute__((aligned(16))) _Float16 sB[kEdges * kSlots];
-  __shared__ float s_best[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
-  __shared__ int s_id[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kEdges : 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int first_tile = SPLIT > 1 ? 0 : wave * kEdgeTilesPerWave;        // of the wave's edges
-  const long long E = a.E;
-  auto edge_at = [&](long long at) { return LIST ? (long long)a.list[at] : at; };
-  // One workgroup's share: the edges from e_wg on, LIST: of these the tiles with their byte set in `tiles`.
-  auto serve = [&](long long e_wg, uint32_t tiles) {
-    // ---- step 1: bias = mean, gain = norm of the centred grid, n = centred / gain ------------
-    for (int q = tid; q < kEdges; q += kThreads) {
-      const long long at = e_wg + q, e = edge_at(min(at, E - 1));
-      float c[kG], mean, g;
-      normalise(a.coef + e * kG, c, mean, g);
-      if (!LIST && at < E) {
-        a.gain[e] = g;
-        a.bias[e] = mean;
-      }
-      _Float16* p = sB + q * kSlots;
-#pragma unroll
-      for (int m = 0; m < kG; ++m) {
-        _Float16 hi, lo;
-        split_h(c[m], hi, lo);
-        p[m] = hi;
-        p[11 + m] = hi;
-        p[21 + m] = lo;
-      }
-      p[10] = (_Float16)1.0f;
-      p[31] = (_Float16)1.0f;
+// The slack for every shape that scores m or more, in steps: d = sqrt(1 - 2 m) at most.
+__device__ __forceinline__ float slack_from(float m) {
+  return m >= 0.f ? 2.97e-3f : (m >= -4.f ? 7.9e-3f : (m >= -420.f ? 0.25f : INFINITY));       // (of d = 1, 3, 29)
+}
+
+template <typename IdxT, bool FILTER>
+__global__ __launch_bounds__(kWholeWaves * kWave, 4) void kan_assign_whole_kernel(const WholeArgs a) {
+  __shared__ uint4 sB[kWholeEdges * 4];
+  // A score that an edge's best shape reaches with the first product alone ([edge of the tile][tile]), and whether that is known to hold
+  __shared__ __attribute__((aligned(16))) float s_near[32][kEdgeTilesPerWave];
+  __shared__ uint8_t s_unit[kWholeEdges];
+  __shared__ float s_best[kWholeWaves][kWholeEdges];
+  __shared__ int s_id[kWholeWaves][kWholeEdges];
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+  const int part = (int)(blockIdx.x % (unsigned)a.parts);
+  const long long e_wg = (long long)(blockIdx.x / (unsigned)a.parts) * kWholeEdges;
+  const int t_end = min(a.n_tiles, (part + 1) * a.part_tiles);
+
+  const uint4* cp = a.cent + lane;
+  auto load_tile = [&](int t, uint4 (&fa)[2]) {
+    const int tc = min(t, t_end - 1);            // past the end: a harmless re-read
+    fa[0] = cp[(long long)(tc * 2) * 64];
+    fa[1] = cp[(long long)(tc * 2) * 64 + 64];
+  };
+  uint4 fa0[2], fa1[2];
+  const int t0 = part * a.part_tiles + wave;
+  load_tile(t0, fa0);
+  load_tile(t0 + kWholeWaves, fa1);
+
+  if (tid < kWholeEdges) {
+    const long long at = e_wg + tid;
+    float c[kG], mean, g, nn = 0.f;
+    normalise(a.coef + min(at, a.E - 1) * kG, c, mean, g);
+    if (part == 0 && at < a.E) {
+      a.gain[at] = g;
+      a.bias[at] = mean;
     }
-    __syncthreads();
-
-    // ---- this wave's edge fragments (MFMA B operand: column = lane & 31, slots (lane/32)*8..+8) --
-    h16x8 fb[kEdgeTilesPerWave][2];
 #pragma unroll
-    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int q = (first_tile + nb) * 32 + (lane & 31);
-        fb[nb][ks] = *(const h16x8*)(sB + q * kSlots + ks * 16 + (lane >> 5) * 8);
-      }
+    for (int m = 0; m < kG; ++m) nn = fmaf(c[m], c[m], nn);
+    s_unit[tid] = nn <= 1.000003f;               // (longer: squares in the subnormal range lose bits; what is no number)
+    store_edge(sB, tid, c);
+    s_near[tid & 31][tid >> 5] = -INFINITY;
+  }
+  __syncthreads();
 
-    float best[kEdgeTilesPerWave];
-    int best_tile[kEdgeTilesPerWave], best_row[kEdgeTilesPerWave];
+  h16x8 fb[kEdgeTilesPerWave][2];
+  float best[kEdgeTilesPerWave];
+  int best_tile[kEdgeTilesPerWave], best_row[kEdgeTilesPerWave];
+#pragma unroll
+  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) fb[nb][ks] = __builtin_bit_cast(h16x8, sB[piece_at(nb * 32 + col, ks * 2 + half)]);
+    best[nb] = -3.0e38f;
+    best_tile[nb] = 0;
+    best_row[nb] = 0;
+  }
+  int unit = 0;
+#pragma unroll
+  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) unit |= s_unit[nb * 32 + col] << nb;
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  auto score_tile = [&](int t, const uint4 (&fa)[2]) {
+    const h16x8 a0 = __builtin_bit_cast(h16x8, fa[0]), a1 = __builtin_bit_cast(h16x8, fa[1]);
+    const f32x4 near = *(const volatile f32x4*)&s_near[col][0];        // (raised meanwhile: more is looked at than need be)
 #pragma unroll
     for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+      f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
+      bool may = true;
+      if constexpr (FILTER) {
+        may = max_of(acc) >= near[nb];
+        if (__ballot(may) == 0) continue;        // (for the whole wave: matrix instructions heed no lane mask)
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
+      const float m = max_of(acc);
+      if constexpr (!FILTER) may = m >= near[nb];
+      // Strictly greater: the earliest tile, and in it the lowest register, keeps a tie.
+      if (may && m > best[nb]) {
+        best[nb] = m;
+        best_tile[nb] = t;
+        best_row[nb] = row_of(acc, m);
+        const float slack = FILTER ? ((unit >> nb) & 1 ? slack_from(m) : INFINITY) : 0.f;
+        __hip_atomic_fetch_max(&s_near[col][nb], m - slack, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  };
+  for (int t = t0; t < t_end; t += 2 * kWholeWaves) {
+    score_tile(t, fa0);
+    load_tile(t + 2 * kWholeWaves, fa0);
+    if (t + kWholeWaves < t_end) score_tile(t + kWholeWaves, fa1);
+    load_tile(t + 3 * kWholeWaves, fa1);
+  }
+
+#pragma unroll
+  for (int nb = 0; nb < kEdgeTilesPerWave; ++nb)
+    keep_better(best[nb], shape_of(best_tile[nb], best_row[nb], half), nb * 32 + col, s_best[wave], s_id[wave]);
+  __syncthreads();
+  const long long at = e_wg + tid;
+  if (tid < kWholeEdges && at < a.E) {
+    const uint2 top = best_of_waves(s_best, s_id, tid);
+    if (a.parts > 1) a.found[part * a.E + at] = top;
+    else ((IdxT*)a.idx)[at] = (IdxT)top.y;
+  }
+}
+
+// Small codebooks, and more edges than the shared form has use for: every wave has TILES * 32 edges of its own.  A lane
+// normalises an edge; the two halves of the wave then exchange pieces of the operands, which puts every piece where the matrix
+// instruction wants it, without LDS.  LOCAL: the workgroup builds the shapes' operands in its LDS and goes through the edges:
+// one launch, and only edges are read in its loop.  256 shapes and 28,672 / 182,784 / 394,240 edges 9.6 / 13.5 / 19.3 us with
+// operands of both kinds stored in pieces of two bytes and fetched from memory, 7.9 / 9.8 / 15.3 so; 2^20 x 4,096 (not LOCAL)
+// 293 -> 282.  Bound: reads and writes of the edges (16 MB in 6 us) beside a new best in almost every tile.
+template <typename IdxT, int TILES, bool LOCAL>
+__global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_own_kernel(const WholeArgs a, const float* __restrict__ cb, int K) {
+  static_assert(TILES % 2 == 0, "a lane per edge of two tiles");
+  extern __shared__ uint4 s_cent[];
+  constexpr int kOwn = TILES * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+  if constexpr (LOCAL) {
+    for (int c = tid; c < a.n_tiles * 32; c += kAssignThreads) {
+      float row[kG];
+#pragma unroll
+      for (int m = 0; m < kG; ++m) row[m] = c < K ? cb[(long long)c * kG + m] : 0.f;
+#pragma unroll
+      for (int piece = 0; piece < 4; ++piece)
+        s_cent[((c >> 5) * 2 + (piece >> 1)) * 64 + (piece & 1) * 32 + (c & 31)] = shape_slots(row, c < K, piece * 8);
+    }
+    __syncthreads();
+  }
+  const uint4* cp = (LOCAL ? (const uint4*)s_cent : a.cent) + lane;
+  auto load_tile = [&](int t, uint4 (&fa)[2]) {
+    const int tc = min(t, a.n_tiles - 1);        // past the end: a harmless re-read
+    fa[0] = cp[(long long)(tc * 2) * 64];
+    fa[1] = cp[(long long)(tc * 2) * 64 + 64];
+  };
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  for (long long e0 = ((long long)blockIdx.x * 4 + wave) * kOwn; e0 < a.E; e0 += (long long)gridDim.x * 4 * kOwn) {
+    h16x8 fb[TILES][2];
+    float best[TILES];
+    int best_tile[TILES], best_row[TILES];
+#pragma unroll
+    for (int h = 0; h < TILES / 2; ++h) {
+      const long long at = e0 + h * 64 + lane;
+      float c[kG], mean, g;
+      normalise(a.coef + min(at, a.E - 1) * kG, c, mean, g);
+      if (at < a.E) {
+        a.gain[at] = g;
+        a.bias[at] = mean;
+      }
+      uint4 piece[4];
+      edge_pieces(c, piece);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        uint32_t lo[4], hi[4];
+        const uint4 x = piece[2 * ks], y = piece[2 * ks + 1];
+        const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {            // (upper half of the first, lower half of the second)
+          const auto sw = __builtin_amdgcn_permlane32_swap(xs[w], ys[w], false, false);
+          lo[w] = sw[0];
+          hi[w] = sw[1];
+        }
+        fb[2 * h][ks] = __builtin_bit_cast(h16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+        fb[2 * h + 1][ks] = __builtin_bit_cast(h16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < TILES; ++nb) {
       best[nb] = -3.0e38f;
       best_tile[nb] = 0;
       best_row[nb] = 0;
     }
-
-    // ---- step 3: stream the centroid tiles (two tiles in flight) -----------------------------------
-    const int n_tiles = LIST ? ((int)*a.groups + 3) / 4 : a.n_tiles;
-    const uint4* cp = a.cent + (LIST ? ((lane & 31) >> 3) * kGroupRecords + (lane >> 5) * kGroupShapes + (lane & 7) : lane);
-    auto load_tile = [&](int t, uint4 (&fa)[2]) {
-      const int tc = t < n_tiles ? t : n_tiles - 1;        // past the end: a harmless re-read
-      fa[0] = cp[(long long)(tc * 2) * 64];
-      fa[1] = cp[(long long)(tc * 2) * 64 + (LIST ? kGroupRecords / 2 : 64)];
-    };
-    f32x16 zero;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
     auto score_tile = [&](int t, const uint4 (&fa)[2]) {
       const h16x8 a0 = __builtin_bit_cast(h16x8, fa[0]), a1 = __builtin_bit_cast(h16x8, fa[1]);
 #pragma unroll
-      for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-        if (LIST && !((tiles >> (8 * nb)) & 1u)) continue;
+      for (int nb = 0; nb < TILES; ++nb) {
         f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
         const float m = max_of(acc);
         // A new best is rare (the t-th tile improves a lane's running maximum with probability
         // ~1/t), so the row is looked for only then.  Strictly greater: the earliest tile, and in
-        // it the lowest register, keeps a tie.  (LIST: the lowest id, whatever tile it lies in.)
-        if constexpr (LIST) {
-          if (m >= best[nb])
-            for_groups_with(acc, best[nb], [&](int g, int r, float mg) {
-              const int id = (int)a.ids[t * 32 + g * kGroupShapes + 4 * (lane >> 5) + r];
-              if (mg > best[nb] || (uint32_t)id < (uint32_t)best_tile[nb]) best_tile[nb] = id;
-              best[nb] = mg;
-            });
-        } else if (m > best[nb]) {
+        // it the lowest register, keeps a tie.
+        if (m > best[nb]) {
           best[nb] = m;
           best_tile[nb] = t;
           best_row[nb] = row_of(acc, m);
@@ -252,73 +424,132 @@ __global__ __launch_bounds__(SPLIT > 1 ? SPLIT * kWave : kAssignThreads, 4) void
       }
     };
     uint4 fa0[2], fa1[2];
-    const int t0 = SPLIT > 1 ? wave : 0;
-    load_tile(t0, fa0);
-    load_tile(t0 + SPLIT, fa1);
-    for (int t = t0; t < n_tiles; t += 2 * SPLIT) {
+    load_tile(0, fa0);
+    load_tile(1, fa1);
+    for (int t = 0; t < a.n_tiles; t += 2) {
       score_tile(t, fa0);
-      load_tile(t + 2 * SPLIT, fa0);
-      if (t + SPLIT < n_tiles) score_tile(t + SPLIT, fa1);
-      load_tile(t + 3 * SPLIT, fa1);
+      load_tile(t + 2, fa0);
+      if (t + 1 < a.n_tiles) score_tile(t + 1, fa1);
+      load_tile(t + 3, fa1);
     }
+    // the two halves hold different rows of the same edges: the better one, the lower id
+    int id[TILES];
+#pragma unroll
+    for (int nb = 0; nb < TILES; ++nb) {
+      id[nb] = shape_of(best_tile[nb], best_row[nb], half);
+      const float sc_o = __shfl_xor(best[nb], 32, kWave);
+      const int id_o = __shfl_xor(id[nb], 32, kWave);
+      if (sc_o > best[nb] || (sc_o == best[nb] && id_o < id[nb])) id[nb] = id_o;
+    }
+#pragma unroll
+    for (int h = 0; h < TILES / 2; ++h) {
+      const long long at = e0 + h * 64 + lane;
+      if (at < a.E) ((IdxT*)a.idx)[at] = (IdxT)(half ? id[2 * h + 1] : id[2 * h]);
+    }
+  }
+}
 
-    // ---- the two half-waves hold different rows of the same edges: keep the better one ------------
+// The edges that the bounded search leaves, against its groups of eight shapes, four to a tile: the same scores, and of
+// equal ones the lowest id, whatever tile it lies in.  Eight waves share 128 edges of its order.
+struct RestArgs {
+  const float* coef;
+  const uint4* cent;        // operands of the groups
+  long long E;
+  const uint32_t* list;     // the edges in the bounded search's order ...
+  const uint8_t* left;      // ... and of every 32 whether they are left (their gains and biases are there already)
+  const uint32_t *groups, *ids;      // the number of groups and the shape of every row
+  void* idx;
+};
+
+template <typename IdxT>
+__global__ __launch_bounds__(kWholeWaves * kWave, 4) void kan_assign_rest_kernel(const RestArgs a) {
+  __shared__ uint4 sB[kWholeEdges * 4];
+  __shared__ float s_best[kWholeWaves][kWholeEdges];
+  __shared__ int s_id[kWholeWaves][kWholeEdges];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+  const int n_tiles = ((int)*a.groups + 3) / 4;
+  const uint4* cp = a.cent + (col >> 3) * kGroupRecords + half * kGroupShapes + (lane & 7);
+  auto load_tile = [&](int t, uint4 (&fa)[2]) {
+    const int tc = min(t, n_tiles - 1);          // past the end: a harmless re-read
+    fa[0] = cp[(long long)(tc * 2) * 64];
+    fa[1] = cp[(long long)(tc * 2) * 64 + kGroupRecords / 2];
+  };
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  // The edges from e_wg on, of these the tiles with their byte set in `tiles`.
+  auto serve = [&](long long e_wg, uint32_t tiles) {
+    if (tid < kWholeEdges) {
+      float c[kG], mean, g;
+      normalise(a.coef + (long long)a.list[min(e_wg + tid, a.E - 1)] * kG, c, mean, g);
+      store_edge(sB, tid, c);
+    }
+    __syncthreads();
+    h16x8 fb[kEdgeTilesPerWave][2];
+    float best[kEdgeTilesPerWave];
+    int best_id[kEdgeTilesPerWave];
 #pragma unroll
     for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
-      const int r = best_row[nb];
-      // D layout of the 32x32 MFMA: register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4
-      int id = LIST ? best_tile[nb] : best_tile[nb] * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      float sc = best[nb];
-      const float sc_o = __shfl_xor(sc, 32, kWave);
-      const int id_o = __shfl_xor(id, 32, kWave);
-      if (sc_o > sc || (sc_o == sc && id_o < id)) {
-        id = id_o;
-        sc = sc_o;
-      }
-      const int q = (first_tile + nb) * 32 + (lane & 31);
-      if constexpr (SPLIT > 1) {
-        if (lane < 32) {
-          s_best[wave][q] = sc;
-          s_id[wave][q] = id;
-        }
-      } else {
-        const long long at = e_wg + q;
-        if (lane < 32 && at < E) ((IdxT*)a.idx)[at] = (IdxT)id;
-      }
-    }
-    if constexpr (SPLIT > 1) {
-      __syncthreads();
-      const long long at = e_wg + tid;
-      if (tid < kEdges && at < E && (!LIST || ((tiles >> (8 * (tid >> 5))) & 1u))) {
-        float sc = s_best[0][tid];
-        int id = s_id[0][tid];
 #pragma unroll
-        for (int w = 1; w < SPLIT; ++w) {
-          const float o = s_best[w][tid];
-          const int io = s_id[w][tid];
-          if (o > sc || (o == sc && io < id)) {
-            sc = o;
-            id = io;
-          }
-        }
-        ((IdxT*)a.idx)[edge_at(at)] = (IdxT)id;
-      }
+      for (int ks = 0; ks < 2; ++ks) fb[nb][ks] = __builtin_bit_cast(h16x8, sB[piece_at(nb * 32 + col, ks * 2 + half)]);
+      best[nb] = -3.0e38f;
+      best_id[nb] = 0;
     }
+    auto score_tile = [&](int t, const uint4 (&fa)[2]) {
+      const h16x8 a0 = __builtin_bit_cast(h16x8, fa[0]), a1 = __builtin_bit_cast(h16x8, fa[1]);
+#pragma unroll
+      for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) {
+        if (!((tiles >> (8 * nb)) & 1u)) continue;
+        f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, fb[nb][0], zero, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, fb[nb][1], acc, 0, 0, 0);
+        if (max_of(acc) >= best[nb])
+          for_groups_with(acc, best[nb], [&](int g, int r, float mg) {
+            const int id = (int)a.ids[t * 32 + g * kGroupShapes + 4 * half + r];
+            if (mg > best[nb] || (uint32_t)id < (uint32_t)best_id[nb]) best_id[nb] = id;
+            best[nb] = mg;
+          });
+      }
+    };
+    uint4 fa0[2], fa1[2];
+    load_tile(wave, fa0);
+    load_tile(wave + kWholeWaves, fa1);
+    for (int t = wave; t < n_tiles; t += 2 * kWholeWaves) {
+      score_tile(t, fa0);
+      load_tile(t + 2 * kWholeWaves, fa0);
+      if (t + kWholeWaves < n_tiles) score_tile(t + kWholeWaves, fa1);
+      load_tile(t + 3 * kWholeWaves, fa1);
+    }
+#pragma unroll
+    for (int nb = 0; nb < kEdgeTilesPerWave; ++nb) keep_better(best[nb], best_id[nb], nb * 32 + col, s_best[wave], s_id[wave]);
+    __syncthreads();
+    const long long at = e_wg + tid;
+    if (tid < kWholeEdges && at < a.E && ((tiles >> (8 * (tid >> 5))) & 1u))
+      ((IdxT*)a.idx)[a.list[at]] = (IdxT)best_of_waves(s_best, s_id, tid).y;
   };
-  if constexpr (LIST) {
-    const long long groups = (E + kEdges - 1) / kEdges;
-    for (long long g0 = blockIdx.x; g0 < groups; g0 += (long long)kWave * gridDim.x) {
-      const long long mine = g0 + (long long)lane * gridDim.x;
-      const uint32_t flags = mine < groups ? ((const uint32_t*)a.left)[mine] : 0u;
-      for (unsigned long long m = __ballot(flags != 0); m; m &= m - 1) {
-        const int l = __ffsll(m) - 1;
-        serve((g0 + (long long)l * gridDim.x) * kEdges, (uint32_t)__builtin_amdgcn_readlane((int)flags, l));
-        __syncthreads();
-      }
+  const long long groups = (a.E + kWholeEdges - 1) / kWholeEdges;
+  for (long long g0 = blockIdx.x; g0 < groups; g0 += (long long)kWave * gridDim.x) {
+    const long long mine = g0 + (long long)lane * gridDim.x;
+    const uint32_t flags = mine < groups ? ((const uint32_t*)a.left)[mine] : 0u;
+    for (unsigned long long m = __ballot(flags != 0); m; m &= m - 1) {
+      const int l = __ffsll(m) - 1;
+      serve((g0 + (long long)l * gridDim.x) * kWholeEdges, (uint32_t)__builtin_amdgcn_readlane((int)flags, l));
+      __syncthreads();
     }
-  } else {
-    serve((long long)blockIdx.x * kEdges, 0u);
   }
+}
+
+// The best of the parts' shapes; they are in the order of the ids, but for an edge without any (id 0 everywhere).
+template <typename IdxT>
+__global__ __launch_bounds__(256) void kan_assign_join_kernel(const uint2* __restrict__ found, int parts, long long E, IdxT* __restrict__ idx) {
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (e >= E) return;
+  uint2 top = found[e];
+#pragma unroll 4
+  for (int p = 1; p < parts; ++p) {
+    const uint2 o = found[p * E + e];
+    if (__uint_as_float(o.x) > __uint_as_float(top.x)) top = o;
+  }
+  idx[e] = (IdxT)top.y;
 }
 
 // ---- bounded search -------------------------------------------------------------------------------
@@ -358,7 +589,6 @@ constexpr float kRestShare = 0.9f;                // (0.6 / 0.7: K = 8,192, unre
 // nearly none is left for (3), which would test the cells again and visit most groups once more.
 constexpr float kFound = 1.8f, kAsk = 1.5f, kApart = 1.3f, kPoor = 1.2f;
 
-constexpr float kFar = 100.0f;                    // distances above are not bounded in fp16
 constexpr int kRestWorkgroups = 1024;             // of the whole search behind it: twice what is resident
 constexpr int kAhead = 2;                         // tiles in flight per wave
 // Lists of a wave in LDS: cells that may hold a best shape (of 32 words of cells), a window of their groups, groups to visit
@@ -1018,13 +1248,6 @@ __global__ __launch_bounds__(kBuildThreads) void kan_cell_build_kernel(const Cel
   }
 }
 
-// What the second product can add to the score of a shape at distance d or less of an edge (|n| = 1): its norm is at
-// most 1 + d, the low parts are at most 2^-11 of what they complete, on either side of n . C and in |C|^2 / 2.
-__device__ __forceinline__ float first_product_slack(float d) {
-  const float r = 1.001f + d;
-  return d <= kFar ? fmaf(r, fmaf(r, 2.45e-4f, 9.8e-4f), 1e-5f) : INFINITY;
-}
-
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
 }
@@ -1352,22 +1575,56 @@ int recon_blocks(long long E) {
 }
 
 namespace {
-dim3 split_grid(long long E) { return dim3((unsigned)((E + kEdgeTilesPerWave * 32 - 1) / (kEdgeTilesPerWave * 32))); }
-}  // namespace
+size_t round256(size_t n) { return (n + 255) / 256 * 256; }
+constexpr int kFilterTiles = 256;                 // tiles of a part (both sides at the head of the whole search)
+// Operands of all shapes in LDS: 32 KB at most.  (8,192 / 28,672 / 131,072 edges x 1,000 shapes 15.6 / 16.0 / 20.1 us so, 10.1 /
+// 10.6 / 20.7 with the waves sharing their edges; x 400 - 500 8.3 / 9.8 / - against 9.1 / 10.4 / -.)
+constexpr int kLocalShapes = 512;
+constexpr unsigned kLocalWorkgroups = 1024;       // what is resident
+// Waves on their own from here: 2^18 / 2^20 edges x 1,024 shapes 44 / 96 us against 34 / 114, 2^19 / 2^20 x 4,096 158 / 282
+// against 151 / 297.
+constexpr long long kOwnMinEdges = 3ll << 18;
 
-// The bounded search pays where its cells, launches and bound tests are small next to the scores they save, for grids
-// that fit their codebook and at little loss for those that do not.  Bounded search with 2 % / 5 % / 15 % noise per
-// coefficient / unrelated grids against the whole search (which does not care), us:
-//     K = 65,536   2^20 edges  332 / 491 / 885 / 908  against 3631      2^15 edges  119 / 159 / 225 / 218  against 190
-//     K = 32,768   2^17 edges  105 / 130 / 193 / 192  against 316       2^16 edges  98 / 121 / 173 / 169  against 175
-//     K = 16,384   2^20 edges  203 / 286 / 552 / 561  against 988       2^18 edges  102 / 131 / 210 / 216  against 291
-//                  2^17 edges  85 / 103 / 152 / 154  against 168        2^16 edges  81 / 99 / 141 / 137  against 100
-//     K = 8,192    2^20 edges  184 / 243 / 445 / 443  against 530       2^19 edges  124 / 159 / 266 / 263  against 285
-//                  2^18 edges  96 / 117 / 178 / 177  against 164
-//     K = 4,096    2^20 edges  168 / 211 / 355 / 362  against 290
+// Parts of the codebook: by the work of the fullest CU.  A step of a workgroup (eight tiles of shapes, 128 edges) takes 0.58 us
+// alone on its CU, 0.92 for two there, 0.47 each for more; the first ones, with a new best in nearly every tile, as long as
+// eight more; the second launch 3 us.  2^13 edges x 65,536 shapes in 4 / 8 / 16 parts 55 / 47 / 54 us, 24,000 in 2 / 4 / 6 110 /
+// 102 / 115, 32,768 in 1 / 2 / 4 151 / 118 / 126, 65,536 in 1 / 2 217 / 217.
+int whole_parts(long long E, int K) {
+  if (K <= kLocalShapes || E >= kOwnMinEdges) return 1;
+  const long long groups = (E + kWholeEdges - 1) / kWholeEdges;
+  const int n_tiles = (K + 31) / 32;
+  int best = 1;
+  double least = 0.0;
+  for (int parts = 1; parts <= std::min(32, std::max(1, n_tiles / kWholeWaves)); ++parts) {
+    const long long n = (groups * parts + 255) / 256;        // workgroups of the fullest CU
+    const int steps = ((n_tiles + parts - 1) / parts + kWholeWaves - 1) / kWholeWaves;
+    const double t = (steps + 8) * (n == 1 ? 0.58 : (n == 2 ? 0.92 : 0.47 * (double)n)) + (parts > 1 ? 3.0 : 0.0);
+    if (parts == 1 || t < least) {
+      least = t;
+      best = parts;
+    }
+  }
+  return best;
+}
+size_t whole_bytes(long long E, int K, int parts) {
+  return round256(centroid_bytes(K)) + (parts > 1 ? (size_t)parts * (size_t)E * sizeof(uint2) : 0);
+}
+}  // namespace
+size_t assign_whole_bytes(long long E, int K) { return whole_bytes(E, K, whole_parts(E, K)); }
+
+// The bounded search pays where its cells, launches and bound tests (90 us and more that hardly depend on the edges) are small
+// next to the scores they save, for grids that fit their codebook and at little loss for those that do not.  Bounded search with
+// 2 % / 5 % / 15 % noise per coefficient / unrelated grids against the whole search (which hardly cares), us:
+//     K = 65,536   2^20 edges  332 / 491 / 885 / 908                  2^16 edges  5 %: 160 against 217
+//                  2^15 edges  119 / 159 / 225 / 218  against 118
+//     K = 32,768   2^17 edges  105 / 130 / 193 / 192                  2^16 edges  98 / 121 / 173 / 169  against 125
+//     K = 16,384   2^20 edges  203 / 286 / 552 / 561                  2^18 edges  102 / 131 / 210 / 216
+//                  2^17 edges  85 / 103 / 152 / 154   against 124     98,304      5 %: 100 against 97
+//     K = 8,192    2^20 edges  184 / 243 / 445 / 443                  2^19 edges  124 / 159 / 266 / 263
+//                  2^18 edges  96 / 117 / 178 / 177
+//     K = 4,096    2^20 edges  168 / 211 / 355 / 362  against 282
 bool assign_bounded_ok(long long E, int K) {
-  const long long work = E * K;
-  return (work >= (3ll << 29) && K >= 16384 || work >= (1ll << 32) && K >= 8192) && cell_layout(1, K).groups_max <= kCellMaxGroups;
+  return ((E - 25000) * K >= 1200000000ll && K >= 16384 || E * K >= (1ll << 32) && K >= 8192) && cell_layout(1, K).groups_max <= kCellMaxGroups;
 }
 size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
 
@@ -1419,7 +1676,7 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   const dim3 grid((unsigned)((E + 127) / 128));
   if (idx_u32) hipLaunchKernelGGL(kan_assign_bounded_kernel<uint32_t>, grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(kan_assign_bounded_kernel<uint16_t>, grid, dim3(256), 0, s, a);
-  AssignArgs rest = {};
+  RestArgs rest = {};
   rest.coef = coef;
   rest.cent = a.frag;
   rest.E = E;
@@ -1429,14 +1686,14 @@ hipError_t launch_assign_bounded(const float* coef, long long E, const float* cb
   rest.ids = a.ids;
   rest.idx = idx;
   const dim3 rest_grid((unsigned)std::min<long long>((E + 127) / 128, kRestWorkgroups));
-  if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
-  else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8, true>), rest_grid, dim3(8 * kWave), 0, s, rest);
+  if (idx_u32) hipLaunchKernelGGL(kan_assign_rest_kernel<uint32_t>, rest_grid, dim3(kWholeWaves * kWave), 0, s, rest);
+  else hipLaunchKernelGGL(kan_assign_rest_kernel<uint16_t>, rest_grid, dim3(kWholeWaves * kWave), 0, s, rest);
   return hipGetLastError();
 }
 
 hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx, float* gain,
-                         float* bias, void* ws, hipStream_t s) {
-  AssignArgs a = {};
+                         float* bias, void* ws, size_t ws_bytes, hipStream_t s) {
+  WholeArgs a = {};
   a.coef = coef;
   a.cent = (const uint4*)ws;
   a.E = E;
@@ -1444,15 +1701,33 @@ hipError_t launch_assign(const float* coef, long long E, const float* cb, int K,
   a.idx = idx;
   a.gain = gain;
   a.bias = bias;
+  auto own = [&](auto tiles, auto local, unsigned most, size_t lds) {
+    constexpr int kOwn = kAssignThreads / kWave * 32 * tiles.value;
+    const dim3 grid((unsigned)std::min<long long>((E + kOwn - 1) / kOwn, most)), block(kAssignThreads);
+    if (idx_u32) hipLaunchKernelGGL((kan_assign_own_kernel<uint32_t, tiles.value, local.value>), grid, block, lds, s, a, cb, K);
+    else hipLaunchKernelGGL((kan_assign_own_kernel<uint16_t, tiles.value, local.value>), grid, block, lds, s, a, cb, K);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  if (K <= kLocalShapes)
+    return own(integral_constant<int, 2>(), std::true_type(), kLocalWorkgroups, (size_t)a.n_tiles * 2 * 64 * sizeof(uint4));
   const long long recs = (long long)a.n_tiles * 2 * 64;
   hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, a.n_tiles, (uint4*)ws);
-  const dim3 grid((unsigned)((E + kEdgesPerWg - 1) / kEdgesPerWg));
-  if (E <= kSplitMaxEdges) {
-    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 8, false>), split_grid(E), dim3(8 * kWave), 0, s, a);
-    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 8, false>), split_grid(E), dim3(8 * kWave), 0, s, a);
-  } else {
-    if (idx_u32) hipLaunchKernelGGL((kan_assign_kernel<uint32_t, 1, false>), grid, dim3(kAssignThreads), 0, s, a);
-    else hipLaunchKernelGGL((kan_assign_kernel<uint16_t, 1, false>), grid, dim3(kAssignThreads), 0, s, a);
+  if (E >= kOwnMinEdges) return own(integral_constant<int, 4>(), std::false_type(), 1u << 30, 0);
+  a.parts = ws_bytes < assign_whole_bytes(E, K) ? 1 : whole_parts(E, K);
+  a.part_tiles = (a.n_tiles + a.parts - 1) / a.parts;
+  a.parts = (a.n_tiles + a.part_tiles - 1) / a.part_tiles;
+  a.found = (uint2*)((char*)ws + round256(centroid_bytes(K)));
+  const dim3 grid((unsigned)((E + kWholeEdges - 1) / kWholeEdges * a.parts)), join((unsigned)((E + 255) / 256));
+  const dim3 block(kWholeWaves * kWave);
+  const bool filter = a.part_tiles >= kFilterTiles;
+  if (idx_u32 && filter) hipLaunchKernelGGL((kan_assign_whole_kernel<uint32_t, true>), grid, block, 0, s, a);
+  else if (idx_u32) hipLaunchKernelGGL((kan_assign_whole_kernel<uint32_t, false>), grid, block, 0, s, a);
+  else if (filter) hipLaunchKernelGGL((kan_assign_whole_kernel<uint16_t, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((kan_assign_whole_kernel<uint16_t, false>), grid, block, 0, s, a);
+  if (a.parts > 1) {
+    if (idx_u32) hipLaunchKernelGGL(kan_assign_join_kernel<uint32_t>, join, dim3(256), 0, s, a.found, a.parts, E, (uint32_t*)idx);
+    else hipLaunchKernelGGL(kan_assign_join_kernel<uint16_t>, join, dim3(256), 0, s, a.found, a.parts, E, (uint16_t*)idx);
   }
   return hipGetLastError();
 }

@@ -406,8 +406,9 @@ hipError_t launch_bucket_prepare(const LayerPtrs&, int idx_u32, int gb_kind, int
 // ---- compression-side assignment (nearest codebook shape per edge) ---------------------------
 size_t assign_centroid_bytes(int K);       // prepared centroid operands (workspace)
 int recon_blocks(long long E);             // workgroups of the reconstruction-sums pass
+size_t assign_whole_bytes(long long E, int K);        // ... and what its parts found
 hipError_t launch_assign(const float* coef, long long E, const float* cb, int K, int idx_u32, void* idx,
-                         float* gain, float* bias, void* ws, hipStream_t);
+                         float* gain, float* bias, void* ws, size_t ws_bytes, hipStream_t);
 // The bounded search over cells of the codebook (large codebooks, many edges): the same result from a larger workspace.
 bool assign_bounded_ok(long long E, int K);
 size_t assign_bounded_bytes(long long E, int K);

@@ -271,3 +271,57 @@ def test_whole_search_shared_and_separate_waves(kb, K, E):
     for s in range(0, E, 8192):
         d2 = 1.0 - 2 * n[s:s + 8192] @ c.T + (c ** 2).sum(1)
         assert float((d2.gather(1, a[s:s + 8192, None])[:, 0] - d2.min(1).values).max()) <= GAP
+
+
+@pytest.mark.parametrize("kind", ["trained", "norms", "duplicates", "far", "no numbers"])
+@pytest.mark.parametrize("K,E", [(512, 130), (513, 257), (8193, 127), (40000, 129), (65536, 4097), (20000, 45000)])
+def test_whole_search_in_parts_and_in_one(kb, kind, K, E):
+    """Shapes in LDS (512), waves that share their edges (513), parts of the codebook, tiles tested by their first product
+    (8,192 shapes of a part and more): the ids are those of one part (a workspace without room for several), and as near as
+    the nearest row wherever the edge and its scores are numbers."""
+    coef, cb = _grids(kind, K, max(E, 8192), K + E)
+    coef = coef.view(-1, 10)[:E].reshape(E, 1, 10).clone()
+    odd = coef.view(E, 10)[5:65].view(6, 10, 10)
+    odd[0] = float("nan")
+    odd[1, :, 3] = float("inf")
+    odd[2] *= 1e30
+    odd[3] = 0.25
+    odd[4] *= 1e-21
+    whole = torch.empty(kb.lib().kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
+    mask = 0xffff if K <= 65536 else 0xffffffff
+    got = kb.kan_vq_assign(coef, cb)
+    one = kb.kan_vq_assign(coef, cb, ws=whole)
+    assert torch.equal(got[0], one[0]) and torch.equal(got[1].nan_to_num(), one[1].nan_to_num())
+    a = got[0].view(-1).long() & mask
+    assert int(a.max()) < K
+    n = coef.view(E, 10).double()
+    n = n - n.mean(1, keepdim=True)
+    g = n.norm(dim=1, keepdim=True)
+    n = torch.where(g > 0, n / g, torch.zeros_like(n))
+    valid = torch.ones(E, dtype=torch.bool, device="cuda")
+    valid[5:65] = False                                   # (no numbers, an overflow, or a norm without bits)
+    rows = torch.isfinite(cb).all(1) & (cb.abs().amax(1) < 200)        # (the others' scores are no numbers in fp16 parts)
+    c = torch.where(rows[:, None], cb, torch.zeros_like(cb)).double()
+    gap = GAP * max(1.0, float((c ** 2).sum(1).max()))
+    for s in range(0, E, 2048):
+        d2 = (n[s:s + 2048] ** 2).sum(1, keepdim=True) - 2 * n[s:s + 2048] @ c.T + (c ** 2).sum(1)
+        d2[:, ~rows] = float("inf")
+        far = d2.gather(1, a[s:s + 2048, None])[:, 0] - d2.min(1).values
+        assert float(far[valid[s:s + 2048]].max()) <= gap
+
+
+@pytest.mark.parametrize("kind,K,E", [("trained", 513, 786433), ("trained", 65536, 45057), ("trained", 131071, 36001),
+                                      ("trained", 262144, 30001), ("trained", 300000, 30001), ("clumps", 65521, 49153)])
+def test_large_searches_give_the_ids_of_one_part(kb, kind, K, E):
+    """Waves with edges of their own (3 * 2^18 edges), and the bounded search from where it begins for codebooks whose cells have
+    eight, four, two parts and one."""
+    coef, cb = _grids(kind, K, E, K + E + 2)
+    whole = torch.empty(kb.lib().kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
+    a, b = kb.kan_vq_assign(coef, cb)[0], kb.kan_vq_assign(coef, cb, ws=whole)[0]
+    assert torch.equal(a, b), int((a != b).sum())
+    flat = coef.view(E, 10)[:64].double()
+    n = flat - flat.mean(1, keepdim=True)
+    n /= n.norm(dim=1, keepdim=True)
+    d2 = 1.0 - 2 * n @ cb.double().T + (cb.double() ** 2).sum(1)
+    ids = a.view(-1)[:64].long() & (0xffff if K <= 65536 else 0xffffffff)
+    assert float((d2.gather(1, ids[:, None])[:, 0] - d2.min(1).values).max()) <= GAP
