@@ -43,6 +43,7 @@ UNITS = [
     ("kan_fused.hip", "kan_fused.o", []),
     ("kan_fused.hip", "kan_fused_chained.o", ["-DKAN_FUSED_CH=1"]),
     ("kan_fused_wave.hip", "kan_fused_wave.o", []),
+    ("kan_fused_wave.hip", "kan_fused_wave_half.o", ["-DKAN_WAVE_HALF=1"]),
     ("kan_bucket.hip", "kan_bucket.o", []),
     ("kan_assign.hip", "kan_assign.o", []),
     ("kan_gather.hip", "kan_gather.o", []),

@@ -114,6 +114,7 @@ struct LayerPlan {
   int n_jt, n_bt, n_chunks, rows_per_chunk;
   int tile_n = 0;              // matrix-core path: outputs per workgroup tile (128: four waves, 256: eight)
   int kind;          // PlanKind
+  bool half = false; // kPlanFusedWave with fp16 operands
   bool wide = false; // kPlanMfma whose workgroups dequantise their own coefficients (kan_wide.hip): cfg.bt samples x tile_n outputs
   bool stream = false;   // kPlanMfma on tiles of 256 x 256 with both operands copied to LDS (kan_stream.hip)
   bool rot() const { return wide || stream; }      // basis words in the rotated form
@@ -211,11 +212,16 @@ constexpr int64_t kHalfFusedMaxBatch = 64;   // fp16 path: fused kernel up to he
 constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here (both paths) for layers of at least
 constexpr long long kFusedTwoTilesMinEdges = 1ll << 22;    // this many edges whose codeword rows are one gather each
 constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers up to here may write partial sums four times as large as their stream
-// Precise path, 2 to 32 samples: the wave-by-wave kernel up to this many edges per launch, tiles of 128 outputs with the
-// basis tile in LDS above (there the wait of one step is another's work, and what counts is how little each does:
-// 4096 x 4096 at batch 16 / 31 105 / 125 against 118 / 132 us, fifty heads of 1024-128-21 at batch 16 68.8 against
-// 71; 2048 x 2048 33.2 against 30.5, ten heads of 2048-256-21 at batch 8 61.0 against 53.8 us).
-constexpr long long kFusedWaveMaxEdges = 6ll << 20;
+// Precise path, 2 to 32 samples: the wave-by-wave kernel, but for launches of this many edges, whose kernel - tiles of 128
+// outputs with the basis tile in LDS - kan_vq_planned_kernel has always named: 4096 x 4096 at batch 4 / 16 / 32 94 / 100 / 140
+// us against 109 / 113 / 145 with the tiles, 3000 x 3001 63 / 65 / 90 against 86 / 88 / 106, forty heads of 1748-162-21 89 / 100 /
+// 133 against 171 / 175 / 221, of 1748-256-21 115 / 122 / 167 against 143 / 146 / 184.  Between the two lines it is ahead as well where
+// the tiles are not full (forty of 1748-97-21 at 4 / 16 / 32 68 / 70 / 98 against 87 / 90 / 112; of 1748-96-21 65 / 69 / 95 against 69 / 70 / 93).
+// 17 to 32 samples on outputs that fill the tiles: up to 15 * 2^20, where the wave-by-wave kernel is ahead by the least (forty of
+// 1748-128-21 at 32 97 / 99, fifty of 200 x 1024 at 24 102 / 104, sixty of 400 x 512 100 / 108) and calls are known to be planned
+// with these slices in the static scratch.
+constexpr long long kFusedTilesMinEdges = 6ll << 20, kFusedTilesMaxEdges = 8ll << 20, kFusedTilesFullMaxEdges = 15ll << 20;
+constexpr bool tiles_full(int n_out) { return (n_out + 63) / 64 == 2 * ((n_out + 127) / 128); }
 constexpr int kFusedMinWgsPerHead = 20;      // fused kernel, several heads: workgroups per head (L2 residency of the codebooks)
 // Precise path: from this batch on the split-operand matrix-core form.  Its time hardly depends on
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
@@ -578,12 +584,13 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // 6.9 / 7.8; 48 x 512, 20, at 16 6.8 / 9.6; 64 x 669, 21, at 8 8.0 / 9.9; 82 x 2736, 19, at 24 46.0 / 47.2; 72 x 385, 47, at 5
 // 14.9 / 13.9; 97 x 1650, 13, at 8 19.0 / 18.0.
 constexpr long long kFusedWaveStepBytes = 512 * 1024;
-LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool compact,
+LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool half, bool compact,
                           bool reduced) {
   LayerPlan p;
   p.mfma = false;
   p.kind = kPlanFusedWave;
-  p.name = "kan_fused_wave";
+  p.half = half;
+  p.name = half ? "kan_fused_f16" : "kan_fused_wave";
   p.cfg = GatherCfg{32, 1, 1, idx_u32, gb_kind, code};
   p.n_jt = (n_out + kFusedWaveCols - 1) / kFusedWaveCols;
   p.n_bt = 1;
@@ -598,19 +605,45 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   if (compact) max_by_count = std::min<long long>(n_in / (2 * kFusedWaveStep), (kTargetWorkgroups + base - 1) / base);
   const long long most = std::max(1ll, std::min({max_by_count, max_by_bytes, (long long)steps}));
   const double reduction = !reduced ? 0.0 : (base > kCUs ? 1.3 : (B > 16 ? 2.0 : 3.3));
+  // Several heads, fp16 form: an XCD works on two or three at a time, as in plan_fused (2048-65-21 at batch 64, forty heads
+  // 95.8 -> 82.1 us, fifty 114.5 -> 109.8; 2048-128-21 at 24, fifty 97.4 -> 89.6; fifty of 1024-128-21 at 64 lose, 71 -> 75).
+  // The precise form gains at batch 8 and loses at 24 (fifty of 2048-65-21 93.9 -> 89.7, 120 -> 123).
+  const long long resident = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency
+                                 ? std::min<long long>(most, (kFusedMinWgsPerHead + p.n_jt - 1) / p.n_jt)
+                                 : 1;
   double least = 0;
   for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
-    const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, 1, most);
+    const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, resident, most);
     const int per = (int)((steps + want - 1) / want), chunks = (steps + per - 1) / per;
     const long long wgs = base * chunks;
     const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B) +
                         (chunks > 1 ? reduction : 0.0);
-    if (least > 0 && cost >= least) continue;
+    // (large launches, which are whole rounds of workgroups in any case: a cut for a tenth at least, as in plan_fused)
+    if (least > 0 && cost >= (reduced && p.n_chunks == 1 && (long long)n_in * n_out * n_heads > kFusedTilesMaxEdges ? 0.9 : 1.0) * least) continue;
     least = cost;
     p.rows_per_chunk = per * kFusedWaveStep;
     p.n_chunks = chunks;
   }
   return p;
+}
+
+// fp16 path up to 64 samples: the wave-by-wave kernel serves most layers; the fused kernel on tiles of 128 outputs is ahead
+// where its tiles and the chip are full, `tiles` being its plan (us, fused / wave by wave):
+//   32-bit ids:  4096 x 4096, K = 262,144, batch 8 / 64 99 / 107, 130 / 143
+//   49 to 64 samples, whose basis a wave evaluates four times a step: two-byte gains 4096 x 4096 112 / 116, 2048 x 2048 37.5 /
+//   38.9, 2048 x 512 20.2 / 21.7, fifty heads of 2048-256-21 191 / 204, of 2048-65-21 95 / 110 - but where the workgroups are
+//   three quarters of the CUs' rounds forty of 2048-256-21 167 / 160 and of 2048-96-21 92 / 83, where the last tile is not needed
+//   by tiles of 64 forty of 2048-192-21 152 / 126, with other gains 2048 x 2048 47 / 39 (q8), 47 / 41 (fp32), fp16 rows 42 / 41;
+//   fp32 rows 2048 x 2048 52 / 58, twenty of 2048-256-21 174 / 185
+// Everything else, for instance: 1000-333-21 at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 507 x 40
+// at 56 10.8 / 8.3, 931-128-50, four heads, at 36 27.6 / 17.7, 1748-162-21, forty, at 16 134 / 82.
+bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, const LayerPlan& tiles, long long edges) {
+  const long long wgs = (long long)n_heads * tiles.n_jt * tiles.n_bt * tiles.n_chunks, slots = (wgs + kCUs - 1) / kCUs * kCUs;
+  const bool full = wgs * 10 >= slots * 9, columns = tiles_full(n_out);
+  const bool bytes = code == kCbI8 || code == kCbBfp8, large = n_heads == 1 ? edges >= 1 << 20 : edges * n_heads > kFusedTilesMinEdges;
+  if (idx_u32 && gb_kind == kGbF16 && bytes && n_out % 16 == 0 && edges * n_heads >= 1 << 22) return full && columns;
+  if (B <= 48 || !large || !columns) return false;
+  return code == kCbF32 ? wgs * 4 >= slots * 3 : bytes && gb_kind == kGbF16 && full;
 }
 
 // Bucket path (prepared layers): one workgroup per (bucket, slice of the outputs, sample).
@@ -684,12 +717,12 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   precise path, prepared layers, B <= kBucketMaxBatch (3 for layers of 2^23 edges or more): the bucket kernel
 //     (codebook in LDS);
 //   precise path (KAN_PATH_GATHER, and AUTO below batch 32): B = 1 the window-gather kernel,
-//     B >= 2 the fused kernel with fp32 matrix-core operands (the fp32 FMA kernel remains the
-//     dense baseline's), from kSplitMinBatch the preparation + streaming contraction of the
+//     B = 2 .. 32 the wave-by-wave kernel (the tiles of the fused kernel for launches around 2^23 edges), above the
+//     fused kernel (the fp32 FMA kernel remains the dense baseline's), from kSplitMinBatch the preparation + streaming contraction of the
 //     fp16 path on operands split into high and low fp16 parts, the contraction making
 //     three passes (hi*lo, lo*hi, hi*hi: fp32-grade sums at matrix-core speed);
-//   fp16 path (KAN_PATH_MFMA, and AUTO from batch 32): up to kHalfFusedMaxBatch the fused
-//     kernel with fp16 operands, above that coefficient/basis preparation + the streaming
+//   fp16 path (KAN_PATH_MFMA, and AUTO from batch 32): up to kHalfFusedMaxBatch the wave-by-wave kernel with
+//     fp16 operands, or the fused kernel where its tiles are full (fused_half_ahead), above that coefficient/basis preparation + the streaming
 //     contraction (small layers, on either path: coefficient preparation + one launch, plan_matrix);
 //   from batch 65, layers of a million edges and more: the contraction that gathers and dequantises its own
 //     coefficients (make_wide), large products the one on tiles of 256 x 256 (make_stream), either path;
@@ -712,6 +745,10 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   if (half_path) {
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
+    const bool compact = min_rows != kMfmaMinRows;
+    if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact &&
+        !fused_half_ahead(L.out, B, n_heads, u32, gbk, code, plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced), (long long)L.in * L.out))
+      return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, true, false, reduced);
     if (B <= fused_max) {
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
       if (wide) make_wide(p, L.in, L.out, B, n_heads, false, x_parts, reduced);
@@ -724,12 +761,14 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   // large batches: the fp16 machinery with both operands split into high and low parts
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide, reduced);
   const long long edges = (long long)L.in * L.out;
-  if (B > 32 || (B >= 2 && edges * n_heads > kFusedWaveMaxEdges)) {
+  const long long tiles_max = B > 16 && tiles_full(L.out) ? kFusedTilesFullMaxEdges : kFusedTilesMaxEdges;
+  const bool tiles = edges * n_heads > kFusedTilesMinEdges && (edges * n_heads <= tiles_max || min_rows != kMfmaMinRows);
+  if (B > 32 || (B >= 2 && tiles)) {
     LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true, x_parts, reduced);
     return p;
   }
-  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, min_rows != kMfmaMinRows, reduced);
+  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
   return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, (long long)L.K * cb_row_bytes(code),
                      min_rows != kMfmaMinRows);
 }
@@ -1043,7 +1082,7 @@ kan_status run_layer_group(const LayerPlan& p, GatherArgs& a, const void* const*
     f.x_tanh = chain.in_tanh;
     memcpy(f.h, a.h, sizeof(f.h));
     dim3 grid((unsigned)(p.n_jt * p.n_bt), (unsigned)p.n_chunks, (unsigned)heads);
-    if (p.kind == kPlanFusedWave) st = run(p.name, s, [&] { return launch_fused_wave(p.cfg, f, grid, s); });
+    if (p.kind == kPlanFusedWave) st = run(p.name, s, [&] { return p.half ? launch_fused_wave_half(p.cfg, f, grid, s) : launch_fused_wave(p.cfg, f, grid, s); });
     else if (chain.in_parts > 1) st = run(p.name, s, [&] { return launch_fused_chained(p.cfg, f, f32, grid, s); });
     else st = run(p.name, s, [&] { return launch_fused(p.cfg, f, f32, grid, s); });
   } else if (p.kind == kPlanDense) {

@@ -1,5 +1,5 @@
-// Fused gather + matrix-core kernel of the precise path for up to 32 samples, fp32 operands
-// (v_mfma_f32_16x16x4f32): Y = Phi * Chat (+ bias), every wave on its own.
+// Fused gather + matrix-core kernel, every wave on its own: Y = Phi * Chat (+ bias).  Precise path, up to 32 samples: fp32
+// operands (v_mfma_f32_16x16x4f32).  fp16 path, up to 64 samples (KAN_WAVE_HALF, an object of its own): see HALF below.
 //
 // At these batches a layer is a chain of latencies and not a stream: metadata, codewords, products, one launch after
 // the other.  The form that came before (tiles of 128 outputs by four waves side by side, the basis tile in LDS, a
@@ -23,6 +23,17 @@
 // Configuration 3 at batch 16, first layer 18.8 -> 17.2 us (of which about 2 pass before every XCD has started, 2 until
 // the ids are there), head 30.9 -> 28.7, with an fp32 codebook at batch 8 47.8 -> 36.2; 64-40-20-8 at batch 5 24.3 ->
 // 18.6; ten heads of 2048-256-21 at batch 8 61.0 -> 53.8.
+//
+// HALF: the same lanes with fp16 operands, a lane's ten weights and coefficients as five pairs, four, four and two of them to
+// a v_mfma_f32_16x16x16_f16 (one instruction shape for all: sums passed between v_mfma_f32_16x16x32_f16 and this one came
+// out wrong).  Int8 rows take the layer's scale at the end, as in kan_fused.hip.  Blocks of 16 samples share a step's
+// coefficients, so 64 samples cost a lane four bases for 256 edges - twice the tiles of kan_fused.hip, whose workgroups share them -,
+// and that is what bounds it there, with the address units (146 - 150 G rows/s, the tiles up to 175); at up to 48 samples it is
+// the gathers and their latency.  Against the tiles of 128 outputs it has no basis tile, no barrier, tiles of half the
+// width (outputs rarely fill 128) and a quarter of the partial sums: 1000-333-21 at batch 37 25.7 -> 19.7 us, its layers 11.7 + 8.4
+// -> 9.2 + 7.1; 2048-1024-256 at 16 / 48 28.7 / 39.5 -> 25.6 / 33.8, 507 x 40 at 56 10.8 -> 8.3, 931-128-50, four heads, at 36
+// 27.6 -> 17.7, forty of 1748-162-21 at 16 134 -> 82.  Steps are kept apart from two blocks on: what two of them hold did not fit
+// into 256 registers (forty of 1748-128-21 with fp32 gains at batch 32 86 -> 69 us, precise 109 -> 95).
 
 #include <type_traits>
 
@@ -34,7 +45,13 @@ namespace kan {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 
+#ifdef KAN_WAVE_HALF
+constexpr bool kHalf = true;
+#else
+constexpr bool kHalf = false;
+#endif
 constexpr int kThreads = 256, kWaves = 4;
 constexpr int kCols = kFusedWaveCols;          // outputs per workgroup
 static_assert(kCols == 64 && kFusedWaveStep == 4 * kWaves, "lane layout");
@@ -94,6 +111,8 @@ __device__ __forceinline__ void shift_down(Raw4<T>& r, int shift) {
   }
 }
 
+__device__ __forceinline__ h16x4 operand(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(h16x4, make_uint2(lo, hi)); }
+
 // Four weights at their places span .. span + 3 among ten: three conditional shifts, by 1, 2 and 4.
 __device__ __forceinline__ void spread(float w0, float w1, float w2, float w3, int span, float (&v)[kG]) {
   const bool s1 = span & 1, s2 = span & 2, s4 = span & 4;
@@ -105,10 +124,23 @@ __device__ __forceinline__ void spread(float w0, float w1, float w2, float w3, i
   for (int n = 0; n < kG; ++n) v[n] = s4 ? (n >= 4 ? b[n - 4] : 0.f) : (n < 7 ? b[n] : 0.f);      // (span 6: b[6] is 0)
 }
 
-// MB: blocks of 16 samples (1 or 2).  CH: the input arrives as the previous layer's partial sums, slices
+// The same as fp16 pairs, slots 0 .. 9 of an operand (the places as above: a 64-bit shift by one place, selects by two and four).
+__device__ __forceinline__ void spread_half(uint32_t w01, uint32_t w23, int span, uint32_t (&v)[5]) {
+  const bool s1 = span & 1, s2 = span & 2, s4 = span & 4;
+  const uint64_t w = (((uint64_t)w23 << 32) | w01) << (s1 ? 16 : 0);
+  const uint32_t a[3] = {(uint32_t)w, (uint32_t)(w >> 32), s1 ? w23 >> 16 : 0u};
+  const uint32_t b[4] = {s2 ? 0u : a[0], s2 ? a[0] : a[1], s2 ? a[1] : a[2], s2 ? a[2] : 0u};
+  v[0] = s4 ? 0u : b[0];
+  v[1] = s4 ? 0u : b[1];
+  v[2] = s4 ? b[0] : b[2];
+  v[3] = s4 ? b[1] : b[3];
+  v[4] = s4 ? b[2] : 0u;
+}
+
+// MB: blocks of 16 samples (1 or 2; 1 to 4 with HALF).  HALF: fp16 operands.  CH: the input arrives as the previous layer's partial sums, slices
 // [x_parts][B][n_in]; the workgroup adds those of its own inputs in slice order, squashes them and keeps them in
 // dynamic shared memory, [sample rows][inputs of the chunk].
-template <typename IdxT, typename GbT, typename CbT, int MB, bool CH>
+template <typename IdxT, typename GbT, typename CbT, int MB, bool CH, bool HALF>
 __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const FusedArgs a) {
   constexpr bool kNt = sizeof(IdxT) == 4 || sizeof(CbT) == 4;     // (32-bit ids: more than 65,536 rows)
   constexpr int kLead = 2;                     // steps between the request of codewords and their use
@@ -139,7 +171,8 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
   const GbT* bias = (const GbT*)hp.bias;
   const Q8Params qp = {hp.gain_log2_lo, hp.gain_log2_step, hp.bias_scale};
   const CbT* cb = (const CbT*)hp.cb;
-  const float gmul = sizeof(CbT) == 1 ? hp.scale : 1.0f;
+  const float scale = sizeof(CbT) == 1 ? hp.scale : 1.0f;
+  const float gmul = HALF ? 1.0f : scale;       // fp16 coefficients: the sums are scaled
   const float* xh = a.x + (long long)head * a.x_head_stride;
 
   // the lane's four outputs; loads start at most four elements before the end of the arrays
@@ -180,16 +213,24 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
     }
   };
 
-  const float* xrow[MB];
+  // (one block: a pointer per lane, 27.0 against 28.0 us for 2048-1024-256 with byte codes at batch 4; several: offsets, a
+  // register each, of at most 64 samples of 2^20 inputs)
+  using Row = std::conditional_t<MB == 1, const float*, uint32_t>;
+  Row xrow[MB];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) xrow[mb] = xh + (long long)min(mb * 16 + c, B - 1) * n_in;
+  for (int mb = 0; mb < MB; ++mb) {
+    const int b = min(mb * 16 + c, B - 1);
+    if constexpr (MB == 1) xrow[mb] = xh + (long long)b * n_in;
+    else xrow[mb] = (uint32_t)b * (uint32_t)n_in;
+  }
   extern __shared__ __attribute__((aligned(16))) float sX[];
   const int x_len = i_end - i_begin;
   auto load_x = [&](int k, float (&u)[MB]) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       if constexpr (CH) u[mb] = sX[min(mb * 16 + c, B - 1) * x_len + min(i_lane + k * kFusedWaveStep, i_end - 1) - i_begin];
-      else u[mb] = xrow[mb][min(i_lane + k * kFusedWaveStep, i_end - 1)];
+      else if constexpr (MB == 1) u[mb] = xrow[mb][min(i_lane + k * kFusedWaveStep, i_end - 1)];
+      else u[mb] = xh[xrow[mb] + (uint32_t)min(i_lane + k * kFusedWaveStep, i_end - 1)];
     }
   };
 
@@ -286,12 +327,15 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
     shift_down(m.g, m.shift);
     shift_down(m.b, m.shift);
     // A: the weights of (sample c, input kg), at their places among ten; none for inputs past the end
-    float w[MB][kG];
+    float w[HALF ? 1 : MB][kG];
+    if constexpr (!HALF) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const BasisW bw = basis_fast(u[t][mb], a.rule);
-      spread(live ? bw.w0 : 0.f, live ? bw.w1 : 0.f, live ? bw.w2 : 0.f, live ? bw.w3 : 0.f, bw.span, w[mb]);
+      for (int mb = 0; mb < MB; ++mb) {
+        const BasisW bw = basis_fast(u[t][mb], a.rule);
+        spread(live ? bw.w0 : 0.f, live ? bw.w1 : 0.f, live ? bw.w2 : 0.f, live ? bw.w3 : 0.f, bw.span, w[mb]);
+      }
     }
+    uint32_t ch[HALF ? 4 : 1][5];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float g, b;
@@ -306,14 +350,33 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
         b = pick(m.b, q);
       }
       bsum[q] += live ? b : 0.f;
-      float cf[kG];
       align_row<CbT>(rows[t % kSlots][q], (odd[t % kSlots] >> q) & 1u);
-      dequant_row_f32<CbT>(rows[t % kSlots][q], g * gmul, cf);
+      if constexpr (HALF) {
+        dequant_row<CbT>(rows[t % kSlots][q], g * gmul, ch[q]);
+      } else {
+        float cf[kG];
+        dequant_row_f32<CbT>(rows[t % kSlots][q], g * gmul, cf);
 #pragma unroll
-      for (int n = 0; n < kG; ++n)
+        for (int n = 0; n < kG; ++n)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          acc[mb][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[mb][n], cf[n], acc[mb][q], 0, 0, 0);
+          for (int mb = 0; mb < MB; ++mb)
+            acc[mb][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[mb][n], cf[n], acc[mb][q], 0, 0, 0);
+      }
+    }
+    if constexpr (HALF) {                         // four, four and two coefficients of the four inputs at a time
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const BasisW bw = basis_fast(u[t][mb], a.rule);
+        const uint32_t w01 = pack_h2(bw.w0, bw.w1), w23 = pack_h2(bw.w2, bw.w3);
+        uint32_t wh[5];
+        spread_half(live ? w01 : 0u, live ? w23 : 0u, bw.span, wh);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[mb][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(operand(wh[0], wh[1]), operand(ch[q][0], ch[q][1]), acc[mb][q], 0, 0, 0);
+          acc[mb][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(operand(wh[2], wh[3]), operand(ch[q][2], ch[q][3]), acc[mb][q], 0, 0, 0);
+          acc[mb][q] = __builtin_amdgcn_mfma_f32_16x16x16f16(operand(wh[4], 0u), operand(ch[q][4], 0u), acc[mb][q], 0, 0, 0);
+        }
+      }
     }
     if constexpr (!kEarly) request();
     if constexpr (decltype(MORE)::value) {
@@ -321,6 +384,7 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
       load_x(k + 4, u[t]);
       load_ids(k + kLead + 4, ids[(t + kLead) % 4]);
     }
+    if constexpr (MB > 1) __builtin_amdgcn_sched_barrier(0);              // (what two steps hold does not fit)
   };
   constexpr auto yes = std::true_type{};
   constexpr auto no = std::false_type{};
@@ -360,7 +424,9 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       s_red[wave][mb][r][lane] =
-          f32x4{acc[mb][0][r] + bsum[0], acc[mb][1][r] + bsum[1], acc[mb][2][r] + bsum[2], acc[mb][3][r] + bsum[3]};
+          HALF ? f32x4{fmaf(scale, acc[mb][0][r], bsum[0]), fmaf(scale, acc[mb][1][r], bsum[1]),
+                       fmaf(scale, acc[mb][2][r], bsum[2]), fmaf(scale, acc[mb][3][r], bsum[3])}
+               : f32x4{acc[mb][0][r] + bsum[0], acc[mb][1][r] + bsum[1], acc[mb][2][r] + bsum[2], acc[mb][3][r] + bsum[3]};
   __syncthreads();
   float* dst = a.dst + (long long)head * a.dst_head_stride + (long long)chunk * a.dst_chunk_stride;
   const bool whole = n_out % 4 == 0 && ((uintptr_t)dst & 15) == 0;
@@ -387,18 +453,24 @@ __global__ __launch_bounds__(kThreads, 2) void kan_fused_wave_kernel(const Fused
   }
 }
 
-template <typename IdxT, typename GbT, typename CbT>
-hipError_t launch_variant(const FusedArgs& a, dim3 grid, hipStream_t s) {
+template <typename IdxT, typename GbT, typename CbT, int MB>
+hipError_t launch_blocks(const FusedArgs& a, dim3 grid, hipStream_t s) {
   const bool ch = a.x_parts > 1;
   const size_t lds = ch ? (size_t)a.B * a.rows_per_chunk * 4 : 0;
-  if (a.B <= 16) {
-    if (ch) hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, 1, true>), grid, dim3(kThreads), lds, s, a);
-    else hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, 1, false>), grid, dim3(kThreads), 0, s, a);
-  } else {
-    if (ch) hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, 2, true>), grid, dim3(kThreads), lds, s, a);
-    else hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, 2, false>), grid, dim3(kThreads), 0, s, a);
-  }
+  if (ch) hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, MB, true, kHalf>), grid, dim3(kThreads), lds, s, a);
+  else hipLaunchKernelGGL((kan_fused_wave_kernel<IdxT, GbT, CbT, MB, false, kHalf>), grid, dim3(kThreads), 0, s, a);
   return hipGetLastError();
+}
+
+template <typename IdxT, typename GbT, typename CbT>
+hipError_t launch_variant(const FusedArgs& a, dim3 grid, hipStream_t s) {
+  if (a.B <= 16) return launch_blocks<IdxT, GbT, CbT, 1>(a, grid, s);
+  if (a.B <= 32) return launch_blocks<IdxT, GbT, CbT, 2>(a, grid, s);
+  if constexpr (kHalf) {
+    if (a.B <= 48) return launch_blocks<IdxT, GbT, CbT, 3>(a, grid, s);
+    return launch_blocks<IdxT, GbT, CbT, 4>(a, grid, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename IdxT>
@@ -417,8 +489,12 @@ hipError_t launch_types(const GatherCfg& c, const FusedArgs& a, dim3 grid, hipSt
 
 }  // namespace
 
+#ifdef KAN_WAVE_HALF
+hipError_t launch_fused_wave_half(const GatherCfg& c, const FusedArgs& a, dim3 grid, hipStream_t s) {
+#else
 hipError_t launch_fused_wave(const GatherCfg& c, const FusedArgs& a, dim3 grid, hipStream_t s) {
-  if (c.code == kDense || a.B < 1 || a.B > 32 || (long long)a.n_in * a.n_out < 4 || a.rows_per_chunk % kFusedWaveStep != 0)
+#endif
+  if (c.code == kDense || a.B < 1 || a.B > (kHalf ? 64 : 32) || (long long)a.n_in * a.n_out < 4 || a.rows_per_chunk % kFusedWaveStep != 0)
     return hipErrorInvalidValue;
   // what the 16-byte loads of the slices and the inputs in LDS assume
   if (a.x_parts > 1 && (a.x_parts > kFusedChainMaxParts || a.n_in % 4 != 0 || a.x_part_stride % 4 != 0 || a.x_head_stride % 4 != 0 ||

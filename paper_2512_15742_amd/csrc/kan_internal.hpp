@@ -268,13 +268,14 @@ constexpr int kFusedChainFloats = 2048;
 constexpr int kFusedChainMaxParts = 64;
 hipError_t launch_fused_chained(const GatherCfg&, const FusedArgs&, bool f32, dim3 grid, hipStream_t);
 
-// ---- fused gather + matrix-core kernel of the precise path, up to 32 samples, a wave on its own ---------------
+// ---- fused gather + matrix-core kernel, a wave on its own: precise path up to 32 samples, fp16 path up to 64 ----
 constexpr int kFusedWaveCols = 64;    // outputs per workgroup
 constexpr int kFusedWaveStep = 16;    // inputs per step of a workgroup: four per wave
 constexpr int kFusedWaveChainFloats = 8192;   // input in slices: samples x inputs of a chunk kept in LDS
 // FusedArgs as above with rows_per_chunk a multiple of kFusedWaveStep, blockIdx.x = output tile, x_parts > 1 allowed;
 // n_in * n_out >= 4 (loads of four edges).
 hipError_t launch_fused_wave(const GatherCfg&, const FusedArgs&, dim3 grid, hipStream_t);
+hipError_t launch_fused_wave_half(const GatherCfg&, const FusedArgs&, dim3 grid, hipStream_t);       // fp16 operands, up to 64 samples
 
 // ---- bucketed small-batch path (prepared layers) ----------------------------------
 // A prepared layer holds its edges regrouped by codebook bucket (a run of consecutive

@@ -77,3 +77,43 @@ def test_chunks_of_heads(kb, dims, heads, B):
     for h in (0, heads - 1):
         rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
         assert rep["headline"] <= TOL_FP32, rep
+
+
+@pytest.mark.parametrize("rule", [0, 1], ids=["bspline", "pli"])
+@pytest.mark.parametrize("n_in,n_out", [(1, 4), (5, 17), (16, 64), (17, 65), (49, 130), (300, 333)])
+@pytest.mark.parametrize("B", [1, 15, 17, 33, 48, 49, 64])
+def test_half_operands(kb, B, n_in, n_out, rule):
+    """fp16 operands, blocks of 16 samples from one to four, every storage type: inputs that end inside a group of four and a
+    step, outputs inside a lane's four and a tile.  Error per sample and output against the sum of |weight x coefficient|:
+    weights, coefficients and gains are rounded to 2^-11 of themselves, an Int8 product once more."""
+    for n, (cb, gb, idx, K) in enumerate((("i8", "f16", "u16", 4099), ("f32", "f32", "u32", 70001), ("f16", "f32", "u16", 300),
+                                          ("i8", "q8", "u16", 65536), ("bfp8", "f16", "u16", 1000))):
+        P = synth.make_layer(9600 + 10 * B + n, n_in, n_out, K, cb_dtype=cb, gb_dtype=gb, idx_dtype=idx)
+        x = np.random.default_rng(B * 131 + n_in).uniform(-1.1, 1.1, size=(B, n_in)).astype(np.float32)
+        x[0, 0], x[-1, -1] = -1.0, 1.0
+        L = kb.VQLayer(P, rule=kb.KAN_RULE_PLI2 if rule else kb.KAN_RULE_BSPLINE3)
+        assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_MFMA) == "kan_fused_f16"
+        y = kb.kan_vq_layer_forward(L, to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
+        assert np.isfinite(y).all()
+        name = "pli" if rule else "bspline"
+        y_ref = ko.vq_layer_forward(x, **P.as_dict(), rule=name)
+        coef = ko.reconstruct_coefficients(**P.as_dict())
+        # (the biases are not rounded; shapes have mean 0, so a grid's mean is its bias and what is rounded is at most this)
+        most = ko.dense_layer_forward(np.abs(coef) + np.abs(coef.mean(-1, keepdims=True)), x, rule=name)
+        assert (np.abs(y - y_ref) <= 4 * 2.0 ** -11 * most + 1e-6 * np.abs(y_ref).max()).all(), (cb, gb, idx, ko.error_report(y, y_ref))
+
+
+@pytest.mark.parametrize("B,dims,heads", [(37, (1000, 333, 21), 1), (64, (320, 96, 24), 20), (33, (70, 64, 32, 10), 3), (48, (128, 200, 17), 60)])
+@pytest.mark.parametrize("cb,gb", [("i8", "f16"), ("f16", "f32")])
+def test_half_operands_of_heads(kb, B, dims, heads, cb, gb):
+    """Layers handed on in slices and reduced, several heads with parameters of their own."""
+    n = min(heads, 3)
+    Ps = [[synth.make_layer(9700 + 5 * h + l, a, b, 701, cb_dtype=cb, gb_dtype=gb) for l, (a, b) in enumerate(zip(dims, dims[1:]))] for h in range(n)]
+    hs = [[kb.VQLayer(p) for p in P] for P in Ps]
+    x = synth.make_x(9800 + B, B, dims[0])
+    y = kb.kan_vq_head_forward([hs[h % n] for h in range(heads)], to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
+    for h in range(heads):
+        assert np.array_equal(y[h], y[h % n])
+    for h in range(n):
+        rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
+        assert rep["headline"] <= 3e-3 * len(dims), rep
