@@ -222,7 +222,18 @@ constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers 
 // with these slices in the static scratch.
 constexpr long long kFusedTilesMinEdges = 6ll << 20, kFusedTilesMaxEdges = 8ll << 20, kFusedTilesFullMaxEdges = 15ll << 20;
 constexpr bool tiles_full(int n_out) { return (n_out + 63) / 64 == 2 * ((n_out + 127) / 128); }
-constexpr int kFusedMinWgsPerHead = 20;      // fused kernel, several heads: workgroups per head (L2 residency of the codebooks)
+constexpr int kFusedMinWgsPerHead = 20;      // fused kernels, several heads: workgroups per head (L2 residency of the codebooks)
+// ... of the wave-by-wave kernel's fp16 form from kFusedLargeCodebook on, three of which do not fit an L2 beside each other, where
+// the heads' together take half of all L2s: an XCD works on one head at a time.  20 / 40 / 64 workgroups per head, us: twenty of
+// 2048-256-21 with 65,536 fp32 rows at batch 40 / 64 156 / 123 / 121, 185 / 147 / 146, fp16 rows 94 / 88 / 88, 105 / 101 / 103,
+// 40,000 of them 112 / 103 / 103, thirty of 1000-200-21 fp16 rows at 16 / 40 80 / 75 / 75, 90 / 90 / 81, fifty of 2048-72-21 at 16
+// 107 / - / 82.  Smaller codebooks and fewer heads lose (forty of 1748-162-21, 65,536 Int8 rows, at 48 100 / 99 / 109; ten of
+// 512-300-40, fp16 rows, at 40 33 / - / 35), but of fp32 rows, whose longer steps do not mind more sums (twenty of 2048-256-21 with
+// 15,000 at 40 116 / 113 / 112, 22 of 1280-224-21 with 6,195 87.6 / 93.4 / 82.3; 25 of 512-300-40 at 16 65 / - / 56, at 40
+// 74 / - / 77).  What 64 workgroups write may take a call past the static scratch: see plan_head.
+constexpr int kFusedOneHeadWgs = 64;
+constexpr long long kFusedLargeCodebook = 768 * 1024;
+constexpr long long kFusedOneHeadMinEdges = 1 << 19;      // from here a head's workgroups have eight steps each
 // Precise path: from this batch on the split-operand matrix-core form.  Its time hardly depends on
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
 // its second tile of 64 samples (config 3: 97 us at 64, 113 at 80; config 2: 33 and 57).
@@ -584,7 +595,7 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // 6.9 / 7.8; 48 x 512, 20, at 16 6.8 / 9.6; 64 x 669, 21, at 8 8.0 / 9.9; 82 x 2736, 19, at 24 46.0 / 47.2; 72 x 385, 47, at 5
 // 14.9 / 13.9; 97 x 1650, 13, at 8 19.0 / 18.0.
 constexpr long long kFusedWaveStepBytes = 512 * 1024;
-LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, bool half, bool compact,
+LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, int large_wgs, bool half, bool compact,
                           bool reduced) {
   LayerPlan p;
   p.mfma = false;
@@ -608,8 +619,10 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   // Several heads, fp16 form: an XCD works on two or three at a time, as in plan_fused (2048-65-21 at batch 64, forty heads
   // 95.8 -> 82.1 us, fifty 114.5 -> 109.8; 2048-128-21 at 24, fifty 97.4 -> 89.6; fifty of 1024-128-21 at 64 lose, 71 -> 75).
   // The precise form gains at batch 8 and loses at 24 (fifty of 2048-65-21 93.9 -> 89.7, 120 -> 123).
+  const bool one_head = code == kCbF32 || (cb_bytes > kFusedLargeCodebook && n_heads * cb_bytes > 4 * kL2Bytes);
+  const int head_wgs = one_head ? large_wgs : kFusedMinWgsPerHead;
   const long long resident = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency
-                                 ? std::min<long long>(most, (kFusedMinWgsPerHead + p.n_jt - 1) / p.n_jt)
+                                 ? std::min<long long>(most, (head_wgs + p.n_jt - 1) / p.n_jt)
                                  : 1;
   double least = 0;
   for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
@@ -634,15 +647,18 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
 //   38.9, 2048 x 512 20.2 / 21.7, fifty heads of 2048-256-21 191 / 204, of 2048-65-21 95 / 110 - but where the workgroups are
 //   three quarters of the CUs' rounds forty of 2048-256-21 167 / 160 and of 2048-96-21 92 / 83, where the last tile is not needed
 //   by tiles of 64 forty of 2048-192-21 152 / 126, with other gains 2048 x 2048 47 / 39 (q8), 47 / 41 (fp32), fp16 rows 42 / 41;
-//   fp32 rows 2048 x 2048 52 / 58, twenty of 2048-256-21 174 / 185
+//   fp32 rows 2048 x 2048 52 / 58, twenty of 1280-256-21 133 / 139, forty of 700-256-21 153 / 157; not the heads of 2^19 edges and
+//   more that do not fit the L2s of all XCDs together and are taken one at a time, 14 / 20 / 40 of 2048-256-21 120 / 110, 170 / 145,
+//   369 / 266
 // Everything else, for instance: 1000-333-21 at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 507 x 40
 // at 56 10.8 / 8.3, 931-128-50, four heads, at 36 27.6 / 17.7, 1748-162-21, forty, at 16 134 / 82.
-bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, const LayerPlan& tiles, long long edges) {
+bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, const LayerPlan& tiles, long long edges) {
   const long long wgs = (long long)n_heads * tiles.n_jt * tiles.n_bt * tiles.n_chunks, slots = (wgs + kCUs - 1) / kCUs * kCUs;
   const bool full = wgs * 10 >= slots * 9, columns = tiles_full(n_out);
   const bool bytes = code == kCbI8 || code == kCbBfp8, large = n_heads == 1 ? edges >= 1 << 20 : edges * n_heads > kFusedTilesMinEdges;
   if (idx_u32 && gb_kind == kGbF16 && bytes && n_out % 16 == 0 && edges * n_heads >= 1 << 22) return full && columns;
   if (B <= 48 || !large || !columns) return false;
+  if (code == kCbF32 && n_heads > 1 && n_heads * cb_bytes > 8 * kL2Bytes && edges >= kFusedOneHeadMinEdges) return false;
   return code == kCbF32 ? wgs * 4 >= slots * 3 : bytes && gb_kind == kGbF16 && full;
 }
 
@@ -729,9 +745,11 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   layers of kFusedTwoTilesMinEdges edges or more (not fp32 codebooks) keep the fused kernel up to
 //     kFusedTwoTilesMaxBatch on either path where make_wide does not take them.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
-                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true) {
+                  bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true,
+                  int large_wgs = kFusedOneHeadWgs) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
+  const long long cb_bytes = (long long)L.K * cb_row_bytes(code);
   const bool half_path = path == KAN_PATH_MFMA || (path == KAN_PATH_AUTO && B >= kAutoMfmaBatch);
   // Large layers stay on the fused kernel for a second batch tile: gathering every row twice costs less
   // than preparing the records of 4 M edges or more and contracting them (4096 x 4096, K = 262,144, batch
@@ -747,8 +765,8 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // path would write 20 bytes per edge and read them back for no reuse)
     const bool compact = min_rows != kMfmaMinRows;
     if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact &&
-        !fused_half_ahead(L.out, B, n_heads, u32, gbk, code, plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced), (long long)L.in * L.out))
-      return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, true, false, reduced);
+        !fused_half_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced), (long long)L.in * L.out))
+      return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced);
     if (B <= fused_max) {
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
       if (wide) make_wide(p, L.in, L.out, B, n_heads, false, x_parts, reduced);
@@ -768,8 +786,8 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true, x_parts, reduced);
     return p;
   }
-  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
-  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, (long long)L.K * cb_row_bytes(code),
+  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, false, min_rows != kMfmaMinRows, reduced);
+  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, cb_bytes,
                      min_rows != kMfmaMinRows);
 }
 
@@ -1155,7 +1173,7 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
 kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                          int min_rows, bool hand_on, bool wide, std::vector<LayerPlan>* plans, WsLayout* ws) {
+                          int min_rows, bool hand_on, bool wide, int large_wgs, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -1184,7 +1202,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced);
+    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced, large_wgs);
   };
   const int last = n_layers - 1;
   for (int l = 0; l <= last; ++l) plans->push_back(plan_of(l, l == last));
@@ -1229,6 +1247,8 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
   return KAN_OK;
 }
 
+// Heads that an XCD takes one at a time get fewer workgroups each before anything else is given up (fifty of 2048-256-21 with
+// 65,536 fp32 rows, fp16 path, batch 40, 20 / 32 / 48 workgroups 368 / 333 / 311 us; with 64, which take 33 MB, planned compact 403).
 // Finer chunks write more partial sums, a layer that hands its sums on keeps a second buffer of them: a call that fits the
 // library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.  Basis words
 // take room that the fused kernel does without, rotated ones of whole tiles of 256 samples more than those of kan_mfma.hip: a
@@ -1238,15 +1258,23 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 // 4095 at 7700: kan_mfma in 28.6 MB, kan_stream would take 34).
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
-  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, plans, ws);
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, kFusedOneHeadWgs, plans, ws);
   if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
   const struct { int min_rows; bool hand_on; } forms[] = {
       {kMfmaMinRows, true}, {kMfmaMinRowsCompact, true}, {kMfmaMinRows, false}, {kMfmaMinRowsCompact, false}};
   std::vector<LayerPlan> other;
   WsLayout other_ws;
+  if (n_heads > 1 && B <= kHalfFusedMaxBatch)
+    for (const int wgs : {kFusedOneHeadWgs * 3 / 4, kFusedOneHeadWgs / 2, kFusedMinWgsPerHead})
+      if (plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, wgs, &other, &other_ws) == KAN_OK &&
+          other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
+        plans->swap(other);
+        *ws = other_ws;
+        return st;
+      }
   auto fits = [&](bool wide) {
     for (const auto& o : forms)
-      if (plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, wide, &other, &other_ws) == KAN_OK &&
+      if (plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, wide, kFusedMinWgsPerHead, &other, &other_ws) == KAN_OK &&
           other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES)
         return true;
     return false;

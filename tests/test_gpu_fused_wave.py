@@ -117,3 +117,18 @@ def test_half_operands_of_heads(kb, B, dims, heads, cb, gb):
     for h in range(n):
         rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
         assert rep["headline"] <= 3e-3 * len(dims), rep
+
+
+@pytest.mark.parametrize("B,cb,gb,K", [(40, "f32", "f32", 65536), (64, "f32", "f16", 65536), (8, "f16", "f16", 45000)])
+def test_one_large_codebook_at_a_time(kb, B, cb, gb, K):
+    """Twenty heads whose codebooks do not fit an L2 beside each other: first layers in up to 64 workgroups each."""
+    heads, dims = 20, (1003, 200, 21)
+    Ps = [[synth.make_layer(9900 + 5 * h + l, a, b, K, cb_dtype=cb, gb_dtype=gb) for l, (a, b) in enumerate(zip(dims, dims[1:]))] for h in range(2)]
+    hs = [[kb.VQLayer(p) for p in P] for P in Ps]
+    x = synth.make_x(9950 + B, B, dims[0])
+    y = kb.kan_vq_head_forward([hs[h % 2] for h in range(heads)], to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
+    for h in range(heads):
+        assert np.array_equal(y[h], y[h % 2])
+    for h in range(2):
+        rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
+        assert rep["headline"] <= 3e-3 * len(dims), rep
