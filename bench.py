@@ -528,7 +528,7 @@ def config3_legs(kb, torch, synth, args, path, facts, with_cpu):
 
 
 def dtype_of(r):
-    return "f16" if r["roofline"]["kernel"].startswith(("kan_mfma@", "kan_wide@", "kan_stream@", "kan_fused_f16")) else "f32"
+    return "f16" if r["roofline"]["kernel"].startswith(("kan_mfma@", "kan_wide@", "kan_stream@", "kan_fused_f16", "kan_fused_wave_f16")) else "f32"
 
 
 def main():

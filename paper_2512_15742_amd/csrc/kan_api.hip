@@ -601,7 +601,7 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   p.mfma = false;
   p.kind = kPlanFusedWave;
   p.half = half;
-  p.name = half ? "kan_fused_f16" : "kan_fused_wave";
+  p.name = half ? "kan_fused_wave_f16" : "kan_fused_wave";
   p.cfg = GatherCfg{32, 1, 1, idx_u32, gb_kind, code};
   p.n_jt = (n_out + kFusedWaveCols - 1) / kFusedWaveCols;
   p.n_bt = 1;

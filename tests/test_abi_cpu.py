@@ -142,7 +142,7 @@ def test_prepare_arguments_and_planning():
     assert L.kan_vq_planned_kernel(C.byref(d), 1, 1, kb.KAN_PATH_GATHER) == b"kan_bucket"
     assert L.kan_vq_planned_kernel(C.byref(d), 4, 1, kb.KAN_PATH_AUTO) == b"kan_bucket"
     assert L.kan_vq_planned_kernel(C.byref(d), 5, 1, kb.KAN_PATH_GATHER) == b"kan_fused_wave"
-    assert L.kan_vq_planned_kernel(C.byref(d), 1, 1, kb.KAN_PATH_MFMA) == b"kan_fused_f16"
+    assert L.kan_vq_planned_kernel(C.byref(d), 1, 1, kb.KAN_PATH_MFMA) == b"kan_fused_wave_f16"
     # per-bucket partial sums: 8 buckets x out floats
     assert L.kan_vq_workspace_bytes(C.byref(d), 1, 1, 1, kb.KAN_PATH_GATHER) == 8 * 1024 * 4
     d.codebook = 0x4008                                  # bucket copies need 16-byte alignment
@@ -164,7 +164,7 @@ def test_fp16_codebook_layers_plan_and_prepare():
     L = kb.lib()
     d = _desc(n_in=2048, n_out=1024, K=65536, cb_dtype=kb.KAN_F16, gb_dtype=kb.KAN_F16, codebook=0x4004)
     for B, path, name in ((1, kb.KAN_PATH_GATHER, b"kan_gather_bt1"), (16, kb.KAN_PATH_GATHER, b"kan_fused_wave"),
-                          (16, kb.KAN_PATH_MFMA, b"kan_fused_f16"), (1024, kb.KAN_PATH_AUTO, b"kan_mfma")):
+                          (16, kb.KAN_PATH_MFMA, b"kan_fused_wave_f16"), (1024, kb.KAN_PATH_AUTO, b"kan_mfma")):
         assert L.kan_vq_planned_kernel(C.byref(d), B, 1, path) == name
         assert L.kan_vq_workspace_bytes(C.byref(d), 1, 1, B, path) != kb.SIZE_INVALID
     E = 2048 * 1024
@@ -285,7 +285,7 @@ def test_planner_accepts_every_shape_and_names_a_known_kernel():
     import numpy as np
     L = kb.lib()
     rng = np.random.default_rng(20251127)
-    known = {b"kan_gather_bt1", b"kan_gather_bt4", b"kan_gather_bt16", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16",
+    known = {b"kan_gather_bt1", b"kan_gather_bt4", b"kan_gather_bt16", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_wave_f16", b"kan_fused_f16",
              b"kan_mfma", b"kan_mfma_split", b"kan_wide", b"kan_wide_split", b"kan_stream", b"kan_stream_split", b"kan_bucket"}
     kinds = [(kb.KAN_F32, kb.KAN_F32), (kb.KAN_I8, kb.KAN_F16), (kb.KAN_I8, kb.KAN_F32), (kb.KAN_F16, kb.KAN_F16),
              (kb.KAN_I8, kb.KAN_Q8)]
@@ -307,7 +307,7 @@ def test_planner_accepts_every_shape_and_names_a_known_kernel():
             arr = (kb.kan_vq_layer * heads)(*([d] * heads))
             ws = L.kan_vq_workspace_bytes(arr, 1, heads, B, path)
             assert ws != kb.SIZE_INVALID and ws % 256 == 0, (n_in, n_out, B, heads, path, ws)
-    assert {b"kan_gather_bt1", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_f16", b"kan_mfma", b"kan_mfma_split",
+    assert {b"kan_gather_bt1", b"kan_fused_f32", b"kan_fused_wave", b"kan_fused_wave_f16", b"kan_fused_f16", b"kan_mfma", b"kan_mfma_split",
             b"kan_wide", b"kan_wide_split", b"kan_stream", b"kan_stream_split"} <= seen
 
 

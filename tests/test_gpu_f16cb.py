@@ -50,7 +50,7 @@ def test_f16cb_every_kernel_family(kb, gb_dtype):
         y_ref, A = ko.vq_layer_forward(x, **P.as_dict(), return_abs=True)
         rep = ko.error_report(y, y_ref, A)
         assert rep["headline"] <= tol and rep["strict"] <= tol, (B, path, rep)
-    assert seen == {"kan_gather_bt1", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_f16", "kan_mfma"}
+    assert seen == {"kan_gather_bt1", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_wave_f16", "kan_mfma"}
 
 
 @pytest.mark.parametrize("n_in,n_out,K,B", [(1, 1, 2, 1), (3, 21, 5, 2), (130, 67, 9000, 5), (257, 530, 20000, 1),

@@ -43,7 +43,7 @@ def _check(kb, Ps, x, path, tol, expect_reduce_after_first):
     Ls = gpu_layers(Ps)
     xd = to_dev(x)
     B = x.shape[0]
-    name = "kan_fused_wave" if path == kb.KAN_PATH_GATHER else "kan_fused_f16"
+    name = "kan_fused_wave" if path == kb.KAN_PATH_GATHER else "kan_fused_wave_f16"
     if B == 1 and path == kb.KAN_PATH_GATHER:
         name = "kan_gather_bt1"
     for L in Ls:

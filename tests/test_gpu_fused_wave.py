@@ -92,7 +92,7 @@ def test_half_operands(kb, B, n_in, n_out, rule):
         x = np.random.default_rng(B * 131 + n_in).uniform(-1.1, 1.1, size=(B, n_in)).astype(np.float32)
         x[0, 0], x[-1, -1] = -1.0, 1.0
         L = kb.VQLayer(P, rule=kb.KAN_RULE_PLI2 if rule else kb.KAN_RULE_BSPLINE3)
-        assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_MFMA) == "kan_fused_f16"
+        assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_MFMA) == "kan_fused_wave_f16"
         y = kb.kan_vq_layer_forward(L, to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
         assert np.isfinite(y).all()
         name = "pli" if rule else "bspline"

@@ -23,7 +23,7 @@ def kb():
 @pytest.mark.parametrize("B,path,prepared,kernel", [
     (1, "gather", True, "kan_bucket"), (1, "gather", False, "kan_gather_bt1"), (3, "gather", True, "kan_bucket"),
     (2, "gather", True, "kan_column"),
-    (16, "gather", False, "kan_fused_wave"), (48, "mfma", False, "kan_fused_f16"), (300, "mfma", False, "kan_mfma")])
+    (16, "gather", False, "kan_fused_wave"), (48, "mfma", False, "kan_fused_wave_f16"), (300, "mfma", False, "kan_mfma")])
 def test_head_forward_replays_from_a_graph(kb, B, path, prepared, kernel):
     dims = [(520, 264), (264, 130), (130, 21)]
     Ps = [synth.make_layer(40 + l, i, o, 20000, cb_dtype="i8", gb_dtype="f16") for l, (i, o) in enumerate(dims)]

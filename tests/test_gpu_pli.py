@@ -102,7 +102,7 @@ def test_pli_every_kernel_family(kb, cb, gb):
         x = rng.uniform(-1.1, 1.1, size=(B, 300)).astype(np.float32)
         x[0, :4] = [1.0, -1.0, np.float32(7.0 / 9.0), np.float32(-1.0 / 9.0)]
         seen.add(_check(kb, P, x, path, tol, prepared))
-    assert seen == {"kan_gather_bt1", "kan_bucket", "kan_column", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_f16",
+    assert seen == {"kan_gather_bt1", "kan_bucket", "kan_column", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_wave_f16",
                     "kan_mfma"}
 
 

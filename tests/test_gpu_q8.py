@@ -49,7 +49,7 @@ def test_q8_every_kernel_family(kb):
         y_ref, A = ko.vq_layer_forward(x, **P.as_dict(), return_abs=True)
         rep = ko.error_report(y, y_ref, A)
         assert rep["headline"] <= tol and rep["strict"] <= tol, (B, path, prepared, rep)
-    assert seen == {"kan_gather_bt1", "kan_bucket", "kan_column", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_f16",
+    assert seen == {"kan_gather_bt1", "kan_bucket", "kan_column", "kan_fused_wave", "kan_fused_f32", "kan_mfma_split", "kan_fused_wave_f16",
                     "kan_mfma"}
 
 
