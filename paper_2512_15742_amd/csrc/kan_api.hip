@@ -221,7 +221,7 @@ constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers 
 // 1748-128-21 at 32 97 / 99, fifty of 200 x 1024 at 24 102 / 104, sixty of 400 x 512 100 / 108) and calls are known to be planned
 // with these slices in the static scratch.
 constexpr long long kFusedTilesMinEdges = 6ll << 20, kFusedTilesMaxEdges = 8ll << 20, kFusedTilesFullMaxEdges = 15ll << 20;
-constexpr bool tiles_full(int n_out) { return (n_out + 63) / 64 == 2 * ((n_out + 127) / 128); }
+constexpr bool tiles_even(int n_out) { return (n_out + 63) / 64 == 2 * ((n_out + 127) / 128); }
 constexpr int kFusedMinWgsPerHead = 20;      // fused kernels, several heads: workgroups per head (L2 residency of the codebooks)
 // ... of the wave-by-wave kernel's fp16 form from kFusedLargeCodebook on, three of which do not fit an L2 beside each other, where
 // the heads' together take half of all L2s: an XCD works on one head at a time.  20 / 40 / 64 workgroups per head, us: twenty of
@@ -640,26 +640,57 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   return p;
 }
 
-// fp16 path up to 64 samples: the wave-by-wave kernel serves most layers; the fused kernel on tiles of 128 outputs is ahead
-// where its tiles and the chip are full, `tiles` being its plan (us, fused / wave by wave):
-//   32-bit ids:  4096 x 4096, K = 262,144, batch 8 / 64 99 / 107, 130 / 143
-//   49 to 64 samples, whose basis a wave evaluates four times a step: two-byte gains 4096 x 4096 112 / 116, 2048 x 2048 37.5 /
-//   38.9, 2048 x 512 20.2 / 21.7, fifty heads of 2048-256-21 191 / 204, of 2048-65-21 95 / 110 - but where the workgroups are
-//   three quarters of the CUs' rounds forty of 2048-256-21 167 / 160 and of 2048-96-21 92 / 83, where the last tile is not needed
-//   by tiles of 64 forty of 2048-192-21 152 / 126, with other gains 2048 x 2048 47 / 39 (q8), 47 / 41 (fp32), fp16 rows 42 / 41;
-//   fp32 rows 2048 x 2048 52 / 58, twenty of 1280-256-21 133 / 139, forty of 700-256-21 153 / 157; not the heads of 2^19 edges and
-//   more that do not fit the L2s of all XCDs together and are taken one at a time, 14 / 20 / 40 of 2048-256-21 120 / 110, 170 / 145,
-//   369 / 266
-// Everything else, for instance: 1000-333-21 at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 507 x 40
-// at 56 10.8 / 8.3, 931-128-50, four heads, at 36 27.6 / 17.7, 1748-162-21, forty, at 16 134 / 82.
+// Whether tiles of 128 outputs compute about as many columns as tiles of 64.
+constexpr bool tiles_full(int n_out) { return (n_out + 127) / 128 * 128 * 100ll <= (n_out + 63) / 64 * 64 * 107ll; }
+
+// fp16 path up to 64 samples: the wave-by-wave kernel is ahead in short chains, the fused kernel on tiles of 128 outputs, whose
+// waves share a step's basis and ask for twice the run of a row at once, where its workgroups have many steps (of 8 inputs).
+// From how many on, 0: at none; by storage types, 16-byte metadata loads (outputs in sixteens) and blocks of 16 samples.
+// Drawn through 32,492 launches of 2^18 to 24 * 2^20 edges, one to fifty heads, by the sum of the logarithms of tiles / wave by
+// wave from a line on.  Mean ratios there, parameters from memory / from the caches; the line before (49 samples and more, from
+// 2^20 edges, on whole tiles, and one 32-bit case) took 30 % of the launches of more than 3 * 2^20 edges with parameters in memory more
+// than 3 % longer than the tiles and 9 % of those from the caches, this one 17 and 4 % (and 1.5 and 5 % longer than wave by wave):
+//   one head, two-byte gains, one-byte rows   1-16 samples 0.91 / 0.93 (32-bit ids)       17-32 0.85 / 1.07, 0.89 / 0.90 (32-bit)
+//                                             33-48 0.85 / 1.04, 0.93 / 0.87              49-64 0.85 / 0.99, 0.91 / 0.89
+//   several heads, likewise                   17-32 0.88 / 1.07    33-48 0.85 / 1.01      49-64 0.80 / 0.95
+//   four-byte gains                           33-48 0.95 / 0.95 (32-bit)                  49-64 0.87 / 1.08, 0.85 / 0.87 (32-bit)
+//   fp16 rows, two-byte gains                 1-16 0.83 / 1.06 (one head), 17-32 0.84 / 1.05 (one), 33-48 0.83 / 1.05 (one), 49-64 0.80 / 0.98
+//   fp32 rows                                 1-16 0.94 / 0.95, 17-32 0.87 / 0.86 (two-byte gains, 16-bit ids)     49-64 0.87 / 0.83
+// For instance, us, tiles / wave by wave: 8192 x 1760 at batch 17 66 / 87, 4712 x 3200, fp16 rows, at 64 105 / 145, 4096 x 4096, fp32 gains
+// and 32-bit ids, at 64 126 / 146, 4096 x 4095 at 8 116 / 127, 8192 x 65, fp32 rows, x 9 at 64 81 / 128; the other way round 1000-333-21
+// at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 931-128-50, four heads, at 36 27.6 / 17.7.
+// One-byte gains never gain; codebooks of less than kFusedSmallCodebook stay in the vector caches, where the wave-by-wave kernel's gathers
+// cost least (1.14 - 1.25).  fp32 rows on outputs that leave an eighth of the tiles of 64 empty: that kernel fetches for the
+// lanes past the last output as well (65 to 112 outputs 0.53 - 0.95).
+constexpr long long kFusedSmallCodebook = 16 * 1024;
+int half_tiles_min_steps(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes) {
+  const bool bytes = code == kCbI8 || code == kCbBfp8, sixteens = n_out % 16 == 0, one = n_heads == 1;
+  const int blocks = (int)((B + 15) / 16);
+  if (gb_kind == kGbQ8 || cb_bytes < kFusedSmallCodebook) return 0;
+  if (code == kCbF32) {
+    if (n_out * 8 <= (n_out + 63) / 64 * 64 * 7) return 6;
+    if (blocks == 4) return one || gb_kind == kGbF32 || !sixteens ? 6 : 13;
+    if (blocks == 3 || gb_kind == kGbF32 || idx_u32) return 0;
+    if (blocks == 2) return one ? (sixteens ? 5 : 10) : (sixteens ? 13 : 0);
+    return one && sixteens ? 6 : 0;
+  }
+  if (gb_kind == kGbF32) {
+    if (!bytes) return 0;
+    if (!idx_u32) return blocks == 4 ? 13 : 0;
+    return blocks == 4 ? (sixteens ? 9 : 4) : (blocks == 3 ? 13 : 0);
+  }
+  if (!bytes) return idx_u32 || !sixteens || (!one && blocks < 4) ? 0 : 13;
+  if (blocks == 4) return one ? (sixteens ? 9 : 5) : (sixteens ? 10 : 0);
+  if (idx_u32) return blocks == 3 ? (sixteens ? 16 : 4) : (sixteens ? 5 : 12);
+  return sixteens && blocks > 1 ? 12 : 0;
+}
+// tiles: the plan of the fused kernel.
 bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, const LayerPlan& tiles, long long edges) {
-  const long long wgs = (long long)n_heads * tiles.n_jt * tiles.n_bt * tiles.n_chunks, slots = (wgs + kCUs - 1) / kCUs * kCUs;
-  const bool full = wgs * 10 >= slots * 9, columns = tiles_full(n_out);
-  const bool bytes = code == kCbI8 || code == kCbBfp8, large = n_heads == 1 ? edges >= 1 << 20 : edges * n_heads > kFusedTilesMinEdges;
-  if (idx_u32 && gb_kind == kGbF16 && bytes && n_out % 16 == 0 && edges * n_heads >= 1 << 22) return full && columns;
-  if (B <= 48 || !large || !columns) return false;
-  if (code == kCbF32 && n_heads > 1 && n_heads * cb_bytes > 8 * kL2Bytes && edges >= kFusedOneHeadMinEdges) return false;
-  return code == kCbF32 ? wgs * 4 >= slots * 3 : bytes && gb_kind == kGbF16 && full;
+  const int least = half_tiles_min_steps(n_out, B, n_heads, idx_u32, gb_kind, code, cb_bytes);
+  if (least == 0 || tiles.rows_per_chunk < 8 * least || !tiles_full(n_out)) return false;
+  // (heads whose fp32 rows do not fit the L2s of all XCDs together are taken one at a time by the wave-by-wave kernel: 14 / 20 / 40 of
+  // 2048-256-21 at batch 64 120 / 110, 170 / 145, 369 / 266; not where most of a tile's outputs are missing)
+  return !(code == kCbF32 && n_heads > 1 && n_heads * cb_bytes > 8 * kL2Bytes && edges >= kFusedOneHeadMinEdges && n_out * 8 > (n_out + 63) / 64 * 64 * 7);
 }
 
 // Bucket path (prepared layers): one workgroup per (bucket, slice of the outputs, sample).
@@ -779,7 +810,7 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   // large batches: the fp16 machinery with both operands split into high and low parts
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide, reduced);
   const long long edges = (long long)L.in * L.out;
-  const long long tiles_max = B > 16 && tiles_full(L.out) ? kFusedTilesFullMaxEdges : kFusedTilesMaxEdges;
+  const long long tiles_max = B > 16 && tiles_even(L.out) ? kFusedTilesFullMaxEdges : kFusedTilesMaxEdges;
   const bool tiles = edges * n_heads > kFusedTilesMinEdges && (edges * n_heads <= tiles_max || min_rows != kMfmaMinRows);
   if (B > 32 || (B >= 2 && tiles)) {
     LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);

@@ -325,6 +325,30 @@ def test_the_reported_kernel_is_that_of_the_planned_call():
         assert L.kan_vq_planned_kernel(C.byref(d), B, 1, kb.KAN_PATH_GATHER) == precise, (n_in, n_out, B)
 
 
+def _name(n_in, n_out, B, heads, cb, gb, K, path):
+    L = kb.lib()
+    d = _desc(n_in=n_in, n_out=n_out, K=K, cb_dtype=cb, gb_dtype=gb, idx_dtype=kb.KAN_U32 if K > 65536 else kb.KAN_U16, scale=0.01,
+              gain_log2_lo=-8.0, gain_log2_step=0.05, bias_scale=1e-3)
+    return L.kan_vq_planned_kernel(C.byref(d), B, heads, path)
+
+
+def test_fp16_launches_with_many_steps_take_the_tiles():
+    """Up to 64 samples on the fp16 path: large launches whose tiles of 128 outputs are measurably ahead, by storage type,
+    alignment of the rows and samples; everything else the wave-by-wave kernel."""
+    F32, F16, I8, Q8, BFP = kb.KAN_F32, kb.KAN_F16, kb.KAN_I8, kb.KAN_Q8, kb.KAN_BFP8
+    for n_in, n_out, B, heads, cb, gb, K in (
+            (8192, 1760, 17, 1, I8, F16, 65536), (8192, 1760, 48, 1, I8, F16, 65536), (4712, 3200, 64, 1, F16, F16, 65536),
+            (5432, 1984, 64, 1, BFP, F16, 65536), (4096, 4096, 64, 1, I8, F32, 262144), (4096, 4095, 8, 1, I8, F16, 262144),
+            (8192, 65, 64, 9, F32, F16, 65536), (8192, 96, 24, 14, F32, F16, 8663), (8192, 201, 64, 9, BFP, F32, 41862),
+            (3717, 224, 64, 20, BFP, F32, 3368), (2048, 256, 64, 50, I8, F16, 65536), (4096, 1024, 8, 1, I8, F16, 262144)):
+        assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_MFMA) == b"kan_fused_f16", (n_in, n_out, B, heads, cb, gb, K)
+    for n_in, n_out, B, heads, cb, gb, K in (
+            (2048, 1024, 16, 1, I8, F16, 65536), (1000, 333, 37, 1, F16, F32, 5000), (8192, 1760, 64, 1, I8, Q8, 65536),
+            (4096, 4096, 64, 1, I8, F16, 1000), (3000, 2200, 48, 1, I8, F16, 65536), (2048, 256, 16, 50, I8, F16, 65536),
+            (2048, 256, 64, 40, F32, F16, 65536)):
+        assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_MFMA) == b"kan_fused_wave_f16", (n_in, n_out, B, heads, cb, gb, K)
+
+
 @pytest.mark.parametrize("widths,B", [((65536, 64), 128), ((16384, 256), 96), ((4096, 4096), 128), ((4096, 1024), 100)])
 def test_calls_that_fit_the_static_scratch_without_basis_words_still_fit(widths, B):
     """Batch 65 to 128 on large layers: the fused kernel's plan needs partial sums only, the kernel that dequantises its own

@@ -40,23 +40,45 @@ def test_mfma_ragged_shapes(kb, n_in, n_out, B):
     assert rep["headline"] >= 0 and np.isfinite(y).all()
 
 
-@pytest.mark.parametrize("gb,cb,idx", [("f16", "i8", "u16"), ("f32", "i8", "u16"), ("q8", "i8", "u16"), ("f16", "i8", "u32"),
-                                       ("f32", "i8", "u32"), ("f16", "f16", "u16"), ("f32", "bfp8", "u16"), ("f16", "bfp8", "u32"),
-                                       ("f32", "f32", "u16")])
-@pytest.mark.parametrize("n_in,n_out,B", [(520, 272, 50), (1001, 48, 64), (24, 16, 33), (300, 400, 40), (2048, 1024, 64)])
-def test_fused_64_sample_tiles_with_staged_metadata(kb, gb, cb, idx, n_in, n_out, B):
-    """Batch 33..64 on the fp16 path: the fused kernel's deep pipeline.  With n_out a multiple of 16 (and
-    aligned arrays) the per-edge metadata of two steps comes in through 16-byte loads and a strip of LDS:
-    output tiles cut short by n_out, chunks whose last pair of steps is ragged or missing, every storage
-    type of index, gain/bias and codebook (fp32 rows take the unstaged pipeline)."""
-    if n_in * n_out > 500000 and (gb, cb, idx) != ("f16", "i8", "u16"):
-        pytest.skip("the large shape runs once")
+def _off_by_one_element(kb, P):
+    """The layer with its per-edge arrays one element past a 16-byte boundary: the narrow metadata loads."""
+    L = kb.VQLayer(P)
+    for name in ("idx", "gain", "bias"):
+        t = getattr(L, name)
+        pad = 16 // t.element_size()
+        buf = torch.empty(t.numel() + 2 * pad, dtype=t.dtype, device="cuda")
+        off = pad + 1
+        buf[off:off + t.numel()] = t.reshape(-1)
+        setattr(L, name + "_shifted", buf)
+        setattr(L.desc, name, buf.data_ptr() + off * t.element_size())
+    return L
+
+
+# Launches whose workgroups have many steps: one layer, or 64 heads that share their parameters (equal outputs)
+@pytest.mark.parametrize("gb,cb,idx,n_in,n_out,heads,B", [
+    (gb, cb, idx, n_in, n_out, 64, B)
+    for gb, cb, idx in (("f16", "i8", "u16"), ("f32", "i8", "u16"), ("f16", "i8", "u32"), ("f32", "i8", "u32"), ("f16", "f16", "u16"),
+                        ("f32", "bfp8", "u16"), ("f16", "bfp8", "u32"), ("f32", "f32", "u16"), ("f16", "f32", "u16"))
+    for n_in, n_out, B in ((120, 496, 50), (235, 240, 64), (136, 496, 40), (243, 496, 24))
+    # (33 to 48 samples: one-byte rows with two-byte gains; 17 to 32: these with 16-bit ids)
+    if B > 48 or (gb, cb) in (("f16", "i8"), ("f16", "bfp8"))
+] + [(gb, "f32", idx, n_in, n_out, 64, B)          # outputs that leave half of the tiles empty
+     for gb, idx in (("f16", "u16"), ("f32", "u32")) for n_in, n_out in ((420, 72), (437, 65)) for B in (5, 24, 40, 64)
+] + [("f32", "i8", "u32", 131, 499, 64, 64), ("f32", "f32", "u16", 131, 501, 64, 55), ("f16", "i8", "u16", 2005, 970, 1, 64),
+     ("f16", "i8", "u32", 2100, 1040, 1, 8), ("f16", "i8", "u32", 2100, 1040, 1, 20), ("f16", "f32", "u16", 2100, 1040, 1, 20)])
+def test_fp16_tiles_of_128_outputs(kb, gb, cb, idx, n_in, n_out, heads, B):
+    """The fused kernel on fp16 operands, tiles of 32 and 64 samples: output tiles cut short by n_out, last steps and pairs of
+    steps that are ragged or missing, storage types of index, gain/bias and codebook.  Beyond 32 samples with n_out a multiple of 16
+    (and aligned arrays) the per-edge metadata of two steps comes in through 16-byte loads and a strip of LDS (fp32 rows
+    take the unstaged pipeline)."""
     K = 70000 if idx == "u32" else 3000
     P = synth.make_layer(n_in + 3 * n_out + B, n_in, n_out, K, cb_dtype=cb, gb_dtype=gb, idx_dtype=idx)
     x = synth.make_x(B + 7, B, n_in)
     (L,) = gpu_layers([P])
-    assert kb.kan_vq_planned_kernel(L, B, 1, kb.KAN_PATH_MFMA) == "kan_fused_f16"
-    y = kb.kan_vq_layer_forward(L, to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
+    assert kb.kan_vq_planned_kernel(L, B, heads, kb.KAN_PATH_MFMA) == "kan_fused_f16"
+    ys = kb.kan_vq_head_forward([[L]] * heads, to_dev(x), path=kb.KAN_PATH_MFMA)
+    assert torch.equal(ys, ys[:1].expand_as(ys))
+    y = ys[0].cpu().numpy()
     if n_in * n_out * B <= 2e8:
         y_ref, A = ko.vq_layer_forward(x, **P.as_dict(), return_abs=True)
         rep = ko.error_report(y, y_ref, A)
@@ -64,19 +86,31 @@ def test_fused_64_sample_tiles_with_staged_metadata(kb, gb, cb, idx, n_in, n_out
     else:
         assert np.isfinite(y).all()
         check_layer_output(y, x, P, TOL_MFMA, n_samples=96, full=False, seed=B)
-    # the same layer with arrays 2 bytes off a 16-byte boundary takes the unstaged pipeline: same sums
-    # up to the order of nothing - both add the same products in the same order
-    L2 = kb.VQLayer(P)
-    for name in ("idx", "gain", "bias"):
-        t = getattr(L2, name)
-        pad = 16 // t.element_size()
-        buf = torch.empty(t.numel() + 2 * pad, dtype=t.dtype, device="cuda")
-        off = pad + 1                                     # one element past a 16-byte boundary
-        buf[off:off + t.numel()] = t.reshape(-1)
-        setattr(L2, name + "_shifted", buf)
-        setattr(L2.desc, name, buf.data_ptr() + off * t.element_size())
-    y2 = kb.kan_vq_layer_forward(L2, to_dev(x), path=kb.KAN_PATH_MFMA).cpu().numpy()
+    # misaligned arrays take the unstaged pipeline: both add the same products in the same order
+    y2 = kb.kan_vq_head_forward([[_off_by_one_element(kb, P)]] * heads, to_dev(x), path=kb.KAN_PATH_MFMA)[0].cpu().numpy()
     assert np.array_equal(y2, y)
+
+
+@pytest.mark.parametrize("gb,cb,idx", [("q8", "i8", "u16"), ("q8", "i8", "u32"), ("f32", "f16", "u16"), ("f16", "f32", "u32")])
+@pytest.mark.parametrize("n_in,hidden,n_out,B", [(60, 1021, 16, 62), (22, 912, 64, 57), (124, 848, 64, 62)])
+def test_fp16_tiles_in_calls_that_fit_the_static_scratch_only_so(kb, gb, cb, idx, n_in, hidden, n_out, B):
+    """Storage types that take the wave-by-wave kernel at these sizes: 64 heads whose second layer's partial sums would not fit
+    beside the activations leave both layers to the tiles, in fewer chunks."""
+    heads = 64
+    K = 70000 if idx == "u32" else 3000
+    Ps = [synth.make_layer(n_in + B + l, a, b, K, cb_dtype=cb, gb_dtype=gb, idx_dtype=idx) for l, (a, b) in enumerate(((n_in, hidden), (hidden, n_out)))]
+    Ls = gpu_layers(Ps)
+    x = synth.make_x(B + 7, B, n_in)
+    xd = to_dev(x)
+    kb.kan_prof_begin(16)
+    y = kb.kan_vq_head_forward_static([Ls] * heads, xd, path=kb.KAN_PATH_MFMA)
+    rec = set(kb.kan_prof_end())
+    assert "kan_fused_f16@L1" in rec and "kan_fused_f16@L2" in rec, rec
+    assert torch.equal(y, y[:1].expand_as(y))
+    rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
+    assert rep["headline"] <= TOL_MFMA, rep
+    y2 = kb.kan_vq_head_forward_static([[_off_by_one_element(kb, Ps[0]), Ls[1]]] * heads, xd, path=kb.KAN_PATH_MFMA)
+    assert torch.equal(y2, y)
 
 
 @pytest.mark.parametrize("gb,cb,idx", [("f32", "i8", "u16"), ("f16", "f32", "u16"), ("f32", "f32", "u32"), ("f16", "i8", "u32")])
