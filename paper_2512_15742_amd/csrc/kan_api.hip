@@ -115,6 +115,8 @@ struct LayerPlan {
   int tile_n = 0;              // matrix-core path: outputs per workgroup tile (128: four waves, 256: eight)
   int kind;          // PlanKind
   bool half = false; // kPlanFusedWave with fp16 operands
+  bool tiles_ahead = false;    // kPlanFused16, kPlanFused32 in the place of the wave-by-wave kernel, because it is the faster one, but by little enough to give way
+  bool one_head = false;       // kPlanFusedWave whose chunks depend on the workgroups that heads taken one at a time get
   bool wide = false; // kPlanMfma whose workgroups dequantise their own coefficients (kan_wide.hip): cfg.bt samples x tile_n outputs
   bool stream = false;   // kPlanMfma on tiles of 256 x 256 with both operands copied to LDS (kan_stream.hip)
   bool rot() const { return wide || stream; }      // basis words in the rotated form
@@ -619,11 +621,11 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   // Several heads, fp16 form: an XCD works on two or three at a time, as in plan_fused (2048-65-21 at batch 64, forty heads
   // 95.8 -> 82.1 us, fifty 114.5 -> 109.8; 2048-128-21 at 24, fifty 97.4 -> 89.6; fifty of 1024-128-21 at 64 lose, 71 -> 75).
   // The precise form gains at batch 8 and loses at 24 (fifty of 2048-65-21 93.9 -> 89.7, 120 -> 123).
-  const bool one_head = code == kCbF32 || (cb_bytes > kFusedLargeCodebook && n_heads * cb_bytes > 4 * kL2Bytes);
-  const int head_wgs = one_head ? large_wgs : kFusedMinWgsPerHead;
-  const long long resident = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency
-                                 ? std::min<long long>(most, (head_wgs + p.n_jt - 1) / p.n_jt)
-                                 : 1;
+  p.one_head = code == kCbF32 || (cb_bytes > kFusedLargeCodebook && n_heads * cb_bytes > 4 * kL2Bytes);
+  const int head_wgs = p.one_head ? large_wgs : kFusedMinWgsPerHead;
+  const bool by_head = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency;
+  const long long resident = by_head ? std::min<long long>(most, (head_wgs + p.n_jt - 1) / p.n_jt) : 1;
+  p.one_head = p.one_head && by_head;
   double least = 0;
   for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
     const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, resident, most);
@@ -691,6 +693,16 @@ bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kin
   // (heads whose fp32 rows do not fit the L2s of all XCDs together are taken one at a time by the wave-by-wave kernel: 14 / 20 / 40 of
   // 2048-256-21 at batch 64 120 / 110, 170 / 145, 369 / 266; not where most of a tile's outputs are missing)
   return !(code == kCbF32 && n_heads > 1 && n_heads * cb_bytes > 8 * kL2Bytes && edges >= kFusedOneHeadMinEdges && n_out * 8 > (n_out + 63) / 64 * 64 * 7);
+}
+
+// ... and by so much that a call is not moved off the tiles to fit the static scratch: 49 samples and more, workgroups of half the
+// columns each that fill nine tenths of the CUs' rounds (of fp32 rows three quarters), 2^20 edges in one head or 6 * 2^20 in several (us,
+// tiles / wave by wave: fifty heads of 2048-256-21 191 / 204, of 2048-65-21 95 / 110, fp32 rows 2048 x 2048 52 / 58).
+bool fused_half_far_ahead(int n_out, int64_t B, int n_heads, int gb_kind, int code, const LayerPlan& tiles, long long edges) {
+  const long long wgs = (long long)n_heads * tiles.n_jt * tiles.n_bt * tiles.n_chunks, slots = (wgs + kCUs - 1) / kCUs * kCUs;
+  const bool even = (n_out + 63) / 64 == 2 * ((n_out + 127) / 128), large = n_heads == 1 ? edges >= 1 << 20 : edges * n_heads > 6 << 20;
+  if (B <= 48 || !even || !large) return false;
+  return code == kCbF32 ? wgs * 4 >= slots * 3 : gb_kind == kGbF16 && code != kCbF16 && wgs * 10 >= slots * 9;
 }
 
 // Bucket path (prepared layers): one workgroup per (bucket, slice of the outputs, sample).
@@ -777,7 +789,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //     kFusedTwoTilesMaxBatch on either path where make_wide does not take them.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
                   bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true,
-                  int large_wgs = kFusedOneHeadWgs) {
+                  int large_wgs = kFusedOneHeadWgs, bool may_tiles = true) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
   const long long cb_bytes = (long long)L.K * cb_row_bytes(code);
@@ -795,11 +807,15 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // one batch tile: every edge is needed once, so nothing is staged in memory (the streaming
     // path would write 20 bytes per edge and read them back for no reuse)
     const bool compact = min_rows != kMfmaMinRows;
-    if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact &&
-        !fused_half_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced), (long long)L.in * L.out))
+    if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact) {
+      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced);
+      const bool ahead = fused_half_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, (long long)L.in * L.out);
+      p.tiles_ahead = !fused_half_far_ahead(L.out, B, n_heads, gbk, code, p, (long long)L.in * L.out);
+      if (ahead && (may_tiles || !p.tiles_ahead)) return p;
       return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced);
+    }
     if (B <= fused_max) {
-      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, min_rows != kMfmaMinRows, reduced);
+      LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, compact, reduced);
       if (wide) make_wide(p, L.in, L.out, B, n_heads, false, x_parts, reduced);
       return p;
     }
@@ -1204,7 +1220,7 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
 kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                          int min_rows, bool hand_on, bool wide, int large_wgs, std::vector<LayerPlan>* plans, WsLayout* ws) {
+                          int min_rows, bool hand_on, bool wide, int large_wgs, bool may_tiles, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -1233,7 +1249,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced, large_wgs);
+    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced, large_wgs, may_tiles);
   };
   const int last = n_layers - 1;
   for (int l = 0; l <= last; ++l) plans->push_back(plan_of(l, l == last));
@@ -1280,6 +1296,8 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 
 // Heads that an XCD takes one at a time get fewer workgroups each before anything else is given up (fifty of 2048-256-21 with
 // 65,536 fp32 rows, fp16 path, batch 40, 20 / 32 / 48 workgroups 368 / 333 / 311 us; with 64, which take 33 MB, planned compact 403).
+// Tiles of 128 outputs that are ahead of the wave-by-wave kernel are cut finer where an XCD takes few heads at a time: where a call
+// does not fit with them, they are the next to go.
 // Finer chunks write more partial sums, a layer that hands its sums on keeps a second buffer of them: a call that fits the
 // library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.  Basis words
 // take room that the fused kernel does without, rotated ones of whole tiles of 256 samples more than those of kan_mfma.hip: a
@@ -1289,33 +1307,39 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 // 4095 at 7700: kan_mfma in 28.6 MB, kan_stream would take 34).
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
-  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, kFusedOneHeadWgs, plans, ws);
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, kFusedOneHeadWgs, true, plans, ws);
   if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
-  const struct { int min_rows; bool hand_on; } forms[] = {
-      {kMfmaMinRows, true}, {kMfmaMinRowsCompact, true}, {kMfmaMinRows, false}, {kMfmaMinRowsCompact, false}};
   std::vector<LayerPlan> other;
   WsLayout other_ws;
-  if (n_heads > 1 && B <= kHalfFusedMaxBatch)
-    for (const int wgs : {kFusedOneHeadWgs * 3 / 4, kFusedOneHeadWgs / 2, kFusedMinWgsPerHead})
-      if (plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, wgs, &other, &other_ws) == KAN_OK &&
-          other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) {
-        plans->swap(other);
-        *ws = other_ws;
-        return st;
-      }
-  auto fits = [&](bool wide) {
-    for (const auto& o : forms)
-      if (plan_head_rows(layers, n_layers, n_heads, B, path, o.min_rows, o.hand_on, wide, kFusedMinWgsPerHead, &other, &other_ws) == KAN_OK &&
-          other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES)
-        return true;
-    return false;
+  auto fits = [&](int min_rows, bool hand_on, bool wide, int large_wgs, bool may_tiles) {
+    return plan_head_rows(layers, n_layers, n_heads, B, path, min_rows, hand_on, wide, large_wgs, may_tiles, &other, &other_ws) == KAN_OK &&
+           other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES;
   };
-  if (!fits(false)) return st;
-  const bool any_wide = std::any_of(plans->begin(), plans->end(), [](const LayerPlan& p) { return p.wide; });
-  if (any_wide && !fits(true)) (void)fits(false);
-  plans->swap(other);
-  *ws = other_ws;
-  return st;
+  auto take_other = [&] {
+    plans->swap(other);
+    *ws = other_ws;
+    return st;
+  };
+  auto any = [&](auto of) { return std::any_of(plans->begin(), plans->end(), of); };
+  const bool any_wide = any([](const LayerPlan& p) { return p.wide; }), any_tiles = any([](const LayerPlan& p) { return p.tiles_ahead; });
+  const int fewer[] = {kFusedOneHeadWgs * 3 / 4, kFusedOneHeadWgs / 2, kFusedMinWgsPerHead};
+  if (any([](const LayerPlan& p) { return p.one_head; }))
+    for (const int wgs : fewer)
+      if (fits(kMfmaMinRows, true, true, wgs, true)) return take_other();
+  if (any_tiles) {
+    if (fits(kMfmaMinRows, true, true, kFusedOneHeadWgs, false)) return take_other();
+    for (const int wgs : fewer)
+      if (fits(kMfmaMinRows, true, true, wgs, false)) return take_other();
+  }
+  auto forms = [&](bool wide) {      // (the first of them is the plan that does not fit, but without kan_wide.hip)
+    return (any_wide && !wide && fits(kMfmaMinRows, true, wide, kFusedMinWgsPerHead, true)) ||
+           fits(kMfmaMinRowsCompact, true, wide, kFusedMinWgsPerHead, true) || fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, true) ||
+           (any_tiles && fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, false)) ||
+           fits(kMfmaMinRowsCompact, false, wide, kFusedMinWgsPerHead, true);
+  };
+  if (!forms(false)) return st;
+  if (any_wide && !forms(true)) (void)forms(false);
+  return take_other();
 }
 
 }  // namespace

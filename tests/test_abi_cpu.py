@@ -357,3 +357,12 @@ def test_calls_that_fit_the_static_scratch_without_basis_words_still_fit(widths,
     for path in (kb.KAN_PATH_GATHER, kb.KAN_PATH_MFMA):
         need = _head_ws(L, widths, 1, B, path, gb_dtype=kb.KAN_F16, cb_dtype=kb.KAN_I8)
         assert 0 < need <= kb.KAN_STATIC_SCRATCH_BYTES, need
+
+
+@pytest.mark.parametrize("n_in,n_out,heads,B,cb,gb", [(592, 1760, 65, 51, "bfp8", "f32"), (272, 2400, 100, 57, "bfp8", "f32"),
+                                                      (1328, 1856, 60, 63, "i8", "f16")])
+def test_heads_on_tiles_still_fit_the_static_scratch(n_in, n_out, heads, B, cb, gb):
+    """Many wide heads on the fp16 path: the tiles that are ahead there are cut in two for the sake of L2, 45 to 70 MB of partial
+    sums; the wave-by-wave kernel needs none."""
+    need = _head_ws(kb.lib(), (n_in, n_out), heads, B, kb.KAN_PATH_MFMA, cb_dtype=getattr(kb, "KAN_" + cb.upper()), gb_dtype=getattr(kb, "KAN_" + gb.upper()))
+    assert need <= kb.KAN_STATIC_SCRATCH_BYTES, need
