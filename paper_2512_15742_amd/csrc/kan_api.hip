@@ -214,16 +214,9 @@ constexpr int64_t kHalfFusedMaxBatch = 64;   // fp16 path: fused kernel up to he
 constexpr int64_t kFusedTwoTilesMaxBatch = 128;            // ... and up to here (both paths) for layers of at least
 constexpr long long kFusedTwoTilesMinEdges = 1ll << 22;    // this many edges whose codeword rows are one gather each
 constexpr long long kFusedSmallLayerEdges = 1 << 19;   // fused kernels: layers up to here may write partial sums four times as large as their stream
-// Precise path, 2 to 32 samples: the wave-by-wave kernel, but for launches of this many edges, whose kernel - tiles of 128
-// outputs with the basis tile in LDS - kan_vq_planned_kernel has always named: 4096 x 4096 at batch 4 / 16 / 32 94 / 100 / 140
-// us against 109 / 113 / 145 with the tiles, 3000 x 3001 63 / 65 / 90 against 86 / 88 / 106, forty heads of 1748-162-21 89 / 100 /
-// 133 against 171 / 175 / 221, of 1748-256-21 115 / 122 / 167 against 143 / 146 / 184.  Between the two lines it is ahead as well where
-// the tiles are not full (forty of 1748-97-21 at 4 / 16 / 32 68 / 70 / 98 against 87 / 90 / 112; of 1748-96-21 65 / 69 / 95 against 69 / 70 / 93).
-// 17 to 32 samples on outputs that fill the tiles: up to 15 * 2^20, where the wave-by-wave kernel is ahead by the least (forty of
-// 1748-128-21 at 32 97 / 99, fifty of 200 x 1024 at 24 102 / 104, sixty of 400 x 512 100 / 108) and calls are known to be planned
-// with these slices in the static scratch.
-constexpr long long kFusedTilesMinEdges = 6ll << 20, kFusedTilesMaxEdges = 8ll << 20, kFusedTilesFullMaxEdges = 15ll << 20;
-constexpr bool tiles_even(int n_out) { return (n_out + 63) / 64 == 2 * ((n_out + 127) / 128); }
+// Precise path, 2 to 32 samples: calls that fit the static scratch only compact take the tiles of 128 outputs, with their smaller
+// partial sums, for launches of more than this many edges.
+constexpr long long kFusedTilesCompactMinEdges = 6ll << 20;
 constexpr int kFusedMinWgsPerHead = 20;      // fused kernels, several heads: workgroups per head (L2 residency of the codebooks)
 // ... of the wave-by-wave kernel's fp16 form from kFusedLargeCodebook on, three of which do not fit an L2 beside each other, where
 // the heads' together take half of all L2s: an XCD works on one head at a time.  20 / 40 / 64 workgroups per head, us: twenty of
@@ -634,7 +627,7 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
     const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B) +
                         (chunks > 1 ? reduction : 0.0);
     // (large launches, which are whole rounds of workgroups in any case: a cut for a tenth at least, as in plan_fused)
-    if (least > 0 && cost >= (reduced && p.n_chunks == 1 && (long long)n_in * n_out * n_heads > kFusedTilesMaxEdges ? 0.9 : 1.0) * least) continue;
+    if (least > 0 && cost >= (reduced && p.n_chunks == 1 && (long long)n_in * n_out * n_heads > (8ll << 20) ? 0.9 : 1.0) * least) continue;
     least = cost;
     p.rows_per_chunk = per * kFusedWaveStep;
     p.n_chunks = chunks;
@@ -644,6 +637,24 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
 
 // Whether tiles of 128 outputs compute about as many columns as tiles of 64.
 constexpr bool tiles_full(int n_out) { return (n_out + 127) / 128 * 128 * 100ll <= (n_out + 63) / 64 * 64 * 107ll; }
+
+constexpr long long kFusedSmallCodebook = 16 * 1024;      // stays in the vector caches, where the wave-by-wave kernel's gathers cost least
+
+// Precise path, 2 to 32 samples: the wave-by-wave kernel is ahead of the tiles of 128 outputs with the basis tile in LDS but for
+// one head with two-byte gains on whole tiles with 16-byte metadata loads (22,878 launches of 2^20 to 24 * 2^20 edges, one to fifty
+// heads; mean time of the tiles over that of the wave-by-wave kernel, parameters from memory / from the caches):
+//   one-byte rows, 32-bit ids, from 3 * 2^20 edges       0.96 / 0.95, at 17 to 32 samples 0.95 / 0.95
+//   one-byte rows, 16-bit ids, 17 to 32 samples, 6.5 * 2^20     0.97 / 1.02;  2 to 16 samples, 12 * 2^20 0.95 / 1.0
+//   fp16 rows, 16-bit ids, 2 to 16 samples, 6.5 * 2^20    0.91 / 1.08
+// Elsewhere: several heads 0.98 - 1.06 / 1.15, fp32 gains 1.16 / 1.25, one-byte gains 1.04 / 1.10, fp32 rows 1.03 / 1.05, outputs in other
+// than sixteens 1.13 - 1.4, half-empty tiles 1.3 - 2.  For instance, us, tiles / wave by wave: 4096 x 2048 at batch 4 / 16 / 32 54.5 / 59.7,
+// 56.1 / 61.7, 69.4 / 72.1 with 16-bit ids and parameters from memory, with fp32 gains 70.8 / 62.3, 72.7 / 64.0, 90.2 / 74.2; 3500 x 4096 at 16
+// 87.8 / 100.7; 3072 x 2200 65.9 / 56.3, 2600 x 2500 62.5 / 54.4; forty heads of 1748-97-21 77.3 / 60.3.
+bool precise_tiles_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, long long edges) {
+  if (n_heads > 1 || gb_kind != kGbF16 || n_out % 16 != 0 || !tiles_full(n_out) || cb_bytes < kFusedSmallCodebook) return false;
+  if (code == kCbF16) return !idx_u32 && B <= 16 && edges >= 13ll << 19;
+  return code != kCbF32 && edges >= (idx_u32 ? 3ll << 20 : (B > 16 ? 13ll << 19 : 12ll << 20));
+}
 
 // fp16 path up to 64 samples: the wave-by-wave kernel is ahead in short chains, the fused kernel on tiles of 128 outputs, whose
 // waves share a step's basis and ask for twice the run of a row at once, where its workgroups have many steps (of 8 inputs).
@@ -661,10 +672,8 @@ constexpr bool tiles_full(int n_out) { return (n_out + 127) / 128 * 128 * 100ll 
 // For instance, us, tiles / wave by wave: 8192 x 1760 at batch 17 66 / 87, 4712 x 3200, fp16 rows, at 64 105 / 145, 4096 x 4096, fp32 gains
 // and 32-bit ids, at 64 126 / 146, 4096 x 4095 at 8 116 / 127, 8192 x 65, fp32 rows, x 9 at 64 81 / 128; the other way round 1000-333-21
 // at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 931-128-50, four heads, at 36 27.6 / 17.7.
-// One-byte gains never gain; codebooks of less than kFusedSmallCodebook stay in the vector caches, where the wave-by-wave kernel's gathers
-// cost least (1.14 - 1.25).  fp32 rows on outputs that leave an eighth of the tiles of 64 empty: that kernel fetches for the
+// One-byte gains never gain, codebooks of less than kFusedSmallCodebook neither (1.14 - 1.25).  fp32 rows on outputs that leave an eighth of the tiles of 64 empty: that kernel fetches for the
 // lanes past the last output as well (65 to 112 outputs 0.53 - 0.95).
-constexpr long long kFusedSmallCodebook = 16 * 1024;
 int half_tiles_min_steps(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes) {
   const bool bytes = code == kCbI8 || code == kCbBfp8, sixteens = n_out % 16 == 0, one = n_heads == 1;
   const int blocks = (int)((B + 15) / 16);
@@ -776,7 +785,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //   precise path, prepared layers, B <= kBucketMaxBatch (3 for layers of 2^23 edges or more): the bucket kernel
 //     (codebook in LDS);
 //   precise path (KAN_PATH_GATHER, and AUTO below batch 32): B = 1 the window-gather kernel,
-//     B = 2 .. 32 the wave-by-wave kernel (the tiles of the fused kernel for launches around 2^23 edges), above the
+//     B = 2 .. 32 the wave-by-wave kernel (the tiles of the fused kernel where precise_tiles_ahead), above the
 //     fused kernel (the fp32 FMA kernel remains the dense baseline's), from kSplitMinBatch the preparation + streaming contraction of the
 //     fp16 path on operands split into high and low fp16 parts, the contraction making
 //     three passes (hi*lo, lo*hi, hi*hi: fp32-grade sums at matrix-core speed);
@@ -826,10 +835,11 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   // large batches: the fp16 machinery with both operands split into high and low parts
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide, reduced);
   const long long edges = (long long)L.in * L.out;
-  const long long tiles_max = B > 16 && tiles_even(L.out) ? kFusedTilesFullMaxEdges : kFusedTilesMaxEdges;
-  const bool tiles = edges * n_heads > kFusedTilesMinEdges && (edges * n_heads <= tiles_max || min_rows != kMfmaMinRows);
+  const bool tiles = min_rows != kMfmaMinRows ? edges * n_heads > kFusedTilesCompactMinEdges
+                                              : may_tiles && precise_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, edges);
   if (B > 32 || (B >= 2 && tiles)) {
     LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);
+    p.tiles_ahead = B <= 32 && min_rows == kMfmaMinRows;
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true, x_parts, reduced);
     return p;
   }

@@ -19,8 +19,7 @@
 //                step take about as long as its gathers.
 //     16-sample tiles (batch <= 16): fp32 operands, v_mfma_f32_16x16x4f32 on two blocks of 16
 //                columns per wave: half the matrix-pipe time, no empty rows (T16 below).
-//                (These two only for launches of kFusedTilesMinEdges to kFusedTilesMaxEdges, or kFusedTilesFullMaxEdges, edges:
-//                kan_fused_wave.hip serves the others.)
+//                (These two where the planner finds the tiles ahead or a call fits the static scratch only so; else kan_fused_wave.hip.)
 //     64-sample tiles: both operands split into high and low fp16 parts (v = hi + lo / 2048,
 //                22 significant bits), three fp16 products per k-step (hi*lo and lo*hi into one
 //                set of accumulators, hi*hi into another); every fp16 x fp16 product is exact in

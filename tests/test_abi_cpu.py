@@ -349,6 +349,21 @@ def test_fp16_launches_with_many_steps_take_the_tiles():
         assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_MFMA) == b"kan_fused_wave_f16", (n_in, n_out, B, heads, cb, gb, K)
 
 
+def test_precise_launches_take_the_tiles_where_these_are_ahead():
+    """2 to 32 samples on the precise path: the choice follows storage types, alignment and size, with no band of sizes kept on the
+    tiles."""
+    F32, F16, I8, Q8, BFP = kb.KAN_F32, kb.KAN_F16, kb.KAN_I8, kb.KAN_Q8, kb.KAN_BFP8
+    for n_in, n_out, B, heads, cb, gb, K in (
+            (4096, 2048, 4, 1, F16, F16, 65536), (7848, 1536, 16, 1, F16, F16, 65536), (4096, 1024, 32, 1, I8, F16, 262144),
+            (6878, 1888, 8, 1, BFP, F16, 262144), (4096, 2048, 24, 1, I8, F16, 65536), (3500, 4096, 16, 1, I8, F16, 65536)):
+        assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_GATHER) == b"kan_fused_f32", (n_in, n_out, B, heads, cb, gb, K)
+    for n_in, n_out, B, heads, cb, gb, K in (
+            (3072, 2200, 16, 1, I8, F16, 65536), (2600, 2500, 32, 1, I8, F16, 65536), (4096, 2048, 16, 1, I8, F32, 65536),
+            (4096, 2048, 4, 1, F32, F32, 65536), (1748, 97, 16, 40, I8, F16, 65536), (1000, 700, 4, 10, I8, F16, 65536),
+            (4096, 2048, 8, 1, I8, Q8, 65536), (2048, 1024, 16, 1, I8, F16, 65536), (3000, 64, 24, 36, I8, F16, 65536)):
+        assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_GATHER) == b"kan_fused_wave", (n_in, n_out, B, heads, cb, gb, K)
+
+
 @pytest.mark.parametrize("widths,B", [((65536, 64), 128), ((16384, 256), 96), ((4096, 4096), 128), ((4096, 1024), 100)])
 def test_calls_that_fit_the_static_scratch_without_basis_words_still_fit(widths, B):
     """Batch 65 to 128 on large layers: the fused kernel's plan needs partial sums only, the kernel that dequantises its own

@@ -230,17 +230,22 @@ def test_random_heads(kb, dims, cb, gb, idx, K, B, seed):
         assert np.array_equal(y, kb.kan_vq_head_forward([Ls], xd, path=path)[0].cpu().numpy())
 
 
-@pytest.mark.parametrize("B", [3, 16, 20])
-@pytest.mark.parametrize("cb,gb,out", [("i8", "f16", 128), ("f16", "f16", 123), ("f32", "f32", 128)])
-def test_large_precise_launches(kb, B, cb, gb, out):
-    """Launches of more than 6 * 2^20 edges take tiles of 128 outputs, on 16 samples and on 32: the second layer of
-    fifty heads adds the slices of the first itself.  (The heads share one set of parameters: equal outputs.)"""
-    Ps = _head(8600, (256, 1280, out), 3001, cb=cb, gb=gb)
-    heads = [gpu_layers(Ps)] * 50
-    x = synth.make_x(8601 + B, B, 256)
-    rec = _launches(kb, heads, to_dev(x), kb.KAN_PATH_GATHER)
-    assert "kan_reduce@L1" not in rec and "kan_fused_f32@L2" in rec, rec
-    y = kb.kan_vq_head_forward(heads, to_dev(x), path=kb.KAN_PATH_GATHER)
+@pytest.mark.parametrize("path,cb,gb,idx,dims,heads,B", [
+    ("gather", "i8", "f16", "u32", (200, 3200, 1024), 1, 3), ("gather", "i8", "f16", "u32", (200, 3332, 1008), 1, 16),
+    ("gather", "bfp8", "f16", "u32", (200, 3200, 1024), 1, 20),
+    ("mfma", "i8", "f16", "u32", (200, 3200, 1024), 1, 8), ("mfma", "bfp8", "f16", "u32", (200, 3332, 1008), 1, 24),
+    ("mfma", "f32", "f16", "u16", (298, 520, 98), 50, 3), ("mfma", "f32", "f16", "u16", (298, 520, 98), 50, 20),
+    ("mfma", "f32", "f32", "u32", (310, 468, 80), 45, 30), ("mfma", "f32", "f32", "u16", (22, 920, 333), 9, 7)])
+def test_tiles_of_128_outputs_add_the_slices_before_them(kb, path, cb, gb, idx, dims, heads, B):
+    """The fused kernel on tiles of 16 and 32 samples, both operand types: the second layer adds the slices of the first
+    itself.  (Heads share one set of parameters: equal outputs.)"""
+    pth, name, tol = (kb.KAN_PATH_GATHER, "kan_fused_f32", TOL_FP32) if path == "gather" else (kb.KAN_PATH_MFMA, "kan_fused_f16", TOL_MFMA)
+    Ps = _head(8600, dims, 70001 if idx == "u32" else 65536, cb=cb, gb=gb, idx=idx)
+    hs = [gpu_layers(Ps)] * heads
+    x = synth.make_x(8601 + B, B, dims[0])
+    rec = _launches(kb, hs, to_dev(x), pth)
+    assert "kan_reduce@L1" not in rec and name + "@L2" in rec, rec
+    y = kb.kan_vq_head_forward(hs, to_dev(x), path=pth)
     assert torch.equal(y, y[:1].expand_as(y))
     rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
-    assert rep["headline"] <= TOL_FP32, rep
+    assert rep["headline"] <= tol, rep

@@ -1,4 +1,4 @@
-"""Precise path, 2 to 32 samples, wave-by-wave kernel (kan_fused_wave.hip): loads of four edges at the ends of rows
+"""Precise path, 2 to 32 samples, and fp16 path, up to 64: wave-by-wave kernel (kan_fused_wave.hip): loads of four edges at the ends of rows
 and arrays, chunks of one to several groups of steps, both sample tiles, every storage width, against the oracle."""
 import numpy as np
 import pytest
@@ -50,14 +50,14 @@ def test_slices_into_the_next_layer(kb, dims, B):
 
 
 def test_call_that_fits_the_static_scratch_only_without_the_hand_over(kb):
-    """63 heads whose partial sums fit the library's 32 MiB once: a reduction between the layers, right results."""
-    B, dims = 23, (16, 216, 1116, 48)
-    Ps = [synth.make_layer(9300 + l, dims[l], dims[l + 1], 4099, cb_dtype="i8", gb_dtype="f16") for l in range(3)]
+    """64 heads whose partial sums fit the library's 32 MiB once: a reduction between the layers, right results."""
+    B, dims, heads = 19, (36, 2992, 120, 184, 116), 64
+    Ps = [synth.make_layer(9300 + l, dims[l], dims[l + 1], 4099, cb_dtype="i8", gb_dtype="f16") for l in range(len(dims) - 1)]
     head = [kb.VQLayer(p) for p in Ps]
     x = synth.make_x(9301, B, dims[0])
-    y = kb.kan_vq_head_forward_static([head] * 63, to_dev(x), path=kb.KAN_PATH_GATHER)
+    y = kb.kan_vq_head_forward_static([head] * heads, to_dev(x), path=kb.KAN_PATH_GATHER)
     kb.kan_prof_begin(16)
-    kb.kan_vq_head_forward_static([head] * 63, to_dev(x), path=kb.KAN_PATH_GATHER)
+    kb.kan_vq_head_forward_static([head] * heads, to_dev(x), path=kb.KAN_PATH_GATHER)
     assert "kan_reduce@L2" in kb.kan_prof_end()
     assert torch.equal(y, y[:1].expand_as(y))
     rep = ko.error_report(y[0].cpu().numpy(), ko.vq_head_forward(x, [p.as_dict() for p in Ps]))
