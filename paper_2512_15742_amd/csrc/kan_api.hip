@@ -635,79 +635,81 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   return p;
 }
 
-// Whether tiles of 128 outputs compute about as many columns as tiles of 64.
-constexpr bool tiles_full(int n_out) { return (n_out + 127) / 128 * 128 * 100ll <= (n_out + 63) / 64 * 64 * 107ll; }
+// Which of the two fused kernels a layer of up to 64 samples takes: the wave-by-wave kernel is ahead in short chains, the one on tiles of
+// 128 outputs, whose waves share a step's basis and ask for twice the run of a row at once, where its workgroups have many
+// steps - from how many on depends on storage types, 16-byte metadata loads (outputs in sixteens) and blocks of 16 samples -
+// and the fullest CU has about the same to do.  Lines drawn through 32,492 launches on the fp16 path and 22,878 on the precise one
+// (2^18 to 24 * 2^20 edges, one to fifty heads) by the sum of the logarithms of tiles / wave by wave from a line on.
+// What the fullest CU has to do, missing outputs included, in steps of 1024 edges (8 x 128 or 16 x 64).
+long long fullest_cu(const LayerPlan& p, int n_heads) {
+  const long long wgs = (long long)n_heads * p.n_jt * p.n_bt * p.n_chunks;
+  return (wgs + kCUs - 1) / kCUs * (p.rows_per_chunk / (p.kind == kPlanFusedWave ? kFusedWaveStep : 8));
+}
+// (1.02 / 1.06 / 1.1 / 1.2 / 1.3: sums of -131 / -142 / -144 / -141 / -138 on the fp16 path, -16.2 / -16.7 / -15.7 / -13.8 / -13.7 on the precise one)
+bool tiles_fill(const LayerPlan& tiles, const LayerPlan& wave, int n_heads) { return fullest_cu(tiles, n_heads) * 12 <= fullest_cu(wave, n_heads) * 13; }
+constexpr long long kFusedSmallCodebook = 16 * 1024;      // stays in the vector caches, where the wave-by-wave kernel's gathers cost least (tiles 1.1 - 1.4; at 49 to 64 samples no line: two-byte gains 0.87 - 0.95)
 
-constexpr long long kFusedSmallCodebook = 16 * 1024;      // stays in the vector caches, where the wave-by-wave kernel's gathers cost least
-
-// Precise path, 2 to 32 samples: the wave-by-wave kernel is ahead of the tiles of 128 outputs with the basis tile in LDS but for
-// one head with two-byte gains on whole tiles with 16-byte metadata loads (22,878 launches of 2^20 to 24 * 2^20 edges, one to fifty
-// heads; mean time of the tiles over that of the wave-by-wave kernel, parameters from memory / from the caches):
-//   one-byte rows, 32-bit ids, from 3 * 2^20 edges       0.96 / 0.95, at 17 to 32 samples 0.95 / 0.95
-//   one-byte rows, 16-bit ids, 17 to 32 samples, 6.5 * 2^20     0.97 / 1.02;  2 to 16 samples, 12 * 2^20 0.95 / 1.0
-//   fp16 rows, 16-bit ids, 2 to 16 samples, 6.5 * 2^20    0.91 / 1.08
+// Precise path, 2 to 32 samples.  Mean time of the tiles over that of the wave-by-wave kernel from the line on, parameters from
+// memory / from the caches, one head, two-byte gains, outputs in sixteens:
+//   one-byte rows, 32-bit ids    2-16 samples 0.96 / 0.96, 17-32 0.96 / 0.95
+//   one-byte rows, 16-bit ids    2-16 0.89 / -, 17-32 0.97 / 1.01;   fp16 rows 2-16 0.89 / 1.08;   fp32 rows 2-16 0.97 / 0.97
 // Elsewhere: several heads 0.98 - 1.06 / 1.15, fp32 gains 1.16 / 1.25, one-byte gains 1.04 / 1.10, fp32 rows 1.03 / 1.05, outputs in other
-// than sixteens 1.13 - 1.4, half-empty tiles 1.3 - 2.  For instance, us, tiles / wave by wave: 4096 x 2048 at batch 4 / 16 / 32 54.5 / 59.7,
-// 56.1 / 61.7, 69.4 / 72.1 with 16-bit ids and parameters from memory, with fp32 gains 70.8 / 62.3, 72.7 / 64.0, 90.2 / 74.2; 3500 x 4096 at 16
-// 87.8 / 100.7; 3072 x 2200 65.9 / 56.3, 2600 x 2500 62.5 / 54.4; forty heads of 1748-97-21 77.3 / 60.3.
-bool precise_tiles_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, long long edges) {
-  if (n_heads > 1 || gb_kind != kGbF16 || n_out % 16 != 0 || !tiles_full(n_out) || cb_bytes < kFusedSmallCodebook) return false;
-  if (code == kCbF16) return !idx_u32 && B <= 16 && edges >= 13ll << 19;
-  return code != kCbF32 && edges >= (idx_u32 ? 3ll << 20 : (B > 16 ? 13ll << 19 : 12ll << 20));
+// than sixteens 1.13 - 1.4, half-empty tiles 1.3 - 2.  For instance, us, tiles / wave by wave: 7848 x 1536, fp16 rows, at batch 16 84 / 100,
+// 4096 x 2048 with fp32 gains at 4 / 32 70.8 / 62.3, 90.2 / 74.2, 3072 x 2200 at 16 65.9 / 56.3, 2600 x 2500 62.5 / 54.4, forty heads of 1748-97-21
+// 77.3 / 60.3.
+bool precise_tiles_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, const LayerPlan& tiles, const LayerPlan& wave) {
+  if (n_heads > 1 || gb_kind != kGbF16 || n_out % 16 != 0 || cb_bytes < kFusedSmallCodebook || !tiles_fill(tiles, wave, n_heads)) return false;
+  const int steps = tiles.rows_per_chunk / 8;
+  if (code == kCbF16 || code == kCbF32) return !idx_u32 && B <= 16 && steps >= 12;
+  return steps >= (idx_u32 ? 5 : (B > 16 ? 10 : 31));
 }
 
-// fp16 path up to 64 samples: the wave-by-wave kernel is ahead in short chains, the fused kernel on tiles of 128 outputs, whose
-// waves share a step's basis and ask for twice the run of a row at once, where its workgroups have many steps (of 8 inputs).
-// From how many on, 0: at none; by storage types, 16-byte metadata loads (outputs in sixteens) and blocks of 16 samples.
-// Drawn through 32,492 launches of 2^18 to 24 * 2^20 edges, one to fifty heads, by the sum of the logarithms of tiles / wave by
-// wave from a line on.  Mean ratios there, parameters from memory / from the caches; the line before (49 samples and more, from
-// 2^20 edges, on whole tiles, and one 32-bit case) took 30 % of the launches of more than 3 * 2^20 edges with parameters in memory more
-// than 3 % longer than the tiles and 9 % of those from the caches, this one 17 and 4 % (and 1.5 and 5 % longer than wave by wave):
-//   one head, two-byte gains, one-byte rows   1-16 samples 0.91 / 0.93 (32-bit ids)       17-32 0.85 / 1.07, 0.89 / 0.90 (32-bit)
-//                                             33-48 0.85 / 1.04, 0.93 / 0.87              49-64 0.85 / 0.99, 0.91 / 0.89
-//   several heads, likewise                   17-32 0.88 / 1.07    33-48 0.85 / 1.01      49-64 0.80 / 0.95
-//   four-byte gains                           33-48 0.95 / 0.95 (32-bit)                  49-64 0.87 / 1.08, 0.85 / 0.87 (32-bit)
-//   fp16 rows, two-byte gains                 1-16 0.83 / 1.06 (one head), 17-32 0.84 / 1.05 (one), 33-48 0.83 / 1.05 (one), 49-64 0.80 / 0.98
-//   fp32 rows                                 1-16 0.94 / 0.95, 17-32 0.87 / 0.86 (two-byte gains, 16-bit ids)     49-64 0.87 / 0.83
-// For instance, us, tiles / wave by wave: 8192 x 1760 at batch 17 66 / 87, 4712 x 3200, fp16 rows, at 64 105 / 145, 4096 x 4096, fp32 gains
-// and 32-bit ids, at 64 126 / 146, 4096 x 4095 at 8 116 / 127, 8192 x 65, fp32 rows, x 9 at 64 81 / 128; the other way round 1000-333-21
-// at batch 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8, 931-128-50, four heads, at 36 27.6 / 17.7.
-// One-byte gains never gain, codebooks of less than kFusedSmallCodebook neither (1.14 - 1.25).  fp32 rows on outputs that leave an eighth of the tiles of 64 empty: that kernel fetches for the
-// lanes past the last output as well (65 to 112 outputs 0.53 - 0.95).
+// fp16 path up to 64 samples: least steps of the tiles, 0: never.  Mean ratios as above:
+//   one head, two-byte gains, one-byte rows   1-16 samples 0.91 / 0.92 (32-bit ids)      17-32 0.86 / 1.06, 0.90 / 0.89 (32-bit)
+//                                             33-48 0.86 / 1.04, 0.93 / 0.89 (32-bit)    49-64 0.86 / 0.99, 0.92 / 0.89 (32-bit)
+//   several heads, likewise                   17-32 0.88 / 1.06    33-48 0.85 / 1.01     49-64 0.80 / 0.95
+//   four-byte gains                           33-48 0.93 / 0.90 (32-bit)                 49-64 0.86 / 1.08, 0.85 / 0.87 (32-bit)
+//   fp16 rows, two-byte gains, one head       1-16 0.83 / 1.06     17-32 0.81 / 1.02     33-48 0.82 / 1.03     49-64 0.85 / 1.01, several 0.84 / 1.05
+//   fp32 rows                                 1-16 0.95 / 0.95, 17-32 0.88 / 0.86 (two-byte gains, 16-bit ids)   49-64 0.96 / 0.94, fp32 gains 0.88 / 0.87
+// One-byte gains never gain.  fp32 rows of several heads that do not fit the L2s of all XCDs together: the wave-by-wave kernel takes these
+// heads one at a time (tiles 1.09 - 1.32).  fp32 rows on 65 to 96 outputs: it fetches for the lanes past the last output as well
+// (tiles 0.53 - 0.95, these heads included).  The line before - 49 samples and more, from 2^20 edges, on whole tiles, and one case of 32-bit
+// ids - took 30 % of the launches of more than 3 * 2^20 edges with parameters from memory more than 3 % longer than the tiles and 9 % of
+// those from the caches, this one 16 and 3.5 % (1.2 and 5.4 % longer than wave by wave).  For instance, us, tiles / wave by wave: 8192 x 1760 at batch 17
+// 66 / 87, 4712 x 3200, fp16 rows, at 64 105 / 145, 4096 x 4096, fp32 gains, 32-bit ids, at 64 126 / 146, 4096 x 4095 at 8 116 / 127,
+// nine heads of 8192 x 65, fp32 rows, at 64 81 / 128; 1000-333-21 at 37 25.7 / 19.7, 2048-1024-256 at 16 / 48 28.7 / 25.6, 39.5 / 33.8,
+// 931-128-50, four heads, at 36 27.6 / 17.7.
 int half_tiles_min_steps(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes) {
   const bool bytes = code == kCbI8 || code == kCbBfp8, sixteens = n_out % 16 == 0, one = n_heads == 1;
   const int blocks = (int)((B + 15) / 16);
-  if (gb_kind == kGbQ8 || cb_bytes < kFusedSmallCodebook) return 0;
+  const bool ids32 = idx_u32 && one;       // (several heads as with 16-bit ids: ten of 2048-256 at batch 8 / 48 48 / 38, 61 / 53 us)
+  if (gb_kind == kGbQ8 || (cb_bytes < kFusedSmallCodebook && !(blocks == 4 && gb_kind == kGbF16))) return 0;
   if (code == kCbF32) {
-    if (n_out * 8 <= (n_out + 63) / 64 * 64 * 7) return 6;
-    if (blocks == 4) return one || gb_kind == kGbF32 || !sixteens ? 6 : 13;
+    if (n_out > 64 && n_out <= 96) return 6;
+    if (!one && n_heads * cb_bytes > 8 * kL2Bytes) return 0;
+    if (blocks == 4) return 5;
     if (blocks == 3 || gb_kind == kGbF32 || idx_u32) return 0;
-    if (blocks == 2) return one ? (sixteens ? 5 : 10) : (sixteens ? 13 : 0);
+    if (blocks == 2) return sixteens ? 5 : (one ? 9 : 0);
     return one && sixteens ? 6 : 0;
   }
   if (gb_kind == kGbF32) {
-    if (!bytes) return 0;
-    if (!idx_u32) return blocks == 4 ? 13 : 0;
-    return blocks == 4 ? (sixteens ? 9 : 4) : (blocks == 3 ? 13 : 0);
+    if (!bytes || (blocks < 4 && !ids32)) return 0;
+    if (blocks == 4) return ids32 ? (sixteens ? 9 : 4) : (sixteens || one ? 14 : 5);
+    return blocks == 3 ? 17 : 0;
   }
-  if (!bytes) return idx_u32 || !sixteens || (!one && blocks < 4) ? 0 : 13;
-  if (blocks == 4) return one ? (sixteens ? 9 : 5) : (sixteens ? 10 : 0);
-  if (idx_u32) return blocks == 3 ? (sixteens ? 16 : 4) : (sixteens ? 5 : 12);
+  if (!bytes) return idx_u32 || !sixteens ? 0 : (blocks == 4 ? 12 : (one ? 15 : 0));
+  if (blocks == 4) return sixteens ? 9 : (one ? (ids32 ? 4 : 9) : 22);
+  if (ids32) return blocks == 3 ? (sixteens ? 19 : 16) : (sixteens ? 5 : 12);
   return sixteens && blocks > 1 ? 12 : 0;
 }
-// tiles: the plan of the fused kernel.
-bool fused_half_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, const LayerPlan& tiles, long long edges) {
+bool half_tiles_ahead(int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, const LayerPlan& tiles, const LayerPlan& wave) {
   const int least = half_tiles_min_steps(n_out, B, n_heads, idx_u32, gb_kind, code, cb_bytes);
-  if (least == 0 || tiles.rows_per_chunk < 8 * least || !tiles_full(n_out)) return false;
-  // (heads whose fp32 rows do not fit the L2s of all XCDs together are taken one at a time by the wave-by-wave kernel: 14 / 20 / 40 of
-  // 2048-256-21 at batch 64 120 / 110, 170 / 145, 369 / 266; not where most of a tile's outputs are missing)
-  return !(code == kCbF32 && n_heads > 1 && n_heads * cb_bytes > 8 * kL2Bytes && edges >= kFusedOneHeadMinEdges && n_out * 8 > (n_out + 63) / 64 * 64 * 7);
+  return least > 0 && tiles.rows_per_chunk >= 8 * least && tiles_fill(tiles, wave, n_heads);
 }
-
 // ... and by so much that a call is not moved off the tiles to fit the static scratch: 49 samples and more, workgroups of half the
 // columns each that fill nine tenths of the CUs' rounds (of fp32 rows three quarters), 2^20 edges in one head or 6 * 2^20 in several (us,
 // tiles / wave by wave: fifty heads of 2048-256-21 191 / 204, of 2048-65-21 95 / 110, fp32 rows 2048 x 2048 52 / 58).
-bool fused_half_far_ahead(int n_out, int64_t B, int n_heads, int gb_kind, int code, const LayerPlan& tiles, long long edges) {
+bool half_tiles_far_ahead(int n_out, int64_t B, int n_heads, int gb_kind, int code, const LayerPlan& tiles, long long edges) {
   const long long wgs = (long long)n_heads * tiles.n_jt * tiles.n_bt * tiles.n_chunks, slots = (wgs + kCUs - 1) / kCUs * kCUs;
   const bool even = (n_out + 63) / 64 == 2 * ((n_out + 127) / 128), large = n_heads == 1 ? edges >= 1 << 20 : edges * n_heads > 6 << 20;
   if (B <= 48 || !even || !large) return false;
@@ -790,7 +792,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //     fp16 path on operands split into high and low fp16 parts, the contraction making
 //     three passes (hi*lo, lo*hi, hi*hi: fp32-grade sums at matrix-core speed);
 //   fp16 path (KAN_PATH_MFMA, and AUTO from batch 32): up to kHalfFusedMaxBatch the wave-by-wave kernel with
-//     fp16 operands, or the fused kernel where its tiles are full (fused_half_ahead), above that coefficient/basis preparation + the streaming
+//     fp16 operands, or the fused kernel on tiles (half_tiles_ahead), above that coefficient/basis preparation + the streaming
 //     contraction (small layers, on either path: coefficient preparation + one launch, plan_matrix);
 //   from batch 65, layers of a million edges and more: the contraction that gathers and dequantises its own
 //     coefficients (make_wide), large products the one on tiles of 256 x 256 (make_stream), either path;
@@ -817,11 +819,10 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // path would write 20 bytes per edge and read them back for no reuse)
     const bool compact = min_rows != kMfmaMinRows;
     if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact) {
+      const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced);
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced);
-      const bool ahead = fused_half_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, (long long)L.in * L.out);
-      p.tiles_ahead = !fused_half_far_ahead(L.out, B, n_heads, gbk, code, p, (long long)L.in * L.out);
-      if (ahead && (may_tiles || !p.tiles_ahead)) return p;
-      return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced);
+      p.tiles_ahead = !half_tiles_far_ahead(L.out, B, n_heads, gbk, code, p, (long long)L.in * L.out);
+      return half_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave) && (may_tiles || !p.tiles_ahead) ? p : wave;
     }
     if (B <= fused_max) {
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, compact, reduced);
@@ -835,17 +836,21 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   // large batches: the fp16 machinery with both operands split into high and low parts
   if (B >= kSplitMinBatch && B > fused_max) return plan_matrix(L.in, L.out, B, n_heads, u32, gbk, code, true, x_parts, min_rows, wide, reduced);
   const long long edges = (long long)L.in * L.out;
-  const bool tiles = min_rows != kMfmaMinRows ? edges * n_heads > kFusedTilesCompactMinEdges
-                                              : may_tiles && precise_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, edges);
-  if (B > 32 || (B >= 2 && tiles)) {
-    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, min_rows != kMfmaMinRows, reduced);
-    p.tiles_ahead = B <= 32 && min_rows == kMfmaMinRows;
+  const bool compact = min_rows != kMfmaMinRows;
+  if (B >= 2 && B <= 32 && edges >= 4) {
+    const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, false, compact, reduced);
+    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, compact, reduced);
+    p.tiles_ahead = !compact;
+    const bool tiles = compact ? edges * n_heads > kFusedTilesCompactMinEdges
+                               : may_tiles && precise_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave);
+    return tiles ? p : wave;
+  }
+  if (B > 32) {
+    LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, compact, reduced);
     if (wide) make_wide(p, L.in, L.out, B, n_heads, true, x_parts, reduced);
     return p;
   }
-  if (B >= 2 && edges >= 4) return plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, false, min_rows != kMfmaMinRows, reduced);
-  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, cb_bytes,
-                     min_rows != kMfmaMinRows);
+  return plan_gather(L.in, L.out, B, n_heads, u32, gbk, code, vec_ok, cb_bytes, compact);
 }
 
 bool layer_vec_ok(const kan_vq_layer& L) {
@@ -1335,7 +1340,7 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
   const int fewer[] = {kFusedOneHeadWgs * 3 / 4, kFusedOneHeadWgs / 2, kFusedMinWgsPerHead};
   if (any([](const LayerPlan& p) { return p.one_head; }))
     for (const int wgs : fewer)
-      if (fits(kMfmaMinRows, true, true, wgs, true)) return take_other();
+      if (fits(kMfmaMinRows, true, true, wgs, any_tiles)) return take_other();      // (no tiles that were not there)
   if (any_tiles) {
     if (fits(kMfmaMinRows, true, true, kFusedOneHeadWgs, false)) return take_other();
     for (const int wgs : fewer)
@@ -1343,7 +1348,7 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
   }
   auto forms = [&](bool wide) {      // (the first of them is the plan that does not fit, but without kan_wide.hip)
     return (any_wide && !wide && fits(kMfmaMinRows, true, wide, kFusedMinWgsPerHead, true)) ||
-           fits(kMfmaMinRowsCompact, true, wide, kFusedMinWgsPerHead, true) || fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, true) ||
+           fits(kMfmaMinRowsCompact, true, wide, kFusedMinWgsPerHead, true) || fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, any_tiles) ||
            (any_tiles && fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, false)) ||
            fits(kMfmaMinRowsCompact, false, wide, kFusedMinWgsPerHead, true);
   };

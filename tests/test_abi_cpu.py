@@ -344,7 +344,7 @@ def test_fp16_launches_with_many_steps_take_the_tiles():
         assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_MFMA) == b"kan_fused_f16", (n_in, n_out, B, heads, cb, gb, K)
     for n_in, n_out, B, heads, cb, gb, K in (
             (2048, 1024, 16, 1, I8, F16, 65536), (1000, 333, 37, 1, F16, F32, 5000), (8192, 1760, 64, 1, I8, Q8, 65536),
-            (4096, 4096, 64, 1, I8, F16, 1000), (3000, 2200, 48, 1, I8, F16, 65536), (2048, 256, 16, 50, I8, F16, 65536),
+            (4096, 4096, 32, 1, I8, F16, 1000), (3000, 2200, 48, 1, I8, F16, 65536), (2048, 256, 16, 50, I8, F16, 65536),
             (2048, 256, 64, 40, F32, F16, 65536)):
         assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_MFMA) == b"kan_fused_wave_f16", (n_in, n_out, B, heads, cb, gb, K)
 
@@ -355,7 +355,7 @@ def test_precise_launches_take_the_tiles_where_these_are_ahead():
     F32, F16, I8, Q8, BFP = kb.KAN_F32, kb.KAN_F16, kb.KAN_I8, kb.KAN_Q8, kb.KAN_BFP8
     for n_in, n_out, B, heads, cb, gb, K in (
             (4096, 2048, 4, 1, F16, F16, 65536), (7848, 1536, 16, 1, F16, F16, 65536), (4096, 1024, 32, 1, I8, F16, 262144),
-            (6878, 1888, 8, 1, BFP, F16, 262144), (4096, 2048, 24, 1, I8, F16, 65536), (3500, 4096, 16, 1, I8, F16, 65536)):
+            (6878, 1888, 8, 1, BFP, F16, 262144), (4096, 2048, 24, 1, I8, F16, 65536), (8192, 2048, 16, 1, I8, F16, 65536)):
         assert _name(n_in, n_out, B, heads, cb, gb, K, kb.KAN_PATH_GATHER) == b"kan_fused_f32", (n_in, n_out, B, heads, cb, gb, K)
     for n_in, n_out, B, heads, cb, gb, K in (
             (3072, 2200, 16, 1, I8, F16, 65536), (2600, 2500, 32, 1, I8, F16, 65536), (4096, 2048, 16, 1, I8, F32, 65536),

@@ -234,8 +234,8 @@ def test_random_heads(kb, dims, cb, gb, idx, K, B, seed):
     ("gather", "i8", "f16", "u32", (200, 3200, 1024), 1, 3), ("gather", "i8", "f16", "u32", (200, 3332, 1008), 1, 16),
     ("gather", "bfp8", "f16", "u32", (200, 3200, 1024), 1, 20),
     ("mfma", "i8", "f16", "u32", (200, 3200, 1024), 1, 8), ("mfma", "bfp8", "f16", "u32", (200, 3332, 1008), 1, 24),
-    ("mfma", "f32", "f16", "u16", (298, 520, 98), 50, 3), ("mfma", "f32", "f16", "u16", (298, 520, 98), 50, 20),
-    ("mfma", "f32", "f32", "u32", (310, 468, 80), 45, 30), ("mfma", "f32", "f32", "u16", (22, 920, 333), 9, 7)])
+    ("mfma", "f32", "f16", "u16", (298, 520, 90), 50, 3), ("mfma", "f32", "f16", "u16", (298, 520, 90), 50, 20),
+    ("mfma", "f32", "f32", "u32", (310, 468, 80), 45, 30), ("mfma", "f32", "f32", "u16", (51, 1824, 73), 20, 4)])
 def test_tiles_of_128_outputs_add_the_slices_before_them(kb, path, cb, gb, idx, dims, heads, B):
     """The fused kernel on tiles of 16 and 32 samples, both operand types: the second layer adds the slices of the first
     itself.  (Heads share one set of parameters: equal outputs.)"""

@@ -60,12 +60,13 @@ def _off_by_one_element(kb, P):
     for gb, cb, idx in (("f16", "i8", "u16"), ("f32", "i8", "u16"), ("f16", "i8", "u32"), ("f32", "i8", "u32"), ("f16", "f16", "u16"),
                         ("f32", "bfp8", "u16"), ("f16", "bfp8", "u32"), ("f32", "f32", "u16"), ("f16", "f32", "u16"))
     for n_in, n_out, B in ((120, 496, 50), (235, 240, 64), (136, 496, 40), (243, 496, 24))
-    # (33 to 48 samples: one-byte rows with two-byte gains; 17 to 32: these with 16-bit ids)
-    if B > 48 or (gb, cb) in (("f16", "i8"), ("f16", "bfp8"))
+    # (17 to 48 samples: one-byte rows with two-byte gains and 16-bit ids)
+    if B > 48 or (gb, cb, idx) == ("f16", "i8", "u16")
 ] + [(gb, "f32", idx, n_in, n_out, 64, B)          # outputs that leave half of the tiles empty
      for gb, idx in (("f16", "u16"), ("f32", "u32")) for n_in, n_out in ((420, 72), (437, 65)) for B in (5, 24, 40, 64)
 ] + [("f32", "i8", "u32", 131, 499, 64, 64), ("f32", "f32", "u16", 131, 501, 64, 55), ("f16", "i8", "u16", 2005, 970, 1, 64),
-     ("f16", "i8", "u32", 2100, 1040, 1, 8), ("f16", "i8", "u32", 2100, 1040, 1, 20), ("f16", "f32", "u16", 2100, 1040, 1, 20)])
+     ("f16", "i8", "u32", 2501, 1008, 1, 8), ("f16", "bfp8", "u32", 2501, 1008, 1, 20), ("f16", "f32", "u16", 2501, 1008, 1, 20),
+     ("f16", "i8", "u32", 6801, 1100, 1, 40)])
 def test_fp16_tiles_of_128_outputs(kb, gb, cb, idx, n_in, n_out, heads, B):
     """The fused kernel on fp16 operands, tiles of 32 and 64 samples: output tiles cut short by n_out, last steps and pairs of
     steps that are ragged or missing, storage types of index, gain/bias and codebook.  Beyond 32 samples with n_out a multiple of 16
