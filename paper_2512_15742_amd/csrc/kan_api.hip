@@ -582,7 +582,8 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // Not more chunks than the next layer takes as they are, unless two steps each would be too many already; chunks of a
 // single step for up to kFusedWaveStepBytes of partial sums, beyond which a caller's workspace would grow with them.
 // (Eight waves to a workgroup for half the slices: 2048-1024-256 at batch 16 30.2 against 28.6 us.)
-// compact: the smaller partial sums of the former rule, for calls that fit the static scratch only so.
+// compact: the smaller partial sums of the former rule, for calls that fit the static scratch only so.  spare: one chunk where the
+// cut saves less than a tenth, likewise.
 // reduced: nobody but a launch of kan_reduce adds the slices (as in plan_fused).  The launch takes about 2.7 us, in units
 // of the cost above: 3.3 where a CU has one workgroup, of 16 samples at most, 2.0 with the longer steps of more samples, 1.3
 // where one chunk is several rounds of workgroups.  One chunk / cut, us: 32 x 128 at batch 4 / 16 / 31 4.7 / 5.4, 4.8 / 5.7,
@@ -590,8 +591,9 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // 6.9 / 7.8; 48 x 512, 20, at 16 6.8 / 9.6; 64 x 669, 21, at 8 8.0 / 9.9; 82 x 2736, 19, at 24 46.0 / 47.2; 72 x 385, 47, at 5
 // 14.9 / 13.9; 97 x 1650, 13, at 8 19.0 / 18.0.
 constexpr long long kFusedWaveStepBytes = 512 * 1024;
+constexpr long long kFusedWaveWholeEdges = 1ll << 20;
 LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, int large_wgs, bool half, bool compact,
-                          bool reduced) {
+                          bool reduced, bool spare) {
   LayerPlan p;
   p.mfma = false;
   p.kind = kPlanFusedWave;
@@ -619,6 +621,10 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   const bool by_head = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency;
   const long long resident = by_head ? std::min<long long>(most, (head_wgs + p.n_jt - 1) / p.n_jt) : 1;
   p.one_head = p.one_head && by_head;
+  // Small launches: a cut that a reduction launch undoes for a tenth at least, as in plan_fused.  Mean time of one chunk over that of
+  // the cut (several heads; one head has no such choice) at 2^18 / 2^18.5 / 2^19 / 2^19.5 / 2^20 / 2^20.5 / 2^21 / 2^22 / 2^23 edges, fp16 path 0.95 / 0.86 /
+  // 0.82 / 0.89 / 0.95 / 1.00 / 1.05 / 1.12 / 1.10, precise 1.03 / 0.96 / 0.92 / 0.96 / 0.99 / 1.01 / 1.10 / 1.12 / 1.08.
+  const bool whole_line = reduced && (spare || (long long)n_in * n_out * n_heads <= kFusedWaveWholeEdges);
   double least = 0;
   for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
     const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, resident, most);
@@ -626,8 +632,7 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
     const long long wgs = base * chunks;
     const double cost = per * std::max((double)((wgs + kCUs - 1) / kCUs), 1.75) + 1.28e-4 * (double)(wgs * B) +
                         (chunks > 1 ? reduction : 0.0);
-    // (large launches, which are whole rounds of workgroups in any case: a cut for a tenth at least, as in plan_fused)
-    if (least > 0 && cost >= (reduced && p.n_chunks == 1 && (long long)n_in * n_out * n_heads > (8ll << 20) ? 0.9 : 1.0) * least) continue;
+    if (least > 0 && cost >= (whole_line && p.n_chunks == 1 ? 0.9 : 1.0) * least) continue;
     least = cost;
     p.rows_per_chunk = per * kFusedWaveStep;
     p.n_chunks = chunks;
@@ -800,7 +805,7 @@ bool layer_prepared_ok(const kan_vq_layer& L) {
 //     kFusedTwoTilesMaxBatch on either path where make_wide does not take them.
 LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bool prepared_ok, int32_t path,
                   bool column_ok, int x_parts = 1, int min_rows = kMfmaMinRows, bool wide = true, bool reduced = true,
-                  int large_wgs = kFusedOneHeadWgs, bool may_tiles = true) {
+                  int large_wgs = kFusedOneHeadWgs, bool spare = false) {
   const int code = code_of(L);
   const int u32 = L.idx_dtype == KAN_U32, gbk = gb_kind_of(L);
   const long long cb_bytes = (long long)L.K * cb_row_bytes(code);
@@ -819,10 +824,10 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
     // path would write 20 bytes per edge and read them back for no reuse)
     const bool compact = min_rows != kMfmaMinRows;
     if (B <= kHalfFusedMaxBatch && (long long)L.in * L.out >= 4 && !compact) {
-      const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced);
+      const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, true, false, reduced, spare);
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, false, reduced);
       p.tiles_ahead = !half_tiles_far_ahead(L.out, B, n_heads, gbk, code, p, (long long)L.in * L.out);
-      return half_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave) && (may_tiles || !p.tiles_ahead) ? p : wave;
+      return half_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave) && !(spare && p.tiles_ahead) ? p : wave;
     }
     if (B <= fused_max) {
       LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, false, compact, reduced);
@@ -838,11 +843,11 @@ LayerPlan plan_vq(const kan_vq_layer& L, int64_t B, int n_heads, bool vec_ok, bo
   const long long edges = (long long)L.in * L.out;
   const bool compact = min_rows != kMfmaMinRows;
   if (B >= 2 && B <= 32 && edges >= 4) {
-    const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, false, compact, reduced);
+    const LayerPlan wave = plan_fused_wave(L.in, L.out, B, n_heads, u32, gbk, code, cb_bytes, large_wgs, false, compact, reduced, spare);
     LayerPlan p = plan_fused(L.in, L.out, B, n_heads, u32, gbk, code, true, compact, reduced);
     p.tiles_ahead = !compact;
     const bool tiles = compact ? edges * n_heads > kFusedTilesCompactMinEdges
-                               : may_tiles && precise_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave);
+                               : !spare && precise_tiles_ahead(L.out, B, n_heads, u32, gbk, code, cb_bytes, p, wave);
     return tiles ? p : wave;
   }
   if (B > 32) {
@@ -1235,7 +1240,7 @@ bool fused_takes_slices(const LayerPlan& from, const LayerPlan& to, int n_in, in
 
 // Validates a [n_heads][n_layers] descriptor table; fills per-layer plans and scratch sizes.
 kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
-                          int min_rows, bool hand_on, bool wide, int large_wgs, bool may_tiles, std::vector<LayerPlan>* plans, WsLayout* ws) {
+                          int min_rows, bool hand_on, bool wide, int large_wgs, bool spare, std::vector<LayerPlan>* plans, WsLayout* ws) {
   if (!layers) return KAN_ERR_NULL;
   if (n_layers < 1 || n_heads < 1 || n_layers > 64 || n_heads > (1 << 16)) return KAN_ERR_SHAPE;
   if (B < 0 || B > kMaxBatch) return KAN_ERR_SHAPE;
@@ -1264,7 +1269,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
       prepared_ok = prepared_ok && layer_prepared_ok(layers[(size_t)h * n_layers + l]);
       column_ok = column_ok && layer_column_ok(layers[(size_t)h * n_layers + l]);
     }
-    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced, large_wgs, may_tiles);
+    return plan_vq(R, B, group, vec_ok, prepared_ok, path, column_ok, l > 0 ? (*plans)[l - 1].n_chunks : 1, min_rows, wide, reduced, large_wgs, spare);
   };
   const int last = n_layers - 1;
   for (int l = 0; l <= last; ++l) plans->push_back(plan_of(l, l == last));
@@ -1312,7 +1317,7 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 // Heads that an XCD takes one at a time get fewer workgroups each before anything else is given up (fifty of 2048-256-21 with
 // 65,536 fp32 rows, fp16 path, batch 40, 20 / 32 / 48 workgroups 368 / 333 / 311 us; with 64, which take 33 MB, planned compact 403).
 // Tiles of 128 outputs that are ahead of the wave-by-wave kernel are cut finer where an XCD takes few heads at a time: where a call
-// does not fit with them, they are the next to go.
+// does not fit with them, they are the next to go, with cuts of the wave-by-wave kernel that save less than a tenth.
 // Finer chunks write more partial sums, a layer that hands its sums on keeps a second buffer of them: a call that fits the
 // library's static scratch only with larger chunks, or with a reduction between the layers, is planned so.  Basis words
 // take room that the fused kernel does without, rotated ones of whole tiles of 256 samples more than those of kan_mfma.hip: a
@@ -1322,12 +1327,12 @@ kan_status plan_head_rows(const kan_vq_layer* layers, int32_t n_layers, int32_t 
 // 4095 at 7700: kan_mfma in 28.6 MB, kan_stream would take 34).
 kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_heads, int64_t B, int32_t path,
                      std::vector<LayerPlan>* plans, WsLayout* ws) {
-  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, kFusedOneHeadWgs, true, plans, ws);
+  kan_status st = plan_head_rows(layers, n_layers, n_heads, B, path, kMfmaMinRows, true, true, kFusedOneHeadWgs, false, plans, ws);
   if (st != KAN_OK || ws->total() <= (size_t)KAN_STATIC_SCRATCH_BYTES) return st;
   std::vector<LayerPlan> other;
   WsLayout other_ws;
-  auto fits = [&](int min_rows, bool hand_on, bool wide, int large_wgs, bool may_tiles) {
-    return plan_head_rows(layers, n_layers, n_heads, B, path, min_rows, hand_on, wide, large_wgs, may_tiles, &other, &other_ws) == KAN_OK &&
+  auto fits = [&](int min_rows, bool hand_on, bool wide, int large_wgs, bool spare) {
+    return plan_head_rows(layers, n_layers, n_heads, B, path, min_rows, hand_on, wide, large_wgs, spare, &other, &other_ws) == KAN_OK &&
            other_ws.total() <= (size_t)KAN_STATIC_SCRATCH_BYTES;
   };
   auto take_other = [&] {
@@ -1337,20 +1342,23 @@ kan_status plan_head(const kan_vq_layer* layers, int32_t n_layers, int32_t n_hea
   };
   auto any = [&](auto of) { return std::any_of(plans->begin(), plans->end(), of); };
   const bool any_wide = any([](const LayerPlan& p) { return p.wide; }), any_tiles = any([](const LayerPlan& p) { return p.tiles_ahead; });
+  const bool any_spare = any_tiles || any([](const LayerPlan& p) { return p.kind == kPlanFusedWave && p.n_chunks > 1; });
   const int fewer[] = {kFusedOneHeadWgs * 3 / 4, kFusedOneHeadWgs / 2, kFusedMinWgsPerHead};
-  if (any([](const LayerPlan& p) { return p.one_head; }))
+  const bool one_head = any([](const LayerPlan& p) { return p.one_head; });
+  if (one_head)
     for (const int wgs : fewer)
-      if (fits(kMfmaMinRows, true, true, wgs, any_tiles)) return take_other();      // (no tiles that were not there)
-  if (any_tiles) {
-    if (fits(kMfmaMinRows, true, true, kFusedOneHeadWgs, false)) return take_other();
-    for (const int wgs : fewer)
-      if (fits(kMfmaMinRows, true, true, wgs, false)) return take_other();
+      if (fits(kMfmaMinRows, true, true, wgs, !any_tiles)) return take_other();      // (no tiles that were not there)
+  if (any_spare) {
+    if (fits(kMfmaMinRows, true, true, kFusedOneHeadWgs, true)) return take_other();
+    if (one_head || any_tiles)
+      for (const int wgs : fewer)
+        if (fits(kMfmaMinRows, true, true, wgs, true)) return take_other();
   }
   auto forms = [&](bool wide) {      // (the first of them is the plan that does not fit, but without kan_wide.hip)
-    return (any_wide && !wide && fits(kMfmaMinRows, true, wide, kFusedMinWgsPerHead, true)) ||
-           fits(kMfmaMinRowsCompact, true, wide, kFusedMinWgsPerHead, true) || fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, any_tiles) ||
-           (any_tiles && fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, false)) ||
-           fits(kMfmaMinRowsCompact, false, wide, kFusedMinWgsPerHead, true);
+    return (any_wide && !wide && fits(kMfmaMinRows, true, wide, kFusedMinWgsPerHead, false)) ||
+           fits(kMfmaMinRowsCompact, true, wide, kFusedMinWgsPerHead, false) || fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, !any_tiles) ||
+           (any_spare && fits(kMfmaMinRows, false, wide, kFusedMinWgsPerHead, true)) ||
+           fits(kMfmaMinRowsCompact, false, wide, kFusedMinWgsPerHead, false);
   };
   if (!forms(false)) return st;
   if (any_wide && !forms(true)) (void)forms(false);

@@ -381,3 +381,14 @@ def test_heads_on_tiles_still_fit_the_static_scratch(n_in, n_out, heads, B, cb, 
     sums; the wave-by-wave kernel needs none."""
     need = _head_ws(kb.lib(), (n_in, n_out), heads, B, kb.KAN_PATH_MFMA, cb_dtype=getattr(kb, "KAN_" + cb.upper()), gb_dtype=getattr(kb, "KAN_" + gb.upper()))
     assert need <= kb.KAN_STATIC_SCRATCH_BYTES, need
+
+
+def test_last_layers_are_cut_by_what_the_reduction_costs():
+    """Several heads, wave-by-wave kernel: launches of up to a million edges stay whole where a cut (1, 2 or 3 chunks) and its
+    reduction launch save less than a tenth, larger ones are cut wherever that saves anything."""
+    L = kb.lib()
+    for n_in, n_out, heads, B, path, cut in ((59, 1791, 8, 33, kb.KAN_PATH_MFMA, False), (72, 3100, 4, 26, kb.KAN_PATH_GATHER, False),
+                                             (73, 1152, 12, 21, kb.KAN_PATH_MFMA, False), (435, 1920, 13, 7, kb.KAN_PATH_GATHER, True),
+                                             (823, 544, 49, 11, kb.KAN_PATH_GATHER, True), (298, 4064, 10, 31, kb.KAN_PATH_MFMA, True)):
+        need = _head_ws(L, (n_in, n_out), heads, B, path, cb_dtype=kb.KAN_I8, gb_dtype=kb.KAN_F16)
+        assert (need > 0) == cut, (n_in, n_out, heads, B, need)
