@@ -33,7 +33,7 @@ typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 // The inputs of samples b0 .. b0 + 31 into xs: the tile's rows are one run of floats in memory, taken in items of four
 // (wherever rows end), U items per thread and round, P slices of each in flight, added in slice order.  Loads are
 // unconditional (clamped addresses; the last item of the run ends with it and repeats what the one before holds).  A
-// tile of eight slices is two trips to memory that way (single floats, half the slices at a time, where rows are no multiple
+// tile of eight slices is two trips to memory that way at most (single floats, half the slices at a time, where rows are no multiple
 // of four: six; 500-333-21 at batch 128 34.0 -> 29.1 us, 399 x 10 at any batch 19.0 -> 13.5).
 template <int U, int P>
 __device__ __forceinline__ void stage_inputs(const TailArgs& a, const float* x, int b0, float* xs) {
@@ -142,9 +142,18 @@ __global__ __launch_bounds__(kTailThreads) void kan_tail_kernel(const TailArgs a
   }
   {
     const float* x = a.x + (long long)head * a.x_head_stride;
+    // (as many items in flight as a thread has, up to 24 and 32 loads: with three items of eight slices whatever the width, two thirds of
+    // the loads of 64 inputs were repeats: 864-64-32 at batch 105 24.4 us, 1560-64-16 precise at 182 39.6, 1024-128-64 at 70 27.4, 600-256-16 at 70 31.4,
+    // now 21.1, 35.6, 25.8 and 29.7)
+    const int own = (8 * n_in + kTailThreads - 1) / kTailThreads;
     if (a.x_parts == 1) {
-      stage_inputs<8, 1>(a, x, b0, buf);
-    } else if (a.x_parts <= 4) {
+      if (own <= 2) stage_inputs<2, 1>(a, x, b0, buf);
+      else stage_inputs<8, 1>(a, x, b0, buf);
+    } else if (own == 1) {
+      stage_inputs<1, 8>(a, x, b0, buf);
+    } else if (own == 2 && a.x_parts > 4) {
+      stage_inputs<2, 8>(a, x, b0, buf);
+    } else if (own == 4 || a.x_parts <= 4) {
       stage_inputs<4, 4>(a, x, b0, buf);
     } else {
       stage_inputs<3, 8>(a, x, b0, buf);

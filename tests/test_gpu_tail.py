@@ -56,3 +56,18 @@ def test_slices_and_heads(kb, dims, B, heads):
         for h in range(heads):
             rep = ko.error_report(y[h], ko.vq_head_forward(x, [p.as_dict() for p in Ps[h]]))
             assert rep["headline"] <= tol * (len(dims) - 1), (path, h, rep)
+
+
+@pytest.mark.parametrize("hidden", [3, 61, 64, 65, 128, 129, 192, 193, 255, 256, 257, 333])
+@pytest.mark.parametrize("n_in,B", [(1024, 97), (160, 66), (32, 70)])
+def test_slices_of_every_width(kb, n_in, hidden, B):
+    """A thread's share of a tile's inputs from one item of four to several, in many slices, few and none: the loads in flight
+    differ."""
+    Ps = [synth.make_layer(9700 + l, a, b, 701, cb_dtype="i8", gb_dtype="f32") for l, (a, b) in enumerate(((n_in, hidden), (hidden, 20)))]
+    x = synth.make_x(9800 + hidden, B, n_in)
+    head = [kb.VQLayer(p) for p in Ps]
+    y_ref = ko.vq_head_forward(x, [p.as_dict() for p in Ps])
+    for path, tol in paths(kb):
+        y = kb.kan_vq_head_forward([head], to_dev(x), path=path)[0].cpu().numpy()
+        rep = ko.error_report(y, y_ref)
+        assert rep["headline"] <= 2 * tol, (path, rep)
