@@ -234,23 +234,23 @@ constexpr long long kFusedOneHeadMinEdges = 1 << 19;      // from here a head's 
 // its second tile of 64 samples (config 3: 97 us at 64, 113 at 80; config 2: 33 and 57).
 constexpr int64_t kSplitMinBatch = 65;
 // Dense baseline: fp32 operands up to 16 samples (one tile of the fp32 instruction), split operands above.  Three forms for
-// these: one pass over the coefficients per tile of 64 samples (kan_dense.hip), the contraction that converts its own
-// coefficients for 128 or 256 samples at a time (kan_wide.hip), converted records (kan_mfma.hip).  Beyond 64 samples
-// the one pass is ahead while a CU has two steps of it (32 inputs x 64 outputs x 64 samples): one pass / kan_wide / records
+// these, chosen by what they cost: one pass over the coefficients per tile of 32 or 64 samples (kan_dense.hip), beyond 64 samples the
+// contraction that converts its own coefficients for 128 or 256 samples at a time (kan_wide.hip), converted records (kan_mfma.hip).
+// One pass / kan_wide / records, us:
 //   1024 x 256 at 256 / 300   18.3 / 21.3 / 28.7,  23.2 / 20.7 / 27.5     300 x 64 at 128 / 300   11.3 / 16.2 / -,  11.5 / 19.3 / 24.9
 //   500 x 333 at 128 / 300    12.9 / 16.0 / -,     19.6 / 19.1 / 26.2     256 x 500 at 256        13.8 / 17.8 / 28.5
-//   2048 x 200 at 128 / 160   20.8 / 20.9 / -,     30.2 / 24.2 / 34.6     2048 x 512 at 80        29.4 / 23.2 / -
-// Beyond it kan_wide, for layers of up to a million edges as far as the work goes, for larger ones below batch 1024; kan_wide /
-// records: 2048 x 512 at 256 / 1024 / 2048 / 3000 30.0 / 49.4, 69.4 / 93.7, 122 / 128, 197 / 180; 1024 x 256 at 3000 / 4096
-// 63.3 / 82.5, 79.3 / 84.5; 2048 x 1024 at 256 / 768 / 1300 44.1 / 77.0, 94.1 / 141, 177 / 171; 4096 x 1024 at 128 / 768 / 1300
-// 56.5 / 107, 181 / 282, 344 / 330.  Layers whose tiles of 64 outputs would be half empty (make_wide) keep one pass up to batch 128,
-// small ones up to 256.
+//   2048 x 200 at 128 / 160   20.8 / 20.9 / -,     30.2 / 24.2 / 34.6     2784 x 88 at 194        26.6 / 32.8 / 35.8
+//   64 x 2481 at 202          15.7 / 19.2 / 28.2   192 x 64 at 4979       36.2 / 28.5 / 33.2      160 x 1820 at 92  18.7 / 17.7 / 28.0
+// kan_wide / records from batch 1024 on, where one pass is left to the smallest layers (two tile steps a CU):
+//   2048 x 512 at 1024 / 2048 / 3000 69.4 / 93.7, 122 / 128, 197 / 180; 1024 x 256 at 3000 / 4096 63.3 / 82.5, 79.3 / 84.5; 2048 x 1024 at 1300
+//   177 / 171, 4096 x 1024 at 1300 344 / 330; 128 x 2993 at 2601 87 / 64, 352 x 512 at 9186 134 / 107, 192 x 544 at 13,756 91 / 132, 800 x 544 at 2861 87 / 124: what
+//   decides is how well the last round of workgroups is filled.
+// Layers whose tiles of 64 outputs would be half empty, which make_wide leaves: one pass as long as it is ahead of the records,
+// whose time grows from 20 us by 93 a million edges and 12 a million inputs.
 constexpr int64_t kDenseSplitMinBatch = 17;
-constexpr int64_t kDenseOnePassMaxBatch = 128, kDenseOnePassSmallMaxBatch = 256;
-constexpr long long kDenseOnePassSmallEdges = 1ll << 18;
-constexpr long long kDenseOnePassMaxSteps = 512;
-constexpr int64_t kDenseWideMaxBatch = 1024;
-constexpr long long kDenseWideMaxWork = 1ll << 31;      // edges x samples, from kDenseWideMaxBatch on
+constexpr int64_t kDenseManySamples = 1024;
+constexpr long long kDenseOnePassMaxSteps = 512;        // tiles of 64 x 64 times steps of 32 inputs
+constexpr long long kDenseWideMaxWork = 1ll << 31;      // edges x samples; records from there (2048 x 1024 at 1300, 4096 x 1024 at 1300, 2048 x 512 at 3000 above)
 constexpr long long kDenseSmallSums = 2ll << 20;        // bytes of partial sums that any layer may write
 constexpr int64_t kAutoMfmaBatch = 32;    // KAN_PATH_AUTO switches to the matrix cores from here (measured crossover 16-32)
 
@@ -1604,12 +1604,6 @@ kan_status kan_vq_layer_forward(const kan_vq_layer* L, const float* x, int64_t B
 // dequantise).
 static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
   const long long edges = (long long)in * out;
-  if (B > 64 && (long long)((out + 63) / 64) * ((B + 63) / 64) * ((in + kDenseStep64 - 1) / kDenseStep64) > kDenseOnePassMaxSteps) {
-    LayerPlan p = plan_mfma(in, out, B, 1, 0, 0, kDense, true);
-    const bool wide = (B < kDenseWideMaxBatch || B * edges < kDenseWideMaxWork) && make_wide(p, in, out, B, 1, true, 1, true);
-    p.name = "kan_dense_split";
-    if (wide || (B > kDenseOnePassMaxBatch && (B > kDenseOnePassSmallMaxBatch || edges > kDenseOnePassSmallEdges))) return p;
-  }
   LayerPlan p;
   p.mfma = false;
   p.kind = kPlanDense;
@@ -1618,20 +1612,61 @@ static LayerPlan plan_dense(int32_t in, int32_t out, int64_t B) {
   const int tile_n = p.cfg.bt == 16 ? 16 : 64, step = p.cfg.bt == 16 ? kDenseStep16 : kDenseStep64;
   p.n_jt = (out + tile_n - 1) / tile_n;
   p.n_bt = (int)((B + p.cfg.bt - 1) / p.cfg.bt);
-  // Workgroups for the whole chip (two per CU of four waves, one of eight), while the partial sums stay below a
-  // quarter of the coefficients, of small layers, whose launch is a latency chain, below all of them (300 x 64 at batch 64 / 256
-  // 11.1 / 31.3 -> 11.1 / 11.4 us, 100 x 100 at 400 25.1 -> 11.6).
-  const long long base = (long long)p.n_jt * p.n_bt, target = p.cfg.bt == 16 ? kTargetWorkgroups : kTargetWorkgroups / 2;
-  long long chunks = (target + base - 1) / base;
-  const long long max_by_rows = (in + step - 1) / step, sums = (long long)in * out * 40 / ((long long)in * out <= kFusedSmallLayerEdges ? 1 : 4);
-  const long long max_by_bytes = std::max(sums, kDenseSmallSums) / (4 * B * out);
-  if (chunks > max_by_rows) chunks = max_by_rows;
-  if (chunks > max_by_bytes) chunks = max_by_bytes;
-  if (chunks < 1) chunks = 1;
-  const int rows = (int)((in + chunks - 1) / chunks);
-  p.rows_per_chunk = (rows + step - 1) / step * step;
-  p.n_chunks = (in + p.rows_per_chunk - 1) / p.rows_per_chunk;
-  return p;
+  // Partial sums below a quarter of the coefficients, of small layers, whose launch is a latency chain, below all of them (300 x 64
+  // at batch 64 / 256 11.1 / 31.3 -> 11.1 / 11.4 us, 100 x 100 at 400 25.1 -> 11.6).
+  const long long base = (long long)p.n_jt * p.n_bt, steps = ((long long)in + step - 1) / step;
+  const long long sums = edges * 40 / (edges <= kFusedSmallLayerEdges ? 1 : 4);
+  const long long most = std::max(1ll, std::min(steps, std::max(sums, kDenseSmallSums) / (4 * B * out)));
+  if (p.cfg.bt == 16) {          // two workgroups of four waves per CU
+    const long long chunks = std::min((kTargetWorkgroups + base - 1) / base, most);
+    const int rows = (int)((in + chunks - 1) / chunks);
+    p.rows_per_chunk = (rows + step - 1) / step * step;
+    p.n_chunks = (in + p.rows_per_chunk - 1) / p.rows_per_chunk;
+    return p;
+  }
+  // One workgroup of eight waves per CU: steps of the rounds that the chunks take, the reduction and the sums (us, fitted
+  // to 22,788 launches, 5 % off).  A chunk for every CU that 256 / base, rounded up, asked for made 296 workgroups of 148:
+  // 64 x 2347 at batch 253 23.5 us, whole 15.4; 1408 x 3750 at 18 92 -> 64, 384 x 2880 at 39 34 -> 25.
+  const bool two = p.cfg.bt == 64;
+  double one_pass = 0;
+  for (long long r = 0; r <= 4; ++r) {                   // whole; as many as r rounds hold
+    const long long c = std::clamp<long long>(r * kCUs / base, 1, most);
+    if (r > 0 && c == 1) continue;
+    const long long per = ((in + c - 1) / c + step - 1) / step, chunks = (steps + per - 1) / per, rounds = (base * chunks + kCUs - 1) / kCUs;
+    const double cost = (two ? 4.5 : 2.9) * (double)(per * rounds) + (two ? 0.8 : 0.9) * (double)per + (two ? 1.1 : 2.3) * (double)rounds +
+                        (chunks > 1 ? 2.3 + 3.2e-6 * (double)(chunks * B * out) : 0.0);
+    if (r > 0 && cost >= one_pass) continue;
+    one_pass = cost;
+    p.rows_per_chunk = (int)(per * step);
+    p.n_chunks = (int)chunks;
+  }
+  if (!two || B <= 64) return p;
+  one_pass += 2.2 + 4.2e-6 * (double)edges;
+  // The other forms, fitted below and from batch 1024 on (6 to 8 % off, records 15; the choice is within 1 % of the best on average).
+  const bool many = B >= kDenseManySamples;
+  const LayerPlan records = plan_mfma(in, out, B, 1, 0, 0, kDense, true);
+  LayerPlan m = records;
+  const double inputs = 1e-6 * (double)B * in, outputs = 4e-6 * (double)(B * out);
+  const long long tile_steps = base * steps;
+  if (make_wide(m, in, out, B, 1, true, 1, true)) {
+    const long long per = m.rows_per_chunk / 16, rounds = ((long long)m.n_jt * m.n_bt * m.n_chunks + kCUs - 1) / kCUs;
+    const bool tall = m.cfg.bt > 128;
+    const double sums_out = m.n_chunks > 1 ? m.n_chunks * outputs : 0.0;
+    const double wide = many ? 7.7 + 2.66 * (double)(rounds * per) + 1.4 * (double)rounds + 6.05 * inputs + 0.23 * outputs + 0.26 * sums_out + (m.n_chunks > 1 ? 3.4 : 0.0)
+                             : 3.4 + (tall ? 2.5 : 1.85) * (double)(rounds * per) + (tall ? 6.0 : 5.6) * (double)rounds + 6.4 * inputs + 1.8e-6 * (double)edges +
+                                   0.39 * sums_out + (m.n_chunks > 1 ? 2.6 : 0.0);
+    if (one_pass <= wide && (!many || tile_steps <= kDenseOnePassMaxSteps)) return p;
+    if (many) {
+      const long long wgs = (long long)records.n_jt * records.n_bt * records.n_chunks, cut = records.n_chunks > 1;
+      const double by_records = 11.0 + 33.4e-6 * (double)edges + 5.9 * inputs + 0.6 * outputs + cut * (1.8 + 0.33 * records.n_chunks * outputs) +
+                                (2.4 * (double)((wgs + 2 * kCUs - 1) / (2 * kCUs)) + 0.8 * (double)((wgs + kCUs - 1) / kCUs)) * (records.rows_per_chunk / 16);
+      if (by_records < wide || B * edges >= kDenseWideMaxWork) m = records;
+    }
+  } else if (many ? tile_steps <= kDenseOnePassMaxSteps : one_pass <= 0.85 * (19.5 + 92.5e-6 * (double)edges + 11.7 * inputs)) {
+    return p;
+  }
+  m.name = "kan_dense_split";
+  return m;
 }
 
 static void dense_ws(const LayerPlan& p, int32_t in, int32_t out, int64_t B, size_t* partial, size_t* cf, size_t* u) {

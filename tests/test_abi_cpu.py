@@ -392,3 +392,11 @@ def test_last_layers_are_cut_by_what_the_reduction_costs():
                                              (823, 544, 49, 11, kb.KAN_PATH_GATHER, True), (298, 4064, 10, 31, kb.KAN_PATH_MFMA, True)):
         need = _head_ws(L, (n_in, n_out), heads, B, path, cb_dtype=kb.KAN_I8, gb_dtype=kb.KAN_F16)
         assert (need > 0) == cut, (n_in, n_out, heads, B, need)
+
+
+def test_dense_layers_are_cut_by_rounds_of_workgroups():
+    """One pass of the dense baseline: no chunk more than a round of workgroups holds (148 of them whole, not 296 of two)."""
+    L = kb.lib()
+    for n_in, n_out, B, chunks in ((64, 2347, 253, 1), (384, 2880, 39, 4), (300, 64, 256, 10), (2080, 1328, 36, 11)):
+        need = L.kan_dense_workspace_bytes(n_in, n_out, B)
+        assert need == (0 if chunks == 1 else -(-4 * chunks * B * n_out // 256) * 256), (n_in, n_out, B, need)

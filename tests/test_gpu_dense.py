@@ -26,7 +26,7 @@ def kb():
 # 16 and 64 and one past them; batches: every tile, full and one past, two tiles of 64 and the last of the rule)
 @pytest.mark.parametrize("n_in,n_out,B", [(1, 1, 1), (15, 16, 2), (16, 17, 16), (65, 15, 7), (129, 33, 16), (2050, 48, 9),
                                           (1, 1, 17), (17, 63, 32), (32, 64, 33), (33, 65, 64), (130, 129, 65),
-                                          (300, 70, 128), (97, 40, 129), (64, 20, 256)])
+                                          (300, 70, 128), (97, 40, 129), (64, 20, 256), (384, 2880, 39), (1408, 750, 18)])
 def test_one_pass_kernels(kb, n_in, n_out, B):
     rng = np.random.default_rng(n_in * 7 + n_out + B)
     coef = (rng.standard_normal((n_in, n_out, 10)) * rng.uniform(1e-3, 2.0, (n_in, n_out, 1))).astype(np.float32)
@@ -40,7 +40,9 @@ def test_one_pass_kernels(kb, n_in, n_out, B):
 @pytest.mark.parametrize("n_in,n_out,B", [(1033, 1021, 65), (2056, 512, 129), (4097, 257, 128), (1640, 640, 257), (300, 1090, 300), (520, 511, 1023),
                                           (1024, 256, 257), (500, 96, 1400),                # the contraction that converts its own coefficients
                                           (1024, 256, 256), (300, 64, 1024), (31, 33, 700),  # the last of the one-pass rule, many tiles of it
-                                          (9000, 40, 128), (9000, 33, 200)])                # tiles of 64 outputs half empty: one pass, records
+                                          (9000, 40, 128), (9000, 33, 200), (2784, 88, 194),  # tiles of 64 outputs half empty, or nearly: one pass
+                                          (64, 2347, 253), (64, 1090, 505), (384, 2880, 65),  # whole, in one round of workgroups and in two
+                                          (192, 64, 4979), (256, 4096, 1030)])                # many samples: the contraction again, records
 def test_beyond_one_tile(kb, n_in, n_out, B):
     rng = np.random.default_rng(n_in + 3 * n_out + B)
     coef = (rng.standard_normal((n_in, n_out, 10)) * rng.uniform(1e-3, 2.0, (n_in, n_out, 1))).astype(np.float32)
