@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kWholeWaves * kWave, 4) void kan_assign_whole_kerne
 // instruction wants it, without LDS.  LOCAL: the workgroup builds the shapes' operands in its LDS and goes through the edges:
 // one launch, and only edges are read in its loop.  256 shapes and 28,672 / 182,784 / 394,240 edges 9.6 / 13.5 / 19.3 us with
 // operands of both kinds stored in pieces of two bytes and fetched from memory, 7.9 / 9.8 / 15.3 so; 2^20 x 4,096 (not LOCAL)
-// 293 -> 282.  Bound: reads and writes of the edges (16 MB in 6 us) beside a new best in almost every tile.
+// 293 -> 271.  Bound: reads and writes of the edges (16 MB in 6 us) beside a new best in almost every tile.
 template <typename IdxT, int TILES, bool LOCAL>
 __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_own_kernel(const WholeArgs a, const float* __restrict__ cb, int K) {
   static_assert(TILES % 2 == 0, "a lane per edge of two tiles");
@@ -432,19 +432,21 @@ __global__ __launch_bounds__(kAssignThreads, 4) void kan_assign_own_kernel(const
       if (t + 1 < a.n_tiles) score_tile(t + 1, fa1);
       load_tile(t + 3, fa1);
     }
-    // the two halves hold different rows of the same edges: the better one, the lower id
-    int id[TILES];
-#pragma unroll
-    for (int nb = 0; nb < TILES; ++nb) {
-      id[nb] = shape_of(best_tile[nb], best_row[nb], half);
+    // the two halves hold different rows of the same edges: the better one, the lower id.  (In registers: an array that a
+    // lane indexes by its half goes to LDS or scratch, and the address in LDS comes from the launch's packet in host memory,
+    // which cost a launch 9 to 12 us: 2^20 edges x 64 / 1,000 / 4,096 shapes in four tiles a wave 28 / 97 / 282 us so, 17 / 84 /
+    // 271 in registers.)
+    auto better = [&](int nb) {
+      const int id = shape_of(best_tile[nb], best_row[nb], half);
       const float sc_o = __shfl_xor(best[nb], 32, kWave);
-      const int id_o = __shfl_xor(id[nb], 32, kWave);
-      if (sc_o > best[nb] || (sc_o == best[nb] && id_o < id[nb])) id[nb] = id_o;
-    }
+      const int id_o = __shfl_xor(id, 32, kWave);
+      return sc_o > best[nb] || (sc_o == best[nb] && id_o < id) ? id_o : id;
+    };
 #pragma unroll
     for (int h = 0; h < TILES / 2; ++h) {
       const long long at = e0 + h * 64 + lane;
-      if (at < a.E) ((IdxT*)a.idx)[at] = (IdxT)(half ? id[2 * h + 1] : id[2 * h]);
+      const int first = better(2 * h), second = better(2 * h + 1);
+      if (at < a.E) ((IdxT*)a.idx)[at] = (IdxT)(half ? second : first);
     }
   }
 }
