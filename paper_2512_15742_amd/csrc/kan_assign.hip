@@ -1579,20 +1579,37 @@ int recon_blocks(long long E) {
 namespace {
 size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 constexpr int kFilterTiles = 256;                 // tiles of a part (both sides at the head of the whole search)
-// Operands of all shapes in LDS: 32 KB at most.  (8,192 / 28,672 / 131,072 edges x 1,000 shapes 15.6 / 16.0 / 20.1 us so, 10.1 /
-// 10.6 / 20.7 with the waves sharing their edges; x 400 - 500 8.3 / 9.8 / - against 9.1 / 10.4 / -.)
-constexpr int kLocalShapes = 512;
+// Operands of all shapes in LDS: 40 KB at most, four workgroups of a CU.  512 shapes and 65,536 / 131,072 / 358,400 edges 9.2 /
+// 11.0 / 21.0 us so, 9.9 / 14.1 / 29.3 with the waves sharing their edges; 640 shapes 10.7 / 13.3 / 25.4 against 10.3 / 15.1 /
+// 32.6.  (700 shapes, three workgroups of a CU: 2^18 edges 24.1 against 22.9 with waves on their own.)
+constexpr int kLocalShapes = 640;
+constexpr long long kLocalMaxWork = 500000000;
 constexpr unsigned kLocalWorkgroups = 1024;       // what is resident
-// Waves on their own from here: 2^18 / 2^20 edges x 1,024 shapes 44 / 96 us against 34 / 114, 2^19 / 2^20 x 4,096 158 / 282
-// against 151 / 297.
+// Every workgroup builds them, which takes longer than shared edges do where a CU has one workgroup of these: 4,096 / 32,768
+// edges x 384 shapes 8.0 / 7.9 against 7.9 / 8.4 us, x 448 8.5 / 8.5 against 8.3 / 8.7, x 512 8.9 / 9.4 against 8.2 / 8.4; and with
+// two where a workgroup has not a row for every thread once more: 65,536 x 512 9.2 against 9.9, 46,948 x 627 11.0 against 10.1.
+bool local_ok(long long E, int K) {
+  if (E * K >= kLocalMaxWork || K > kLocalShapes) return false;
+  return E > (1ll << 16) || K <= 384 || (E > (1ll << 15) && K <= 512);
+}
+// Waves on their own with operands from memory, four tiles of edges each, from 3 * 2^18 edges.  Against operands in LDS (from
+// kLocalMaxWork): 2^20 / 1,536,000 edges x 300 shapes 34.5 / 47.3 us against 35.7 / 50.9, 953,281 x 305 34.8 against 33.1, 786,432 x
+// 640 45.2 against 48.7.  Against shared edges: 665,600 / 786,432 edges x 4,096 205 / 210 against 194 / 223; with fewer shapes the
+// first edges come to more of the time: 229,376 x 641 21 against 24, 196,608 / 2^18 x 768 24 / 24 against 23 / 28, 2^18 / 358,400 x
+// 1,000 30 / 38 against 32 / 41, 358,400 / 402,408 / 524,288 x 1,500 52 / 61 / 65 against 52 / 59 / 72, 358,400 / 524,288 x 2,048
+// 64 / 83 against 63 / 88.
 constexpr long long kOwnMinEdges = 3ll << 18;
+bool own_ok(long long E, int K) { return E >= kOwnMinEdges || (E >= (7ll << 15) && E >= 320ll * K); }
+
+enum class Search { kLocal, kOwn, kWhole };
+Search search_of(long long E, int K) { return local_ok(E, K) ? Search::kLocal : (own_ok(E, K) ? Search::kOwn : Search::kWhole); }
 
 // Parts of the codebook: by the work of the fullest CU.  A step of a workgroup (eight tiles of shapes, 128 edges) takes 0.58 us
 // alone on its CU, 0.92 for two there, 0.47 each for more; the first ones, with a new best in nearly every tile, as long as
 // eight more; the second launch 3 us.  2^13 edges x 65,536 shapes in 4 / 8 / 16 parts 55 / 47 / 54 us, 24,000 in 2 / 4 / 6 110 /
 // 102 / 115, 32,768 in 1 / 2 / 4 151 / 118 / 126, 65,536 in 1 / 2 217 / 217.
 int whole_parts(long long E, int K) {
-  if (K <= kLocalShapes || E >= kOwnMinEdges) return 1;
+  if (search_of(E, K) != Search::kWhole) return 1;
   const long long groups = (E + kWholeEdges - 1) / kWholeEdges;
   const int n_tiles = (K + 31) / 32;
   int best = 1;
@@ -1711,11 +1728,12 @@ hipError_t launch_assign(const float* coef, long long E, const float* cb, int K,
     return hipGetLastError();
   };
   using std::integral_constant;
-  if (K <= kLocalShapes)
+  const Search search = search_of(E, K);
+  if (search == Search::kLocal)
     return own(integral_constant<int, 2>(), std::true_type(), kLocalWorkgroups, (size_t)a.n_tiles * 2 * 64 * sizeof(uint4));
   const long long recs = (long long)a.n_tiles * 2 * 64;
   hipLaunchKernelGGL(kan_assign_prep_kernel, dim3((unsigned)((recs + 255) / 256)), dim3(256), 0, s, cb, K, a.n_tiles, (uint4*)ws);
-  if (E >= kOwnMinEdges) return own(integral_constant<int, 4>(), std::false_type(), 1u << 30, 0);
+  if (search == Search::kOwn) return own(integral_constant<int, 4>(), std::false_type(), 1u << 30, 0);
   a.parts = ws_bytes < assign_whole_bytes(E, K) ? 1 : whole_parts(E, K);
   a.part_tiles = (a.n_tiles + a.parts - 1) / a.parts;
   a.parts = (a.n_tiles + a.part_tiles - 1) / a.part_tiles;

@@ -325,3 +325,32 @@ def test_large_searches_give_the_ids_of_one_part(kb, kind, K, E):
     d2 = 1.0 - 2 * n @ cb.double().T + (cb.double() ** 2).sum(1)
     ids = a.view(-1)[:64].long() & (0xffff if K <= 65536 else 0xffffffff)
     assert float((d2.gather(1, ids[:, None])[:, 0] - d2.min(1).values).max()) <= GAP
+
+
+@pytest.mark.parametrize("kind", ["trained", "duplicates", "no numbers"])
+@pytest.mark.parametrize("K,E,piece", [(385, 32769, 32768), (512, 40001, 20001), (640, 65537, 32769), (640, 781249, 781248),
+                                       (500, 1000001, 500001), (513, 974659, 974658), (640, 800001, 65536), (641, 229376, 229375), (819, 262080, 262079),
+                                       (1500, 480001, 240001)])
+def test_searches_of_few_shapes_give_the_ids_of_their_pieces(kb, kind, K, E, piece):
+    """Either side of the lines between the forms of the search (operands in LDS, waves with edges of their own, shared edges):
+    a call's ids, gains and biases are those of calls on pieces of its edges, which take another form; and near the nearest row."""
+    coef, cb = _grids(kind, K, E, K + E + 3)
+    odd = coef.view(E, 10)[E - 60:].view(6, 10, 10)
+    odd[0] = float("nan")
+    odd[1, :, 3] = float("inf")
+    odd[2] *= 1e30
+    odd[3] = 0.25
+    odd[4] *= 1e-21
+    got = kb.kan_vq_assign(coef, cb)
+    for at in range(0, E, piece):
+        part = kb.kan_vq_assign(coef[at:at + piece].clone(), cb)
+        for a, b in zip(got, part):
+            a, b = a.view(-1)[at:at + piece], b.view(-1)
+            assert torch.equal(a, b) if a.dtype != torch.float32 else torch.equal(a.nan_to_num(), b.nan_to_num())
+    if kind == "trained":
+        n = coef.view(E, 10)[:8192].double()
+        n = n - n.mean(1, keepdim=True)
+        n /= n.norm(dim=1, keepdim=True)
+        d2 = 1.0 - 2 * n @ cb.double().T + (cb.double() ** 2).sum(1)
+        ids = got[0].view(-1)[:8192].long() & 0xffff
+        assert float((d2.gather(1, ids[:, None])[:, 0] - d2.min(1).values).max()) <= GAP
