@@ -1642,8 +1642,16 @@ size_t assign_whole_bytes(long long E, int K) { return whole_bytes(E, K, whole_p
 //     K = 8,192    2^20 edges  184 / 243 / 445 / 443                  2^19 edges  124 / 159 / 266 / 263
 //                  2^18 edges  96 / 117 / 178 / 177
 //     K = 4,096    2^20 edges  168 / 211 / 355 / 362  against 282
+//     K = 119,045  34,440 edges  171 / 220 / -         against 267    K = 131,072  66,030 edges  - / - / 374  against 480
+//     K = 262,144  16,524 edges  - / 448 / 634         against 283    33,304  - / - / 588  against 530
+//     K = 330,923  13,760 edges  - / 513 / 758         against 266
+// The call does not know the noise: the line is where both take as long with 5 % (in 1,179 calls of 8,192 to 331,338 shapes
+// the one taken is 0.9 % behind the better one there on average, 2.1 % with 2 % and 1.4 % with 15 %).  So grids that fit their codebook
+// better gain less than they could (65,536 shapes and 34,020 edges with 2 % 159 against 122) and worse ones lose (53,436 edges
+// with 15 % 237 against 194); a caller who knows them passes the smaller workspace and gets the whole search.
 bool assign_bounded_ok(long long E, int K) {
-  return ((E - 25000) * K >= 1200000000ll && K >= 16384 || E * K >= (1ll << 32) && K >= 8192) && cell_layout(1, K).groups_max <= kCellMaxGroups;
+  const bool pays = K >= 16384 ? (E - 24000) * K >= 1200000000ll : (K >= 8192 && E * K >= (1ll << 32));
+  return pays && cell_layout(1, K).groups_max <= kCellMaxGroups;
 }
 size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
 

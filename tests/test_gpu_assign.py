@@ -153,8 +153,15 @@ def _grids(kind, K, E, seed):
     return coef.contiguous(), cb.contiguous()
 
 
-@pytest.mark.parametrize("kind,K,E", [("trained", 16384, 98304), ("trained", 16421, 98101), ("trained", 50001, 33333),
-                                      ("trained", 70000, 24001), ("far", 16384, 98337), ("duplicates", 16384, 98304),
+def _bounded_is_taken(kb, n_in, n_out, K):
+    """The faster workspace is none of the whole search's: the shapes' operands, and eight bytes an edge and part of the codebook."""
+    L = kb.lib()
+    whole, fast = L.kan_vq_assign_workspace_bytes(K), L.kan_vq_assign_fast_workspace_bytes(n_in, n_out, K)
+    return fast not in {(whole + (8 * n_in * n_out * parts if parts > 1 else 0) + 255) // 256 * 256 for parts in range(1, 33)}
+
+
+@pytest.mark.parametrize("kind,K,E", [("trained", 16384, 98304), ("trained", 16421, 98101), ("trained", 50001, 48001),
+                                      ("trained", 70000, 41201), ("far", 16384, 98337), ("duplicates", 16384, 98304),
                                       ("norms", 16384, 98304), ("flat", 16384, 98304), ("one cell", 16384, 98304),
                                       ("one row", 16384, 98304), ("unused", 20000, 98304)])
 def test_bounded_search_finds_the_nearest_row(kb, kind, K, E):
@@ -163,7 +170,7 @@ def test_bounded_search_finds_the_nearest_row(kb, kind, K, E):
     coef, cb = _grids(kind, K, E, K + E)
     L = kb.lib()
     whole = torch.empty(L.kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
-    assert L.kan_vq_assign_fast_workspace_bytes(E, 1, K) > whole.numel()
+    assert _bounded_is_taken(kb, E, 1, K)
     idx, gain, bias = kb.kan_vq_assign(coef, cb)
     ref = kb.kan_vq_assign(coef, cb, ws=whole)
     assert torch.equal(gain, ref[1]) and torch.equal(bias, ref[2])
@@ -189,7 +196,7 @@ def _both_searches(kb, coef, cb):
     E, K = coef.shape[0] * coef.shape[1], cb.shape[0]
     L = kb.lib()
     whole = torch.empty(L.kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
-    assert L.kan_vq_assign_fast_workspace_bytes(coef.shape[0], coef.shape[1], K) > whole.numel()
+    assert _bounded_is_taken(kb, coef.shape[0], coef.shape[1], K)
     mask = 0xffff if K <= 65536 else 0xffffffff
     return [kb.kan_vq_assign(coef, cb, ws=ws)[0].view(-1).long() & mask for ws in (None, whole)]
 
@@ -210,14 +217,16 @@ def test_bounded_search_scores_as_well_as_the_whole_search(kb, K, E):
     assert wrong[0] <= wrong[1] + 4 * wrong[1] ** 0.5, wrong
 
 
-@pytest.mark.parametrize("kind,K,E", [("trained", 16421, 98101), ("trained", 70000, 24001), ("far", 16384, 98337),
+@pytest.mark.parametrize("kind,K,E", [("trained", 16421, 98101), ("trained", 70000, 41201), ("far", 16384, 98337),
                                       ("duplicates", 16384, 98304), ("norms", 16384, 98304), ("near ties", 16384, 98304),
                                       ("flat", 16384, 98304), ("one cell", 16384, 98304), ("one row", 16384, 98304),
-                                      ("unused", 16384, 98304), ("unused", 70001, 30001),
+                                      ("unused", 16384, 98304), ("unused", 70001, 41203),
                                       # parts of a cell: 8 up to 1024 cells, 4, 2, 1 (K / 64 cells, at most 8192 parts)
-                                      ("trained", 65536, 24607), ("trained", 131071, 12301), ("trained", 262144, 6151),
-                                      ("trained", 300000, 5377), ("clumps", 16384, 98304), ("clumps", 65521, 33001),
-                                      ("no numbers", 16384, 98304)])
+                                      ("trained", 65536, 42331), ("trained", 131071, 33161), ("trained", 262144, 28603),
+                                      ("trained", 300000, 28009), ("clumps", 16384, 98304), ("clumps", 65521, 42331),
+                                      ("no numbers", 16384, 98304), ("duplicates", 70001, 41203), ("flat", 131071, 33161),
+                                      ("no numbers", 131071, 33161), ("no numbers", 262144, 28603), ("no numbers", 300000, 28009),
+                                      ("trained", 8193, 524289)])
 def test_bounded_search_gives_the_ids_of_the_whole_search(kb, kind, K, E):
     """Not one id differs, whichever edges share a wave and are handed over: equal scores go to the lowest id in both,
     edges of gain 0 to the same shape, and grids that are no numbers or overflow to what the whole search gives."""
@@ -317,6 +326,7 @@ def test_large_searches_give_the_ids_of_one_part(kb, kind, K, E):
     eight, four, two parts and one."""
     coef, cb = _grids(kind, K, E, K + E + 2)
     whole = torch.empty(kb.lib().kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
+    assert _bounded_is_taken(kb, E, 1, K) == (K > 513)
     a, b = kb.kan_vq_assign(coef, cb)[0], kb.kan_vq_assign(coef, cb, ws=whole)[0]
     assert torch.equal(a, b), int((a != b).sum())
     flat = coef.view(E, 10)[:64].double()
