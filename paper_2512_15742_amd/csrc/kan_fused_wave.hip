@@ -25,8 +25,11 @@
 // 18.6; ten heads of 2048-256-21 at batch 8 61.0 -> 53.8.
 //
 // HALF: the same lanes with fp16 operands, a lane's ten weights and coefficients as five pairs, four, four and two of them to
-// a v_mfma_f32_16x16x16_f16 (one instruction shape for all: sums passed between v_mfma_f32_16x16x32_f16 and this one came
-// out wrong).  Int8 rows take the layer's scale at the end, as in kan_fused.hip.  Blocks of 16 samples share a step's
+// a v_mfma_f32_16x16x16_f16.  (One instruction shape for all: next behind a v_mfma_f32_16x16x32_f16 with the same sums, this one
+// takes them before they are written, and the compiler puts no wait between the two - it does not for two of one shape, where
+// none is needed.  A chain of whole numbers in one accumulator had every sum wrong, with three other accumulators in between
+// none; here, 2.7e7 in place of 0.9.  16x16x32 for the first eight measured the same time, 19.4 and 19.2 us for 2048-1024-256 at 16.)
+// Int8 rows take the layer's scale at the end, as in kan_fused.hip.  Blocks of 16 samples share a step's
 // coefficients, so 64 samples cost a lane four bases for 256 edges - twice the tiles of kan_fused.hip, whose workgroups share them -,
 // and that is what bounds it there, with the address units (146 - 150 G rows/s, the tiles up to 175); at up to 48 samples it is
 // the gathers and their latency.  Against the tiles of 128 outputs it has no basis tile, no barrier, tiles of half the
