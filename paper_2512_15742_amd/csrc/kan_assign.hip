@@ -1645,12 +1645,14 @@ size_t assign_whole_bytes(long long E, int K) { return whole_bytes(E, K, whole_p
 //     K = 119,045  34,440 edges  171 / 220 / -         against 267    K = 131,072  66,030 edges  - / - / 374  against 480
 //     K = 262,144  16,524 edges  - / 448 / 634         against 283    33,304  - / - / 588  against 530
 //     K = 330,923  13,760 edges  - / 513 / 758         against 266
-// The call does not know the noise: the line is where both take as long with 5 % (in 1,179 calls of 8,192 to 331,338 shapes
-// the one taken is 0.9 % behind the better one there on average, 2.1 % with 2 % and 1.4 % with 15 %).  So grids that fit their codebook
-// better gain less than they could (65,536 shapes and 34,020 edges with 2 % 159 against 122) and worse ones lose (53,436 edges
-// with 15 % 237 against 194); a caller who knows them passes the smaller workspace and gets the whole search.
+// The call does not know the noise: the line is where both take as long with 5 %, by measured sizes of 110,000 to 115,000 edges
+// for 16,384 shapes, 70,000 for 32,768, 39,000 to 47,000 for 65,536, 33,000 to 36,000 for 131,072 and 28,000 to 33,000 for 262,144.  In
+// 1,179 calls of 8,192 to 331,338 shapes the search taken is 0.9 % behind the better one on average, 2.5 % with 2 % and 1.0 % with
+// 15 %: near the line, grids that fit their codebook better gain less than they could (65,536 shapes and 34,020 edges with 2 % 159
+// against 122) and worse ones lose (53,436 edges with 15 % 237 against 194).  A caller who knows them passes the smaller workspace
+// and gets the whole search.
 bool assign_bounded_ok(long long E, int K) {
-  const bool pays = K >= 16384 ? (E - 24000) * K >= 1200000000ll : (K >= 8192 && E * K >= (1ll << 32));
+  const bool pays = K >= 16384 ? (E - 24000) * K >= 1400000000ll : (K >= 8192 && E * K >= (1ll << 32));
   return pays && cell_layout(1, K).groups_max <= kCellMaxGroups;
 }
 size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
