@@ -332,7 +332,9 @@ LayerPlan plan_mfma(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, in
 //     34.1 / 35.0 / 36.2 / 38.0, 2048 x 1024 58.8 / 62.8 / 67.3 / 66.6 against 52.0 / 53.3 / 55.3 / 58.8, 1500 x 1100
 //     79.9 / 80.5 / 61.0 / 86.0 against 46.5 / 47.6 / 50.3 / 53.1 (kan_mfma.hip pads 1100 outputs to 1280), 1900 x 1100 at 900
 //     101.6 against 62.0; fp32 rows 2048 x 1024 at 1024 74.8 against 75.8;
-//   - up to batch 1024 where the next layer adds the slices (2048-1024-256 at 640 / 1024 83.0 / 90.9 against 79.8 / 87.6);
+//   - up to batch 1024 where the next layer adds the slices (2048-1024-256 at 640 / 1024 83.0 / 90.9 against 79.8 / 87.6).  From
+//     there to batch 1500 it is 9 to 23 % behind where the records' tiles of 256 outputs are full (900 to 1024, 1281 to 1536 and 1793
+//     to 2048 outputs, by 14 % at most on average, 11 % ahead elsewhere), so the line stays;
 //   - layers of 2^18 edges with 512 outputs and more, up to batch 256 fp16 and 768 split: 512 x 512 fp16 at 80 / 256 / 400
 //     16.0 / 17.6 / 20.1 against 14.6 / 16.9 / 20.7, split at 80 / 256 / 700 21.2 / 22.9 / 31.4 against 18.3 / 21.5 / 27.9, 1024 x 512
 //     fp16 at 80 / 256 19.6 / 22.1 against 17.3 / 19.1, split at 256 / 700 30.6 / 45.9 against 24.2 / 37.9, 700 x 900 split at 128 / 512
