@@ -78,21 +78,24 @@ typedef enum kan_dtype {
  *   KAN_PATH_GATHER  the precise path: fp32 operands, fp32 accumulation; matches the
  *                    float64 definition to ~1e-6 (bound 1e-5).  Batch 1: one 4-byte
  *                    codeword-window gather per edge on the vector ALUs; from batch 2:
- *                    fused gather + matrix-core kernel (fp32 operands up to batch 32; from
+ *                    fused gather + matrix-core kernels (fp32 operands up to batch 32; from
  *                    33 coefficients and basis weights split into high and low fp16 parts,
  *                    three products, fp32-grade sums); from batch 65: the kernels of the
  *                    fp16 path on such split operands (layers of a million edges and more,
- *                    heads of a launch together, up to batch 768: a kernel that gathers and
- *                    dequantises its own coefficients for tiles of 128 or 256 samples; large
+ *                    heads of a launch together, and single layers of 2^18 edges with 512
+ *                    outputs whose codebook is not fp32, up to batch 768: a kernel that gathers
+ *                    and dequantises its own coefficients for tiles of 128 or 256 samples; large
  *                    products: tiles of 256 x 256).  Prepared layers (see kan_vq_prepare),
  *                    batch <= 4 (<= 3 for layers of 2^23 edges or more): codebook buckets
  *                    in LDS.
  *   KAN_PATH_MFMA    fp16 operands on the matrix cores, fp32 accumulation; ~3e-4
  *                    relative per layer (bound 2e-2).  Batch <= 64: fused gather + MFMA
- *                    kernel; above: coefficients dequantised once per call into the workspace
+ *                    kernels; above: coefficients dequantised once per call into the workspace
  *                    in matrix-core operand order, then a streaming contraction (large
  *                    products: on tiles of 256 x 256); layers of a million edges and more
- *                    between batch 65 and 512 (1024 from 2^22 edges): coefficients dequantised
+ *                    between batch 65 and 512 (1024 from 2^22 edges; single layers whose codebook
+ *                    is not fp32 also up to 900 above 512 outputs, up to 1024 in front of another
+ *                    layer, and of 2^18 edges with 512 outputs up to 256): coefficients dequantised
  *                    by the contraction itself for tiles of up to 512 samples.
  *                    Either path, batch 65 to 128, layers of 2^22 edges or more whose codebook
  *                    is not fp32: the kernel of batch 64 again where it fits the static
@@ -205,7 +208,8 @@ kan_status kan_dense_layer_forward(const float* coef, int32_t in, int32_t out, i
  * 4096 fp16 or 2048 fp32 consecutive codewords, 80 KB: what one CU's LDS holds beside the
  * basis table, or 4096 block-floating-point rows, 48 KB; half of that for layers with more
  * than 2048 inputs),
- * then by output, then by input; per edge the buffer keeps (input index u16, codeword id
+ * then by output, then by input (layers of more than 2^20 edges: so that
+ * lanes side by side read different LDS banks); per edge the buffer keeps (input index u16, codeword id
  * within the bucket u16, gain), and per output the sum of its biases (the bases sum to 1 on
  * [-1,1], so the bias term does not depend on x), and tables that cut the work into blocks
  * of about equal edge counts whatever the histogram of the codewords.  With L->prepared set, the precise path
