@@ -593,7 +593,6 @@ LayerPlan plan_fused(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, i
 // 6.9 / 7.8; 48 x 512, 20, at 16 6.8 / 9.6; 64 x 669, 21, at 8 8.0 / 9.9; 82 x 2736, 19, at 24 46.0 / 47.2; 72 x 385, 47, at 5
 // 14.9 / 13.9; 97 x 1650, 13, at 8 19.0 / 18.0.
 constexpr long long kFusedWaveStepBytes = 512 * 1024;
-constexpr long long kFusedWaveWholeEdges = 1ll << 20;
 LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u32, int gb_kind, int code, long long cb_bytes, int large_wgs, bool half, bool compact,
                           bool reduced, bool spare) {
   LayerPlan p;
@@ -623,10 +622,11 @@ LayerPlan plan_fused_wave(int n_in, int n_out, int64_t B, int n_heads, int idx_u
   const bool by_head = half && !compact && n_heads > 1 && (long long)n_in * n_out > kFusedMinEdgesForResidency;
   const long long resident = by_head ? std::min<long long>(most, (head_wgs + p.n_jt - 1) / p.n_jt) : 1;
   p.one_head = p.one_head && by_head;
-  // Small launches: a cut that a reduction launch undoes for a tenth at least, as in plan_fused.  Mean time of one chunk over that of
-  // the cut (several heads; one head has no such choice) at 2^18 / 2^18.5 / 2^19 / 2^19.5 / 2^20 / 2^20.5 / 2^21 / 2^22 / 2^23 edges, fp16 path 0.95 / 0.86 /
-  // 0.82 / 0.89 / 0.95 / 1.00 / 1.05 / 1.12 / 1.10, precise 1.03 / 0.96 / 0.92 / 0.96 / 0.99 / 1.01 / 1.10 / 1.12 / 1.08.
-  const bool whole_line = reduced && (spare || (long long)n_in * n_out * n_heads <= kFusedWaveWholeEdges);
+  // A workgroup for more than half of the CUs and none with two: a cut that a reduction launch undoes for a tenth at least, as in
+  // plan_fused.  Mean time of one chunk over that of the cut (2,592 launches) with 64 to 95 / 96 / 128 / 160 / 192 / 224 to 256 / 257 / 288 /
+  // 320 / 352 / 384 and more workgroups: 1.01 / 0.98 / 0.88 / 0.86 / 0.84 / 0.85 / 1.09 / 1.07 / 1.06 / 1.05 / 1.09; with two and three of them - the last layers of
+  // single heads - 1.1 to 1.2 (271-48-152, fp32 rows, at batch 13 18.7 / 15.5 us, 160-44-96 at 5 17.3 / 14.7).
+  const bool whole_line = reduced && (spare || (2 * base > kCUs && base <= kCUs));
   double least = 0;
   for (int per_cu = 0; per_cu <= 8; ++per_cu) {          // one chunk; the fewest steps with at most so many workgroups on a CU
     const long long want = compact ? most : std::clamp<long long>((long long)per_cu * kCUs / base, resident, most);

@@ -384,11 +384,14 @@ def test_heads_on_tiles_still_fit_the_static_scratch(n_in, n_out, heads, B, cb, 
 
 
 def test_last_layers_are_cut_by_what_the_reduction_costs():
-    """Several heads, wave-by-wave kernel: launches of up to a million edges stay whole where a cut (1, 2 or 3 chunks) and its
-    reduction launch save less than a tenth, larger ones are cut wherever that saves anything."""
+    """Wave-by-wave kernel: launches of 129 to 256 workgroups stay whole where a cut and its reduction launch save less than a
+    tenth, others are cut wherever that saves anything (the last layers of single heads, more than a workgroup per CU)."""
     L = kb.lib()
     for n_in, n_out, heads, B, path, cut in ((59, 1791, 8, 33, kb.KAN_PATH_MFMA, False), (72, 3100, 4, 26, kb.KAN_PATH_GATHER, False),
-                                             (73, 1152, 12, 21, kb.KAN_PATH_MFMA, False), (435, 1920, 13, 7, kb.KAN_PATH_GATHER, True),
+                                             (73, 1152, 12, 21, kb.KAN_PATH_MFMA, False), (49, 339, 25, 38, kb.KAN_PATH_MFMA, False),
+                                             (48, 152, 1, 13, kb.KAN_PATH_MFMA, True), (46, 96, 1, 16, kb.KAN_PATH_GATHER, True),
+                                             (58, 128, 38, 8, kb.KAN_PATH_GATHER, True), (66, 584, 27, 10, kb.KAN_PATH_GATHER, True),
+                                             (142, 400, 37, 47, kb.KAN_PATH_MFMA, True), (435, 1920, 13, 7, kb.KAN_PATH_GATHER, True),
                                              (823, 544, 49, 11, kb.KAN_PATH_GATHER, True), (298, 4064, 10, 31, kb.KAN_PATH_MFMA, True)):
         need = _head_ws(L, (n_in, n_out), heads, B, path, cb_dtype=kb.KAN_I8, gb_dtype=kb.KAN_F16)
         assert (need > 0) == cut, (n_in, n_out, heads, B, need)
