@@ -24,6 +24,7 @@
 // finds the same shapes from a small part of the scores.
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "kan_device.hpp"
@@ -1608,8 +1609,7 @@ Search search_of(long long E, int K) { return local_ok(E, K) ? Search::kLocal : 
 // alone on its CU, 0.92 for two there, 0.47 each for more; the first ones, with a new best in nearly every tile, as long as
 // eight more; the second launch 3 us.  2^13 edges x 65,536 shapes in 4 / 8 / 16 parts 55 / 47 / 54 us, 24,000 in 2 / 4 / 6 110 /
 // 102 / 115, 32,768 in 1 / 2 / 4 151 / 118 / 126, 65,536 in 1 / 2 217 / 217.
-int whole_parts(long long E, int K) {
-  if (search_of(E, K) != Search::kWhole) return 1;
+int whole_parts_of(long long E, int K, double* us) {
   const long long groups = (E + kWholeEdges - 1) / kWholeEdges;
   const int n_tiles = (K + 31) / 32;
   int best = 1;
@@ -1623,8 +1623,10 @@ int whole_parts(long long E, int K) {
       best = parts;
     }
   }
+  if (us) *us = least;
   return best;
 }
+int whole_parts(long long E, int K) { return search_of(E, K) == Search::kWhole ? whole_parts_of(E, K, nullptr) : 1; }
 size_t whole_bytes(long long E, int K, int parts) {
   return round256(centroid_bytes(K)) + (parts > 1 ? (size_t)parts * (size_t)E * sizeof(uint2) : 0);
 }
@@ -1645,15 +1647,23 @@ size_t assign_whole_bytes(long long E, int K) { return whole_bytes(E, K, whole_p
 //     K = 119,045  34,440 edges  171 / 220 / -         against 267    K = 131,072  66,030 edges  - / - / 374  against 480
 //     K = 262,144  16,524 edges  - / 448 / 634         against 283    33,304  - / - / 588  against 530
 //     K = 330,923  13,760 edges  - / 513 / 758         against 266
-// The call does not know the noise: the line is where both take as long with 5 %, by measured sizes of 110,000 to 115,000 edges
-// for 16,384 shapes, 70,000 for 32,768, 39,000 to 47,000 for 65,536, 33,000 to 36,000 for 131,072 and 28,000 to 33,000 for 262,144.  In
-// 1,179 calls of 8,192 to 331,338 shapes the search taken is 0.9 % behind the better one on average, 2.5 % with 2 % and 1.0 % with
-// 15 %: near the line, grids that fit their codebook better gain less than they could (65,536 shapes and 34,020 edges with 2 % 159
-// against 122) and worse ones lose (53,436 edges with 15 % 237 against 194).  A caller who knows them passes the smaller workspace
-// and gets the whole search.
+// The call does not know the noise.  The bounded search is taken where it is ahead with 5 %: 72 us + 1.28 ns a shape + 0.125 to 0.38
+// ns an edge, growing by 0.047 as the shapes double from 8,192 on (15 % off at most in 19 of 20 of 1,116 calls), against the
+// whole search's steps above, whose time jumps with the workgroups of the fullest CU (98,304 edges are three of them there, 98,944
+// four: 16,384 and 17,688 shapes, bounded / whole 100 / 97 and 106 / 123 us).  Near that line grids with 15 % lose up to half (43,168 x
+// 65,536 shapes), so a plain line in front of it keeps calls whole where they would lose that for little: (E - 25000) K >= 1.2e9 from 16,384
+// shapes on, 2^32 scores from 8,192 on.  In 1,179 calls of 8,192 to 331,338 shapes the search taken is behind the better one by 0.9 % on
+// average with 5 %, 2.4 % with 2 % and 1.0 % with 15 % (the plain line alone 1.6, 2.4 and 2.6: it took few edges against very many
+// shapes, 13,760 x 330,923 513 / 266).  Grids that fit their codebook better would gain below it (34,020 edges x 65,536 shapes with 2 %
+// 122 / 159); a caller who knows of a poor fit passes the smaller workspace and gets the whole search.
 bool assign_bounded_ok(long long E, int K) {
-  const bool pays = K >= 16384 ? (E - 24000) * K >= 1400000000ll : (K >= 8192 && E * K >= (1ll << 32));
-  return pays && cell_layout(1, K).groups_max <= kCellMaxGroups;
+  if (K < 8192 || cell_layout(1, K).groups_max > kCellMaxGroups) return false;
+  if (K < 16384) return E * K >= (1ll << 32);
+  if ((E - 25000) * K < 1200000000ll) return false;
+  if (E >= kOwnMinEdges) return true;
+  double whole;
+  whole_parts_of(E, K, &whole);
+  return 72.0 + 1.28e-3 * K + (double)E * (1.25e-4 + 4.7e-5 * std::log2(K / 8192.0)) < whole;
 }
 size_t assign_bounded_bytes(long long E, int K) { return cell_layout(E, K).bytes; }
 

@@ -403,3 +403,14 @@ def test_dense_layers_are_cut_by_rounds_of_workgroups():
     for n_in, n_out, B, chunks in ((64, 2347, 253, 1), (384, 2880, 39, 4), (300, 64, 256, 10), (2080, 1328, 36, 11)):
         need = L.kan_dense_workspace_bytes(n_in, n_out, B)
         assert need == (0 if chunks == 1 else -(-4 * chunks * B * n_out // 256) * 256), (n_in, n_out, B, need)
+
+
+def test_bounded_search_is_taken_where_it_is_ahead():
+    """The faster workspace is the whole search's (the shapes' operands, and eight bytes an edge and part of the codebook) where
+    the edges are few for their shapes or fill whole rounds of its workgroups."""
+    L = kb.lib()
+    for K, edges, bounded in ((330923, 13760, False), (262144, 16524, False), (16384, 98304, False), (65536, 43008, False),
+                              (8192, 524287, False), (17688, 98944, True), (16384, 131072, True), (65536, 43520, True), (262144, 29700, True),
+                              (8192, 524288, True), (8192, 1 << 20, True), (65536, 1 << 20, True), (4096, 1 << 20, False), (400000, 1 << 20, False)):
+        whole, fast = L.kan_vq_assign_workspace_bytes(K), L.kan_vq_assign_fast_workspace_bytes(edges, 1, K)
+        assert (fast not in {(whole + (8 * edges * n if n > 1 else 0) + 255) // 256 * 256 for n in range(1, 33)}) == bounded, (K, edges)
