@@ -228,7 +228,6 @@ constexpr int kFusedMinWgsPerHead = 20;      // fused kernels, several heads: wo
 // 74 / - / 77).  What 64 workgroups write may take a call past the static scratch: see plan_head.
 constexpr int kFusedOneHeadWgs = 64;
 constexpr long long kFusedLargeCodebook = 768 * 1024;
-constexpr long long kFusedOneHeadMinEdges = 1 << 19;      // from here a head's workgroups have eight steps each
 // Precise path: from this batch on the split-operand matrix-core form.  Its time hardly depends on
 // the batch below 128 (config 3: 96 us, config 2: 44 us) while the fused fp32 kernel's doubles with
 // its second tile of 64 samples (config 3: 97 us at 64, 113 at 80; config 2: 33 and 57).
