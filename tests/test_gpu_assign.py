@@ -267,9 +267,11 @@ def test_shapes_of_large_norm_win_over_rows_past_the_last(kb, K, E):
         assert float((d2.gather(1, idx[s:s + 4096, None])[:, 0] - d2.min(1).values).max()) <= 0.05
 
 
-@pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073)])
+@pytest.mark.parametrize("K,E", [(1, 1), (33, 127), (257, 129), (1000, 4096), (4096, 131072), (300, 131073),
+                                 (820, 262399), (820, 262400), (4096, 786431), (4096, 786432), (512, 976562), (512, 976563)])
 def test_whole_search_shared_and_separate_waves(kb, K, E):
-    """Either side of the switch between eight waves on 128 edges and four on 512: gathers the nearest row."""
+    """Operands in LDS (1, 33, 257 and 300 shapes, 512 in its last call but one), and either side of the switches between eight
+    waves on 128 edges and four on 512: gathers the nearest row."""
     coef, cb = _grids("trained", K, E, K + E)
     idx, _, _ = kb.kan_vq_assign(coef, cb)
     a = idx.view(-1).long() & 0xffff
@@ -283,9 +285,9 @@ def test_whole_search_shared_and_separate_waves(kb, K, E):
 
 
 @pytest.mark.parametrize("kind", ["trained", "norms", "duplicates", "far", "no numbers"])
-@pytest.mark.parametrize("K,E", [(512, 130), (513, 257), (8193, 127), (40000, 129), (65536, 4097), (20000, 45000)])
+@pytest.mark.parametrize("K,E", [(384, 130), (512, 130), (513, 257), (8193, 127), (40000, 129), (65536, 4097), (20000, 45000)])
 def test_whole_search_in_parts_and_in_one(kb, kind, K, E):
-    """Shapes in LDS (512), waves that share their edges (513), parts of the codebook, tiles tested by their first product
+    """Shapes in LDS (384), waves that share their edges (512, 513), parts of the codebook, tiles tested by their first product
     (8,192 shapes of a part and more): the ids are those of one part (a workspace without room for several), and as near as
     the nearest row wherever the edge and its scores are numbers."""
     coef, cb = _grids(kind, K, max(E, 8192), K + E)
@@ -319,14 +321,14 @@ def test_whole_search_in_parts_and_in_one(kb, kind, K, E):
         assert float(far[valid[s:s + 2048]].max()) <= gap
 
 
-@pytest.mark.parametrize("kind,K,E", [("trained", 513, 786433), ("trained", 65536, 49153), ("trained", 131071, 36001),
+@pytest.mark.parametrize("kind,K,E", [("trained", 513, 786433), ("trained", 1000, 786433), ("trained", 65536, 49153), ("trained", 131071, 36001),
                                       ("trained", 262144, 30001), ("trained", 300000, 30001), ("clumps", 65521, 49153)])
 def test_large_searches_give_the_ids_of_one_part(kb, kind, K, E):
-    """Waves with edges of their own (3 * 2^18 edges), and the bounded search from where it begins for codebooks whose cells have
-    eight, four, two parts and one."""
+    """Operands in LDS and waves with edges of their own (3 * 2^18 edges), and the bounded search from about where it begins for codebooks
+    whose cells have eight, four, two parts and one."""
     coef, cb = _grids(kind, K, E, K + E + 2)
     whole = torch.empty(kb.lib().kan_vq_assign_workspace_bytes(K), dtype=torch.uint8, device="cuda")
-    assert _bounded_is_taken(kb, E, 1, K) == (K > 513)
+    assert _bounded_is_taken(kb, E, 1, K) == (K > 1000)
     a, b = kb.kan_vq_assign(coef, cb)[0], kb.kan_vq_assign(coef, cb, ws=whole)[0]
     assert torch.equal(a, b), int((a != b).sum())
     flat = coef.view(E, 10)[:64].double()
